@@ -33,32 +33,30 @@ constexpr int PM_BLOCK = 128;
 // NC = 0: state only.  NC > 0: state and tangent columns g NC .. g NC + NC - 1
 // of DF, g = thread index within its state.
 template <int NC>
-__global__ void __launch_bounds__(PM_BLOCK) k_pm_flow(const double *__restrict__ in, double *out,
-                                                      double *__restrict__ stm, int64_t n, Model md, Tableau T,
-                                                      double ecc, int steps, int64_t nsteps, double h)
+__global__ void __launch_bounds__(PM_BLOCK) __attribute__((amdgpu_waves_per_eu(NC == 0 ? 5 : NC == 1 ? 3 : NC == 2 ? 2 : W4, 8))) k_pm_flow(RkCoef, const double *__restrict__ in, double *out,
+                                                      double *__restrict__ stm, int64_t n, Model md, double ecc,
+                                                      int steps, int64_t nsteps)
 {
-#pragma clang fp contract(fast)
     constexpr int G = NC > 0 ? 4 / NC : 1;   // threads per state
-    constexpr int NV = NC > 0 ? NC : 1;
+    constexpr int D = 4 + 4 * NC;            // the state, then the thread's columns
     __shared__ double2 s_rn[RK_CHUNK * S];
     __shared__ double s_c[S];
 #pragma unroll
     for (int i = 0; i < S; ++i)
-        if (threadIdx.x == i) s_c[i] = T.c[i];
+        if (threadIdx.x == i) s_c[i] = RK_T.c[i];
     const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const bool live = gid < n * G;      // every thread of the block fills the stage values
     const int64_t p = live ? gid / G : 0;
     const int g = (int)(gid - (gid / G) * G);
-    double z[4] = {0.0, 0.0, 0.0, 0.0};
+    double z[D];
     if (live) {
         const d4 s = load_d4(in + 4 * p);
         z[0] = s.x; z[1] = s.y; z[2] = s.z; z[3] = s.w;
     }
-    double v[NV][4];
 #pragma unroll
-    for (int c = 0; c < NV; ++c)
+    for (int c = 0; c < NC; ++c)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) v[c][i] = (i == g * NC + c) ? 1.0 : 0.0;
+        for (int i = 0; i < 4; ++i) z[4 + 4 * c + i] = (i == g * NC + c) ? 1.0 : 0.0;
     int64_t n_in = 0;
     for (int64_t st0 = 0; st0 < nsteps; st0 += RK_CHUNK) {
         const int cnt = nsteps - st0 < RK_CHUNK ? (int)(nsteps - st0) : RK_CHUNK;
@@ -69,55 +67,7 @@ __global__ void __launch_bounds__(PM_BLOCK) k_pm_flow(const double *__restrict__
         if (!live) continue;
         for (int jj = 0; jj < cnt; ++jj) {
             const double2 *row = s_rn + jj * S;
-            double k[S][4];
-            double kv[S][NV][4];
-#pragma unroll
-            for (int i = 0; i < S; ++i) {
-                double zs[4], vs[NV][4];
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    double acc = 0.0;
-#pragma unroll
-                    for (int j = 0; j < i; ++j)
-                        if (RK_NZ[i][j]) acc += T.a[i][j] * k[j][c];
-                    zs[c] = z[c] + h * acc;
-                }
-                if constexpr (NC > 0) {
-#pragma unroll
-                    for (int q = 0; q < NC; ++q)
-#pragma unroll
-                        for (int c = 0; c < 4; ++c) {
-                            double acc = 0.0;
-#pragma unroll
-                            for (int j = 0; j < i; ++j)
-                                if (RK_NZ[i][j]) acc += T.a[i][j] * kv[j][q][c];
-                            vs[q][c] = v[q][c] + h * acc;
-                        }
-                }
-                const double2 rn = row[i];
-                if constexpr (NC > 0) pm_field_var<NC>(md, rn.x, rn.y, zs, vs, k[i], kv[i]);
-                else pm_field(md, rn.x, rn.y, zs, k[i]);
-            }
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                double acc = 0.0;
-#pragma unroll
-                for (int i = 0; i < S; ++i)
-                    if (RK_NZB[i]) acc += T.b[i] * k[i][c];
-                z[c] = z[c] + h * acc;
-            }
-            if constexpr (NC > 0) {
-#pragma unroll
-                for (int q = 0; q < NC; ++q)
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        double acc = 0.0;
-#pragma unroll
-                        for (int i = 0; i < S; ++i)
-                            if (RK_NZB[i]) acc += T.b[i] * kv[i][q][c];
-                        v[q][c] = v[q][c] + h * acc;
-                    }
-            }
+            rk_step<D>(z, step_coef(), [&](int i, double (&s)[D]) { pm_field<NC>(md, row[i].x, row[i].y, s); });
         }
     }
     if (!live) return;
@@ -131,7 +81,7 @@ __global__ void __launch_bounds__(PM_BLOCK) k_pm_flow(const double *__restrict__
 #pragma unroll
         for (int q = 0; q < NC; ++q)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) stm[16 * p + 4 * i + g * NC + q] = v[q][i];
+            for (int i = 0; i < 4; ++i) stm[16 * p + 4 * i + g * NC + q] = z[4 + 4 * q + i];
     }
 }
 
@@ -157,8 +107,8 @@ int pm_launch(const double *in, double *out, double *stm, int64_t n, const map_p
     // The launch counts work-items in 32 bits.
     if (n > (((int64_t)1 << 32) - PM_BLOCK) / G) return fail(MS_E_ARG, "pertbp: too many states for one launch");
     Model md{p->mu, 1.0 - p->mu};
-    hipLaunchKernelGGL(k_pm_flow<NC>, dim3((unsigned)ceil_div(threads, PM_BLOCK)), dim3(PM_BLOCK), 0, st, in, out,
-                       stm, n, md, cv_tableau(), p->e, p->steps_per_period, nsteps, h);
+    hipLaunchKernelGGL(k_pm_flow<NC>, dim3((unsigned)ceil_div(threads, PM_BLOCK)), dim3(PM_BLOCK), 0, st, rk_coef(h),
+                       in, out, stm, n, md, p->e, p->steps_per_period, nsteps);
     MS_HIP(hipGetLastError());
     return MS_OK;
 }

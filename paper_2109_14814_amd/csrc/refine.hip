@@ -40,13 +40,13 @@ constexpr int RF_BLOCK = 64;
 struct SideMap {
     const double *w;       // stage values w(f), steps x S (in the workspace)
     const double *dwde;    // stage values dw/de, steps x S (in the workspace)
-    double h;              // signed step
     int64_t nsteps;
     int32_t steps;         // steps per period
     int32_t pad;
 };
 
 struct RefArgs {
+    RkCoef hc[2];           // scaled coefficients of each side (first: step_coef reads them from the kernel arguments)
     const double *params;   // K x 4 (th1, s1, th2, s2)
     const double *U, *Sp;   // patches, 12 doubles each (base, d1, d2)
     int64_t K;
@@ -61,7 +61,7 @@ struct RefArgs {
     const int32_t *status;  // K Newton status words; only hits with status < 0 run (NULL: all run)
 };
 
-MS_D void store_d4(double *p, const double y[4])
+MS_D void store_d4(double *p, const double *y)
 {
     double2 *o = reinterpret_cast<double2 *>(p);
     o[0] = make_double2(y[0], y[1]);
@@ -84,91 +84,27 @@ MS_D int traj_start(const RefArgs &a, int64_t t, int &side, int64_t &k, double y
 
 MS_D bool hit_active(const RefArgs &a, int64_t k) { return a.status == nullptr || a.status[k] < 0; }
 
-// One step of the map on the state alone.  Not inlined, so that the forward
-// pass and the adjoint's recomputation of a segment run the very same code
-// and reproduce the same states bit for bit.
-__device__ __noinline__ d4 rk_state_step(d4 y0, const double *__restrict__ w, double h, Model md)
+// Trajectory of a thread: the grid's y index is the side, so that the step
+// and its coefficients are the same for every thread of a wave.
+MS_D CoefPtr side_coef(int side) { return step_coef() + side * RK_NC; }
+
+// One step of the map on the state alone.  Every operation of rk_step and of
+// the field is written out, so that the forward pass and the adjoint's
+// recomputation of a segment reproduce the same states bit for bit.
+MS_D void rk_state_step(double (&y)[4], const double *__restrict__ w, int side, const Model &md)
 {
-#pragma clang fp contract(fast)
-    double y[4] = {y0.x, y0.y, y0.z, y0.w};
-    double k[S][4];
-#pragma unroll
-    for (int i = 0; i < S; ++i) {
-        double ys[4];
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            double acc = 0.0;
-#pragma unroll
-            for (int j = 0; j < i; ++j)
-                if (RK_NZ[i][j]) acc += c_cv.a[i][j] * k[j][c];
-            ys[c] = y[c] + h * acc;
-        }
-        rk_field(md, w[i], ys, k[i]);
-    }
-    d4 r;
-    double out[4];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        double acc = 0.0;
-#pragma unroll
-        for (int i = 0; i < S; ++i)
-            if (RK_NZB[i]) acc += c_cv.b[i] * k[i][c];
-        out[c] = y[c] + h * acc;
-    }
-    r.x = out[0]; r.y = out[1]; r.z = out[2]; r.w = out[3];
-    return r;
+    rk_step<4>(y, side_coef(side), [&](int i, double (&s)[4]) { puls_field(md, w[i], s); });
 }
 
-// One step of the state together with one tangent column v: the variational
-// equations v' = A(f, y) v (+ dF/de when `ecol`), integrated with the same
-// stages, which is the exact derivative of the discrete step.
-MS_D void rk_tangent_step(double y[4], double v[4], const double *__restrict__ w, const double *__restrict__ dwde,
-                          double h, const Model &md, bool ecol)
+// One step of the state (y[0..3]) together with one tangent column
+// (y[4..7]): the variational equations v' = A(f, y) v (+ dF/de when `ecol`),
+// integrated with the same stages, which is the exact derivative of the
+// discrete step.
+MS_D void rk_tangent_step(double (&y)[8], const double *__restrict__ w, const double *__restrict__ dwde, int side,
+                          const Model &md, bool ecol)
 {
-#pragma clang fp contract(fast)
-    double k[S][4], kv[S][4];
-#pragma unroll
-    for (int i = 0; i < S; ++i) {
-        double ys[4], vs[4];
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            double acc = 0.0, accv = 0.0;
-#pragma unroll
-            for (int j = 0; j < i; ++j)
-                if (RK_NZ[i][j]) {
-                    acc += c_cv.a[i][j] * k[j][c];
-                    accv += c_cv.a[i][j] * kv[j][c];
-                }
-            ys[c] = y[c] + h * acc;
-            vs[c] = v[c] + h * accv;
-        }
-        OmegaD o = omega_derivs(md, ys[0], ys[1]);
-        double wi = w[i];
-        k[i][0] = ys[2];
-        k[i][1] = ys[3];
-        k[i][2] = 2.0 * ys[3] + wi * o.Ox;
-        k[i][3] = -2.0 * ys[2] + wi * o.Oy;
-        kv[i][0] = vs[2];
-        kv[i][1] = vs[3];
-        kv[i][2] = wi * (o.Oxx * vs[0] + o.Oxy * vs[1]) + 2.0 * vs[3];
-        kv[i][3] = wi * (o.Oxy * vs[0] + o.Oyy * vs[1]) - 2.0 * vs[2];
-        if (ecol) {
-            kv[i][2] += dwde[i] * o.Ox;
-            kv[i][3] += dwde[i] * o.Oy;
-        }
-    }
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        double acc = 0.0, accv = 0.0;
-#pragma unroll
-        for (int i = 0; i < S; ++i)
-            if (RK_NZB[i]) {
-                acc += c_cv.b[i] * k[i][c];
-                accv += c_cv.b[i] * kv[i][c];
-            }
-        y[c] = y[c] + h * acc;
-        v[c] = v[c] + h * accv;
-    }
+    rk_step<8>(y, side_coef(side),
+               [&](int i, double (&s)[8]) { puls_field_var(md, w[i], ecol ? dwde[i] : 0.0, s); });
 }
 
 MS_D const double *stage_row(const double *tab, int64_t s, int32_t steps)
@@ -180,50 +116,48 @@ MS_D const double *stage_row(const double *tab, int64_t s, int32_t steps)
 // every ck-th step.
 __global__ void __launch_bounds__(RF_BLOCK) k_ref_state(RefArgs a)
 {
-    int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= 2 * a.K) return;
-    int side;
-    int64_t k;
-    double y0[4];
-    const double *patch;
-    traj_start(a, t, side, k, y0, patch);
-    if (!hit_active(a, k)) return;
-    const SideMap sm = a.side[side];
-    const int64_t T2 = 2 * a.K;
-    d4 y{y0[0], y0[1], y0[2], y0[3]};
-    for (int64_t s = 0; s < sm.nsteps; ++s) {
-        if (a.ckpt && s % a.ck == 0) {
-            double v[4] = {y.x, y.y, y.z, y.w};
-            store_d4(a.ckpt + ((s / a.ck) * T2 + t) * 4, v);
-        }
-        y = rk_state_step(y, stage_row(sm.w, s, sm.steps), sm.h, a.md);
-    }
-    double v[4] = {y.x, y.y, y.z, y.w};
-    store_d4(a.yend + 4 * t, v);
-}
-
-// Tangent pass: thread (column c, trajectory t); columns d/dth, d/ds, d/de.
-__global__ void __launch_bounds__(RF_BLOCK) k_ref_tangent(RefArgs a)
-{
-    const int64_t T2 = 2 * a.K;
-    int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (gid >= 3 * T2) return;
-    int col = (int)(gid / T2);
-    int64_t t = gid - col * T2;
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= a.K) return;
+    const int64_t t = blockIdx.y * a.K + i;
     int side;
     int64_t k;
     double y[4];
     const double *patch;
     traj_start(a, t, side, k, y, patch);
     if (!hit_active(a, k)) return;
-    const SideMap sm = a.side[side];
-    double v[4];
+    const SideMap sm = a.side[blockIdx.y];
+    const int64_t T2 = 2 * a.K;
+    for (int64_t s = 0; s < sm.nsteps; ++s) {
+        if (a.ckpt && s % a.ck == 0) store_d4(a.ckpt + ((s / a.ck) * T2 + t) * 4, y);
+        rk_state_step(y, stage_row(sm.w, s, sm.steps), blockIdx.y, a.md);
+    }
+    store_d4(a.yend + 4 * t, y);
+}
+
+// Tangent pass: thread (column c, trajectory t); columns d/dth, d/ds, d/de.
+__global__ void __launch_bounds__(RF_BLOCK) k_ref_tangent(RefArgs a)
+{
+    const int64_t T2 = 2 * a.K;
+    const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (gid >= 3 * a.K) return;
+    const int col = (int)(gid / a.K);
+    const int64_t t = blockIdx.y * a.K + (gid - col * a.K);
+    int side;
+    int64_t k;
+    double y0[4], y[8];
+    const double *patch;
+    traj_start(a, t, side, k, y0, patch);
+    if (!hit_active(a, k)) return;
+    const SideMap sm = a.side[blockIdx.y];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) v[c] = col == 2 ? 0.0 : patch[4 * (col + 1) + c];
+    for (int c = 0; c < 4; ++c) {
+        y[c] = y0[c];
+        y[4 + c] = col == 2 ? 0.0 : patch[4 * (col + 1) + c];
+    }
     const bool ecol = col == 2;
     for (int64_t s = 0; s < sm.nsteps; ++s)
-        rk_tangent_step(y, v, stage_row(sm.w, s, sm.steps), stage_row(sm.dwde, s, sm.steps), sm.h, a.md, ecol);
-    store_d4(a.dend + ((int64_t)col * T2 + t) * 4, v);
+        rk_tangent_step(y, stage_row(sm.w, s, sm.steps), stage_row(sm.dwde, s, sm.steps), blockIdx.y, a.md, ecol);
+    store_d4(a.dend + ((int64_t)col * T2 + t) * 4, y + 4);
     if (col == 0) store_d4(a.yend + 4 * t, y);
 }
 
@@ -280,20 +214,19 @@ __global__ void __launch_bounds__(RF_BLOCK) k_adj_states(RefArgs a, int64_t s_lo
 {
     const int64_t T2 = 2 * a.K;
     const int64_t nseg = (s_hi - s_lo + a.ck - 1) / a.ck;
-    int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (gid >= nseg * T2) return;
-    const int64_t sg = gid / T2, t = gid - sg * T2;
-    const int side = t >= a.K ? 1 : 0;
-    const SideMap sm = a.side[side];
+    const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (gid >= nseg * a.K) return;
+    const int64_t sg = gid / a.K, t = blockIdx.y * a.K + (gid - sg * a.K);
+    const SideMap sm = a.side[blockIdx.y];
     const int64_t s0 = s_lo + sg * a.ck;
     int64_t s1 = s0 + a.ck < s_hi ? s0 + a.ck : s_hi;
     if (s1 > sm.nsteps) s1 = sm.nsteps;
     if (s0 >= s1) return;
-    d4 y = load_d4(a.ckpt + ((s0 / a.ck) * T2 + t) * 4);
+    const d4 c = load_d4(a.ckpt + ((s0 / a.ck) * T2 + t) * 4);
+    double y[4] = {c.x, c.y, c.z, c.w};
     for (int64_t s = s0; s < s1; ++s) {
-        double v[4] = {y.x, y.y, y.z, y.w};
-        store_d4(states + ((s - s_lo) * T2 + t) * 4, v);
-        if (s + 1 < s1) y = rk_state_step(y, stage_row(sm.w, s, sm.steps), sm.h, a.md);
+        store_d4(states + ((s - s_lo) * T2 + t) * 4, y);
+        if (s + 1 < s1) rk_state_step(y, stage_row(sm.w, s, sm.steps), blockIdx.y, a.md);
     }
 }
 
@@ -301,21 +234,20 @@ __global__ void __launch_bounds__(RF_BLOCK) k_adj_jac(RefArgs a, int64_t s_lo, i
                                                       double *jac)
 {
     const int64_t T2 = 2 * a.K;
-    int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (gid >= (s_hi - s_lo) * T2 * 5) return;
+    const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (gid >= (s_hi - s_lo) * a.K * 5) return;
     const int64_t cell = gid / 5;
     const int col = (int)(gid - cell * 5);
-    const int64_t sl = cell / T2, t = cell - sl * T2;
-    const int side = t >= a.K ? 1 : 0;
-    const SideMap sm = a.side[side];
+    const int64_t sl = cell / a.K, t = blockIdx.y * a.K + (cell - sl * a.K);
+    const SideMap sm = a.side[blockIdx.y];
     const int64_t s = s_lo + sl;
     if (s >= sm.nsteps) return;
     const d4 ys = load_d4(states + (sl * T2 + t) * 4);
-    double y[4] = {ys.x, ys.y, ys.z, ys.w};
-    double v[4] = {0.0, 0.0, 0.0, 0.0};
-    if (col < 4) v[col] = 1.0;
-    rk_tangent_step(y, v, stage_row(sm.w, s, sm.steps), stage_row(sm.dwde, s, sm.steps), sm.h, a.md, col == 4);
-    store_d4(jac + gid * 4, v);
+    double y[8] = {ys.x, ys.y, ys.z, ys.w, 0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int c = 0; c < 4; ++c) y[4 + c] = c == col ? 1.0 : 0.0;
+    rk_tangent_step(y, stage_row(sm.w, s, sm.steps), stage_row(sm.dwde, s, sm.steps), blockIdx.y, a.md, col == 4);
+    store_d4(jac + ((sl * T2 + t) * 5 + col) * 4, y + 4);
 }
 
 // lam (4) and ge per trajectory live in adj[5 t ...]; init seeds lam = +-2 f.
@@ -546,7 +478,7 @@ int make_args(RefArgs &a, const double *params, int64_t K, const patch_t *U, con
         sm.dwde = need_dwde ? t.dwde[sd] : t.w[sd];
         sm.nsteps = side_steps(m[sd]);
         sm.steps = m[sd]->steps_per_period;
-        sm.h = (m[sd]->n_periods < 0 ? -RK_TWO_PI : RK_TWO_PI) / (double)m[sd]->steps_per_period;
+        a.hc[sd] = rk_coef((m[sd]->n_periods < 0 ? -RK_TWO_PI : RK_TWO_PI) / (double)m[sd]->steps_per_period);
     }
     const int64_t n = ((int64_t)t.steps[0] + t.steps[1]) * S;
     MS_LAUNCH("k_ref_tables", k_ref_tables, dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, st, t);
@@ -602,12 +534,12 @@ extern "C" int refine_grad(const double *params_dev, int64_t K, const patch_t *U
     a.gpart = (double *)(w + L.o_gpart);
     const int64_t T2 = 2 * K;
     if (mode == MS_REFINE_TANGENT) {
-        MS_LAUNCH("k_ref_tangent", k_ref_tangent, dim3(blocks_for(3 * T2)), dim3(RF_BLOCK), 0, st, a);
+        MS_LAUNCH("k_ref_tangent", k_ref_tangent, dim3(blocks_for(3 * K), 2), dim3(RF_BLOCK), 0, st, a);
         MS_LAUNCH("k_ref_combine", k_ref_combine, dim3(blocks_for(K)), dim3(RF_BLOCK), 0, st, a, 1, f_dev, r_dev, J_dev,
                   grad_dev);
     } else {
         if (mode == MS_REFINE_ADJOINT) a.ckpt = (double *)(w + L.o_ckpt);
-        MS_LAUNCH("k_ref_state", k_ref_state, dim3(blocks_for(T2)), dim3(RF_BLOCK), 0, st, a);
+        MS_LAUNCH("k_ref_state", k_ref_state, dim3(blocks_for(K), 2), dim3(RF_BLOCK), 0, st, a);
         MS_LAUNCH("k_ref_combine", k_ref_combine, dim3(blocks_for(K)), dim3(RF_BLOCK), 0, st, a, 0, f_dev, r_dev,
                   (double *)nullptr, (double *)nullptr);
         if (mode == MS_REFINE_ADJOINT) {
@@ -620,10 +552,10 @@ extern "C" int refine_grad(const double *params_dev, int64_t K, const patch_t *U
                 const int64_t s_hi = s_lo + W < L.n_steps_max ? s_lo + W : L.n_steps_max;
                 const int64_t nseg = ceil_div(s_hi - s_lo, (int64_t)ck);
                 if (s_hi > s_lo) {
-                    MS_LAUNCH("k_adj_states", k_adj_states, dim3(blocks_for(nseg * T2)), dim3(RF_BLOCK), 0, st, a, s_lo,
+                    MS_LAUNCH("k_adj_states", k_adj_states, dim3(blocks_for(nseg * K), 2), dim3(RF_BLOCK), 0, st, a, s_lo,
                               s_hi, states);
-                    MS_LAUNCH("k_adj_jac", k_adj_jac, dim3(blocks_for((s_hi - s_lo) * T2 * 5)), dim3(RF_BLOCK), 0, st, a,
-                              s_lo, s_hi, (const double *)states, jac);
+                    MS_LAUNCH("k_adj_jac", k_adj_jac, dim3(blocks_for((s_hi - s_lo) * K * 5), 2), dim3(RF_BLOCK), 0, st,
+                              a, s_lo, s_hi, (const double *)states, jac);
                 }
                 MS_LAUNCH("k_adj_reverse", k_adj_reverse, dim3(blocks_for(T2)), dim3(RF_BLOCK), 0, st, a, s_lo, s_hi,
                           (const double *)jac, adj, (const double *)f_dev, (int)(wi == nwin - 1));
@@ -680,10 +612,9 @@ extern "C" int refine_newton(const double *params_in_dev, double *params_out_dev
     cfg.alpha0 = np->alpha0;
     cfg.alpha_min = np->alpha_min;
     cfg.max_trials = np->max_trials;
-    const int64_t T2 = 2 * K;
     MS_LAUNCH("k_newton_init", k_newton_init, dim3(blocks_for(K)), dim3(RF_BLOCK), 0, st, params_in_dev, ns, K);
     for (int it = 0; it <= np->max_trials; ++it) {
-        MS_LAUNCH("k_ref_tangent", k_ref_tangent, dim3(blocks_for(3 * T2)), dim3(RF_BLOCK), 0, st, a);
+        MS_LAUNCH("k_ref_tangent", k_ref_tangent, dim3(blocks_for(3 * K), 2), dim3(RF_BLOCK), 0, st, a);
         MS_LAUNCH("k_newton_update", k_newton_update, dim3(blocks_for(K)), dim3(RF_BLOCK), 0, st, a, ns, cfg);
     }
     MS_LAUNCH("k_newton_finish", k_newton_finish, dim3(blocks_for(K)), dim3(RF_BLOCK), 0, st, ns, K, params_out_dev,

@@ -39,18 +39,30 @@ bool cv_pattern_ok()
     return true;
 }
 
+RkCoef rk_coef(double h)
+{
+    const Tableau &T = cv_tableau();
+    RkCoef c;
+    int n = 0;
+    for (int i = 1; i < S; ++i)
+        for (int j = 0; j < i; ++j)
+            if (RK_NZ[i][j]) c.v[n++] = h * T.a[i][j];
+    for (int i = 0; i < S; ++i)
+        if (RK_NZB[i]) c.v[n++] = h * T.b[i];
+    return c;
+}
+
 namespace {
 
-__global__ void __launch_bounds__(RK_BLOCK) k_rk8_map(const double *__restrict__ in, double *__restrict__ out,
-                                                      int64_t n, Model md, Tableau T, double e, int steps,
-                                                      int64_t nsteps, double h)
+__global__ void __launch_bounds__(RK_BLOCK) __attribute__((amdgpu_waves_per_eu(5, 8))) k_rk8_map(RkCoef, const double *__restrict__ in,
+                                                      double *__restrict__ out, int64_t n, Model md, double e,
+                                                      int steps, int64_t nsteps)
 {
-#pragma clang fp contract(fast)
     __shared__ double s_w[RK_CHUNK * S];
     __shared__ double s_c[S];
 #pragma unroll
     for (int i = 0; i < S; ++i)
-        if (threadIdx.x == i) s_c[i] = T.c[i];
+        if (threadIdx.x == i) s_c[i] = RK_T.c[i];
     const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const bool live = v < n;      // every thread of the block fills the weights
     double y[4] = {0.0, 0.0, 0.0, 0.0};
@@ -67,28 +79,7 @@ __global__ void __launch_bounds__(RK_BLOCK) k_rk8_map(const double *__restrict__
         if (live) {
             for (int jj = 0; jj < cnt; ++jj) {
                 const double *w = s_w + jj * S;
-                double k[S][4];
-#pragma unroll
-                for (int i = 0; i < S; ++i) {
-                    double ys[4];
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        double acc = 0.0;
-#pragma unroll
-                        for (int j = 0; j < i; ++j)
-                            if (RK_NZ[i][j]) acc += T.a[i][j] * k[j][c];
-                        ys[c] = y[c] + h * acc;
-                    }
-                    rk_field(md, w[i], ys, k[i]);
-                }
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    double acc = 0.0;
-#pragma unroll
-                    for (int i = 0; i < S; ++i)
-                        if (RK_NZB[i]) acc += T.b[i] * k[i][c];
-                    y[c] = y[c] + h * acc;
-                }
+                rk_step<4>(y, step_coef(), [&](int i, double (&s)[4]) { puls_field(md, w[i], s); });
             }
         }
         n_in = (n_in + cnt) % steps;
@@ -125,8 +116,8 @@ extern "C" int propagate_vertices(const double *in_dev, double *out_dev, int64_t
         return MS_OK;
     }
     Model md{p->mu, 1.0 - p->mu};
-    hipLaunchKernelGGL(k_rk8_map, dim3((unsigned)ceil_div(n_vertices, RK_BLOCK)), dim3(RK_BLOCK), 0, st, in_dev,
-                       out_dev, n_vertices, md, cv_tableau(), p->e, p->steps_per_period, nsteps, h);
+    hipLaunchKernelGGL(k_rk8_map, dim3((unsigned)ceil_div(n_vertices, RK_BLOCK)), dim3(RK_BLOCK), 0, st, rk_coef(h),
+                       in_dev, out_dev, n_vertices, md, p->e, p->steps_per_period, nsteps);
     MS_HIP(hipGetLastError());
     return MS_OK;
 }

@@ -62,6 +62,9 @@ constexpr Tableau cv_make_tableau()
     return T;
 }
 
+// The abscissae c_i as compile-time constants.
+constexpr Tableau RK_T = cv_make_tableau();
+
 // Host: the tableau; whether sqrt(21.0) rounds to RK_SQRT21 and the zeros
 // match RK_NZ.
 const Tableau &cv_tableau();
@@ -135,113 +138,252 @@ struct Model {
     double mu, one_minus_mu;
 };
 
-// x^(-1/2) for x = r^2 > 0: the hardware reciprocal square root (about 23
-// correct bits) refined by two Newton steps y <- y (3/2 - x y^2 / 2), each of
-// which doubles the number of correct bits; the result is within a few ulp
-// of the correctly rounded value, for about half the instructions of a
-// square root followed by a division.  The force terms m / r^3 = m y^3 and
-// the Hessian terms 3 m / r^5 = 3 m y^5 all come from this one value.
-MS_D double inv_sqrt(double x)
+// The tableau's 44 non-zero entries times the signed step h, row by row: the
+// a_ij of stages 1..10, then the b_i.  With h in the coefficients a stage
+// value is y plus one multiply-add per entry.
+constexpr int RK_NC = 44;
+
+struct RkCoef {
+    double v[RK_NC];
+};
+
+RkCoef rk_coef(double h);
+
+// m / r^3 from x = r^2 > 0: the hardware reciprocal square root y (about 23
+// correct bits) gives y^3, corrected by the series of (1 - e)^(-3/2) in the
+// residual e = 1 - x y^2 to second order; e is below 2^-21, so the first
+// term left out is below 2^-61.  One cubic correction of the product takes
+// 7 operations where two Newton steps of y followed by its cube took 10, and
+// its rounding error is smaller (under 2 ulp, against up to 4).
+MS_D double cube_series(double e)
 {
-#pragma clang fp contract(fast)
-    double y = __builtin_amdgcn_rsq(x);
-    const double h = 0.5 * x;
-    y = fma(y, fma(-h, y * y, 0.5), y);
-    y = fma(y, fma(-h, y * y, 0.5), y);
-    return y;
+    // 3/2 + 15/8 e.  Neither constant has an inline encoding; written as a
+    // fused multiply-add the compiler moves 3/2 into the destination of
+    // every use (a multiply-add in place, two 32-bit moves or one of 64 bits
+    // before it: 22 a step).  The three-register form takes both as they are.
+    double r;
+    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "v"(e), "s"(1.875), "v"(1.5));
+    return r;
 }
 
-// Right-hand side at stage weight w: (x', y', w Omega_x + 2 y', w Omega_y - 2 x'),
-// Omega = (x^2 + y^2)/2 + (1 - mu)/r1 + mu/r2, r1 = |(x + mu, y)|,
-// r2 = |(x - 1 + mu, y)|.
-MS_D void rk_field(const Model &md, double w, const double y[4], double k[4])
+MS_D double mass_over_r3(double m, double x)
 {
-#pragma clang fp contract(fast)
-    double x = y[0], yy = y[1];
-    double dx1 = x + md.mu, dx2 = x - md.one_minus_mu;
-    double yy2 = yy * yy;
-    double r1s = dx1 * dx1 + yy2, r2s = dx2 * dx2 + yy2;
-    double i1 = inv_sqrt(r1s), i2 = inv_sqrt(r2s);
-    double g1 = md.one_minus_mu * (i1 * i1) * i1, g2 = md.mu * (i2 * i2) * i2;   // m_i / r_i^3
-    double Ox = x - g1 * dx1 - g2 * dx2;
-    double Oy = yy - (g1 + g2) * yy;
-    k[0] = y[2];
-    k[1] = y[3];
-    k[2] = 2.0 * y[3] + w * Ox;
-    k[3] = -2.0 * y[2] + w * Oy;
+    const double y = __builtin_amdgcn_rsq(x);
+    const double y2 = y * y;
+    const double e = fma(-x, y2, 1.0);
+    const double c = m * (y2 * y);
+    return fma(c * e, cube_series(e), c);
+}
+
+// The same, and q = 1 / r^2 = y^2 (1 + e + e^2).
+MS_D double mass_over_r3(double m, double x, double &q)
+{
+    const double y = __builtin_amdgcn_rsq(x);
+    const double y2 = y * y;
+    const double e = fma(-x, y2, 1.0);
+    const double c = m * (y2 * y);
+    q = fma(y2, fma(e, e, e), y2);
+    return fma(c * e, cube_series(e), c);
+}
+
+// Right-hand sides, evaluated in place: on entry s holds a stage value, on
+// return its derivative.  Every operation is written out (fused where it
+// says fma), so that each kernel that evaluates them rounds alike.
+//
+// Pulsating frame at stage weight w: (x', y', w Omega_x + 2 y', w Omega_y -
+// 2 x'), Omega = (x^2 + y^2)/2 + (1 - mu)/r1 + mu/r2, r1 = |(x + mu, y)|,
+// r2 = |(x - 1 + mu, y)|.
+MS_D void puls_field(const Model &md, double w, double (&s)[4])
+{
+    const double x = s[0], y = s[1], p = s[2], q = s[3];
+    const double d1 = x + md.mu, d2 = x - md.one_minus_mu, y2 = y * y;
+    const double g1 = mass_over_r3(md.one_minus_mu, fma(d1, d1, y2));
+    const double g2 = mass_over_r3(md.mu, fma(d2, d2, y2));
+    s[0] = p;
+    s[1] = q;
+    s[2] = fma(w, fma(-g1, d1, fma(-g2, d2, x)), q + q);
+    s[3] = fma(w, fma(-(g1 + g2), y, y), -(p + p));
+}
+
+// The pulsating field with one tangent column in s[4..7]: v' = A v, plus
+// dF/de (dwde = dw/de at the stage, 0 for a column of the state).
+MS_D void puls_field_var(const Model &md, double w, double dwde, double (&s)[8])
+{
+    const double x = s[0], y = s[1], p = s[2], q = s[3];
+    const double d1 = x + md.mu, d2 = x - md.one_minus_mu, y2 = y * y;
+    double q1, q2;
+    const double g1 = mass_over_r3(md.one_minus_mu, fma(d1, d1, y2), q1);
+    const double g2 = mass_over_r3(md.mu, fma(d2, d2, y2), q2);
+    const double h1 = 3.0 * g1 * q1, h2 = 3.0 * g2 * q2;                 // 3 m_i / r_i^5
+    const double gs = g1 + g2, u = 1.0 - gs, t1 = h1 * d1, t2 = h2 * d2;
+    const double ox = fma(-g1, d1, fma(-g2, d2, x)), oy = fma(-gs, y, y);
+    const double oxx = fma(t1, d1, fma(t2, d2, u)), oyy = fma(h1 + h2, y2, u), oxy = (t1 + t2) * y;
+    const double a = s[4], b = s[5], c = s[6], d = s[7];
+    s[0] = p;
+    s[1] = q;
+    s[2] = fma(w, ox, q + q);
+    s[3] = fma(w, oy, -(p + p));
+    s[4] = c;
+    s[5] = d;
+    s[6] = fma(w, fma(oxx, a, oxy * b), fma(dwde, ox, d + d));
+    s[7] = fma(w, fma(oxy, a, oyy * b), fma(dwde, oy, -(c + c)));
 }
 
 // Position-momentum model (Sec. 3.3) at a stage with separation rho and
 // frame rate n: z' = J grad H for
 //   H = (px^2 + py^2)/2 + n (px y - py x) - (1 - mu)/r1 - mu/r2,
-//   r1 = |(x + mu rho, y)|, r2 = |(x - (1 - mu) rho, y)|.
-MS_D void pm_field(const Model &md, double rho, double n, const double z[4], double k[4])
-{
-#pragma clang fp contract(fast)
-    double x = z[0], y = z[1];
-    double d1 = x + md.mu * rho, d2 = x - md.one_minus_mu * rho;
-    double y2 = y * y;
-    double r1s = d1 * d1 + y2, r2s = d2 * d2 + y2;
-    double i1 = inv_sqrt(r1s), i2 = inv_sqrt(r2s);
-    double a1 = md.one_minus_mu * (i1 * i1) * i1, a2 = md.mu * (i2 * i2) * i2;   // m_i / r_i^3
-    k[0] = z[2] + n * y;
-    k[1] = z[3] - n * x;
-    k[2] = n * z[3] - a1 * d1 - a2 * d2;
-    k[3] = -n * z[2] - (a1 + a2) * y;
-}
-
-// The same field with NC tangent columns v: v' = J Hess(H) v.
+//   r1 = |(x + mu rho, y)|, r2 = |(x - (1 - mu) rho, y)|,
+// with NC tangent columns v' = J Hess(H) v behind the state (column c in
+// s[4 + 4 c ..]).
 template <int NC>
-MS_D void pm_field_var(const Model &md, double rho, double n, const double z[4], const double v[NC][4],
-                       double k[4], double kv[NC][4])
+MS_D void pm_field(const Model &md, double rho, double n, double (&s)[4 + 4 * NC])
 {
-#pragma clang fp contract(fast)
-    double x = z[0], y = z[1];
-    double d1 = x + md.mu * rho, d2 = x - md.one_minus_mu * rho;
-    double y2 = y * y;
-    double r1s = d1 * d1 + y2, r2s = d2 * d2 + y2;
-    double i1 = inv_sqrt(r1s), i2 = inv_sqrt(r2s);
-    double q1 = i1 * i1, q2 = i2 * i2;                                     // 1 / r_i^2
-    double a1 = md.one_minus_mu * q1 * i1, a2 = md.mu * q2 * i2;          // m_i / r_i^3
-    double b1 = 3.0 * a1 * q1, b2 = 3.0 * a2 * q2;                         // 3 m_i / r_i^5
-    double hxx = a1 + a2 - b1 * d1 * d1 - b2 * d2 * d2;
-    double hyy = a1 + a2 - (b1 + b2) * y2;
-    double hxy = -(b1 * d1 + b2 * d2) * y;
-    k[0] = z[2] + n * y;
-    k[1] = z[3] - n * x;
-    k[2] = n * z[3] - a1 * d1 - a2 * d2;
-    k[3] = -n * z[2] - (a1 + a2) * y;
+    const double x = s[0], y = s[1], p = s[2], q = s[3];
+    const double d1 = fma(md.mu, rho, x), d2 = fma(-md.one_minus_mu, rho, x), y2 = y * y;
+    const double r1 = fma(d1, d1, y2), r2 = fma(d2, d2, y2);
+    double g1, g2, q1 = 0.0, q2 = 0.0;
+    if constexpr (NC > 0) {
+        g1 = mass_over_r3(md.one_minus_mu, r1, q1);
+        g2 = mass_over_r3(md.mu, r2, q2);
+    } else {
+        g1 = mass_over_r3(md.one_minus_mu, r1);
+        g2 = mass_over_r3(md.mu, r2);
+    }
+    const double gs = g1 + g2;
+    s[0] = fma(n, y, p);
+    s[1] = fma(-n, x, q);
+    s[2] = fma(-g1, d1, fma(-g2, d2, n * q));
+    s[3] = fma(-gs, y, -(n * p));
+    if constexpr (NC > 0) {
+        const double h1 = 3.0 * g1 * q1, h2 = 3.0 * g2 * q2;             // 3 m_i / r_i^5
+        const double t1 = h1 * d1, t2 = h2 * d2;
+        const double hxx = fma(-t1, d1, fma(-t2, d2, gs)), hyy = fma(-(h1 + h2), y2, gs), hxy = -((t1 + t2) * y);
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-        kv[c][0] = v[c][2] + n * v[c][1];
-        kv[c][1] = v[c][3] - n * v[c][0];
-        kv[c][2] = n * v[c][3] - hxx * v[c][0] - hxy * v[c][1];
-        kv[c][3] = -n * v[c][2] - hxy * v[c][0] - hyy * v[c][1];
+        for (int c = 0; c < NC; ++c) {
+            double *v = s + 4 + 4 * c;
+            const double a = v[0], b = v[1], pa = v[2], pb = v[3];
+            v[0] = fma(n, b, pa);
+            v[1] = fma(-n, a, pb);
+            v[2] = fma(-hxx, a, fma(-hxy, b, n * pb));
+            v[3] = fma(-hxy, a, fma(-hyy, b, -(n * pa)));
+        }
     }
 }
 
-// Gradient and Hessian of Omega at (x, y).
-struct OmegaD {
-    double Ox, Oy, Oxx, Oxy, Oyy;
-};
-
-MS_D OmegaD omega_derivs(const Model &md, double x, double yy)
+// One step of y (D components) with the scaled coefficients c[0..43];
+// field(i, s) evaluates the right-hand side of stage i in place.  The stage
+// sums are taken in an order that keeps at most five D-vectors live (and y):
+// stage 6 is opened before stages 2 and 3 are dropped, and stages 8 to 10
+// and the increment are opened as soon as stage 6 is known, when the stages
+// 0, 4, 5 and 6 are dropped.  The increment is summed on its own and added
+// to y once, so that a step rounds at y's magnitude once; the stage values,
+// whose rounding enters the step times h, are summed from y.  (With all stage derivatives kept to the end, the map
+// needed 118 registers, and the state with four tangent columns 440, of
+// which it moved the part above 256 to and from the accumulation registers,
+// 770 moves a step.)
+template <int D, typename C, typename F>
+MS_D void rk_step(double (&y)[D], const C &c, F &&field)
 {
-#pragma clang fp contract(fast)
-    double dx1 = x + md.mu, dx2 = x - md.one_minus_mu;
-    double yy2 = yy * yy;
-    double r1s = dx1 * dx1 + yy2, r2s = dx2 * dx2 + yy2;
-    double i1 = inv_sqrt(r1s), i2 = inv_sqrt(r2s);
-    double q1 = i1 * i1, q2 = i2 * i2;                                    // 1 / r_i^2
-    double g1 = md.one_minus_mu * q1 * i1, g2 = md.mu * q2 * i2;         // (1-mu)/r1^3, mu/r2^3
-    double h1 = 3.0 * g1 * q1, h2 = 3.0 * g2 * q2;                        // 3(1-mu)/r1^5, 3 mu/r2^5
-    OmegaD o;
-    o.Ox = x - g1 * dx1 - g2 * dx2;
-    o.Oy = yy - (g1 + g2) * yy;
-    o.Oxx = 1.0 - g1 - g2 + h1 * dx1 * dx1 + h2 * dx2 * dx2;
-    o.Oyy = 1.0 - g1 - g2 + (h1 + h2) * yy2;
-    o.Oxy = (h1 * dx1 + h2 * dx2) * yy;
-    return o;
+    // Nothing is moved across a stage's end (nor, within one, the sums ahead
+    // of the field): the scheduler would trade registers for latency there.
+    auto fence = [] { if constexpr (D > 8) __builtin_amdgcn_sched_barrier(0); };
+    double k0[D], k1[D], k2[D], k3[D], k4[D], k5[D], k6[D], k7[D], k8[D], b[D];
+#define MS_EACH for (int d = 0; d < D; ++d)
+#pragma unroll
+    MS_EACH k0[d] = y[d];
+    field(0, k0);
+    fence();
+#pragma unroll
+    MS_EACH k1[d] = fma(c[0], k0[d], y[d]);
+    fence();
+    field(1, k1);
+    fence();
+#pragma unroll
+    MS_EACH k2[d] = fma(c[2], k1[d], fma(c[1], k0[d], y[d]));
+#pragma unroll
+    MS_EACH k1[d] = fma(c[4], k1[d], fma(c[3], k0[d], y[d]));      // stage 3, opened
+    fence();
+    field(2, k2);
+    fence();
+#pragma unroll
+    MS_EACH k3[d] = fma(c[5], k2[d], k1[d]);
+    fence();
+    field(3, k3);
+    fence();
+#pragma unroll
+    MS_EACH k4[d] = fma(c[8], k3[d], fma(c[7], k2[d], fma(c[6], k0[d], y[d])));
+    fence();
+    field(4, k4);
+    fence();
+#pragma unroll
+    MS_EACH {
+        k5[d] = fma(c[12], k4[d], fma(c[11], k3[d], fma(c[10], k2[d], fma(c[9], k0[d], y[d]))));
+        k6[d] = fma(c[16], k4[d], fma(c[15], k3[d], fma(c[14], k2[d], fma(c[13], k0[d], y[d]))));
+    }
+    fence();
+    field(5, k5);
+    fence();
+#pragma unroll
+    MS_EACH k6[d] = fma(c[17], k5[d], k6[d]);
+    fence();
+    field(6, k6);
+    fence();
+#pragma unroll
+    MS_EACH {
+        const double z0 = k0[d], z4 = k4[d], z5 = k5[d], z6 = k6[d];
+        k7[d] = fma(c[21], z6, fma(c[20], z5, fma(c[19], z4, fma(c[18], z0, y[d]))));
+        k8[d] = fma(c[25], z6, fma(c[24], z5, fma(c[23], z4, fma(c[22], z0, y[d]))));
+        k5[d] = fma(c[30], z6, fma(c[29], z5, fma(c[28], z4, fma(c[27], z0, y[d]))));     // stage 9
+        k6[d] = fma(c[35], z6, fma(c[34], z5, fma(c[33], z4, y[d])));                     // stage 10
+        b[d] = c[39] * z0;
+    }
+    fence();
+    field(7, k7);
+    fence();
+#pragma unroll
+    MS_EACH {
+        k8[d] = fma(c[26], k7[d], k8[d]);
+        k5[d] = fma(c[31], k7[d], k5[d]);
+        k6[d] = fma(c[36], k7[d], k6[d]);
+        b[d] = fma(c[40], k7[d], b[d]);
+    }
+    fence();
+    field(8, k8);
+    fence();
+#pragma unroll
+    MS_EACH {
+        k5[d] = fma(c[32], k8[d], k5[d]);
+        k6[d] = fma(c[37], k8[d], k6[d]);
+        b[d] = fma(c[41], k8[d], b[d]);
+    }
+    fence();
+    field(9, k5);
+    fence();
+#pragma unroll
+    MS_EACH {
+        k6[d] = fma(c[38], k5[d], k6[d]);
+        b[d] = fma(c[42], k5[d], b[d]);
+    }
+    fence();
+    field(10, k6);
+    fence();
+#pragma unroll
+    MS_EACH y[d] += fma(c[43], k6[d], b[d]);
+#undef MS_EACH
+}
+
+// The scaled coefficients of a kernel whose first parameter is an RkCoef, as
+// a pointer that the compiler knows nothing about: taken once per step, so
+// that the 88 scalar registers they fill are loaded again (from the scalar
+// cache) where they are used.  Kept across the loop they would be spilled
+// to vector lanes, two v_readlane each use.
+using CoefPtr = const __attribute__((address_space(4))) double *;
+
+MS_D CoefPtr step_coef()
+{
+    CoefPtr p = (CoefPtr)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return p;
 }
 
 }  // namespace ms
