@@ -2,7 +2,8 @@
 // problem (pulsating rotating coordinates, true anomaly as time), fixed-step
 // explicit Runge-Kutta of order 8 (Cooper & Verner 1972, 11 stages).
 //
-// One thread per state; the tableau is a kernel argument (scalar loads).  The
+// One thread per state; the scaled tableau is a kernel argument (scalar
+// loads).  Five waves per SIMD (96 registers, nothing spilled).  The
 // stage weights w(f) = 1 / (1 + e cos f) are the same for every state, so
 // each block computes them for RK_CHUNK steps at a time into LDS (w is 2 pi
 // periodic and even, so the values of one period serve every period and
