@@ -381,8 +381,8 @@ typedef struct {
  * AoS 4 doubles each, by the 11-stage order-8 explicit Runge-Kutta method of
  * Cooper & Verner (1972) with fixed steps (the globalization maps
  * F^{+-k} of Sec. 4.3).  in_dev may equal out_dev.  Asynchronous: queues one
- * kernel (the stage weights w(f) are computed on the GPU inside it), allocates
- * nothing, never synchronises, and can be captured into a HIP graph.
+ * kernel, or several that each take part of the steps (the stage weights w(f)
+ * are computed on the GPU inside them), allocates nothing, never synchronises, and can be captured into a HIP graph.
  */
 int propagate_vertices(const double *in_dev, double *out_dev, int64_t n_vertices,
                        const map_params_t *params, void *stream);
@@ -418,9 +418,10 @@ int pertbp_map(const double *in_dev, double *out_dev, int64_t n_states, const ma
  *   stm_dev  n_states x 16, row-major per state: stm[16 p + 4 i + j] =
  *            d out_i / d in_j; must not overlap in_dev or out_dev.
  *   cols_per_thread  1, 2 or 4 columns of DF per GPU thread (4 / cols
- *            threads per state), or 0 for the default (4 from 131,072 states
- *            up, 2 from 65,536, else 1); a tuning choice only, the results
- *            are identical.
+ *            threads per state), a tuning choice only, the results are
+ *            identical; or 0 for the default (4 above 32,768 states, 2 above
+ *            16,384, 1 above 6,144, else two lanes per column, whose sums
+ *            may round differently in the last bits).
  * Asynchronous; errors as pertbp_map. */
 int pertbp_map_stm(const double *in_dev, double *out_dev, double *stm_dev, int64_t n_states,
                    const map_params_t *params, int32_t cols_per_thread, void *stream);
@@ -554,8 +555,8 @@ enum {
  * hits.  Holds the stage values of one period per side (steps_per_period x 11
  * doubles of w(f), and as many of dw/de except in residual mode, computed by
  * the call itself); the adjoint also needs K x 2 x (steps / ckpt_every) x 32 B
- * of checkpoints plus a window of recomputed states and step Jacobians (at
- * most 256 MiB, at least one checkpoint segment). */
+ * of checkpoints plus a window of segment start states and segment Jacobians
+ * (at most 256 MiB, at least one segment). */
 int refine_workspace_size(int64_t K, const map_params_t *fwd, const map_params_t *bwd, int32_t ckpt_every,
                           int32_t mode, size_t *bytes);
 
@@ -567,10 +568,11 @@ int refine_workspace_size(int64_t K, const map_params_t *fwd, const map_params_t
  *   grad_dev    K x 5: dr/d(th1, s1, th2, s2, e) (adjoint and tangent modes);
  *   J_dev       K x 4 x 5, row-major (tangent mode, optional).
  * The adjoint runs the map forwards keeping the state every ckpt_every steps,
- * then goes backwards over windows of whole checkpoint segments: the states of
- * a window are recomputed from their checkpoints, the Jacobian of every step
- * of the window (and its derivative with respect to e) is formed in parallel,
- * and the cotangent is carried back through the transposed steps; the result
+ * then goes backwards over windows of whole segments of 100 steps: the states
+ * at a window's segment starts are recomputed from the checkpoints (with
+ * ckpt_every = 100 they are the checkpoints), the Jacobian of every segment's
+ * steps (and its derivative with respect to e) is formed in parallel, and the
+ * cotangent is carried back through the transposed segments; the result
  * does not depend on ckpt_every (bit for bit).  The tangent integrates the
  * variational equations with the same method, so both give the derivative of
  * the discrete map.  ws: refine_workspace_size bytes (the call writes every

@@ -23,20 +23,20 @@
 
 #include <string>
 
-#include "rk8_core.hpp"
+#include "rk8_pair.hpp"
 
 namespace ms {
 namespace {
 
 constexpr int S = RK_S;
-constexpr int PM_BLOCK = 128;
+constexpr int PM_BLOCK = FLOW_BLOCK;
 
 // NC = 0: state only.  NC > 0: state and tangent columns g NC .. g NC + NC - 1
 // of DF, g = thread index within its state.
 template <int NC>
-__global__ void __launch_bounds__(PM_BLOCK) __attribute__((amdgpu_waves_per_eu(NC == 0 ? 5 : NC == 1 ? 3 : NC == 2 ? 2 : 1, 8))) k_pm_flow(RkCoef, const double *__restrict__ in, double *out,
-                                                      double *__restrict__ stm, int64_t n, Model md, double ecc,
-                                                      int steps, int64_t nsteps)
+__global__ void __launch_bounds__(PM_BLOCK) __attribute__((amdgpu_waves_per_eu(NC == 0 ? 5 : NC == 1 ? 3 : NC == 2 ? 2 : 1, 8)))
+k_pm_flow(RkCoef, const double *in, double *out, double *stm, int64_t n, Model md, double ecc, int steps,
+          int64_t nsteps, FlowPlan plan, int64_t unit0)
 {
     constexpr int G = NC > 0 ? 4 / NC : 1;   // threads per state
     constexpr int D = 4 + 4 * NC;            // the state, then the thread's columns
@@ -45,22 +45,25 @@ __global__ void __launch_bounds__(PM_BLOCK) __attribute__((amdgpu_waves_per_eu(N
 #pragma unroll
     for (int i = 0; i < S; ++i)
         if (threadIdx.x == i) s_c[i] = RK_T.c[i];
-    const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const FlowUnit u = flow_unit(plan, unit0 + blockIdx.x, nsteps);
+    if (!u.ok) return;
+    const int64_t gid = u.block * blockDim.x + threadIdx.x;
     const bool live = gid < n * G;      // every thread of the block fills the stage values
     const int64_t p = live ? gid / G : 0;
     const int g = (int)(gid - (gid / G) * G);
     double z[D];
     if (live) {
-        const d4 s = load_d4(in + 4 * p);
+        const d4 s = load_d4((u.s0 == 0 ? in : out) + 4 * p);
         z[0] = s.x; z[1] = s.y; z[2] = s.z; z[3] = s.w;
     }
 #pragma unroll
     for (int c = 0; c < NC; ++c)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) z[4 + 4 * c + i] = (i == g * NC + c) ? 1.0 : 0.0;
-    int64_t n_in = 0;
-    for (int64_t st0 = 0; st0 < nsteps; st0 += RK_CHUNK) {
-        const int cnt = nsteps - st0 < RK_CHUNK ? (int)(nsteps - st0) : RK_CHUNK;
+        for (int i = 0; i < 4; ++i)
+            z[4 + 4 * c + i] = u.s0 > 0 && live ? stm[16 * p + 4 * i + g * NC + c] : (i == g * NC + c) ? 1.0 : 0.0;
+    int64_t n_in = u.s0 % steps;
+    for (int64_t st0 = u.s0; st0 < u.s1; st0 += RK_CHUNK) {
+        const int cnt = u.s1 - st0 < RK_CHUNK ? (int)(u.s1 - st0) : RK_CHUNK;
         __syncthreads();      // the previous chunk's values are no longer read (and s_c is written)
         fill_stage_chunk(s_rn, s_c, n_in, cnt, steps, [&](double t) { return kepler_rho_n(t, ecc); });
         __syncthreads();
@@ -86,6 +89,16 @@ __global__ void __launch_bounds__(PM_BLOCK) __attribute__((amdgpu_waves_per_eu(N
     }
 }
 
+// COLS = 0 or 4: the map, or the map and DF, on pairs of lanes.
+template <int COLS>
+__global__ void __launch_bounds__(PAIR_BLOCK) k_pm_pair(RkCoef hc, const double *in, double *out, double *stm,
+                                                        int64_t n, Model md, double ecc, int steps, int64_t nsteps)
+{
+    pair_flow<double2, COLS>(
+        hc, in, out, stm, n, md, steps, nsteps, [&](double t) { return kepler_rho_n(t, ecc); },
+        [](const PairLane &L, const double2 &rn, double (&s)[COLS ? 4 : 2]) { pm_pair<COLS != 0>(L, rn.x, rn.y, s); });
+}
+
 int pm_check(const char *who, const double *in_dev, const void *out_dev, int64_t n, const map_params_t *p)
 {
     const std::string w(who);
@@ -94,6 +107,18 @@ int pm_check(const char *who, const double *in_dev, const void *out_dev, int64_t
     if (!(p->e >= 0.0 && p->e < 1.0) || !(p->mu >= 0.0 && p->mu <= 1.0))
         return fail(MS_E_ARG, w + ": need 0 <= e < 1 and 0 <= mu <= 1");
     if (!cv_pattern_ok()) return fail(MS_E_ARG, w + ": internal tableau pattern mismatch");
+    return MS_OK;
+}
+
+template <int COLS>
+int pm_pair_launch(const double *in, double *out, double *stm, int64_t n, const map_params_t *p, hipStream_t st)
+{
+    const int np = p->n_periods < 0 ? -p->n_periods : p->n_periods;
+    const int64_t nsteps = (int64_t)p->steps_per_period * np;
+    const double h = (p->n_periods < 0 ? -RK_TWO_PI : RK_TWO_PI) / (double)p->steps_per_period;
+    hipLaunchKernelGGL(k_pm_pair<COLS>, dim3(pair_blocks(n * (COLS ? COLS : 1))), dim3(PAIR_BLOCK), 0, st, rk_coef(h),
+                       in, out, stm, n, Model{p->mu, 1.0 - p->mu}, p->e, p->steps_per_period, nsteps);
+    MS_HIP(hipGetLastError());
     return MS_OK;
 }
 
@@ -108,9 +133,13 @@ int pm_launch(const double *in, double *out, double *stm, int64_t n, const map_p
     // The launch counts work-items in 32 bits.
     if (n > (((int64_t)1 << 32) - PM_BLOCK) / G) return fail(MS_E_ARG, "pertbp: too many states for one launch");
     Model md{p->mu, 1.0 - p->mu};
-    hipLaunchKernelGGL(k_pm_flow<NC>, dim3((unsigned)ceil_div(threads, PM_BLOCK)), dim3(PM_BLOCK), 0, st, rk_coef(h),
-                       in, out, stm, n, md, p->e, p->steps_per_period, nsteps);
-    MS_HIP(hipGetLastError());
+    // between launches the state waits in out (the columns in stm)
+    const FlowPlan plan = flow_plan(ceil_div(threads, PM_BLOCK), nsteps, out != nullptr);
+    for (int l = 0; l < plan.launches; ++l) {
+        hipLaunchKernelGGL(k_pm_flow<NC>, dim3(plan.grid), dim3(PM_BLOCK), 0, st, rk_coef(h), in, out, stm, n, md, p->e,
+                           p->steps_per_period, nsteps, plan, (int64_t)l * plan.grid);
+        MS_HIP(hipGetLastError());
+    }
     return MS_OK;
 }
 
@@ -124,6 +153,7 @@ extern "C" int pertbp_map(const double *in_dev, double *out_dev, int64_t n_state
 {
     int rc = pm_check("pertbp_map", in_dev, out_dev, n_states, p);
     if (rc || n_states == 0) return rc;
+    if (n_states <= PAIR_STATES) return pm_pair_launch<0>(in_dev, out_dev, nullptr, n_states, p, (hipStream_t)stream);
     return pm_launch<0>(in_dev, out_dev, nullptr, n_states, p, (hipStream_t)stream);
 }
 
@@ -132,9 +162,15 @@ extern "C" int pertbp_map_stm(const double *in_dev, double *out_dev, double *stm
 {
     int rc = pm_check("pertbp_map_stm", in_dev, stm_dev, n_states, p);
     if (rc) return rc;
-    // default: four columns per thread (the least work per state) once the
-    // batch fills the chip with them, else more threads per state
-    if (cols_per_thread == 0) cols_per_thread = n_states >= (1 << 17) ? 4 : n_states >= (1 << 16) ? 2 : 1;
+    // default: the fewest instructions a state whose threads leave no SIMD
+    // with more than one wave (a second wave doubles the time: a lone wave
+    // issues at nine tenths of the rate): a period of 4000 steps takes 6.2 ms
+    // on pairs of lanes up to 6,144 states, 8.5 ms at 1 column per thread up
+    // to 16,384, 11.1 ms at 2 up to 32,768 and 15.0 ms at 4 up to 65,536;
+    // beyond, 4 columns take the least work (60 ms for 262,144 states; 78 at
+    // 2, 122 at 1)
+    const bool pair = cols_per_thread == 0 && n_states <= PAIR_MATRICES;
+    if (cols_per_thread == 0) cols_per_thread = n_states <= 16384 ? 1 : n_states <= 32768 ? 2 : 4;
     if (cols_per_thread != 1 && cols_per_thread != 2 && cols_per_thread != 4)
         return fail(MS_E_ARG, "pertbp_map_stm: cols_per_thread must be 0, 1, 2 or 4");
     if (n_states == 0) return MS_OK;
@@ -145,6 +181,7 @@ extern "C" int pertbp_map_stm(const double *in_dev, double *out_dev, double *stm
         (const void *)stm_dev < (const void *)(in_dev + 4 * n_states))
         return fail(MS_E_ARG, "pertbp_map_stm: in and stm overlap");
     hipStream_t st = (hipStream_t)stream;
+    if (pair) return pm_pair_launch<4>(in_dev, out_dev, stm_dev, n_states, p, st);
     switch (cols_per_thread) {
     case 1: return pm_launch<1>(in_dev, out_dev, stm_dev, n_states, p, st);
     case 2: return pm_launch<2>(in_dev, out_dev, stm_dev, n_states, p, st);

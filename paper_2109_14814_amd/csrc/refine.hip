@@ -10,21 +10,22 @@
 //     matrices DF^m of Sec. 7, applied to the patch directions), exactly the
 //     derivative of the discrete map; e enters through w(f) = 1/(1 + e cos f);
 //   * adjoint: the gradient of r by the discrete adjoint (transpose) of every
-//     Runge-Kutta step, run backwards from the seed dr/dF = +-2f, with the
-//     forward states kept only every `ckpt_every` steps and recomputed one
-//     window of segments at a time;
+//     Runge-Kutta step, run backwards from the seed dr/dF = +-2f a segment of
+//     steps at a time, with the forward states kept only every `ckpt_every`
+//     steps;
 //   * damped Newton (Sec. 7): x <- x - alpha Df^{-1} f, alpha halved until r
 //     decreases.
 //
-// One thread per trajectory (hit, side) for the state pass, per (trajectory,
-// tangent column) for the tangent pass and per (step, trajectory, column) for
-// the adjoint's step Jacobians; blocks of one wave, so that the few hundred to
+// Two lanes per trajectory (hit, side) for the state pass and per
+// (trajectory, tangent column) for the tangent pass (one each in batches that
+// fill the chip), one thread per (segment, trajectory, column) for the
+// adjoint's segment Jacobians; blocks of one wave, so that the few hundred to
 // few thousand trajectories spread over the compute units.
 #include <math.h>
 #include <string.h>
 
 #include "newton.hpp"
-#include "rk8_core.hpp"
+#include "rk8_pair.hpp"
 
 namespace ms {
 
@@ -68,97 +69,177 @@ MS_D void store_d4(double *p, const double *y)
     o[1] = make_double2(y[2], y[3]);
 }
 
-// Start of trajectory t: side, hit, patch point x(th, s) = base + th d1 + s d2
-// (each operation rounded as written).
-MS_D int traj_start(const RefArgs &a, int64_t t, int &side, int64_t &k, double y[4], const double *&patch)
+// Start of a hit's trajectory on one side: the patch point x(th, s) =
+// base + th d1 + s d2 (each operation rounded as written).
+MS_D void traj_start(const RefArgs &a, int side, int64_t k, double y[4], const double *&patch)
 {
-    side = t >= a.K ? 1 : 0;
-    k = t - (side ? a.K : 0);
     const double *pr = a.params + 4 * k + 2 * side;
     patch = (side ? a.Sp : a.U) + a.pstride * k;
     double th = pr[0], s = pr[1];
 #pragma unroll
     for (int c = 0; c < 4; ++c) y[c] = (patch[c] + th * patch[4 + c]) + s * patch[8 + c];
-    return 0;
 }
 
 MS_D bool hit_active(const RefArgs &a, int64_t k) { return a.status == nullptr || a.status[k] < 0; }
 
-// Trajectory of a thread: the grid's y index is the side, so that the step
-// and its coefficients are the same for every thread of a wave.
+// The coefficients of a side for one-lane steps (k_adj_segments and large
+// batches): scalar, as the side is the grid's y index and so the same for
+// every thread.
 MS_D CoefPtr side_coef(int side) { return step_coef() + side * RK_NC; }
 
-// One step of the map on the state alone.  Every operation of rk_step and of
-// the field is written out, so that the forward pass and the adjoint's
-// recomputation of a segment reproduce the same states bit for bit.
-MS_D void rk_state_step(double (&y)[4], const double *__restrict__ w, int side, const Model &md)
+// Hits up to which trajectories run on pairs of lanes (one wave per SIMD then
+// holds them all: 12,000 steps in 9.1 ms, 16 ms with one lane each); the rule
+// depends on K alone, so that the forward pass and the adjoint's
+// recomputation run the same code.
+constexpr int64_t PAIR_HITS = 16384;
+
+// Steps [s0, s1) of a trajectory, on a block of one wave: of the state alone
+// (COL = false) or of the state and one tangent column (the variational
+// equations v' = A(f, y) v, plus dF/de when `ecol`, integrated with the same
+// stages, which is the exact derivative of the discrete step).  PAIR: two
+// lanes per trajectory, y = (own coordinate, own velocity, then the
+// column's); else y = (x, y, x', y', then the column).  The stage values of
+// RK_CHUNK steps lie in LDS and the next chunk's are on their way from the
+// tables meanwhile.  before(s, y) sees the state before step s.
+template <bool PAIR, bool COL>
+constexpr int flow_dim() { return (PAIR ? 2 : 4) * (COL ? 2 : 1); }
+
+template <bool PAIR, bool COL, typename BEFORE>
+MS_D void ref_flow(const RefArgs &a, int side, bool live, int64_t s0, int64_t s1, bool ecol,
+                   double (&y)[flow_dim<PAIR, COL>()], BEFORE &&before)
 {
-    rk_step<4>(y, side_coef(side), [&](int i, double (&s)[4]) { puls_field(md, w[i], s); });
+    constexpr int D = flow_dim<PAIR, COL>(), N = RK_CHUNK * S, PER = (N + RF_BLOCK - 1) / RF_BLOCK;
+    __shared__ double s_w[N], s_d[COL ? N : 1];
+    const SideMap &sm = a.side[side];
+    const int64_t tot = (int64_t)sm.steps * S;
+    const double ec = ecol ? 1.0 : 0.0;
+    double nw[PER], nd[COL ? PER : 1];
+    auto fetch = [&](int64_t s) {
+        const int64_t base = (s % sm.steps) * S;
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const int i = threadIdx.x + q * RF_BLOCK;
+            int64_t k = base + i;
+            while (k >= tot) k -= tot;
+            if (i < N) {
+                nw[q] = sm.w[k];
+                if constexpr (COL) nd[q] = sm.dwde[k];
+            }
+        }
+    };
+    PairCoef pc;
+    PairLane L;
+    if constexpr (PAIR) {
+        pair_coef(pc, a.hc[side]);
+        L = pair_lane(a.md, threadIdx.x & 1);
+    }
+    if (s0 < s1) fetch(s0);
+    for (int64_t sc = s0; sc < s1; sc += RK_CHUNK) {
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const int i = threadIdx.x + q * RF_BLOCK;
+            if (i < N) {
+                s_w[i] = nw[q];
+                if constexpr (COL) s_d[i] = nd[q];
+            }
+        }
+        __syncthreads();
+        if (sc + RK_CHUNK < s1) fetch(sc + RK_CHUNK);
+        const int cnt = s1 - sc < RK_CHUNK ? (int)(s1 - sc) : RK_CHUNK;
+        if (!live) continue;
+#pragma unroll 1
+        for (int jj = 0; jj < cnt; ++jj) {
+            before(sc + jj, y);
+            const double *w = s_w + jj * S, *d = s_d + jj * S;
+            if constexpr (PAIR) {
+                rk_step<D>(y, pc, [&](int i, double (&s)[D]) {
+                    puls_pair<COL>(L, w[i], COL ? ec * d[i] : 0.0, s);
+                });
+            } else {
+                rk_step<D>(y, side_coef(side), [&](int i, double (&s)[D]) {
+                    if constexpr (COL) puls_field_var(a.md, w[i], ec * d[i], s);
+                    else puls_field(a.md, w[i], s);
+                });
+            }
+        }
+    }
 }
 
-// One step of the state (y[0..3]) together with one tangent column
-// (y[4..7]): the variational equations v' = A(f, y) v (+ dF/de when `ecol`),
-// integrated with the same stages, which is the exact derivative of the
-// discrete step.
-MS_D void rk_tangent_step(double (&y)[8], const double *__restrict__ w, const double *__restrict__ dwde, int side,
-                          const Model &md, bool ecol)
+// A trajectory's four components to or from the lane's part of y (v: the
+// first of them, at y[OFF]).
+template <bool PAIR, int OFF, int D>
+MS_D void put_state(double *p, const double (&y)[D])
 {
-    rk_step<8>(y, side_coef(side),
-               [&](int i, double (&s)[8]) { puls_field_var(md, w[i], ecol ? dwde[i] : 0.0, s); });
+    if constexpr (PAIR) {
+        const int l = threadIdx.x & 1;
+        p[l] = y[OFF];
+        p[2 + l] = y[OFF + 1];
+    } else {
+        store_d4(p, y + OFF);
+    }
 }
 
-MS_D const double *stage_row(const double *tab, int64_t s, int32_t steps)
+template <bool PAIR, int OFF, int D>
+MS_D void get_state(const double *p, double (&y)[D])
 {
-    return tab + (size_t)(s % steps) * S;
+    if constexpr (PAIR) {
+        const int l = threadIdx.x & 1;
+        y[OFF] = p[l];
+        y[OFF + 1] = p[2 + l];
+    } else {
+        const d4 v = load_d4(p);
+        y[OFF] = v.x; y[OFF + 1] = v.y; y[OFF + 2] = v.z; y[OFF + 3] = v.w;
+    }
 }
 
 // State pass: endpoint of every trajectory; with a.ckpt, the state before
-// every ck-th step.
+// every ck-th step.  The grid's y index is the side.
+template <bool PAIR>
 __global__ void __launch_bounds__(RF_BLOCK) k_ref_state(RefArgs a)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= a.K) return;
-    const int64_t t = blockIdx.y * a.K + i;
-    int side;
-    int64_t k;
-    double y[4];
-    const double *patch;
-    traj_start(a, t, side, k, y, patch);
-    if (!hit_active(a, k)) return;
-    const SideMap sm = a.side[blockIdx.y];
-    const int64_t T2 = 2 * a.K;
-    for (int64_t s = 0; s < sm.nsteps; ++s) {
-        if (a.ckpt && s % a.ck == 0) store_d4(a.ckpt + ((s / a.ck) * T2 + t) * 4, y);
-        rk_state_step(y, stage_row(sm.w, s, sm.steps), blockIdx.y, a.md);
+    constexpr int D = flow_dim<PAIR, false>();
+    const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / (PAIR ? 2 : 1);
+    const int64_t T2 = 2 * a.K, t = blockIdx.y * a.K + i;
+    const bool live = i < a.K && hit_active(a, i);
+    double y[D] = {};
+    if (live) {
+        double y0[4];
+        const double *patch;
+        traj_start(a, blockIdx.y, i, y0, patch);
+        get_state<PAIR, 0>(y0, y);
     }
-    store_d4(a.yend + 4 * t, y);
+    int64_t next = 0;      // the next checkpoint's step
+    ref_flow<PAIR, false>(a, blockIdx.y, live, 0, a.side[blockIdx.y].nsteps, false, y, [&](int64_t s, double (&v)[D]) {
+        if (a.ckpt && s == next) {
+            put_state<PAIR, 0>(a.ckpt + ((s / a.ck) * T2 + t) * 4, v);
+            next += a.ck;
+        }
+    });
+    if (live) put_state<PAIR, 0>(a.yend + 4 * t, y);
 }
 
-// Tangent pass: thread (column c, trajectory t); columns d/dth, d/ds, d/de.
+// Tangent pass: a trajectory and one of its columns d/dth, d/ds, d/de.
+template <bool PAIR>
 __global__ void __launch_bounds__(RF_BLOCK) k_ref_tangent(RefArgs a)
 {
-    const int64_t T2 = 2 * a.K;
-    const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (gid >= 3 * a.K) return;
+    constexpr int D = flow_dim<PAIR, true>(), C = D / 2;
+    const int64_t gid = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / (PAIR ? 2 : 1);
     const int col = (int)(gid / a.K);
-    const int64_t t = blockIdx.y * a.K + (gid - col * a.K);
-    int side;
-    int64_t k;
-    double y0[4], y[8];
-    const double *patch;
-    traj_start(a, t, side, k, y0, patch);
-    if (!hit_active(a, k)) return;
-    const SideMap sm = a.side[blockIdx.y];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        y[c] = y0[c];
-        y[4 + c] = col == 2 ? 0.0 : patch[4 * (col + 1) + c];
+    const int64_t k = gid - col * a.K, T2 = 2 * a.K, t = blockIdx.y * a.K + k;
+    const bool live = gid < 3 * a.K && hit_active(a, k), ecol = col == 2;
+    double y[D] = {};
+    if (live) {
+        double y0[4];
+        const double *patch;
+        traj_start(a, blockIdx.y, k, y0, patch);
+        get_state<PAIR, 0>(y0, y);
+        if (!ecol) get_state<PAIR, C>(patch + 4 * (col + 1), y);
     }
-    const bool ecol = col == 2;
-    for (int64_t s = 0; s < sm.nsteps; ++s)
-        rk_tangent_step(y, stage_row(sm.w, s, sm.steps), stage_row(sm.dwde, s, sm.steps), blockIdx.y, a.md, ecol);
-    store_d4(a.dend + ((int64_t)col * T2 + t) * 4, y + 4);
-    if (col == 0) store_d4(a.yend + 4 * t, y);
+    ref_flow<PAIR, true>(a, blockIdx.y, live, 0, a.side[blockIdx.y].nsteps, ecol, y, [](int64_t, double (&)[D]) {});
+    if (!live) return;
+    put_state<PAIR, C>(a.dend + ((int64_t)col * T2 + t) * 4, y);
+    if (col == 0) put_state<PAIR, 0>(a.yend + 4 * t, y);
 }
 
 // f, r (and J, grad = 2 J^T f in tangent mode) per hit.
@@ -198,56 +279,71 @@ __global__ void __launch_bounds__(RF_BLOCK) k_ref_combine(RefArgs a, int tangent
         }
 }
 
-// The adjoint runs backwards over windows of consecutive steps (whole
-// checkpoint segments).  For one window:
-//   k_adj_states  per (segment, trajectory): the states before every step of
-//                 the segment, recomputed from its checkpoint;
-//   k_adj_jac     per (step, trajectory, column): the step's Jacobian
-//                 M_n = d y_{n+1} / d y_n (columns 0-3, a tangent step from a
-//                 unit vector) and d y_{n+1} / d e (column 4), all steps of the
-//                 window in parallel;
-//   k_adj_reverse per trajectory: lam <- M_n^T lam and ge += (d y_{n+1}/de) . lam
-//                 for n from the last step of the window down to the first.
-// This is the transpose of the discrete map, step by step (the discrete
-// adjoint), with the sequential part reduced to 4 x 4 products.
-__global__ void __launch_bounds__(RF_BLOCK) k_adj_states(RefArgs a, int64_t s_lo, int64_t s_hi, double *states)
+// The adjoint goes backwards over segments of ADJ_SEG steps (counted from
+// the first step, whatever the checkpoint interval, so that the result does
+// not depend on that), a window of segments at a time.  For one window:
+//   k_adj_states    per (checkpoint interval, trajectory): the states at the
+//                   starts of the window's segments, recomputed from the
+//                   checkpoints (not needed when these lie at the starts);
+//   k_adj_segments  per (segment, trajectory, column): the Jacobian of the
+//                   segment's steps, P = d y_end / d y_start (columns 0-3, a
+//                   unit vector carried by the tangent steps) and
+//                   d y_end / d e (column 4), all segments in parallel;
+//   k_adj_reverse   per trajectory: lam <- P^T lam and ge += (d y_end/de) . lam
+//                   from the last segment of the window down to the first.
+// This is the transpose of the discrete map, segment by segment.  With a
+// Jacobian per step instead (kept in memory, 160 bytes a step, and applied
+// one after another) the backward part of 128 hits took 6.3 ms, 5.0 of them
+// the 12,000 dependent loads and products of each trajectory; with segments
+// 0.72 ms (0.67 for the Jacobians, which are bound by FP64 issue).
+constexpr int64_t ADJ_SEG = 100;
+
+template <bool PAIR>
+__global__ void __launch_bounds__(RF_BLOCK) k_adj_states(RefArgs a, int64_t s_lo, int64_t s_hi, int64_t nblk,
+                                                         double *states)
 {
-    const int64_t T2 = 2 * a.K;
-    const int64_t nseg = (s_hi - s_lo + a.ck - 1) / a.ck;
-    const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (gid >= nseg * a.K) return;
-    const int64_t sg = gid / a.K, t = blockIdx.y * a.K + (gid - sg * a.K);
-    const SideMap sm = a.side[blockIdx.y];
-    const int64_t s0 = s_lo + sg * a.ck;
+    constexpr int D = flow_dim<PAIR, false>();
+    const int64_t T2 = 2 * a.K, seg = blockIdx.x / nblk;
+    const int64_t i = ((blockIdx.x - seg * nblk) * blockDim.x + threadIdx.x) / (PAIR ? 2 : 1);
+    const int64_t t = blockIdx.y * a.K + i, ck0 = s_lo / a.ck + seg;
+    const int64_t s0 = ck0 * a.ck;
     int64_t s1 = s0 + a.ck < s_hi ? s0 + a.ck : s_hi;
-    if (s1 > sm.nsteps) s1 = sm.nsteps;
+    if (s1 > a.side[blockIdx.y].nsteps) s1 = a.side[blockIdx.y].nsteps;
     if (s0 >= s1) return;
-    const d4 c = load_d4(a.ckpt + ((s0 / a.ck) * T2 + t) * 4);
-    double y[4] = {c.x, c.y, c.z, c.w};
-    for (int64_t s = s0; s < s1; ++s) {
-        store_d4(states + ((s - s_lo) * T2 + t) * 4, y);
-        if (s + 1 < s1) rk_state_step(y, stage_row(sm.w, s, sm.steps), blockIdx.y, a.md);
-    }
+    const bool live = i < a.K;
+    double y[D] = {};
+    if (live) get_state<PAIR, 0>(a.ckpt + (ck0 * T2 + t) * 4, y);
+    // the first segment start at or after s0, and the last before s1: no
+    // step past it is needed
+    int64_t next = (s0 > s_lo ? (s0 + ADJ_SEG - 1) / ADJ_SEG * ADJ_SEG : s_lo);
+    const int64_t last = (s1 - 1) / ADJ_SEG * ADJ_SEG;
+    if (next > last) return;
+    ref_flow<PAIR, false>(a, blockIdx.y, live, s0, last + 1, false, y, [&](int64_t s, double (&v)[D]) {
+        if (s == next) {
+            put_state<PAIR, 0>(states + ((s - s_lo) / ADJ_SEG * T2 + t) * 4, v);
+            next += ADJ_SEG;
+        }
+    });
 }
 
-__global__ void __launch_bounds__(RF_BLOCK) k_adj_jac(RefArgs a, int64_t s_lo, int64_t s_hi, const double *states,
-                                                      double *jac)
+__global__ void __launch_bounds__(RF_BLOCK) __attribute__((amdgpu_waves_per_eu(3, 8)))
+k_adj_segments(RefArgs a, int64_t s_lo, int64_t s_hi, int64_t nblk, const double *states, double *jac)
 {
-    const int64_t T2 = 2 * a.K;
-    const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (gid >= (s_hi - s_lo) * a.K * 5) return;
-    const int64_t cell = gid / 5;
-    const int col = (int)(gid - cell * 5);
-    const int64_t sl = cell / a.K, t = blockIdx.y * a.K + (cell - sl * a.K);
-    const SideMap sm = a.side[blockIdx.y];
-    const int64_t s = s_lo + sl;
-    if (s >= sm.nsteps) return;
-    const d4 ys = load_d4(states + (sl * T2 + t) * 4);
-    double y[8] = {ys.x, ys.y, ys.z, ys.w, 0.0, 0.0, 0.0, 0.0};
+    const int64_t T2 = 2 * a.K, sg = blockIdx.x / nblk;
+    const int64_t gid = (blockIdx.x - sg * nblk) * blockDim.x + threadIdx.x;
+    const int64_t i = gid / 5, t = blockIdx.y * a.K + i;
+    const int col = (int)(gid - i * 5);
+    const int64_t s0 = s_lo + sg * ADJ_SEG;
+    int64_t s1 = s0 + ADJ_SEG < s_hi ? s0 + ADJ_SEG : s_hi;
+    if (s1 > a.side[blockIdx.y].nsteps) s1 = a.side[blockIdx.y].nsteps;
+    if (s0 >= s1) return;
+    const bool live = i < a.K;
+    double y[8] = {};
+    if (live) get_state<false, 0>(states + (sg * T2 + t) * 4, y);
 #pragma unroll
     for (int c = 0; c < 4; ++c) y[4 + c] = c == col ? 1.0 : 0.0;
-    rk_tangent_step(y, stage_row(sm.w, s, sm.steps), stage_row(sm.dwde, s, sm.steps), blockIdx.y, a.md, col == 4);
-    store_d4(jac + ((sl * T2 + t) * 5 + col) * 4, y + 4);
+    ref_flow<false, true>(a, blockIdx.y, live, s0, s1, col == 4, y, [](int64_t, double (&)[8]) {});
+    if (live) put_state<false, 4>(jac + ((sg * T2 + t) * 5 + col) * 4, y);
 }
 
 // lam (4) and ge per trajectory live in adj[5 t ...]; init seeds lam = +-2 f.
@@ -259,7 +355,6 @@ __global__ void __launch_bounds__(RF_BLOCK) k_adj_reverse(RefArgs a, int64_t s_l
     if (t >= T2) return;
     const int side = t >= a.K ? 1 : 0;
     const int64_t k = t - (side ? a.K : 0);
-    const SideMap sm = a.side[side];
     double lam[4], ge;
     if (init) {
         const double sg = side ? -2.0 : 2.0;
@@ -269,9 +364,10 @@ __global__ void __launch_bounds__(RF_BLOCK) k_adj_reverse(RefArgs a, int64_t s_l
         for (int c = 0; c < 4; ++c) lam[c] = adj[5 * t + c];
         ge = adj[5 * t + 4];
     }
-    const int64_t hi = s_hi < sm.nsteps ? s_hi : sm.nsteps;
-    for (int64_t s = hi - 1; s >= s_lo; --s) {
-        const double *J = jac + ((s - s_lo) * T2 + t) * 20;   // 5 columns of 4
+    const int64_t hi = s_hi < a.side[side].nsteps ? s_hi : a.side[side].nsteps;
+#pragma unroll 4
+    for (int64_t sg = (hi - s_lo + ADJ_SEG - 1) / ADJ_SEG - 1; sg >= 0; --sg) {
+        const double *J = jac + (sg * T2 + t) * 20;   // 5 columns of 4
         double m[5][4];
 #pragma unroll
         for (int c = 0; c < 5; ++c) {
@@ -407,10 +503,10 @@ int check_maps(const map_params_t *fwd, const map_params_t *bwd)
     return MS_OK;
 }
 
-// Steps per adjoint window: whole checkpoint segments, as many as fit
-// ADJ_WINDOW_BYTES of states and step Jacobians (at least one segment).
+// Segments per adjoint window: as many as fit ADJ_WINDOW_BYTES of start
+// states and segment Jacobians (at least one).
 constexpr int64_t ADJ_WINDOW_BYTES = (int64_t)256 << 20;
-constexpr int64_t ADJ_BYTES_PER_STEP = 32 + 5 * 32;   // per trajectory: state + 5 Jacobian columns
+constexpr int64_t ADJ_BYTES_PER_SEG = 32 + 5 * 32;   // per trajectory: state + 5 Jacobian columns
 
 RefLayout ref_layout(int64_t K, const map_params_t *fwd, const map_params_t *bwd, int32_t ck, int32_t mode)
 {
@@ -432,13 +528,15 @@ RefLayout ref_layout(int64_t K, const map_params_t *fwd, const map_params_t *bwd
         const int64_t a = side_steps(fwd), b = side_steps(bwd);
         L.n_steps_max = a > b ? a : b;
         L.n_ck = ceil_div(L.n_steps_max, ck);
-        int64_t segs = ADJ_WINDOW_BYTES / ((int64_t)(T2 > 0 ? T2 : 1) * ADJ_BYTES_PER_STEP * ck);
+        const int64_t n_seg = ceil_div(L.n_steps_max, ADJ_SEG);
+        int64_t segs = ADJ_WINDOW_BYTES / ((int64_t)(T2 > 0 ? T2 : 1) * ADJ_BYTES_PER_SEG);
+        if (segs > n_seg) segs = n_seg;
+        if (segs > (1 << 20) / ADJ_SEG) segs = (1 << 20) / ADJ_SEG;     // (launch sizes in 32 bits)
         if (segs < 1) segs = 1;
-        if (segs > L.n_ck) segs = L.n_ck > 0 ? L.n_ck : 1;
-        L.win_steps = segs * ck;
+        L.win_steps = segs * ADJ_SEG;
         L.o_ckpt = take((size_t)L.n_ck * T2 * 32);
-        L.o_states = take((size_t)L.win_steps * T2 * 32);
-        L.o_jac = take((size_t)L.win_steps * T2 * 160);
+        L.o_states = take((size_t)segs * T2 * 32);
+        L.o_jac = take((size_t)segs * T2 * 160);
         L.o_adj = take(T2 * 40);
     } else {
         L.o_ckpt = take(0);
@@ -488,6 +586,14 @@ int make_args(RefArgs &a, const double *params, int64_t K, const patch_t *U, con
 
 unsigned blocks_for(int64_t n) { return (unsigned)ceil_div(n > 0 ? n : 1, RF_BLOCK); }
 
+void launch_tangent(const RefArgs &a, hipStream_t st)
+{
+    if (a.K <= PAIR_HITS)
+        MS_LAUNCH("k_ref_tangent", k_ref_tangent<true>, dim3(blocks_for(6 * a.K), 2), dim3(RF_BLOCK), 0, st, a);
+    else
+        MS_LAUNCH("k_ref_tangent", k_ref_tangent<false>, dim3(blocks_for(3 * a.K), 2), dim3(RF_BLOCK), 0, st, a);
+}
+
 }  // namespace
 }  // namespace ms
 
@@ -533,13 +639,17 @@ extern "C" int refine_grad(const double *params_dev, int64_t K, const patch_t *U
     a.dend = (double *)(w + L.o_dend);
     a.gpart = (double *)(w + L.o_gpart);
     const int64_t T2 = 2 * K;
+    const bool pair = K <= PAIR_HITS;
     if (mode == MS_REFINE_TANGENT) {
-        MS_LAUNCH("k_ref_tangent", k_ref_tangent, dim3(blocks_for(3 * K), 2), dim3(RF_BLOCK), 0, st, a);
+        launch_tangent(a, st);
         MS_LAUNCH("k_ref_combine", k_ref_combine, dim3(blocks_for(K)), dim3(RF_BLOCK), 0, st, a, 1, f_dev, r_dev, J_dev,
                   grad_dev);
     } else {
         if (mode == MS_REFINE_ADJOINT) a.ckpt = (double *)(w + L.o_ckpt);
-        MS_LAUNCH("k_ref_state", k_ref_state, dim3(blocks_for(K), 2), dim3(RF_BLOCK), 0, st, a);
+        if (pair)
+            MS_LAUNCH("k_ref_state", k_ref_state<true>, dim3(blocks_for(2 * K), 2), dim3(RF_BLOCK), 0, st, a);
+        else
+            MS_LAUNCH("k_ref_state", k_ref_state<false>, dim3(blocks_for(K), 2), dim3(RF_BLOCK), 0, st, a);
         MS_LAUNCH("k_ref_combine", k_ref_combine, dim3(blocks_for(K)), dim3(RF_BLOCK), 0, st, a, 0, f_dev, r_dev,
                   (double *)nullptr, (double *)nullptr);
         if (mode == MS_REFINE_ADJOINT) {
@@ -550,12 +660,25 @@ extern "C" int refine_grad(const double *params_dev, int64_t K, const patch_t *U
             for (int64_t wi = nwin - 1; wi >= 0; --wi) {
                 const int64_t s_lo = wi * W;
                 const int64_t s_hi = s_lo + W < L.n_steps_max ? s_lo + W : L.n_steps_max;
-                const int64_t nseg = ceil_div(s_hi - s_lo, (int64_t)ck);
+                // the window's start states: the checkpoints themselves when they
+                // lie at the segments' starts
+                const double *from = ck == ADJ_SEG ? a.ckpt + (s_lo / ADJ_SEG) * T2 * 4 : states;
                 if (s_hi > s_lo) {
-                    MS_LAUNCH("k_adj_states", k_adj_states, dim3(blocks_for(nseg * K), 2), dim3(RF_BLOCK), 0, st, a, s_lo,
-                              s_hi, states);
-                    MS_LAUNCH("k_adj_jac", k_adj_jac, dim3(blocks_for((s_hi - s_lo) * K * 5), 2), dim3(RF_BLOCK), 0, st,
-                              a, s_lo, s_hi, (const double *)states, jac);
+                    if (ck != ADJ_SEG) {
+                        const int64_t nck = ceil_div(s_hi, (int64_t)ck) - s_lo / ck;
+                        const unsigned nb = blocks_for(pair ? 2 * K : K);
+                        const dim3 grid((unsigned)(nck * nb), 2);
+                        if (pair)
+                            MS_LAUNCH("k_adj_states", k_adj_states<true>, grid, dim3(RF_BLOCK), 0, st, a, s_lo, s_hi,
+                                      (int64_t)nb, states);
+                        else
+                            MS_LAUNCH("k_adj_states", k_adj_states<false>, grid, dim3(RF_BLOCK), 0, st, a, s_lo, s_hi,
+                                      (int64_t)nb, states);
+                    }
+                    const unsigned nb = blocks_for(5 * K);
+                    MS_LAUNCH("k_adj_segments", k_adj_segments,
+                              dim3((unsigned)(ceil_div(s_hi - s_lo, ADJ_SEG) * nb), 2), dim3(RF_BLOCK), 0, st, a, s_lo,
+                              s_hi, (int64_t)nb, from, jac);
                 }
                 MS_LAUNCH("k_adj_reverse", k_adj_reverse, dim3(blocks_for(T2)), dim3(RF_BLOCK), 0, st, a, s_lo, s_hi,
                           (const double *)jac, adj, (const double *)f_dev, (int)(wi == nwin - 1));
@@ -614,7 +737,7 @@ extern "C" int refine_newton(const double *params_in_dev, double *params_out_dev
     cfg.max_trials = np->max_trials;
     MS_LAUNCH("k_newton_init", k_newton_init, dim3(blocks_for(K)), dim3(RF_BLOCK), 0, st, params_in_dev, ns, K);
     for (int it = 0; it <= np->max_trials; ++it) {
-        MS_LAUNCH("k_ref_tangent", k_ref_tangent, dim3(blocks_for(3 * K), 2), dim3(RF_BLOCK), 0, st, a);
+        launch_tangent(a, st);
         MS_LAUNCH("k_newton_update", k_newton_update, dim3(blocks_for(K)), dim3(RF_BLOCK), 0, st, a, ns, cfg);
     }
     MS_LAUNCH("k_newton_finish", k_newton_finish, dim3(blocks_for(K)), dim3(RF_BLOCK), 0, st, ns, K, params_out_dev,

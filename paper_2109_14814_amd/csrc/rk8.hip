@@ -11,14 +11,14 @@
 #include <math.h>
 #include <string.h>
 
-#include "rk8_core.hpp"
+#include "rk8_pair.hpp"
 
 namespace ms {
 
 namespace {
 
 constexpr int S = RK_S;
-constexpr int RK_BLOCK = 128;
+constexpr int RK_BLOCK = FLOW_BLOCK;
 
 }  // namespace
 
@@ -55,25 +55,27 @@ RkCoef rk_coef(double h)
 
 namespace {
 
-__global__ void __launch_bounds__(RK_BLOCK) __attribute__((amdgpu_waves_per_eu(5, 8))) k_rk8_map(RkCoef, const double *__restrict__ in,
-                                                      double *__restrict__ out, int64_t n, Model md, double e,
-                                                      int steps, int64_t nsteps)
+__global__ void __launch_bounds__(RK_BLOCK) __attribute__((amdgpu_waves_per_eu(5, 8)))
+k_rk8_map(RkCoef, const double *in, double *out, int64_t n, Model md, double e, int steps, int64_t nsteps,
+          FlowPlan plan, int64_t unit0)
 {
     __shared__ double s_w[RK_CHUNK * S];
     __shared__ double s_c[S];
 #pragma unroll
     for (int i = 0; i < S; ++i)
         if (threadIdx.x == i) s_c[i] = RK_T.c[i];
-    const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const FlowUnit u = flow_unit(plan, unit0 + blockIdx.x, nsteps);
+    if (!u.ok) return;
+    const int64_t v = u.block * blockDim.x + threadIdx.x;
     const bool live = v < n;      // every thread of the block fills the weights
     double y[4] = {0.0, 0.0, 0.0, 0.0};
     if (live) {
-        const d4 s = load_d4(in + 4 * v);
+        const d4 s = load_d4((u.s0 == 0 ? in : out) + 4 * v);
         y[0] = s.x; y[1] = s.y; y[2] = s.z; y[3] = s.w;
     }
-    int64_t n_in = 0;
-    for (int64_t st0 = 0; st0 < nsteps; st0 += RK_CHUNK) {
-        const int cnt = nsteps - st0 < RK_CHUNK ? (int)(nsteps - st0) : RK_CHUNK;
+    int64_t n_in = u.s0 % steps;
+    for (int64_t st0 = u.s0; st0 < u.s1; st0 += RK_CHUNK) {
+        const int cnt = u.s1 - st0 < RK_CHUNK ? (int)(u.s1 - st0) : RK_CHUNK;
         __syncthreads();      // the previous chunk's weights are no longer read (and s_c is written)
         fill_stage_chunk(s_w, s_c, n_in, cnt, steps, [&](double f) { return 1.0 / (1.0 + e * cos(f)); });
         __syncthreads();
@@ -90,6 +92,14 @@ __global__ void __launch_bounds__(RK_BLOCK) __attribute__((amdgpu_waves_per_eu(5
         o[0] = make_double2(y[0], y[1]);
         o[1] = make_double2(y[2], y[3]);
     }
+}
+
+__global__ void __launch_bounds__(PAIR_BLOCK) k_rk8_pair(RkCoef hc, const double *in, double *out, int64_t n, Model md,
+                                                         double e, int steps, int64_t nsteps)
+{
+    pair_flow<double, 0>(
+        hc, in, out, nullptr, n, md, steps, nsteps, [&](double f) { return 1.0 / (1.0 + e * cos(f)); },
+        [](const PairLane &L, double w, double (&s)[2]) { puls_pair<false>(L, w, 0.0, s); });
 }
 
 }  // namespace
@@ -117,8 +127,17 @@ extern "C" int propagate_vertices(const double *in_dev, double *out_dev, int64_t
         return MS_OK;
     }
     Model md{p->mu, 1.0 - p->mu};
-    hipLaunchKernelGGL(k_rk8_map, dim3((unsigned)ceil_div(n_vertices, RK_BLOCK)), dim3(RK_BLOCK), 0, st, rk_coef(h),
-                       in_dev, out_dev, n_vertices, md, p->e, p->steps_per_period, nsteps);
-    MS_HIP(hipGetLastError());
+    if (n_vertices <= PAIR_STATES) {
+        hipLaunchKernelGGL(k_rk8_pair, dim3(pair_blocks(n_vertices)), dim3(PAIR_BLOCK), 0, st, rk_coef(h), in_dev,
+                           out_dev, n_vertices, md, p->e, p->steps_per_period, nsteps);
+        MS_HIP(hipGetLastError());
+        return MS_OK;
+    }
+    const FlowPlan plan = flow_plan(ceil_div(n_vertices, RK_BLOCK), nsteps, true);
+    for (int l = 0; l < plan.launches; ++l) {
+        hipLaunchKernelGGL(k_rk8_map, dim3(plan.grid), dim3(RK_BLOCK), 0, st, rk_coef(h), in_dev, out_dev, n_vertices,
+                           md, p->e, p->steps_per_period, nsteps, plan, (int64_t)l * plan.grid);
+        MS_HIP(hipGetLastError());
+    }
     return MS_OK;
 }

@@ -392,4 +392,64 @@ MS_D CoefPtr step_coef()
     return p;
 }
 
+// How the maps with one thread per state share out a batch's blocks.
+//
+// A block is four waves, one a SIMD of a CU, and a wave alone on a SIMD
+// issues at nine tenths of the rate of several: the time of one launch is
+// that of the fullest CU, ceil(blocks / 256) rounds of a block's time, however
+// little the last round holds (526,593 states are 2,058 blocks: 9 rounds for
+// 8.04 of work; 71,680 states are 280: 2 for 1.09).  So the steps are cut
+// into chunks and the (chunk, block) units, chunk by chunk, are dealt to
+// launches of m x 256 blocks, m = blocks / 256 rounded down: a launch holds
+// no block twice, and a block's chunks fall in successive launches.  Between
+// launches a state waits in the output array.  The last launch alone is
+// part empty: at most 1 / (chunks) of the time.
+constexpr int FLOW_BLOCK = 256;
+constexpr int64_t FLOW_CUS = 256;
+
+struct FlowPlan {
+    int64_t blocks;     // blocks of the whole batch
+    int64_t chunk;      // steps of a unit
+    int32_t launches;
+    uint32_t grid;      // blocks of a launch
+};
+
+struct FlowUnit {
+    int64_t block, s0, s1;      // steps [s0, s1) of the block's states
+    bool ok;                    // false: past the last unit
+};
+
+MS_D FlowUnit flow_unit(const FlowPlan &p, int64_t u, int64_t nsteps)
+{
+    FlowUnit f;
+    const int64_t c = u / p.blocks;
+    f.block = u - c * p.blocks;
+    f.s0 = c * p.chunk;
+    f.ok = c == 0 || f.s0 < nsteps;     // (a call of no steps copies its states)
+    f.s1 = f.s0 + p.chunk < nsteps ? f.s0 + p.chunk : nsteps;
+    return f;
+}
+
+// resume: whether the states can be kept between launches.
+inline FlowPlan flow_plan(int64_t blocks, int64_t nsteps, bool resume)
+{
+    FlowPlan p{blocks, nsteps > 0 ? nsteps : 1, 1, (uint32_t)blocks};
+    const int64_t m = blocks / FLOW_CUS;
+    const int64_t most = nsteps / (4 * RK_CHUNK);       // chunks of at least 128 steps
+    if (!resume || m == 0 || blocks % FLOW_CUS == 0 || most < 4) return p;
+    const int64_t n = most < 32 ? most : 32;
+    const int64_t chunk = ceil_div(ceil_div(nsteps, n), RK_CHUNK) * RK_CHUNK;
+    const int64_t launches = ceil_div(blocks * ceil_div(nsteps, chunk), m * FLOW_CUS);
+    // the time in steps of a round: one wave a SIMD runs at 1.1 times a
+    // round's time among several, and a launch costs about ten steps (10 us)
+    const double one = (double)nsteps * (double)(m + 1);
+    const double cut = (double)launches * ((double)chunk * (m == 1 ? 1.1 : (double)m) + 10.0);
+    if (cut < one) {
+        p.chunk = chunk;
+        p.launches = (int32_t)launches;
+        p.grid = (uint32_t)(m * FLOW_CUS);
+    }
+    return p;
+}
+
 }  // namespace ms
