@@ -929,29 +929,39 @@ def _mismatch_fn():
     class MismatchFn(torch.autograd.Function):
         """r = |F^{n_u}(x_u(th1, s1)) - F^{n_s}(x_s(th2, s2))|^2 per row of
         params, as a differentiable function of params (K, 4) and the
-        eccentricity e (0-dim tensor).  forward: refine_grad residual mode;
-        backward: the discrete adjoint (refine_grad adjoint mode)."""
+        eccentricity e (0-dim tensor).  Where a gradient is asked for,
+        forward runs refine_grad in adjoint mode and keeps the K x 5
+        gradients: the adjoint needs the forward pass with its checkpoints,
+        and what follows that pass is 8% of it (128 hits: 9.1 ms and 0.7), so
+        a backward that ran the pass again took twice the time (19.1 ms for
+        both against 10.0).  Else forward is the residual alone."""
 
         @staticmethod
-        def forward(ctx, params, e, U, S, mu, steps_per_period, n_u, n_s, ckpt_every):
+        def forward(ctx, params, e, U, S, mu, steps_per_period, n_u, n_s, ckpt_every, grad_mode=True):
             ev = float(e.detach().cpu())
             fwd = MapParams(float(mu), ev, int(steps_per_period), int(n_u))
             bwd = MapParams(float(mu), ev, int(steps_per_period), int(n_s))
-            out = refine_grad(params.detach(), U, S, fwd, bwd, MS_REFINE_RESIDUAL)
-            ctx.save_for_backward(params.detach())
-            ctx.maps = (fwd, bwd, U, S, int(ckpt_every))
+            # (grad_mode: whether gradients are enabled where the function is
+            # called, they never are in here; an interval that the adjoint
+            # refuses is refused by backward)
+            now = grad_mode and any(ctx.needs_input_grad[:2]) and int(ckpt_every) > 0
+            out = refine_grad(params.detach(), U, S, fwd, bwd, MS_REFINE_ADJOINT if now else MS_REFINE_RESIDUAL,
+                              int(ckpt_every) if now else 1)
+            ctx.save_for_backward(out["grad"] if now else params.detach())
+            ctx.maps = None if now else (fwd, bwd, U, S, int(ckpt_every))
             ctx.e_shape = e.shape
             return out["r"]
 
         @staticmethod
         def backward(ctx, grad_r):
-            (params,) = ctx.saved_tensors
-            fwd, bwd, U, S, ck = ctx.maps
-            g = refine_grad(params, U, S, fwd, bwd, MS_REFINE_ADJOINT, ck)["grad"]
+            (g,) = ctx.saved_tensors
+            if ctx.maps is not None:
+                fwd, bwd, U, S, ck = ctx.maps
+                g = refine_grad(g, U, S, fwd, bwd, MS_REFINE_ADJOINT, ck)["grad"]
             gr = grad_r.to(g.dtype)
             g_params = gr[:, None] * g[:, :4]
             g_e = (gr * g[:, 4]).sum().reshape(ctx.e_shape)
-            return g_params, g_e, None, None, None, None, None, None, None
+            return g_params, g_e, None, None, None, None, None, None, None, None
 
     return MismatchFn
 
@@ -964,4 +974,4 @@ def mismatch_r(params, e, U, S, mu: float, steps_per_period: int, n_u: int, n_s:
     global _MISMATCH
     if _MISMATCH is None:
         _MISMATCH = _mismatch_fn()
-    return _MISMATCH.apply(params, e, U, S, mu, steps_per_period, n_u, n_s, ckpt_every)
+    return _MISMATCH.apply(params, e, U, S, mu, steps_per_period, n_u, n_s, ckpt_every, _torch().is_grad_enabled())

@@ -104,3 +104,29 @@ def test_refinement_on_both_sides_of_the_pair_size(ms):
         for k in a:
             u, v = a[k][:-1].cpu().numpy(), b[k].cpu().numpy()
             assert np.max(np.abs(u - v)) <= 1e-11 * max(1.0, np.max(np.abs(v))), (mode, k)
+
+
+def test_mismatch_gradient_is_of_the_call(ms):
+    """The gradient that the forward call keeps is that of its inputs, also
+    after they are overwritten; without gradients, and where the adjoint's
+    interval is refused, the call is the residual alone."""
+    import torch
+    rng = np.random.default_rng(3)
+    x = torch.tensor(rng.uniform(-1e-3, 1e-3, (6, 4)), device="cuda")
+    e = torch.tensor(ECC, dtype=torch.float64, device="cuda")
+    U, S = ms.patch_row(synth.patch_dirs(3, synth.UNSTABLE_BASE)), ms.patch_row(synth.patch_dirs(4, synth.STABLE_BASE))
+    fwd, bwd = ms.MapParams(MU, ECC, 60, 1), ms.MapParams(MU, ECC, 60, -1)
+    ref = ms.refine_grad(x, U, S, fwd, bwd, ms.MS_REFINE_ADJOINT)
+    call = lambda p, ck=100: ms.mismatch_r(p, e, U, S, MU, 60, 1, -1, ck)  # noqa: E731
+    p = x.clone().requires_grad_(True)
+    r = call(p)
+    with torch.no_grad():
+        assert torch.equal(call(p), r)
+        p.zero_()
+    r.sum().backward()
+    assert torch.equal(p.grad, ref["grad"][:, :4]) and torch.equal(r.detach(), ref["r"])
+    q = x.clone().requires_grad_(True)
+    r = call(q, 0)
+    assert torch.equal(r.detach(), ref["r"])
+    with pytest.raises(ms.MSearchError):
+        r.sum().backward()
