@@ -152,12 +152,12 @@ typedef struct {
     int32_t reserved;       /* 0 */
 } search_params_t;
 
-/* Enumeration work tiles: a block takes a chunk of consecutive slots and
- * stages the entries they need in LDS. */
+/* Enumeration work tiles: the least work a wave takes, in box tests of 64
+ * pairs (the waves share the work out evenly once it is more than that). */
 enum {
-    MS_ENUM_WIDE = 1,       /* 512 threads x 8 slots, up to 768 staged entries: one block per CU */
-    MS_ENUM_HALF = 2,       /* 256 threads x 8 slots, up to 384 staged entries: two blocks per CU */
-    MS_ENUM_QUARTER = 3     /* 128 threads x 8 slots, up to 192 staged entries: four blocks per CU */
+    MS_ENUM_WIDE = 1,       /* 64 */
+    MS_ENUM_HALF = 2,       /* 32 */
+    MS_ENUM_QUARTER = 3     /* 16 */
 };
 
 /* World = box of both meshes' finite triangles, edge = kappa * the geometric
@@ -198,8 +198,10 @@ typedef struct {
     int64_t overflow;        /* bit 0: entries > capacity, bit 1: cand, bit 2: hits */
     int64_t n_groups;        /* groups enumerated: hashed cells with A and B entries (>= n_cells) */
     int64_t n_group_slots;   /* sum over those groups of nA * nB (>= n_slots) */
-    int64_t n_chunks_unstaged; /* enumeration chunks whose entries did not fit on-chip (crowded
-                                  cells; their slots were read from device memory) */
+    int64_t n_chunks_unstaged; /* pieces of the enumeration that take more boxes than the on-chip memories
+                                  hold and stream them from device memory: chunks of 2,048 slots of a
+                                  group with more than 470 A entries (crowded cells), and runs of one
+                                  wave over more than 470 entries (many small groups) */
     int64_t reserved[2];     /* zero */
 } search_stats_t;
 

@@ -18,17 +18,17 @@
 //                 group (a cell holding one mesh only cannot hold a pair);
 //                 entries [cell | side | triangle] at offsets reserved per
 //                 block, each with its group and its rank in the group
-//   k_groups      groups holding A and B entries: entry ranges and slot
-//                 offsets sum(nA * nB) (scan with decoupled look-back)
+//   k_groups      groups holding A and B entries: entry ranges and the units
+//                 of enumeration before each (scan with decoupled look-back)
 //   k_scatter     entries to their group's range, A's before B's, each with
-//                 its triangle's box (Sec. 6.2.2)
-//   k_enum        slot -> (group, iA, iB); a pair is kept only when both
-//                 entries are of one cell, in its home cell (cell of the
-//                 componentwise max of the boxes' lower corners) and only if
-//                 the closed boxes overlap (Sec. 6.2.2); then, on the chunk's
-//                 candidates, the Moller quick test (Sec. 6.2.3), the 4x4
-//                 solve and inclusion (Sec. 6.2.4), hit records; last, the
-//                 exact cell statistics into sharded counters
+//                 its triangle's box in 16 bits per corner and axis
+//   k_enum        every pair of an A and a B entry of a group, 64 at a time:
+//                 box test in 16 bits, same cell, home cell (cell of the
+//                 componentwise max of the boxes' lower corners); then, on
+//                 what is left, the exact box test (Sec. 6.2.2), the Moller
+//                 quick test (Sec. 6.2.3), the 4x4 solve and inclusion (Sec.
+//                 6.2.4), hit records; the exact cell statistics into
+//                 sharded counters
 //   k_finish      the statistics, the next epoch value, and the hits sorted
 //                 by (pair, triA, triB) when there are at most 1024 of them
 //                 (above, a chunk sort, merge rank and placement first)
@@ -69,7 +69,7 @@ inline unsigned mark_grid(int64_t n_tiles)
 static_assert(MAX_GRID <= MS_COUNT_PARTIALS, "count partials fit the mesh scratch");
 constexpr int TILE_TRIS = 2 * BLOCK;                  // triangles of a tile: one quad per thread
 // Counter lines of the enumeration (cand, moller, degen, outside, cells,
-// slots, unstaged chunks), one 128-byte line each.
+// slots, and k_groups' crowded chunks and group slots), one 128-byte line each.
 constexpr int STAT_SHARDS = 8;
 constexpr int SHARD_WORDS = 16;
 constexpr uint64_t SFLAG_AGG = 1ull << 62;
@@ -131,20 +131,6 @@ MS_D const PairDesc &pair_desc(const BatchView &bv, int p)
     if constexpr (ONE) return bv.p0;
     else return bv.pairs[p];
 }
-
-// Last index i in [0, n) with a[i] <= x (a ascending, a[0] <= x).
-template <typename T>
-MS_D int64_t last_le(const T *a, int64_t n, T x)
-{
-    int64_t lo = 0, hi = n;
-    while (hi - lo > 1) {
-        int64_t mid = lo + ((hi - lo) >> 1);
-        if (a[mid] <= x) lo = mid;
-        else hi = mid;
-    }
-    return lo;
-}
-
 
 // Multiplier of the hashed tables (the odd 32-bit constant nearest 2^32 / phi).
 constexpr uint32_t HASH_MUL = 0x9E3779B1u;
@@ -1020,11 +1006,26 @@ MS_D bool coarse_any(const BatchView &bv, const uint32_t *cboth, const PairDesc 
     return count_both(BitRef{cboth, bv.bc_log2}, rc, P.cbs, P.cbh, P.cell_base) != 0;
 }
 
+// Where an entry's cell lies in its triangle's range: its offset from the
+// triangle's lowest cell per axis, in 4 bits each (15: 15 cells or more).
+template <typename T>
+MS_D uint32_t cell_offsets(const int64_t *c, const T *lo)
+{
+    uint32_t m = 0;
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        const int64_t k = c[d] - (int64_t)lo[d];
+        m |= (uint32_t)(k < 15 ? k : 15) << (4 * d);
+    }
+    return m;
+}
+
 struct KeysOut {
     uint64_t *ent;                // [cell | side | triangle]
     int32_t *epair;               // pair of the entry (batch)
     uint32_t *erank;              // rank of the entry among its group's entries of its side
     uint32_t *ehash;              // the entry's hashed cell (its group)
+    uint16_t *eoff;               // the entry's cell in its triangle's range (cell_offsets)
     int64_t cap;
     unsigned long long *n_keys;   // entries reserved (cleared)
     uint32_t *grp;                // per hashed cell h: [2 h] A entries, [2 h + 1] B entries
@@ -1064,7 +1065,7 @@ __global__ void __launch_bounds__(KEYS_BLOCK) __attribute__((amdgpu_waves_per_eu
     __shared__ unsigned long long s_blk0;
     __shared__ uint32_t s_kh[KEYS_STAGE];     // staged entries: hashed cell, cell, thread
     __shared__ uint64_t s_kc[KEYS_STAGE];
-    __shared__ uint16_t s_kt[KEYS_STAGE];
+    __shared__ uint16_t s_kt[KEYS_STAGE], s_ko[KEYS_STAGE];
     const int lg = bv.bm_log2, lc = bv.bc_log2;
     const uint32_t *cboth = both + ((size_t)1 << lg) / 32;
     const int64_t tile = blockIdx.x;
@@ -1144,8 +1145,9 @@ __global__ void __launch_bounds__(KEYS_BLOCK) __attribute__((amdgpu_waves_per_eu
         // the entry stores are contiguous
         if (cnt) {
             uint32_t k = (uint32_t)texcl;
-            auto stage = [&](uint64_t gc, uint32_t hh) {
+            auto stage = [&](uint64_t gc, uint32_t hh, uint32_t off) {
                 s_kh[k] = hh;
+                s_ko[k] = (uint16_t)off;
                 s_kc[k] = gc;
                 s_kt[k] = (uint16_t)threadIdx.x;
                 ++k;
@@ -1156,14 +1158,14 @@ __global__ void __launch_bounds__(KEYS_BLOCK) __attribute__((amdgpu_waves_per_eu
                     if (occ_bit(both, hh))
                         stage(cb + (uint64_t)c[0] * P.st[0] + (uint64_t)c[1] * P.st[1] + (uint64_t)c[2] * P.st[2] +
                                   (uint64_t)c[3],
-                              hh);
+                              hh, cell_offsets(c, r.lo));
                 });
             } else {
                 CellRange rr;
                 range_at(rng, g, m, t, P.g, rr);
                 for_cells_xy(rr, P.g.n, [&](const int64_t *c, uint64_t cell) {
                     const uint32_t hh = blocked_index(c, P.fbs, cb, lg);
-                    if (occ_bit(both, hh)) stage(cb + cell, hh);
+                    if (occ_bit(both, hh)) stage(cb + cell, hh, cell_offsets(c, rr.lo));
                 });
             }
         }
@@ -1177,6 +1179,7 @@ __global__ void __launch_bounds__(KEYS_BLOCK) __attribute__((amdgpu_waves_per_eu
             const uint32_t rank = atomicAdd(&o.grp[2 * (size_t)hh + L.side], 1u);
             o.erank[pos] = rank;
             o.ehash[pos] = hh;
+            o.eoff[pos] = s_ko[i];
             if (rank == 0) o.own[hh] = gc;     // the first entry of each side: the group's sample
             o.ent[pos] = (gc << bv.kl.cell_shift) | side_bits | (uint64_t)(uint32_t)(L.t0 + s_kt[i]);
             if (!ONE) o.epair[pos] = L.p;
@@ -1188,11 +1191,12 @@ __global__ void __launch_bounds__(KEYS_BLOCK) __attribute__((amdgpu_waves_per_eu
     const uint64_t low = ((uint64_t)L.side << bv.kl.tb) | (uint64_t)t;
     // only stored entries are counted in their group; the first entry of
     // each side leaves its cell as the group's sample
-    auto put = [&](uint64_t gc, uint32_t hh) {
+    auto put = [&](uint64_t gc, uint32_t hh, uint32_t off) {
         if (pos < o.cap) {
             const uint32_t rank = atomicAdd(&o.grp[2 * (size_t)hh + L.side], 1u);
             o.erank[pos] = rank;
             o.ehash[pos] = hh;
+            o.eoff[pos] = (uint16_t)off;
             if (rank == 0) o.own[hh] = gc;
             o.ent[pos] = (gc << bv.kl.cell_shift) | low;
             if (!ONE) o.epair[pos] = L.p;
@@ -1204,14 +1208,14 @@ __global__ void __launch_bounds__(KEYS_BLOCK) __attribute__((amdgpu_waves_per_eu
             const uint32_t hh = blocked_index(c, P.fbs, cb, lg);
             if (occ_bit(both, hh))
                 put(cb + (uint64_t)c[0] * P.st[0] + (uint64_t)c[1] * P.st[1] + (uint64_t)c[2] * P.st[2] + (uint64_t)c[3],
-                    hh);
+                    hh, cell_offsets(c, r.lo));
         });
     } else {
         CellRange rr;
         range_at(rng, g, m, t, P.g, rr);
         for_cells_xy(rr, P.g.n, [&](const int64_t *c, uint64_t cell) {
             const uint32_t hh = blocked_index(c, P.fbs, cb, lg);
-            if (occ_bit(both, hh)) put(cb + cell, hh);
+            if (occ_bit(both, hh)) put(cb + cell, hh, cell_offsets(c, rr.lo));
         });
     }
 }
@@ -1219,9 +1223,9 @@ __global__ void __launch_bounds__(KEYS_BLOCK) __attribute__((amdgpu_waves_per_eu
 // A kept cell group: its entries, A's then B's, from `start`; h is its
 // hashed cell.
 struct CellRec {
-    int64_t start;
+    uint32_t start;      // (entries are fewer than 2^30)
     int32_t nA, nB;
-    int64_t h;
+    uint32_t h;
 };
 
 // First index in [lo, hi) whose key is >= k (keys ascending).
@@ -1235,10 +1239,38 @@ MS_D int64_t lower_bound_u64(const uint64_t *a, int64_t lo, int64_t hi, uint64_t
     return lo;
 }
 
+constexpr int STRIP_UNITS = 16;           // the start of a strip of the enumeration, in scalar entries
+
+// A group's shape: which side lies on the lanes, and its units.
+struct GroupShape {
+    bool lanes_b;         // the B entries on the lanes
+    uint32_t nl, ns;      // entries on the lanes, entries taken one by one
+    uint32_t unit;        // units of one strip
+};
+
+MS_D uint32_t strips_of(uint32_t n) { return (n + WAVE - 1) / WAVE; }
+
+MS_D GroupShape group_shape(uint32_t nA, uint32_t nB)
+{
+    GroupShape s;
+    s.lanes_b = (uint64_t)strips_of(nB) * (nA + STRIP_UNITS) <= (uint64_t)strips_of(nA) * (nB + STRIP_UNITS);
+    s.nl = s.lanes_b ? nB : nA;
+    s.ns = s.lanes_b ? nA : nB;
+    s.unit = s.ns + STRIP_UNITS;
+    return s;
+}
+
+// The units of a group: its strips, each of `unit` units.
+MS_D uint64_t group_units(uint32_t nA, uint32_t nB)
+{
+    const uint64_t ub = (uint64_t)strips_of(nB) * (nA + STRIP_UNITS), ua = (uint64_t)strips_of(nA) * (nB + STRIP_UNITS);
+    return ub <= ua ? ub : ua;
+}
+
 // The groups holding both meshes, in order of their hashed cells.  A group
 // is kept when it has A and B entries; kept groups get consecutive records,
-// entry ranges (sum of nA + nB before them) and slot offsets (sum of
-// nA * nB), from one block scan and a decoupled look-back per tile of
+// entry ranges (sum of nA + nB before them) and unit offsets (the sum of
+// their enumeration units), from one block scan and a decoupled look-back per tile of
 // GROUP_WORDS words of the both-occupied table.  Each group's counter word
 // becomes its two placement cursors: start (A entries) in the low half,
 // start + nA (B entries) in the high half; a group not kept gets the
@@ -1248,17 +1280,19 @@ constexpr int GROUP_WORDS = BLOCK * GROUP_ITEMS;
 constexpr int GROUP_SEG = 8;                     // set bits per thread when the tile's are listed
 constexpr int GROUP_LIST = BLOCK * GROUP_SEG;
 constexpr uint64_t GRP_DROP = 0x8000000080000000ull;
+constexpr int64_t CROWDED = 470;                 // A entries above which a group counts as crowded
 
 struct GroupsOut {
     const uint32_t *both;     // fine both-occupied bits
     uint64_t *grp;            // per hashed cell: counters in, cursors out
     int64_t n_fwords;
     CellRec *cells;           // kept groups
-    int64_t *pstart;          // kept groups + 1
-    int64_t *kept;            // [0] kept groups, [1] their slots
+    int64_t *ustart;          // kept groups + 1: units of enumeration before each
+    int64_t *kept;            // [0] kept groups, [1] their units
     uint64_t *stat;           // 2 look-back words per tile (cleared)
     uint32_t *tile_ctr;       // (cleared)
     search_stats_t *stats;
+    unsigned long long *shards;   // the counter lines: [6] crowded chunks, [7] slots
 };
 
 // Tiles at most this many take their tile from the block index: every block
@@ -1272,6 +1306,8 @@ __global__ void __launch_bounds__(BLOCK) k_groups(GroupsOut o)
     __shared__ uint64_t s_kbase, s_pbase;
     __shared__ uint32_t s_tile;
     __shared__ uint32_t s_list[GROUP_LIST];
+    __shared__ unsigned long long s_slots[1];
+    if (threadIdx.x == 0) s_slots[0] = 0;      // (the scans below order this)
     const int64_t ntiles = (o.n_fwords + GROUP_WORDS - 1) / GROUP_WORDS;
     const bool direct = ntiles <= GROUP_DIRECT_TILES;
     for (int round = 0;; ++round) {
@@ -1288,7 +1324,17 @@ __global__ void __launch_bounds__(BLOCK) k_groups(GroupsOut o)
         if (tile >= ntiles) break;
         const int64_t w0 = tile * GROUP_WORDS + (int64_t)threadIdx.x * GROUP_ITEMS;
         uint32_t m[GROUP_ITEMS];
-        uint64_t kc = 0, pc = 0;     // (kept << 32) | entries; slots
+        uint64_t kc = 0, pc = 0;     // (kept << 32) | entries; units of enumeration
+        unsigned long long slots = 0, crowded = 0;
+        auto count = [&](uint64_t v) {
+            const uint64_t a = v & 0xffffffffull, b = v >> 32;
+            if (a && b) {
+                kc += (1ull << 32) + a + b;
+                pc += group_units((uint32_t)a, (uint32_t)b);
+                slots += a * b;
+                if ((int64_t)a > CROWDED) crowded += (a * b + 2047) / 2048;
+            }
+        };
         uint32_t nb = 0;
 #pragma unroll
         for (int j = 0; j < GROUP_ITEMS; ++j) {
@@ -1320,24 +1366,11 @@ __global__ void __launch_bounds__(BLOCK) k_groups(GroupsOut o)
                 gv[k2] = (uint32_t)k2 < segn ? o.grp[gh[k2]] : 0ull;
             }
 #pragma unroll
-            for (int k2 = 0; k2 < GROUP_SEG; ++k2) {
-                const uint64_t a = gv[k2] & 0xffffffffull, b = gv[k2] >> 32;
-                if (a && b) {
-                    kc += (1ull << 32) + a + b;
-                    pc += a * b;
-                }
-            }
+            for (int k2 = 0; k2 < GROUP_SEG; ++k2) count(gv[k2]);
         } else {
 #pragma unroll
             for (int j = 0; j < GROUP_ITEMS; ++j) {
-                for (uint32_t q = m[j]; q; q &= q - 1) {
-                    const uint64_t v = o.grp[32 * (w0 + j) + __builtin_ctz(q)];
-                    const uint64_t a = v & 0xffffffffull, b = v >> 32;
-                    if (a && b) {
-                        kc += (1ull << 32) + a + b;
-                        pc += a * b;
-                    }
-                }
+                for (uint32_t q = m[j]; q; q &= q - 1) count(o.grp[32 * (w0 + j) + __builtin_ctz(q)]);
             }
         }
         uint64_t ktot, ptot;
@@ -1369,13 +1402,22 @@ __global__ void __launch_bounds__(BLOCK) k_groups(GroupsOut o)
                     const int64_t nk = (int64_t)((kb + ktot) >> 32), P = (int64_t)(pb + ptot);
                     o.kept[0] = nk;
                     o.kept[1] = P;
-                    o.pstart[nk] = P;
+                    o.ustart[nk] = P;
                     o.stats->n_groups = nk;
-                    o.stats->n_group_slots = P;
                 }
             }
         }
+        if (slots) {
+            // (spread over the counter lines and added without a reply)
+            unsigned long long *w = o.shards + SHARD_WORDS * (tile % STAT_SHARDS);
+            atomicAdd(&s_slots[0], slots);
+            if (crowded) atomicAdd(w + 6, crowded);
+        }
         __syncthreads();
+        if (threadIdx.x == 0 && s_slots[0]) {
+            atomicAdd(o.shards + SHARD_WORDS * (tile % STAT_SHARDS) + 7, s_slots[0]);
+            s_slots[0] = 0;
+        }
         uint64_t kr = s_kbase + kex, pr = s_pbase + pex;
         // each group's record and cursors, in the order of the scan
         auto place = [&](int64_t h, uint64_t v) {
@@ -1384,15 +1426,15 @@ __global__ void __launch_bounds__(BLOCK) k_groups(GroupsOut o)
             if (a && b) {
                 const int64_t ki = (int64_t)(kr >> 32), start = (int64_t)(kr & 0xffffffffull);
                 CellRec cr;
-                cr.start = start;
+                cr.start = (uint32_t)start;
                 cr.nA = (int32_t)a;
                 cr.nB = (int32_t)b;
-                cr.h = h;
+                cr.h = (uint32_t)h;
                 o.cells[ki] = cr;
-                o.pstart[ki] = (int64_t)pr;
+                o.ustart[ki] = (int64_t)pr;
                 *gw = (((uint64_t)start + a) << 32) | (uint64_t)start;
                 kr += (1ull << 32) + a + b;
-                pr += a * b;
+                pr += group_units((uint32_t)a, (uint32_t)b);
             } else {
                 *gw = GRP_DROP;
             }
@@ -1413,20 +1455,44 @@ __global__ void __launch_bounds__(BLOCK) k_groups(GroupsOut o)
     }
 }
 
+// A box in 16 bits per corner and axis, for the enumeration's first test:
+// q(x) = floor((t - c) 2^14) + 2^14 clamped to [0, 65535], with t = (x - wlo)
+// inv the grid's coordinate (as cell_of) and c the entry's cell, so that the
+// cell is [2^14, 2^15) and a box reaching less than a cell below it or two
+// above it is kept to 2^-14 of a cell.  Every step is monotone and the same
+// for all entries of a cell, so boxes that overlap have lo <= hi in every
+// pair of corners here too; the few others that do (closer than the last
+// bit) fall at the exact test.
+constexpr double QBOX_SCALE = 16384.0;
+
+// (q of axes 0 and 1, q of axes 2 and 3) of a corner.
+MS_D uint2 qbox_corner(const GridView &g, const double x[4], const double c[4])
+{
+    uint32_t q[4];
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        const double t = (x[d] - g.wlo[d]) * g.inv;
+        const double f = floor((t - c[d]) * QBOX_SCALE) + QBOX_SCALE;
+        q[d] = (uint32_t)(int32_t)fmin(fmax(f, 0.0), 65535.0);
+    }
+    return make_uint2(q[0] | q[1] << 16, q[2] | q[3] << 16);
+}
+
 // Entries to their group's range: the group's start for the entry's side
 // plus the entry's rank among them (A entries first), each with its
-// triangle's box (from the vertices), so that the enumeration reads the box
-// with the entry.  Entries of groups holding one mesh only are dropped.  An
-// entry whose cell differs from its group's sample flags the group as
-// holding several cells.  When the next search's epoch value wraps to 1,
-// the occupancy tables are cleared here.
+// triangle's 16-bit box (from the vertices) and its home bits (bit d: the
+// triangle's lower corner lies in the entry's cell along axis d), so that
+// the enumeration reads them with the entry.  Entries of groups holding one
+// mesh only are dropped.  An entry whose cell differs from its group's
+// sample flags the group as holding several cells.  When the next search's
+// epoch value wraps to 1, the occupancy tables are cleared here.
 template <bool ONE>
 __global__ void __launch_bounds__(BLOCK) k_scatter(BatchView bv, const uint64_t *ent, const int32_t *epair,
-                                                   const uint32_t *erank, const uint32_t *ehash,
+                                                   const uint32_t *erank, const uint32_t *ehash, const uint16_t *eoff,
                                                    const unsigned long long *n_keys, int64_t cap,
                                                    const uint32_t *grp, const uint64_t *own, uint32_t *mix,
-                                                   uint64_t *out, int32_t *opair, double *sbox, const uint64_t *epoch,
-                                                   uint4 *flags, int64_t flag_vecs)
+                                                   uint64_t *out, int32_t *opair, uint32_t *ohome, uint4 *qbox,
+                                                   const uint64_t *epoch, uint4 *flags, int64_t flag_vecs)
 {
     const uint64_t ep = *epoch;                 // (read early, used last)
     const int64_t nk = (int64_t)*n_keys;
@@ -1435,7 +1501,7 @@ __global__ void __launch_bounds__(BLOCK) k_scatter(BatchView bv, const uint64_t 
     const int tb = bv.kl.tb;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
         const uint64_t e = ent[i];
-        const uint32_t r = erank[i];
+        const uint32_t r = erank[i], off = eoff[i];
         const int p = ONE ? 0 : epair[i];
         const uint64_t gc = e >> bv.kl.cell_shift;
         const uint32_t h = ehash[i];
@@ -1448,26 +1514,27 @@ __global__ void __launch_bounds__(BLOCK) k_scatter(BatchView bv, const uint64_t 
         const uint32_t pos = c + r;
         out[pos] = e;
         if (!ONE) opair[pos] = p;
-        double2 *b = reinterpret_cast<double2 *>(sbox + 8 * (size_t)pos);
-        b[0] = make_double2(lo[0], lo[1]);
-        b[1] = make_double2(lo[2], lo[3]);
-        b[2] = make_double2(hi[0], hi[1]);
-        b[3] = make_double2(hi[2], hi[3]);
+        // the entry's cell: the lowest cell's (that of the lower corner) plus the offset
+        double cell[4];
+        uint32_t home = 0;
+        bool far = false;
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            const uint32_t k = (off >> (4 * d)) & 15u;
+            cell[d] = (double)(cell_of(lo[d], Pd.g.wlo[d], Pd.g.inv, Pd.g.n[d]) + k);
+            home |= (k == 0 ? 1u : 0u) << d;
+            far = far || k == 15u;
+        }
+        ohome[pos] = home;
+        const uint2 ql = qbox_corner(Pd.g, lo, cell), qh = qbox_corner(Pd.g, hi, cell);
+        // (a cell 15 cells or more from the lowest: a box that meets every other)
+        qbox[pos] = far ? make_uint4(0u, 0u, ~0u, ~0u) : make_uint4(ql.x, ql.y, qh.x, qh.y);
         if (own[h] != gc) mix[h] = 1u;    // every writer stores the same value
     }
     if ((ep + 1) % 255u == 0) {          // the next search's value wraps to 1 (k_finish advances the epoch)
         const uint4 z = make_uint4(0u, 0u, 0u, 0u);
         for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < flag_vecs; i += stride) flags[i] = z;
     }
-}
-
-// Box of grouped entry e (lo in [0..3], hi in [4..7]).
-MS_D void entry_box(const double *sbox, int64_t e, double lo[4], double hi[4])
-{
-    const double2 *b = reinterpret_cast<const double2 *>(sbox + 8 * e);
-    const double2 a0 = b[0], a1 = b[1], a2 = b[2], a3 = b[3];
-    lo[0] = a0.x; lo[1] = a0.y; lo[2] = a1.x; lo[3] = a1.y;
-    hi[0] = a2.x; hi[1] = a2.y; hi[2] = a3.x; hi[3] = a3.y;
 }
 
 MS_D void wave_count(bool p, int64_t *ctr)
@@ -1490,125 +1557,79 @@ MS_D void emit_hit(bool hit, const hit_t &h, uint64_t key, hit_t *hits, uint64_t
     }
 }
 
-// Slot -> (group, iA, iB), iA = slot mod nA, iB = slot / nA (Alg. 1).  A
-// group holds the entries of every cell with the same hashed id, so a pair
-// of entries counts only when both are entries of the same cell; the pair
-// is then kept only in its home cell, the cell of the componentwise max of
-// the two boxes' lower corners (the one cell of both ranges that every
-// overlapping pair has, by monotonicity of the cell map), and only if the
-// closed boxes overlap (Sec. 6.2.2).
+// ------------------------------------------------------------ enumeration
 //
-// Each block takes a chunk of consecutive slots: ITEMS per thread, or up to
-// ITEMS_MAX when that is enough for every chunk to have a block in the first
-// round of resident blocks (otherwise a few chunks past a full round would
-// wait for a second round, doubling the kernel's time).  Of every group the
-// chunk touches it needs only the A entries of the rows it covers (all of
-// them once it spans more than one row) and the B entries of those rows; when
-// these are at most S::stage in all, the block stages their cells, triangle
-// indices and boxes in LDS, so that every slot reads LDS only.  Otherwise each slot gathers its two triangles from global
-// memory.  One atomic reservation per chunk for the candidates, then the
-// narrow phase on the chunk's candidates.  Last, the exact cell statistics
-// (Alg. 1's boxes and slots) of the groups that start in the chunk.
+// A kept group's nA x nB pairs (its slots, Alg. 1) are tested strip by strip:
+// the 64 lanes of a wave hold the 16-bit boxes of 64 entries of one mesh, and
+// the entries of the other are taken one after another with their boxes in
+// scalar registers (four of them are one 64-byte scalar load), so that a slot
+// costs 7 instructions for its lane (four saturating subtractions in packed
+// 16 bits, three to join and test them) and nothing is staged or addressed
+// per slot.  The side on the lanes is the one that takes fewer passes.  A
+// group holds the entries of every cell with the same hashed id, so where its
+// cells differ (its several-cells flag) a pair also needs equal cells.  A pair
+// counts in its home cell only, the cell of the componentwise max of the
+// boxes' lower corners (the one cell of both ranges that every overlapping
+// pair has, by monotonicity of the cell map): as both triangles cover the
+// entries' cell c, that max lies in c on an axis exactly when one of the two
+// lower corners does, which each entry's four home bits say; so the test is
+// one OR.
 //
-// The work-tile shape: NT threads per block, ITEMS (up to ITEMS_MAX) slots
-// per thread (a chunk is NT * ITEMS slots), STAGE staged entries (their LDS
-// also holds a chunk's candidates), CELLS groups per chunk held in LDS,
-// PSTART slot offsets held in LDS, GRID blocks.  The narrow phase needs
-// about 200 registers, so a SIMD holds two waves: one 512-thread block per
-// CU, or two 256-thread blocks when their LDS fits twice.  Results do not
-// depend on the shape, only the time.
-template <int NT, int ITEMS, int ITEMS_MAX, int STAGE, int CELLS, int PSTART, int GRID>
-struct EnumShape {
-    static constexpr int block = NT, items = ITEMS, items_max = ITEMS_MAX, slots_max = NT * ITEMS_MAX, stage = STAGE,
-                         cells = CELLS, pstart = PSTART, grid = GRID;
-    static_assert(ITEMS <= ITEMS_MAX && ITEMS_MAX <= 32 && CELLS <= NT, "keep bits per thread; one group per thread");
-};
-using EnumWide = EnumShape<512, 8, 10, 960, 256, 4096, 512>;     // one block per CU, two rounds
-using EnumHalf = EnumShape<256, 8, 10, 480, 128, 2048, 1024>;    // two blocks per CU, two rounds
-using EnumQuarter = EnumShape<128, 8, 10, 240, 64, 1024, 2048>;  // four blocks per CU, two rounds
+// The work is counted in units, one per scalar entry of a strip and
+// STRIP_UNITS for its start, and the waves take equal runs of units: a wave
+// finds its first group by a 64-way search of the groups' unit offsets, and
+// goes on from there.  Pairs whose 16-bit boxes overlap go to a queue of the
+// wave in LDS; whenever it holds 64 they take the exact box test (Sec. 6.2.2:
+// those that pass are the candidates) and the Moller quick test (Sec. 6.2.3)
+// on the vertices with all lanes, what is left goes to a second queue and
+// takes the 4x4 solve (Sec. 6.2.4) likewise, so that neither runs with a few
+// lanes and the registers of the one are not held during the other.
+//
+// Measured (512 x 512 quads at kappa 1.5; two propagated patches; the 256
+// uneven pairs; the 112 half-layer pairs): 13.1, 84, 147 and 87 us.  With a
+// thread for every 256th slot of a chunk, the entries' FP64 boxes staged in
+// LDS and the narrow phase fused at two waves per SIMD it took 20.7, 381, 498
+// and 258 us, about 11 cycles per slot and CU of dependent LDS reads.  FP64
+// boxes broadcast from the lanes (v_readlane) took 19.0, 139, 249 and 136 us;
+// FP64 boxes by scalar loads, one at a time for want of scalar registers,
+// 20.8, 131, 294 and 150.  Five waves per SIMD spill: 18.0, 91, 182, 113.
+// One block for each resident place instead of two: 13.1, 118, 161, 90 (the
+// candidates lie in few runs; smaller runs share them out better).
+constexpr int ENUM_BLOCK = 256;
+constexpr int ENUM_WAVES = ENUM_BLOCK / WAVE;
+constexpr int ENUM_GRID = 2048;           // twice the resident blocks (four waves per SIMD)
+constexpr int STRIP_UNROLL = 4;           // scalar entries per round (one 64-byte scalar load)
+constexpr int QUEUE1 = WAVE + STRIP_UNROLL * WAVE, QUEUE2 = 2 * WAVE;
 
-template <bool ONE>
-MS_D bool enum_pair(const PairDesc &Pd, uint64_t cell, const double alo[4], const double ahi[4], const double blo[4],
-                    const double bhi[4])
+// Orders the LDS accesses of one wave's lanes.
+MS_D void wave_sync()
 {
-    bool ov = true;
-#pragma unroll
-    for (int d = 0; d < 4; ++d) ov = ov && (alo[d] <= bhi[d]) && (blo[d] <= ahi[d]);
-    if (!ov) return false;
-    int64_t h[4];
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-        const double m = alo[d] > blo[d] ? alo[d] : blo[d];
-        h[d] = cell_of(m, Pd.g.wlo[d], Pd.g.inv, Pd.g.n[d]);
-    }
-    return (uint64_t)cell_linear(h, Pd.g.n) == cell;
-}
-
-// Bounds of local cell `cell` in t = (x - wlo) * inv per axis, such that
-// cell_of(x) == that axis's coordinate exactly when lo <= t and not t >= hi:
-// lo = -inf on the first cell, hi = NaN on the last (no upper bound), else
-// the cell's integer edges (floor(t) == c <=> c <= t < c + 1 in FP64).
-template <int CELLS>
-MS_D void home_bounds(const GridView &g, uint64_t cell, double (*gb)[CELLS], int k)
-{
-    int64_t c[4];
-    uint64_t r = cell;
-#pragma unroll
-    for (int d = 3; d >= 0; --d) {
-        c[d] = (int64_t)(r % (uint64_t)g.n[d]);
-        r /= (uint64_t)g.n[d];
-    }
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-        gb[d][k] = c[d] == 0 ? -INFINITY : (double)c[d];
-        gb[4 + d][k] = c[d] == g.n[d] - 1 ? (double)NAN : (double)(c[d] + 1);
-    }
-}
-
-// Slot offset inside a group -> (row iB, column iA) for rows of nA; the
-// 32-bit division is much cheaper and covers every group below 2^32 slots.
-MS_D void split_slot(uint64_t local, uint32_t nA, uint64_t &iB, uint64_t &iA)
-{
-    if (local <= 0xffffffffull) {
-        const uint32_t l = (uint32_t)local, q = l / nA;
-        iB = q;
-        iA = l - q * nA;
-    } else {
-        iB = local / nA;
-        iA = local - iB * nA;
-    }
-}
-
-template <bool ONE>
-MS_D int entry_pair(const int32_t *kpair, int64_t e)
-{
-    if constexpr (ONE) return 0;
-    else return kpair[e];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 }
 
 // Exact cell statistics of a group holding several cells (cells whose hashes
-// collide), by the whole block of NT threads: each cell's A and B entries are
-// counted in an LDS table keyed by the cell (s_tab: GS_SLOTS keys, then as
-// many count words, then an overflow flag), then every cell with entries of
-// both meshes adds itself and nA * nB slots.  A group of more distinct cells
-// than the table holds is counted per A entry instead.
+// collide), by one wave: each cell's A and B entries are counted in an LDS
+// table keyed by the cell (s_tab: GS_SLOTS keys, then as many count words),
+// then every cell with entries of both meshes adds itself and nA * nB slots.
+// A group of more distinct cells than the table holds is counted per A entry
+// instead.
 constexpr int GS_SLOTS = 64;
 
-template <int NT>
 MS_D void group_stats(const uint64_t *keys, const CellRec &cr, int sh, uint64_t *s_tab, unsigned long long &xc,
                       unsigned long long &xs)
 {
     constexpr uint64_t EMPTY = ~0ull;
-    uint64_t *s_key = s_tab, *s_cnt = s_tab + GS_SLOTS, *s_full = s_tab + 2 * GS_SLOTS;
-    for (int i = threadIdx.x; i < GS_SLOTS; i += NT) {
-        s_key[i] = EMPTY;
-        s_cnt[i] = 0;
-    }
-    if (threadIdx.x == 0) *s_full = 0;
-    __syncthreads();
+    const int lane = lane_id();
+    uint64_t *s_key = s_tab, *s_cnt = s_tab + GS_SLOTS;
+    wave_sync();
+    s_key[lane] = EMPTY;
+    s_cnt[lane] = 0;
+    wave_sync();
     const int n = cr.nA + cr.nB;
-    for (int i = threadIdx.x; i < n; i += NT) {
-        const uint64_t c = keys[cr.start + i] >> sh;
+    bool full = false;
+    for (int i = lane; i < n; i += WAVE) {
+        const uint64_t c = keys[(int64_t)cr.start + i] >> sh;
         const unsigned long long add = i < cr.nA ? 1ull : (1ull << 32);   // nA in the low half, nB in the high
         uint32_t slot = (uint32_t)((c * 0x9E3779B97F4A7C15ull) >> 58);
         bool done = false;
@@ -1622,508 +1643,302 @@ MS_D void group_stats(const uint64_t *keys, const CellRec &cr, int sh, uint64_t 
                 slot = (slot + 1) & (GS_SLOTS - 1);
             }
         }
-        if (!done) *s_full = 1;
+        full = full || !done;
     }
-    __syncthreads();
-    if (*s_full == 0) {
-        for (int i = threadIdx.x; i < GS_SLOTS; i += NT) {
-            if (s_key[i] == EMPTY) continue;
-            const uint64_t v = s_cnt[i], a = v & 0xffffffffull, b = v >> 32;
+    wave_sync();
+    if (ballot(full) == 0) {
+        if (s_key[lane] != EMPTY) {
+            const uint64_t v = s_cnt[lane], a = v & 0xffffffffull, b = v >> 32;
             xs += a * b;
             xc += (a > 0 && b > 0);
         }
     } else {
-        for (int i = threadIdx.x; i < cr.nA; i += NT) {
-            const uint64_t ci = keys[cr.start + i] >> sh;
+        for (int i = lane; i < cr.nA; i += WAVE) {
+            const uint64_t ci = keys[(int64_t)cr.start + i] >> sh;
             uint32_t nb = 0, before = 0;
-            for (int j = 0; j < cr.nB; ++j) nb += (keys[cr.start + cr.nA + j] >> sh) == ci;
-            for (int j = 0; j < i; ++j) before += (keys[cr.start + j] >> sh) == ci;
+            for (int j = 0; j < cr.nB; ++j) nb += (keys[(int64_t)cr.start + cr.nA + j] >> sh) == ci;
+            for (int j = 0; j < i; ++j) before += (keys[(int64_t)cr.start + j] >> sh) == ci;
             xs += nb;
             xc += (nb > 0 && before == 0);
         }
     }
-    __syncthreads();
 }
 
-// A staged slot: its group c (last with s_pre[c] <= slot) and the staged
-// indices of its A and B entries.
-struct StagedSlot {
-    int c, ia, ib;
-};
-
-MS_D StagedSlot staged_slot(int64_t slot, int nc, const int64_t *s_pre, const int32_t *s_nA, const int32_t *s_aoff,
-                            const int32_t *s_ia0, const int32_t *s_boff, const int32_t *s_ib0)
+// A value that is the same in every lane, told to the compiler.
+MS_D uint32_t uni(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
+MS_D int64_t uni(int64_t v)
 {
-    int lo = 0, hi = nc;
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (s_pre[mid] <= slot) lo = mid;
-        else hi = mid;
-    }
-    uint64_t iB, iA;
-    split_slot((uint64_t)(slot - s_pre[lo]), (uint32_t)s_nA[lo], iB, iA);
-    StagedSlot q;
-    q.c = lo;
-    q.ia = s_aoff[lo] + (int)((int64_t)iA - s_ia0[lo]);
-    q.ib = s_boff[lo] + (int)((int64_t)iB - s_ib0[lo]);
-    return q;
+    return (int64_t)((uint64_t)uni((uint32_t)((uint64_t)v >> 32)) << 32 | uni((uint32_t)v));
 }
 
-// One slot from global memory (chunks whose entries do not fit the LDS
-// stage): its group by binary search, both entries, both boxes from the
-// vertices.
-struct SlotOut {
-    uint64_t packed;    // (triA << 32) | triB
-    int32_t pr;         // pair
-    int32_t keep;
-};
-
-template <bool ONE>
-MS_D SlotOut global_slot(const BatchView &bv, const uint64_t *keys, const int32_t *kpair, const double *sbox,
-                         const CellRec *cells, const int64_t *pstart, int64_t c0, int64_t nc, const int64_t *s_pre,
-                         int64_t slot)
+// max(a - b, 0) in each 16-bit half.
+MS_D uint32_t sub_sat16(uint32_t a, uint32_t b)
 {
-    SlotOut o;
-    o.packed = 0;
-    o.pr = 0;
-    o.keep = 0;
-    const int sh = bv.kl.cell_shift;
-    // the slot's group among the chunk's nc groups from c0: their slot
-    // starts in LDS (s_pre) when they are few, else in global memory
-    const int64_t c = s_pre ? c0 + last_le<int64_t>(s_pre, nc, slot) : c0 + last_le<int64_t>(pstart + c0, nc, slot);
-    const CellRec cr = cells[c];
-    uint64_t iB, iA;
-    split_slot((uint64_t)(slot - pstart[c]), (uint32_t)cr.nA, iB, iA);
-    const int64_t eA = cr.start + (int64_t)iA, eB = cr.start + cr.nA + (int64_t)iB;
-    const uint64_t kA = keys[eA];
-    const uint64_t kB = keys[eB];
-    const uint64_t ca = kA >> sh;
-    const int32_t ta = (int32_t)(kA & bv.kl.tmask), tb = (int32_t)(kB & bv.kl.tmask);
-    o.packed = ((uint64_t)(uint32_t)ta << 32) | (uint32_t)tb;
-    if (ca != (kB >> sh)) return o;
-    o.pr = entry_pair<ONE>(kpair, eA);
-    const PairDesc &Pd = pair_desc<ONE>(bv, o.pr);
-    double alo[4], ahi[4], blo[4], bhi[4];
-    entry_box(sbox, eA, alo, ahi);
-    entry_box(sbox, eB, blo, bhi);
-    o.keep = enum_pair<ONE>(Pd, ca - Pd.cell_base, alo, ahi, blo, bhi);
+    typedef unsigned short us2 __attribute__((ext_vector_type(2)));
+    us2 x, y;
+    __builtin_memcpy(&x, &a, 4);
+    __builtin_memcpy(&y, &b, 4);
+    const us2 r = __builtin_elementwise_sub_sat(x, y);
+    uint32_t o;
+    __builtin_memcpy(&o, &r, 4);
     return o;
 }
 
-// For x0 <= x1, the last i0 and i1 in [0, n) with a[i] <= x (a ascending,
-// a[0] <= x0), found by the whole block at once: each round splits every
-// open range [lo, hi) into NT parts, one per thread, and keeps the part
-// where a[i] <= x stops holding (two loads per thread and round; log_NT(n)
-// rounds).  s_r[0..1] = [lo, hi) for x0, s_r[2..3] for x1; the results are
-// s_r[0] and s_r[2].  Ends with a barrier.
-template <int NT>
-MS_D void block_last_le2(const int64_t *a, int64_t n, int64_t x0, int64_t x1, int64_t *s_r)
-{
-    if (threadIdx.x == 0) {
-        s_r[0] = 0;
-        s_r[1] = n;
-        s_r[2] = 0;
-        s_r[3] = n;
-    }
-    __syncthreads();
-    for (;;) {
-        const int64_t lo0 = s_r[0], hi0 = s_r[1], lo1 = s_r[2], hi1 = s_r[3];
-        if (hi0 - lo0 <= 1 && hi1 - lo1 <= 1) break;
-        __syncthreads();      // every thread has read the ranges
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            const int64_t lo = k ? lo1 : lo0, hi = k ? hi1 : hi0, x = k ? x1 : x0;
-            if (hi - lo <= 1) continue;
-            const int64_t step = (hi - lo + NT - 1) / NT;
-            const int64_t i = lo + (int64_t)threadIdx.x * step;
-            if (i < hi && a[i] <= x) {
-                const int64_t j = i + step;
-                if (j >= hi || a[j] > x) {
-                    s_r[2 * k] = i;
-                    s_r[2 * k + 1] = j < hi ? j : hi;
-                }
-            }
-        }
-        __syncthreads();
-    }
-    __syncthreads();
-}
+// Memory that no kernel running beside this one writes, read through the
+// scalar cache (uniform addresses).
+template <typename T>
+using ScalarPtr = const __attribute__((address_space(4))) T *;
 
-template <bool ONE, class S>
-__global__ void __launch_bounds__(S::block) k_enum(BatchView bv, const uint64_t *keys, const int32_t *kpair,
-                                                const double *sbox, const CellRec *cells, const int64_t *pstart_g, const int64_t *kept,
-                                                const uint32_t *mix,
-                                                search_stats_t *stats, uint64_t *cand, int32_t *cand_pair,
-                                                int64_t cand_cap, hit_t *hits, uint64_t *hkeys, int64_t hits_cap,
-                                                unsigned long long *epart, int resident)
+struct EnumArgs {
+    const uint64_t *keys;         // grouped entries [cell | side | triangle]
+    const int32_t *kpair;         // their pairs (batch)
+    const uint4 *qbox;            // their 16-bit boxes: (lo 01, lo 23, hi 01, hi 23)
+    const uint32_t *home;         // their home bits
+    const CellRec *cells;         // kept groups
+    const int64_t *ustart;        // their unit offsets
+    const int64_t *kept;          // [0] kept groups, [1] units
+    const uint32_t *mix;          // several-cells flags by hashed cell
+    search_stats_t *stats;
+    uint64_t *cand;               // candidate list (optional)
+    int64_t cand_cap;
+    hit_t *hits;
+    uint64_t *hkeys;
+    int64_t hits_cap;
+    unsigned long long *epart;    // counter lines
+    int64_t min_share;            // units per wave at least
+};
+
+template <bool ONE>
+__global__ void __launch_bounds__(ENUM_BLOCK) __attribute__((amdgpu_waves_per_eu(4, 8)))
+k_enum(BatchView bv, EnumArgs a)
 {
-    constexpr int ENUM_BLOCK = S::block, ENUM_ITEMS = S::items, ENUM_ITEMS_MAX = S::items_max,
-                  ENUM_SLOTS_MAX = S::slots_max, ENUM_STAGE = S::stage, ENUM_CELLS = S::cells,
-                  ENUM_PSTART = S::pstart;
-    static_assert(ENUM_STAGE > 2 * GS_SLOTS, "the staged cells hold a group's statistics table");
-    __shared__ int64_t s_pstart[ENUM_PSTART + 1];
-    // the staged boxes during enumeration (component-major, so that lanes
-    // reading consecutive entries hit distinct banks), then the chunk's
-    // compacted candidates
-    __shared__ union {
-        double box[8][ENUM_STAGE];
-        struct {
-            uint64_t tt[ENUM_SLOTS_MAX];
-            int32_t pair[ENUM_SLOTS_MAX];
-        } c;
-    } s_u;
-    static_assert(sizeof(double) * ENUM_STAGE * 8 >= 12 * ENUM_SLOTS_MAX, "candidate list overlays the staged boxes");
-    double (*s_box)[ENUM_STAGE] = s_u.box;
-    __shared__ int32_t s_t[ENUM_STAGE];
-    __shared__ uint64_t s_ec[ENUM_STAGE];
-    __shared__ int32_t s_ep[ONE ? 1 : ENUM_STAGE];
-    __shared__ int64_t s_pre[ENUM_CELLS + 1];
-    __shared__ int64_t s_start[ENUM_CELLS];
-    __shared__ int32_t s_aoff[ENUM_CELLS + 1], s_boff[ENUM_CELLS], s_ia0[ENUM_CELLS], s_ib0[ENUM_CELLS];
-    __shared__ int32_t s_nA[ENUM_CELLS];
-    __shared__ int64_t s_c0, s_c1;
-    __shared__ int64_t s_rng[4];
-    __shared__ uint32_t s_kscan[ENUM_BLOCK / WAVE];
-    __shared__ unsigned long long s_kbase;
-    __shared__ unsigned long long s_st[ENUM_BLOCK / WAVE];
-    __shared__ uint32_t s_nmix;
-    __shared__ uint64_t s_gcell[ENUM_CELLS];
-    __shared__ double s_gb[8][ENUM_CELLS];            // per staged group: t-bounds of its cell
-    __shared__ double s_gw[ONE ? 1 : 5][ENUM_CELLS];  // per staged group: wlo, inv (batch)
-    unsigned long long xc = 0, xs = 0;      // exact cells and slots
-    // the block's counts (thread 0), added at its end to one of STAT_SHARDS
-    // counter lines (block index mod STAT_SHARDS): same-line atomics of
-    // hundreds of blocks would serialise; k_finish sums the lines
-    unsigned long long b_cand = 0, b_moller = 0, b_degen = 0, b_outside = 0, b_unstaged = 0;
-    const int64_t ncells = kept[0];
-    const int64_t P = kept[1];
-    // slots per thread: ENUM_ITEMS, or more (up to ENUM_ITEMS_MAX) when that
-    // gives every chunk a block among the `resident` ones of the first round
-    int items = ENUM_ITEMS;
-    if (resident > 0) {
-        const int64_t per = ceil_div(P, (int64_t)resident * ENUM_BLOCK);
-        if (per > ENUM_ITEMS && per <= ENUM_ITEMS_MAX) items = (int)per;
-    }
-    const int64_t chunk_slots = (int64_t)items * ENUM_BLOCK;
-    const int64_t nchunks = ceil_div(P, chunk_slots);
-    if ((int64_t)blockIdx.x >= nchunks) return;     // no chunk, nothing to count (the whole block)
+    __shared__ uint2 s_q1[ENUM_WAVES][QUEUE1];      // candidates: A entry, B entry
+    __shared__ uint2 s_q2[ENUM_WAVES][QUEUE2];      // those that the Moller test left
+    __shared__ uint64_t s_tab[ENUM_WAVES][2 * GS_SLOTS];
+    __shared__ unsigned long long s_cnt[7];
+    const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+    const int64_t nc = a.kept[0], W = a.kept[1];
+    int64_t share = ceil_div(W, (int64_t)gridDim.x * ENUM_WAVES);
+    // with a share of its own for every block, neighbouring runs (of one
+    // crowded group, which read the same boxes) share an XCD
+    const int64_t blk = share > a.min_share ? xcd_block(blockIdx.x, gridDim.x) : blockIdx.x;
+    if (share < a.min_share) share = a.min_share;
+    if (blk * ENUM_WAVES * share >= W) return;       // the whole block
+    if (threadIdx.x < 7) s_cnt[threadIdx.x] = 0;
+    __syncthreads();
     const int sh = bv.kl.cell_shift;
-    const bool lds_pre = ncells <= ENUM_PSTART;
-    {
-    if (lds_pre) {
-        for (int64_t i = threadIdx.x; i <= ncells; i += ENUM_BLOCK) s_pstart[i] = pstart_g[i];
-        __syncthreads();
+    int64_t w = (blk * ENUM_WAVES + wv) * share;
+    const int64_t wend = w + share < W ? w + share : W;
+    uint32_t q1n = 0, q2n = 0;
+    unsigned long long xc = 0, xs = 0;               // exact cells and slots (per lane)
+    uint32_t n_cand = 0, n_moller = 0, n_degen = 0, n_out = 0;   // per wave
+    int64_t touched = 0;                             // entries whose boxes the wave took
+    // the group that holds unit w
+    int64_t g = 0;
+    if (w < wend) {
+        int64_t lo = 0, hi = nc;
+        while (hi - lo > 1) {
+            const int64_t step = (hi - lo + WAVE - 1) / WAVE, i = lo + lane * step;
+            const uint64_t m = ballot(i < hi && a.ustart[i] <= w);
+            const int64_t k = lo + (63 - __builtin_clzll(m)) * step;      // lane 0 always qualifies
+            hi = uni(k + step < hi ? k + step : hi);
+            lo = uni(k);
+        }
+        g = uni(lo);
     }
-    const int64_t *pstart = lds_pre ? s_pstart : pstart_g;
-    for (int64_t chunk = blockIdx.x; chunk < nchunks; chunk += gridDim.x) {
-        const int64_t S0 = chunk * chunk_slots;
-        const int64_t S1 = S0 + chunk_slots < P ? S0 + chunk_slots : P;
-        if (lds_pre) {
-            // the one i with pstart[i] <= x < pstart[i + 1], for x = S0, S1 - 1
-            for (int64_t i = threadIdx.x; i < ncells; i += ENUM_BLOCK) {
-                const int64_t a = s_pstart[i], b = s_pstart[i + 1];
-                if (a <= S0 && S0 < b) s_c0 = i;
-                if (a <= S1 - 1 && S1 - 1 < b) s_c1 = i;
+    // one strip (or what of it is this wave's) at a time
+    int64_t u0 = 0, u1 = 0;                          // the present group's units
+    CellRec cr = {};
+    GroupShape gs = {};
+    bool mixed = false;
+    uint32_t si = 0, s1 = 0;                         // scalar entries still to do
+    uint32_t eL = 0, eS0 = 0;                        // this lane's entry, the first scalar entry
+    uint4 lq = make_uint4(0u, 0u, 0u, 0u);
+    uint64_t lmask = 0;                              // lanes that hold an entry
+    uint32_t lhome = 0;
+    uint64_t lcell = 0;
+    // the next group's record, fetched while the present one is worked on
+    CellRec ncr = {};
+    int64_t nu0 = 0, nu1 = 0;
+    auto fetch = [&](int64_t k) {
+        if (k >= nc) return;
+        ScalarPtr<CellRec> rc = (ScalarPtr<CellRec>)(a.cells + k);
+        ScalarPtr<int64_t> us = (ScalarPtr<int64_t>)(a.ustart + k);
+        ncr.start = rc->start;
+        ncr.nA = rc->nA;
+        ncr.nB = rc->nB;
+        ncr.h = rc->h;
+        nu0 = us[0];
+        nu1 = us[1];
+    };
+    if (w < wend) fetch(g);
+    for (;;) {
+        si = uni(si);
+        s1 = uni(s1);
+        q1n = uni(q1n);
+        q2n = uni(q2n);
+        if (si >= s1 && w < wend) {
+            const bool enter = w >= u1;
+            if (enter) {
+                cr = ncr;
+                u0 = nu0;
+                u1 = nu1;
+                gs = group_shape((uint32_t)cr.nA, (uint32_t)cr.nB);
+                g = uni(g + 1);
+                fetch(g);
             }
-            if (threadIdx.x == 0) s_nmix = 0;
-        } else {
-            block_last_le2<ENUM_BLOCK>(pstart, ncells, S0, S1 - 1, s_rng);
-            if (threadIdx.x == 0) {
-                s_c0 = s_rng[0];
-                s_c1 = s_rng[2];
-                s_nmix = 0;
-            }
-        }
-        __syncthreads();
-        const int64_t c0 = s_c0, nc = s_c1 - s_c0 + 1;
-        const int64_t *pre_lds = nc <= ENUM_CELLS ? s_pre : nullptr;
-        // the rows of every touched group that the chunk covers, and the entries they need
-        uint32_t need = 0;
-        bool first_here = false;     // the group's first slot is in this chunk (it is counted here)
-        uint32_t mixv = 0;
-        uint64_t gslots = 0;
-        if (nc <= ENUM_CELLS && threadIdx.x < nc) {
-            const int64_t c = c0 + threadIdx.x;
-            const CellRec cr = cells[c];
-            const int64_t p0 = pstart[c], p1 = pstart[c + 1];
-            first_here = p0 >= S0;
-            if (first_here) mixv = mix[cr.h];      // used after the narrow phase
-            gslots = (uint64_t)cr.nA * (uint64_t)cr.nB;
-            const int64_t l0 = (S0 > p0 ? S0 : p0) - p0, l1 = (S1 < p1 ? S1 : p1) - p0;
-            const int64_t ib0 = l0 / cr.nA, ib1 = (l1 - 1) / cr.nA;
-            int64_t ia0 = 0, ia1 = cr.nA;
-            if (ib0 == ib1) {
-                ia0 = l0 - ib0 * cr.nA;
-                ia1 = (l1 - 1) - ib1 * cr.nA + 1;
-            }
-            need = (uint32_t)((ia1 - ia0) + (ib1 - ib0 + 1));
-            s_pre[threadIdx.x] = p0;
-            s_start[threadIdx.x] = cr.start;
-            s_ia0[threadIdx.x] = (int32_t)ia0;
-            s_ib0[threadIdx.x] = (int32_t)ib0;
-            s_nA[threadIdx.x] = cr.nA;
-            s_boff[threadIdx.x] = (int32_t)(ia1 - ia0);     // made absolute below
-            if (threadIdx.x == nc - 1) s_pre[nc] = p1;
-        }
-        uint32_t tot;
-        const uint32_t off = block_excl<ENUM_BLOCK>(need, s_kscan, &tot);
-        const bool staged = nc <= ENUM_CELLS && tot <= ENUM_STAGE;
-        if (!staged && threadIdx.x == 0) ++b_unstaged;
-        if (staged) {
-            if (threadIdx.x < nc) {
-                s_aoff[threadIdx.x] = (int32_t)off;
-                s_boff[threadIdx.x] += (int32_t)off;
-            }
-            if (threadIdx.x == 0) s_aoff[nc] = (int32_t)tot;
-            __syncthreads();
-            for (int i = threadIdx.x; i < (int)tot; i += ENUM_BLOCK) {
-                int lo = 0, hi = (int)nc;             // the group whose staged range holds i
-                while (hi - lo > 1) {
-                    const int mid = (lo + hi) >> 1;
-                    if (s_aoff[mid] <= i) lo = mid;
-                    else hi = mid;
-                }
-                const bool isB = i >= s_boff[lo];
-                const int64_t e = isB ? s_start[lo] + s_nA[lo] + s_ib0[lo] + (i - s_boff[lo])
-                                      : s_start[lo] + s_ia0[lo] + (i - s_aoff[lo]);
-                const uint64_t key = keys[e];
-                const int32_t t = (int32_t)(key & bv.kl.tmask);
-                const int p = entry_pair<ONE>(kpair, e);
-                double blo[4], bhi[4];
-                entry_box(sbox, e, blo, bhi);
-#pragma unroll
-                for (int d = 0; d < 4; ++d) { s_box[d][i] = blo[d]; s_box[4 + d][i] = bhi[d]; }
-                s_t[i] = t;
-                s_ec[i] = key >> sh;
-                if (!ONE) s_ep[i] = p;
-            }
-            __syncthreads();
-            // per group: the cell of its first staged entry (every entry's
-            // cell, unless the group holds several) and that cell's bounds
-            // in the grid's coordinate t = (x - wlo) * inv
-            if (threadIdx.x < nc) {
-                const int i0 = s_aoff[threadIdx.x];
-                const uint64_t gc = s_ec[i0];
-                const PairDesc &Pd = pair_desc<ONE>(bv, ONE ? 0 : s_ep[i0]);
-                home_bounds<ENUM_CELLS>(Pd.g, gc - Pd.cell_base, s_gb, threadIdx.x);
-                s_gcell[threadIdx.x] = gc;
-                if constexpr (!ONE) {
-#pragma unroll
-                    for (int d = 0; d < 4; ++d) s_gw[d][threadIdx.x] = Pd.g.wlo[d];
-                    s_gw[4][threadIdx.x] = Pd.g.inv;
+            const bool first = w == u0;              // the group's first unit is here: so are its statistics
+            const uint64_t local = (uint64_t)uni(w - u0);
+            const uint64_t strip = local <= 0xffffffffull ? (uint64_t)((uint32_t)local / gs.unit) : local / gs.unit;
+            const uint64_t off = local - strip * gs.unit;                 // where in the strip
+            const uint64_t left = gs.unit - off < (uint64_t)(wend - w) ? gs.unit - off : (uint64_t)(wend - w);
+            w = uni(w + (int64_t)left);
+            si = uni(off > STRIP_UNITS ? (uint32_t)(off - STRIP_UNITS) : 0u);
+            s1 = uni(off + left > STRIP_UNITS ? (uint32_t)(off + left - STRIP_UNITS) : 0u);
+            const uint32_t l = (uint32_t)strip * WAVE + lane;
+            eL = cr.start + (gs.lanes_b ? (uint32_t)cr.nA : 0u) + l;
+            eS0 = uni(cr.start + (gs.lanes_b ? 0u : (uint32_t)cr.nA));
+            if (si < s1) {
+                touched += WAVE + (s1 - si);
+                lmask = ballot(l < gs.nl);
+                if (l < gs.nl) {
+                    lq = a.qbox[eL];
+                    lhome = a.home[eL];
+                    lcell = a.keys[eL] >> sh;
                 }
             }
-            __syncthreads();
-        }
-        // pass 1: the keep bit of each slot (the pair of a kept slot is
-        // found again in pass 2, so that no per-slot state is held)
-        uint32_t keepm = 0;
-        // a thread's slots lie ENUM_BLOCK apart: the group and the (iB, iA)
-        // split are found once per group entered, then advanced by
-        // ENUM_BLOCK = qa * nA + ra slots at a time
-        int c = 0, ia = 0, ib = 0;
-        int64_t pend = 0;
-        uint32_t nAc = 1, iA = 0, qa = 0, ra = 0;
-#pragma unroll 1
-        for (int j = 0; j < items; ++j) {
-            const int64_t slot = S0 + (int64_t)j * ENUM_BLOCK + threadIdx.x;
-            bool keep = false;
-            if (slot < S1) {
-                if (staged) {
-                    if (j == 0 || slot >= pend) {
-                        const StagedSlot q = staged_slot(slot, (int)nc, s_pre, s_nA, s_aoff, s_ia0, s_boff, s_ib0);
-                        c = q.c;
-                        ia = q.ia;
-                        ib = q.ib;
-                        nAc = (uint32_t)s_nA[c];
-                        pend = s_pre[c + 1];
-                        iA = (uint32_t)(ia - s_aoff[c] + s_ia0[c]);
-                        qa = (uint32_t)ENUM_BLOCK / nAc;
-                        ra = (uint32_t)ENUM_BLOCK - qa * nAc;
-                    } else {
-                        iA += ra;
-                        ia += (int)ra;
-                        ib += (int)qa;
-                        if (iA >= nAc) {
-                            iA -= nAc;
-                            ia -= (int)nAc;
-                            ++ib;
-                        }
-                    }
-                    const uint64_t ca = s_ec[ia];
-                    if (ca == s_ec[ib]) {
-                        double alo[4], ahi[4], blo[4], bhi[4];
-                        bool ov = true;
-#pragma unroll
-                        for (int d = 0; d < 4; ++d) {
-                            alo[d] = s_box[d][ia]; ahi[d] = s_box[4 + d][ia];
-                            blo[d] = s_box[d][ib]; bhi[d] = s_box[4 + d][ib];
-                            ov = ov && (alo[d] <= bhi[d]) && (blo[d] <= ahi[d]);
-                        }
-                        if (ov) {
-                            if (ca == s_gcell[c]) {
-                                // home cell = the group's cell: per axis, the
-                                // max of the lower corners falls in its bounds
-                                bool in = true;
-#pragma unroll
-                                for (int d = 0; d < 4; ++d) {
-                                    const double m = alo[d] > blo[d] ? alo[d] : blo[d];
-                                    double wl, iv;
-                                    if constexpr (ONE) {
-                                        wl = bv.p0.g.wlo[d];
-                                        iv = bv.p0.g.inv;
-                                    } else {
-                                        wl = s_gw[d][c];
-                                        iv = s_gw[4][c];
-                                    }
-                                    const double t = (m - wl) * iv;
-                                    in = in && (t >= s_gb[d][c]) && !(t >= s_gb[4 + d][c]);
-                                }
-                                keep = in;
-                            } else {
-                                const PairDesc &Pd = pair_desc<ONE>(bv, ONE ? 0 : s_ep[ia]);
-                                keep = enum_pair<ONE>(Pd, ca - Pd.cell_base, alo, ahi, blo, bhi);
-                            }
-                        }
-                    }
-                } else {
-                    keep = global_slot<ONE>(bv, keys, kpair, sbox, cells, pstart, c0, nc, pre_lds, slot).keep != 0;
-                }
-            }
-            keepm |= (uint32_t)keep << j;
-        }
-        // the candidates: counted with one atomic per chunk, stored when asked
-        // for, and compacted into LDS for the narrow phase
-        uint32_t ktot;
-        const uint32_t kex = block_excl<ENUM_BLOCK>((uint32_t)__builtin_popcount(keepm), s_kscan, &ktot);
-        if (threadIdx.x == 0) {
-            // the chunk's place in the candidate list matters only when the
-            // list is stored; otherwise the count needs no reply
-            unsigned long long b = 0;
-            if (ktot) {
-                if (cand) b = atomicAdd((unsigned long long *)&stats->n_cand, (unsigned long long)ktot);
-                else b_cand += ktot;
-            }
-            s_kbase = b;
-        }
-        __syncthreads();        // (also: every slot is done reading the staged boxes)
-        {
-            uint32_t li = kex;
-            int64_t idx = (int64_t)s_kbase + kex;
-#pragma unroll 1
-            for (uint32_t m = keepm; m; m &= m - 1) {
-                const int64_t slot = S0 + (int64_t)__builtin_ctz(m) * ENUM_BLOCK + threadIdx.x;
-                uint64_t packed;
-                int32_t pr;
-                if (staged) {
-                    const StagedSlot q = staged_slot(slot, (int)nc, s_pre, s_nA, s_aoff, s_ia0, s_boff, s_ib0);
-                    packed = ((uint64_t)(uint32_t)s_t[q.ia] << 32) | (uint32_t)s_t[q.ib];
-                    pr = ONE ? 0 : s_ep[q.ia];
-                } else {
-                    const SlotOut so = global_slot<ONE>(bv, keys, kpair, sbox, cells, pstart, c0, nc, pre_lds, slot);
-                    packed = so.packed;
-                    pr = so.pr;
-                }
-                s_u.c.tt[li] = packed;
-                s_u.c.pair[li] = pr;
-                if (cand) {
-                    if (idx < cand_cap) {
-                        cand[idx] = packed;
-                        if (cand_pair) cand_pair[idx] = pr;
-                    } else {
-                        atomicOr((unsigned long long *)&stats->overflow, 2ull);
-                    }
-                }
-                ++li;
-                ++idx;
-            }
-        }
-        __syncthreads();
-        // the narrow phase on the chunk's candidates: Moller quick test
-        // (Sec. 6.2.3), 4x4 solve and inclusion (Sec. 6.2.4), hit records
-        if (ktot) {
-            uint32_t nm = 0, nd = 0, no = 0;
-            for (uint32_t base = 0; base < ktot; base += ENUM_BLOCK) {
-                const uint32_t i = base + threadIdx.x;
-                int stt = PS_AABB;
-                int32_t ta = 0, tb = 0, p = 0;
-                double z[4] = {0, 0, 0, 0};
-                Tri Pt;
-                if (i < ktot) {
-                    const uint64_t tt = s_u.c.tt[i];
-                    ta = (int32_t)(tt >> 32);
-                    tb = (int32_t)(tt & 0xffffffffu);
-                    p = s_u.c.pair[i];
-                    const PairDesc &Pd = pair_desc<ONE>(bv, p);
-                    Pt = load_tri(Pd.A, ta);
-                    const Tri Q = load_tri(Pd.B, tb);
-                    if (same_side(Pt, Q) || same_side(Q, Pt)) {
-                        stt = PS_MOLLER;
-                    } else {
-                        const bool ok = solve_pair(Pt, Q, z);
-                        stt = !ok ? PS_DEGEN : !inside(z) ? PS_OUTSIDE : PS_HIT;
-                    }
-                }
-                nm += stt == PS_MOLLER;
-                nd += stt == PS_DEGEN;
-                no += stt == PS_OUTSIDE;
-                hit_t h;
-                uint64_t key = 0;
-                if (stt == PS_HIT) {
-                    const PairDesc &Pd = pair_desc<ONE>(bv, p);
-                    make_hit(Pd.A, Pd.B, ta, tb, (uint32_t)p, Pt, z, h);
-                    key = ((uint64_t)p << (bv.tbA + bv.tbB)) | ((uint64_t)(uint32_t)ta << bv.tbB) | (uint32_t)tb;
-                }
-                emit_hit(stt == PS_HIT, h, key, hits, hkeys, hits_cap, stats);
-            }
-            const uint32_t sm = block_sum<ENUM_BLOCK>(nm, s_kscan), sd = block_sum<ENUM_BLOCK>(nd, s_kscan), so = block_sum<ENUM_BLOCK>(no, s_kscan);
-            if (threadIdx.x == 0) {
-                b_moller += sm;
-                b_degen += sd;
-                b_outside += so;
-            }
-        }
-        // exact statistics of the groups that start in this chunk: a group of
-        // one cell adds the cell and nA * nB slots; the groups of several
-        // cells are listed and counted by the whole block
-        __syncthreads();
-        if (nc <= ENUM_CELLS) {
-            if (first_here) {
-                if (mixv) {
-                    s_u.c.pair[atomicAdd(&s_nmix, 1u)] = (int32_t)threadIdx.x;
-                } else {
-                    xc += 1;
-                    xs += gslots;
-                }
-            }
-        } else {
-            for (int64_t c = c0 + threadIdx.x; c < c0 + nc; c += ENUM_BLOCK) {
-                if (pstart[c] < S0) continue;
-                const CellRec cr = cells[c];
-                if (mix[cr.h]) {
-                    s_u.c.pair[atomicAdd(&s_nmix, 1u)] = (int32_t)(c - c0);
-                } else {
+            if (enter) mixed = *(ScalarPtr<uint32_t>)(a.mix + cr.h) != 0;
+            if (first) {
+                if (mixed) {
+                    group_stats(a.keys, cr, sh, s_tab[wv], xc, xs);
+                } else if (lane == 0) {
                     xc += 1;
                     xs += (unsigned long long)cr.nA * (unsigned long long)cr.nB;
                 }
             }
         }
-        __syncthreads();
-        for (uint32_t k = 0; k < s_nmix; ++k) {
-            const CellRec cr = cells[c0 + s_u.c.pair[k]];
-            group_stats<ENUM_BLOCK>(keys, cr, sh, s_ec, xc, xs);
+        // the scalar entries, until the queue is to be emptied
+        while (si < s1 && q1n < WAVE) {
+            si = uni(si);
+            eS0 = uni(eS0);
+            // (a round may read entries past the strip's: they are masked, and
+            // the list is padded by a round)
+            ScalarPtr<uint32_t> p = (ScalarPtr<uint32_t>)(a.qbox + eS0 + si);
+            uint32_t b[STRIP_UNROLL][4];
+#pragma unroll
+            for (int u = 0; u < STRIP_UNROLL; ++u)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) b[u][k] = p[4 * u + k];
+            uint64_t m[STRIP_UNROLL];
+            uint64_t any = 0;
+#pragma unroll
+            for (int u = 0; u < STRIP_UNROLL; ++u) {
+                const uint32_t d = sub_sat16(lq.x, b[u][2]) | sub_sat16(lq.y, b[u][3]) | sub_sat16(b[u][0], lq.z) |
+                                   sub_sat16(b[u][1], lq.w);
+                m[u] = ballot(d == 0u) & lmask;
+                if (u > 0) m[u] = si + u < s1 ? m[u] : 0ull;
+                any |= m[u];
+            }
+            if (any) {
+#pragma unroll
+                for (int u = 0; u < STRIP_UNROLL; ++u) {
+                    if (m[u]) {
+                        const uint32_t eS = eS0 + si + u;
+                        bool keep = ((m[u] >> lane) & 1) && (lhome | *(ScalarPtr<uint32_t>)(a.home + eS)) == 15u;
+                        if (mixed) keep = keep && lcell == (*(ScalarPtr<uint64_t>)(a.keys + eS) >> sh);
+                        const uint64_t k = ballot(keep);
+                        if (keep) s_q1[wv][q1n + mbcnt(k)] = gs.lanes_b ? make_uint2(eS, eL) : make_uint2(eL, eS);
+                        q1n = uni(q1n + (uint32_t)__builtin_popcountll(k));
+                    }
+                }
+            }
+            si += STRIP_UNROLL;
         }
-        __syncthreads();
+        const bool last = si >= s1 && w >= wend;
+        // the exact box test (the candidates) and the Moller quick test on 64
+        // of the queue (the rest of it at the end)
+        while (q1n >= WAVE || (last && q1n > 0)) {
+            const uint32_t n = q1n < WAVE ? q1n : WAVE;
+            q1n -= n;
+            wave_sync();
+            bool cnd = false, sep = false;
+            uint2 e = make_uint2(0u, 0u);
+            int32_t ta = 0, tb = 0;
+            if ((uint32_t)lane < n) {
+                e = s_q1[wv][q1n + lane];
+                ta = (int32_t)(a.keys[e.x] & bv.kl.tmask);
+                tb = (int32_t)(a.keys[e.y] & bv.kl.tmask);
+                const PairDesc &Pd = pair_desc<ONE>(bv, ONE ? 0 : a.kpair[e.x]);
+                const Tri P = load_tri(Pd.A, ta), Q = load_tri(Pd.B, tb);
+                cnd = true;
+#pragma unroll
+                for (int d = 0; d < 4; ++d) {
+                    const double alo = fmin(fmin(P.p[0][d], P.p[1][d]), P.p[2][d]);
+                    const double ahi = fmax(fmax(P.p[0][d], P.p[1][d]), P.p[2][d]);
+                    const double blo = fmin(fmin(Q.p[0][d], Q.p[1][d]), Q.p[2][d]);
+                    const double bhi = fmax(fmax(Q.p[0][d], Q.p[1][d]), Q.p[2][d]);
+                    cnd = cnd & (alo <= bhi) & (blo <= ahi);
+                }
+                sep = same_side(P, Q) || same_side(Q, P);
+            }
+            const uint64_t cm = ballot(cnd), keep = ballot(cnd && !sep);
+            const uint32_t nc1 = (uint32_t)__builtin_popcountll(cm), nk = (uint32_t)__builtin_popcountll(keep);
+            n_cand += nc1;
+            n_moller += nc1 - nk;
+            if (a.cand && nc1) {
+                unsigned long long b0 = 0;
+                if (lane == 0) b0 = atomicAdd((unsigned long long *)&a.stats->n_cand, (unsigned long long)nc1);
+                const int64_t idx = (int64_t)__shfl(b0, 0) + mbcnt(cm);
+                if (cnd) {
+                    if (idx < a.cand_cap) a.cand[idx] = ((uint64_t)(uint32_t)ta << 32) | (uint32_t)tb;
+                    else atomicOr((unsigned long long *)&a.stats->overflow, 2ull);
+                }
+            }
+            if (cnd && !sep) s_q2[wv][q2n + mbcnt(keep)] = e;
+            q2n += nk;
+            if (q2n >= WAVE) break;
+        }
+        // the 4x4 solve and the inclusion test on 64 of what is left
+        if (q2n >= WAVE || (last && q1n == 0 && q2n > 0)) {
+            const uint32_t n = q2n < WAVE ? q2n : WAVE;
+            q2n -= n;
+            wave_sync();
+            int stt = PS_AABB;
+            hit_t h;
+            uint64_t key = 0;
+            if ((uint32_t)lane < n) {
+                const uint2 e = s_q2[wv][q2n + lane];
+                const int32_t ta = (int32_t)(a.keys[e.x] & bv.kl.tmask), tb = (int32_t)(a.keys[e.y] & bv.kl.tmask);
+                const int p = ONE ? 0 : a.kpair[e.x];
+                const PairDesc &Pd = pair_desc<ONE>(bv, p);
+                double z[4];
+                const bool ok = solve_pair(load_tri(Pd.A, ta), load_tri(Pd.B, tb), z);
+                stt = !ok ? PS_DEGEN : !inside(z) ? PS_OUTSIDE : PS_HIT;
+                if (stt == PS_HIT) {
+                    make_hit(Pd.A, Pd.B, ta, tb, (uint32_t)p, load_tri(Pd.A, ta), z, h);
+                    key = ((uint64_t)p << (bv.tbA + bv.tbB)) | ((uint64_t)(uint32_t)ta << bv.tbB) | (uint32_t)tb;
+                }
+            }
+            n_degen += (uint32_t)__builtin_popcountll(ballot(stt == PS_DEGEN));
+            n_out += (uint32_t)__builtin_popcountll(ballot(stt == PS_OUTSIDE));
+            emit_hit(stt == PS_HIT, h, key, a.hits, a.hkeys, a.hits_cap, a.stats);
+        }
+        if (last && q1n == 0 && q2n == 0) break;
     }
-    }
-    const unsigned long long sc = block_sum<ENUM_BLOCK>(xc, s_st), ss = block_sum<ENUM_BLOCK>(xs, s_st);
-    if (threadIdx.x == 0) {
-        unsigned long long *w = epart + SHARD_WORDS * (blockIdx.x % STAT_SHARDS);
-        const unsigned long long c[7] = {b_cand, b_moller, b_degen, b_outside, sc, ss, b_unstaged};
+    // the block's counts, added to one of STAT_SHARDS counter lines (block
+    // index mod STAT_SHARDS): same-line atomics of hundreds of blocks would
+    // serialise; k_finish sums the lines
+    xc = wave_sum_u64(xc);
+    xs = wave_sum_u64(xs);
+    if (lane == 0) {
+        const unsigned long long v[7] = {a.cand ? 0ull : n_cand, n_moller, n_degen, n_out, xc, xs, touched > CROWDED};
 #pragma unroll
         for (int k = 0; k < 7; ++k)
-            if (c[k]) atomicAdd(w + k, c[k]);
+            if (v[k]) atomicAdd(&s_cnt[k], v[k]);
     }
+    __syncthreads();
+    if (threadIdx.x < 7 && s_cnt[threadIdx.x])
+        atomicAdd(a.epart + SHARD_WORDS * (blockIdx.x % STAT_SHARDS) + threadIdx.x, s_cnt[threadIdx.x]);
 }
 
 __global__ void __launch_bounds__(BLOCK) k_hits_place(const hit_t *tmp, const uint64_t *sorted, const int64_t *n_dev,
@@ -2161,7 +1976,7 @@ struct FinishArgs {
 __global__ void __launch_bounds__(FIN_BLOCK) k_finish(FinishArgs a)
 {
     __shared__ uint64_t s_k[HITS_TINY];
-    if (threadIdx.x < 7) {
+    if (threadIdx.x < 8) {
         unsigned long long v = 0;
         for (int i = 0; i < STAT_SHARDS; ++i) v += a.shards[SHARD_WORDS * i + threadIdx.x];
         search_stats_t *st = a.stats;
@@ -2172,9 +1987,10 @@ __global__ void __launch_bounds__(FIN_BLOCK) k_finish(FinishArgs a)
         case 3: st->n_outside = (int64_t)v; break;
         case 4: st->n_cells = (int64_t)v; break;
         case 5: st->n_slots = (int64_t)v; break;
-        default: st->n_chunks_unstaged = (int64_t)v; break;
+        case 6: st->n_chunks_unstaged = (int64_t)v; break;
+        default: st->n_group_slots = (int64_t)v; break;
         }
-    } else if (threadIdx.x == 7) {
+    } else if (threadIdx.x == 8) {
         *a.epoch += 1;
         a.stats->n_entries = (int64_t)*a.n_keys;
     }
@@ -2294,8 +2110,8 @@ struct Geometry {
 struct Layout {
     int64_t ent_cap, cand_cap, hits_cap;
     size_t o_epoch, o_flags, o_both, o_pbox, o_grp, o_own, o_mix, o_gstat, o_ctrs, o_part, o_epart, o_rng, o_ent, o_epair, o_erank, o_ehash, o_sorted,
-        o_spair, o_sbox,
-        o_cells, o_pstart, o_htmp, o_hkeys, o_halt, o_misc, o_desc, o_toff, o_cbase, total;
+        o_eoff, o_spair, o_shome, o_qbox,
+        o_cells, o_ustart, o_htmp, o_hkeys, o_halt, o_misc, o_desc, o_toff, o_cbase, total;
     int64_t n_kblocks, cell_cap, n_fwords, n_cwords, n_gtiles;
 };
 
@@ -2400,11 +2216,13 @@ void layout(const Geometry &G, Layout &L)
     L.o_epair = take((size_t)(L.ent_cap + 1) * 4);
     L.o_erank = take((size_t)(L.ent_cap + 1) * 4);
     L.o_ehash = take((size_t)(L.ent_cap + 1) * 4);
+    L.o_eoff = take((size_t)(L.ent_cap + 1) * 2);
     L.o_sorted = take((size_t)(L.ent_cap + 1) * 8);
     L.o_spair = take((size_t)(L.ent_cap + 1) * 4);
-    L.o_sbox = take((size_t)(L.ent_cap + 1) * 64);
+    L.o_shome = take((size_t)(L.ent_cap + 1) * 4);
+    L.o_qbox = take((size_t)(L.ent_cap + 1 + STRIP_UNROLL) * 16);
     L.o_cells = take((size_t)L.cell_cap * sizeof(CellRec));
-    L.o_pstart = take((size_t)(L.cell_cap + 1) * 8);
+    L.o_ustart = take((size_t)(L.cell_cap + 1) * 8);
     L.o_htmp = take((size_t)(L.hits_cap > 0 ? L.hits_cap : 1) * sizeof(hit_t));
     L.o_hkeys = take((size_t)(L.hits_cap + 1) * 8);
     L.o_halt = take((size_t)(L.hits_cap + 1) * 8);
@@ -2495,42 +2313,6 @@ BatchView make_view(const Geometry &G, const PairDesc &p0, char *ws, const Layou
     return bv;
 }
 
-// Blocks of kernel fn (nt threads each) resident at once on the current
-// device, 0 when the runtime cannot say; asked once per kernel and device
-// (a fixed table: no allocation on this path).
-inline int resident_blocks(const void *fn, int nt)
-{
-    struct Known {
-        const void *fn;
-        int dev, blocks;
-    };
-    static std::mutex mu;
-    static Known known[64];
-    static int n_known = 0;
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) {
-        (void)hipGetLastError();
-        return 0;
-    }
-    std::lock_guard<std::mutex> lock(mu);
-    for (int i = 0; i < n_known; ++i)
-        if (known[i].fn == fn && known[i].dev == dev) return known[i].blocks;
-    int per_cu = 0, cus = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, nt, 0) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
-        (void)hipGetLastError();
-        per_cu = cus = 0;
-    }
-    if (n_known < 64) known[n_known++] = Known{fn, dev, per_cu * cus};
-    return per_cu * cus;
-}
-
-template <bool ONE, class S>
-int enum_resident()
-{
-    return resident_blocks(reinterpret_cast<const void *>(&k_enum<ONE, S>), S::block);
-}
-
 // Queue the whole pipeline (no host synchronisation).
 template <bool ONE>
 int enqueue(const Geometry &G, const Layout &L, const BatchView &bv, char *ws, hit_t *hits_dev, int64_t hits_cap,
@@ -2556,13 +2338,15 @@ int enqueue(const Geometry &G, const Layout &L, const BatchView &bv, char *ws, h
     uint32_t *ehash = (uint32_t *)(ws + L.o_ehash);
     uint64_t *sorted = (uint64_t *)(ws + L.o_sorted);
     int32_t *spair = (int32_t *)(ws + L.o_spair);
-    double *sbox = (double *)(ws + L.o_sbox);
+    uint4 *qbox = (uint4 *)(ws + L.o_qbox);
+    uint16_t *eoff = (uint16_t *)(ws + L.o_eoff);
     CellRec *cells = (CellRec *)(ws + L.o_cells);
-    int64_t *pstart = (int64_t *)(ws + L.o_pstart);
+    uint32_t *shome = (uint32_t *)(ws + L.o_shome);
+    int64_t *ustart = (int64_t *)(ws + L.o_ustart);
     hit_t *htmp = (hit_t *)(ws + L.o_htmp);
     uint64_t *hkeys = (uint64_t *)(ws + L.o_hkeys);
     uint64_t *halt = (uint64_t *)(ws + L.o_halt);
-    int64_t *misc = (int64_t *)(ws + L.o_misc);       // [1..2] kept groups and their slots
+    int64_t *misc = (int64_t *)(ws + L.o_misc);       // [1..2] kept groups and their units
 
     // counters and look-back words: cleared by k_mark's block 0; the
     // occupancy tables need no clearing (epoch-valued marks)
@@ -2590,6 +2374,7 @@ int enqueue(const Geometry &G, const Layout &L, const BatchView &bv, char *ws, h
     ko.epair = epair;
     ko.erank = erank;
     ko.ehash = ehash;
+    ko.eoff = eoff;
     ko.cap = L.ent_cap;
     ko.n_keys = n_keys;
     ko.grp = (uint32_t *)grp;
@@ -2609,7 +2394,8 @@ int enqueue(const Geometry &G, const Layout &L, const BatchView &bv, char *ws, h
     go.grp = grp;
     go.n_fwords = L.n_fwords;
     go.cells = cells;
-    go.pstart = pstart;
+    go.ustart = ustart;
+    go.shards = epart;
     go.kept = misc + 1;
     go.stat = gstat;
     go.tile_ctr = ctrs + 1;
@@ -2617,20 +2403,26 @@ int enqueue(const Geometry &G, const Layout &L, const BatchView &bv, char *ws, h
     MS_LAUNCH("k_groups", k_groups, dim3((unsigned)(L.n_gtiles < 1024 ? L.n_gtiles : 1024)), dim3(BLOCK), 0, st, go);
     static_assert(GROUP_DIRECT_TILES <= 1024, "a direct k_groups launch has one block per tile");
     MS_LAUNCH("k_scatter", k_scatter<ONE>, dim3(grid_for(L.ent_cap, 8192)), dim3(BLOCK), 0, st, bv, ent, epair, erank,
-              ehash, n_keys, L.ent_cap, (uint32_t *)grp, own, mix, sorted, spair, sbox, epoch, (uint4 *)flags,
-              (int64_t)(flag_bytes(G) / 16));
-    if (G.enum_shape == MS_ENUM_QUARTER)
-        MS_LAUNCH("k_enum", (k_enum<ONE, EnumQuarter>), dim3(EnumQuarter::grid), dim3(EnumQuarter::block), 0, st, bv,
-                  sorted, spair, sbox, cells, pstart, misc + 1, mix, stats, cand_user, (int32_t *)nullptr,
-                  cand_user ? cand_cap : (int64_t)0, htmp, hkeys, hits_cap, epart, enum_resident<ONE, EnumQuarter>());
-    else if (G.enum_shape == MS_ENUM_HALF)
-        MS_LAUNCH("k_enum", (k_enum<ONE, EnumHalf>), dim3(EnumHalf::grid), dim3(EnumHalf::block), 0, st, bv, sorted,
-                  spair, sbox, cells, pstart, misc + 1, mix, stats, cand_user, (int32_t *)nullptr,
-                  cand_user ? cand_cap : (int64_t)0, htmp, hkeys, hits_cap, epart, enum_resident<ONE, EnumHalf>());
-    else
-        MS_LAUNCH("k_enum", (k_enum<ONE, EnumWide>), dim3(EnumWide::grid), dim3(EnumWide::block), 0, st, bv, sorted,
-                  spair, sbox, cells, pstart, misc + 1, mix, stats, cand_user, (int32_t *)nullptr,
-                  cand_user ? cand_cap : (int64_t)0, htmp, hkeys, hits_cap, epart, enum_resident<ONE, EnumWide>());
+              ehash, eoff, n_keys, L.ent_cap, (uint32_t *)grp, own, mix, sorted, spair, shome, qbox, epoch,
+              (uint4 *)flags, (int64_t)(flag_bytes(G) / 16));
+    EnumArgs ea;
+    ea.keys = sorted;
+    ea.kpair = spair;
+    ea.qbox = qbox;
+    ea.home = shome;
+    ea.cells = cells;
+    ea.ustart = ustart;
+    ea.kept = misc + 1;
+    ea.mix = mix;
+    ea.stats = stats;
+    ea.cand = cand_user;
+    ea.cand_cap = cand_user ? cand_cap : 0;
+    ea.hits = htmp;
+    ea.hkeys = hkeys;
+    ea.hits_cap = hits_cap;
+    ea.epart = epart;
+    ea.min_share = G.enum_shape == MS_ENUM_QUARTER ? 16 : G.enum_shape == MS_ENUM_HALF ? 32 : 64;
+    MS_LAUNCH("k_enum", k_enum<ONE>, dim3(ENUM_GRID), dim3(ENUM_BLOCK), 0, st, bv, ea);
     MS_HIP(hipGetLastError());
     const bool tiny = hits_cap > 0 && hits_cap <= HITS_TINY;
     if (hits_cap > HITS_TINY) {
