@@ -11,9 +11,9 @@
 //                 ranges, holding the search's epoch value (no clearing
 //                 between searches); compact ranges; per-block totals;
 //                 block 0 clears the counters
-//   k_pack        hashed cells occupied by both meshes as bit tables (fine
-//                 and coarse); each both-occupied fine cell is a group whose
-//                 counters are cleared here
+//   k_pack        hashed cells occupied by both meshes as a bit table; each
+//                 both-occupied cell is a group whose counters are cleared
+//                 here
 //   k_keys        per triangle: the cells of its range in a both-occupied
 //                 group (a cell holding one mesh only cannot hold a pair);
 //                 entries [cell | side | triangle] at offsets reserved per
@@ -103,10 +103,10 @@ struct PairDesc {
     int32_t nA, nB;
     int32_t tilesA, prune;     // prune: MS_SEARCH_PRUNE
     uint64_t st[4];     // linear-id strides of the cells: n1 n2 n3, n2 n3, n3, 1
-    uint32_t fbs[4];    // fine table: linear-id strides of its blocks (cell index / 2 per axis), mod 2^32
+    uint32_t fbs[4];    // hashed table: linear-id strides of its blocks (cell index / 2 per axis), mod 2^32
     uint32_t fbh[4];    //   and fbs * HASH_MUL mod 2^32
-    uint32_t cbs[4];    // coarse table (cell index / 2 per axis): strides of its blocks, mod 2^32
-    uint32_t cbh[4];    //   (cell index / 4 per axis) and cbs * HASH_MUL mod 2^32
+    uint32_t rbs[4];    // region table: linear-id strides of the regions (cell index / 8 per axis), mod 2^32
+    uint32_t rbh[4];    //   and rbs * HASH_MUL mod 2^32
     double nm1[4];      // n_d - 1
 };
 
@@ -115,10 +115,11 @@ struct BatchView {
     const PairDesc *pairs;       // device array of a batch
     const int64_t *tile_off;     // n_pairs + 1 (batch): first triangle tile of each pair
     const uint64_t *cell_base;   // n_pairs + 1 (batch)
+    int32_t *tile_pair;          // pair of each tile (batch; k_mark for k_keys)
     int64_t n_tiles;             // triangle tiles of all pairs
     int32_t n_pairs;
     int32_t bm_log2;             // occupancy flags per side: 2^bm_log2 bytes, then as many bits
-    int32_t bc_log2;             // the same for the coarse cells (2x the edge): 2^bc_log2 per side
+    int32_t br_log2;             // the same for the regions: 2^br_log2 per side
     int32_t packable;            // every grid has <= 4096 cells per axis
     int32_t c32;                 // every grid has < 2^31 cells per axis (32-bit cell ranges)
     int32_t pb, tbA, tbB;        // bits of the pair, A- and B-triangle fields of hit keys
@@ -134,7 +135,6 @@ MS_D const PairDesc &pair_desc(const BatchView &bv, int p)
 
 // Multiplier of the hashed tables (the odd 32-bit constant nearest 2^32 / phi).
 constexpr uint32_t HASH_MUL = 0x9E3779B1u;
-
 
 // The top log2 bits (1 <= log2 <= 31) of a product id * HASH_MUL mod 2^32 (of
 // the id mod 2^32: ids that differ by a multiple of 2^32 share a hash, which
@@ -169,32 +169,7 @@ MS_D int64_t range_count(const CellRange &r)
     return (r.hi[0] - r.lo[0] + 1) * (r.hi[1] - r.lo[1] + 1) * (r.hi[2] - r.lo[2] + 1) * (r.hi[3] - r.lo[3] + 1);
 }
 
-// The cells of a grid with twice the edge (cell index / 2 per axis), used to
-// skip at once the triangles whose neighbourhood holds no cell of the other
-// mesh.
-MS_D void coarse_of(const CellRange &r, const int64_t n[4], CellRange &rc, int64_t nc[4])
-{
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-        rc.lo[d] = r.lo[d] >> 1;
-        rc.hi[d] = r.hi[d] >> 1;
-        nc[d] = (n[d] + 1) >> 1;
-    }
-}
-
-// Visit every cell of a range in lexicographic order (linear cell ids).
-template <typename F>
-MS_D void for_cells(const CellRange &r, const int64_t n[4], F &&f)
-{
-    for (int64_t c0 = r.lo[0]; c0 <= r.hi[0]; ++c0)
-        for (int64_t c1 = r.lo[1]; c1 <= r.hi[1]; ++c1)
-            for (int64_t c2 = r.lo[2]; c2 <= r.hi[2]; ++c2) {
-                int64_t base = ((c0 * n[1] + c1) * n[2] + c2) * n[3];
-                for (int64_t c3 = r.lo[3]; c3 <= r.hi[3]; ++c3) f((uint64_t)(base + c3));
-            }
-}
-
-// The same with the coordinates of each cell: f(c, linear id).
+// Visit every cell of a range in lexicographic order: f(coordinates, linear id).
 template <typename F>
 MS_D void for_cells_xy(const CellRange &r, const int64_t n[4], F &&f)
 {
@@ -247,18 +222,6 @@ MS_D bool tri_box_d(const MeshView &m, int32_t t, double lo[4], double hi[4])
     return fin;
 }
 
-// The range on the coarse grid (cell index / 2 per axis).
-MS_D Range32 coarse_range(const Range32 &r)
-{
-    Range32 c;
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-        c.lo[d] = r.lo[d] >> 1;
-        c.e[d] = ((r.lo[d] + r.e[d]) >> 1) - c.lo[d];
-    }
-    return c;
-}
-
 // True when every axis of the range has one or two cells: its cells are then
 // lo + b for the positions b in {0,1}^4 (bit 3 - d of b for axis d, so that
 // ascending b is the lexicographic order) with b inside the extent mask.
@@ -273,17 +236,17 @@ MS_D unsigned long long range_cells(const Range32 &r)
            (unsigned long long)(r.e[3] + 1);
 }
 
-
 // ------------------------------------------------- blocked hashed tables
 //
-// The occupancy tables (fine cells, and coarse cells of twice the edge) are
-// hashed by blocks: a cell's 2x2x2x2 block (cell index / 2 per axis) picks a
-// 16-byte line of the table -- the top lg - 4 bits of (pair's cell base +
-// the block's linear id) * HASH_MUL mod 2^32 -- and the low bit of each cell index
-// the byte in it.  Neighbouring cells thus share cache lines, so that the
-// marks and tests of a wave touch few lines; two cells share a hashed index
-// only when their blocks' hashes collide.  bs: linear-id strides of the
-// blocks of the table's grid.
+// The occupancy tables are hashed by blocks: a cell's 2x2x2x2 block (cell
+// index / 2 per axis) picks a line of 16 cells -- the top lg - 4 bits of
+// (pair's cell base + the block's linear id) * HASH_MUL mod 2^32 -- and the low
+// bit of each cell index the cell in it (its parities, axis 0 highest).  A
+// line is 16 bytes of a side's occupancy table and 16 bits of the
+// both-occupied table, so that one 16-bit load tells of all of a range's
+// cells in a block (a range of two cells per axis lies in 1 to 16 blocks); neighbouring cells share cache lines; two cells share a
+// hashed index only when their blocks' hashes collide.  bs: linear-id strides
+// of the blocks.
 
 // Hashed index of cell c (coordinates on the table's grid).
 MS_D uint32_t blocked_index(const int64_t c[4], const uint32_t bs[4], uint64_t cb, int lg)
@@ -345,11 +308,6 @@ struct TabRef {
     int lg;
 };
 
-struct BitRef {
-    const uint32_t *w;
-    int lg;
-};
-
 // Marks (value v) the cells of the small range u whose positions are in m.
 template <int... Ks>
 MS_D void mark_walk(const TabRef &t, BlockWalk w, uint32_t m, uint8_t v, std::integer_sequence<int, Ks...>)
@@ -358,32 +316,6 @@ MS_D void mark_walk(const TabRef &t, BlockWalk w, uint32_t m, uint8_t v, std::in
         const uint32_t i = walk_index<Ks>(w, t.lg);
         if ((m >> GrayStep<Ks>::b) & 1u) t.base[t.off + i] = v;
     }(), ...);
-}
-
-// Both-occupied bits of the cells of the small range u whose positions are
-// in m, as a mask over the positions (bit b for position b); the loads are
-// independent, so they are in flight together.
-template <int... Ks>
-MS_D uint32_t bits_walk(const BitRef &t, BlockWalk w, uint32_t m, std::integer_sequence<int, Ks...>)
-{
-    uint32_t r = 0;
-    ((void)[&] {
-        const uint32_t i = walk_index<Ks>(w, t.lg);
-        if ((m >> GrayStep<Ks>::b) & 1u) r |= ((t.w[i >> 5] >> (i & 31)) & 1u) << GrayStep<Ks>::b;
-    }(), ...);
-    return r;
-}
-
-// The cells of a range of any size, in lexicographic order, with their
-// coordinates (Range32 form).
-template <typename F>
-MS_D void for_cells32(const Range32 &r, F &&f)
-{
-    int64_t c[4];
-    for (c[0] = r.lo[0]; c[0] <= r.lo[0] + r.e[0]; ++c[0])
-        for (c[1] = r.lo[1]; c[1] <= r.lo[1] + r.e[1]; ++c[1])
-            for (c[2] = r.lo[2]; c[2] <= r.lo[2] + r.e[2]; ++c[2])
-                for (c[3] = r.lo[3]; c[3] <= r.lo[3] + r.e[3]; ++c[3]) f(c);
 }
 
 // The positions of a small range r inside its own extent: starting from
@@ -399,7 +331,100 @@ MS_D uint32_t range_positions(const Range32 &r)
     return m;
 }
 
-// Marks every cell of range r (any size).
+// Regions of 8 cells per axis, marked and tested like the cells, one byte and
+// bit each (hashed by their linear ids): a triangle none of whose regions holds
+// the other mesh has no entry.  Neighbouring triangles share their regions, so
+// most waves are done with this test and its one cached bit; and a cell that
+// collides in the cells' table rarely does in both, which keeps false entries
+// out.  8 cells per axis: all kernels of a search of the 192-pair family take
+// 1195 us (patch pairs 484, 14 layers 1066) against 1340 (518, 1266) with
+// regions of 2 cells, 1200 (464, 1082) of 4, 1195 (492, 1064) of 16, and 1434
+// (604, 1215) with a table of hashed 2x2x2x2 blocks looked up per cell instead.
+constexpr int REGION = 3;
+
+// The hash product of the first region of the cells lo .. lo + e, and how
+// many regions follow it per axis.
+MS_D uint32_t first_region(const Range32 &r, const uint32_t rs[4], uint64_t cb, int32_t more[4])
+{
+    uint32_t lin = (uint32_t)cb;
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        const int32_t b = r.lo[d] >> REGION;
+        lin += (uint32_t)b * rs[d];
+        more[d] = ((r.lo[d] + r.e[d]) >> REGION) - b;
+    }
+    return lin * HASH_MUL;
+}
+
+// Visits all of them; stops when f(hashed region) returns true, and says
+// whether it did.
+template <typename F>
+MS_D bool each_region(uint32_t p, const int32_t more[4], const uint32_t rh[4], int lr, F &&f)
+{
+    for (int32_t a = 0; a <= more[0]; ++a)
+        for (int32_t b = 0; b <= more[1]; ++b)
+            for (int32_t c = 0; c <= more[2]; ++c)
+                for (int32_t d = 0; d <= more[3]; ++d)
+                    if (f(hash_of_product(p + (uint32_t)a * rh[0] + (uint32_t)b * rh[1] + (uint32_t)c * rh[2] +
+                                              (uint32_t)d * rh[3],
+                                          lr)))
+                        return true;
+    return false;
+}
+
+// The parities of axis d (0..3) of a line's 16 cells: the cells of parity 1.
+constexpr uint32_t PAR1[4] = {0xff00u, 0xf0f0u, 0xccccu, 0xaaaau};
+
+// Visits the blocks of range r (any size): f(o, m, line) with the block's
+// offset from the range's first block per axis, its parities in the range
+// per axis (bit 0: parity 0, bit 1: parity 1) and its line of the table.
+template <typename F>
+MS_D void for_blocks(const Range32 &r, const uint32_t bs[4], const uint32_t bh[4], uint64_t cb, int lg, F &&f)
+{
+    int32_t nb[4];
+    uint32_t lin = (uint32_t)cb;
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        nb[d] = ((r.lo[d] + r.e[d]) >> 1) - (r.lo[d] >> 1) + 1;
+        lin += (uint32_t)(r.lo[d] >> 1) * bs[d];
+    }
+    auto par = [&](int d, int32_t o) {
+        uint32_t m = 3u;
+        if (o == 0 && (r.lo[d] & 1)) m &= 2u;
+        if (o == nb[d] - 1 && !((r.lo[d] + r.e[d]) & 1)) m &= 1u;
+        return m;
+    };
+    const uint32_t p = lin * HASH_MUL;
+    int32_t o[4];
+    uint32_t m[4];
+    for (o[0] = 0; o[0] < nb[0]; ++o[0]) {
+        m[0] = par(0, o[0]);
+        for (o[1] = 0; o[1] < nb[1]; ++o[1]) {
+            m[1] = par(1, o[1]);
+            for (o[2] = 0; o[2] < nb[2]; ++o[2]) {
+                m[2] = par(2, o[2]);
+                const uint32_t q = p + (uint32_t)o[0] * bh[0] + (uint32_t)o[1] * bh[1] + (uint32_t)o[2] * bh[2];
+                for (o[3] = 0; o[3] < nb[3]; ++o[3]) {
+                    m[3] = par(3, o[3]);
+                    f(o, m, hash_of_product(q + (uint32_t)o[3] * bh[3], lg - 4));
+                }
+            }
+        }
+    }
+}
+
+// The cells of a line with the given parities, as 16 bits.
+MS_D uint32_t parity_cells(const uint32_t m[4])
+{
+    uint32_t c = 0xffffu;
+#pragma unroll
+    for (int d = 0; d < 4; ++d) c &= (m[d] & 1 ? 0xffffu ^ PAR1[d] : 0u) | (m[d] & 2 ? PAR1[d] : 0u);
+    return c;
+}
+
+// Marks every cell of range r (any size).  The cells of a block are a product
+// of parities: per pair of parities of axes 0 and 1 they are 1, 2 or 4 of the
+// 4 bytes of a word, stored together where they are neighbours.
 MS_D void mark_range(const TabRef &t, const Range32 &r, const uint32_t bs[4], const uint32_t bh[4], uint64_t cb,
                      uint8_t v)
 {
@@ -409,20 +434,60 @@ MS_D void mark_range(const TabRef &t, const Range32 &r, const uint32_t bs[4], co
         mark_walk(t, w, range_positions(r), v, std::make_integer_sequence<int, 16>{});
         return;
     }
-    for_cells32(r, [&](const int64_t *c) { t.base[t.off + blocked_index(c, bs, cb, t.lg)] = v; });
+    const uint32_t v4 = 0x01010101u * v;
+    for_blocks(r, bs, bh, cb, t.lg, [&](const int32_t *, const uint32_t *m, uint32_t line) {
+        uint8_t *l = t.base + t.off + 16 * (size_t)line;
+        for (uint32_t p0 = 0; p0 < 2; ++p0) {
+            if (!((m[0] >> p0) & 1)) continue;
+            for (uint32_t p1 = 0; p1 < 2; ++p1) {
+                if (!((m[1] >> p1) & 1)) continue;
+                uint8_t *w = l + 8 * p0 + 4 * p1;
+                if ((m[2] & m[3]) == 3u) {
+                    *reinterpret_cast<uint32_t *>(w) = v4;
+                } else if (m[3] == 3u) {
+                    *reinterpret_cast<uint16_t *>(w + (m[2] & 2)) = (uint16_t)v4;
+                } else {
+                    const uint32_t b = m[3] >> 1;
+                    if (m[2] & 1) w[b] = v;
+                    if (m[2] & 2) w[2 + b] = v;
+                }
+            }
+        }
+    });
 }
 
-// Number of cells of range r whose both-occupied bit is set (any range).
-MS_D uint32_t count_both(const BitRef &t, const Range32 &r, const uint32_t bs[4], const uint32_t bh[4], uint64_t cb)
+// The both-occupied cells of a small range r, as bits over the parities of its
+// 16 possible cells (each occurs once).  An axis straddles two blocks when
+// its lowest cell is odd and it has two; the lines of all the blocks are
+// loaded together.
+template <int... Ss>
+MS_D uint32_t small_both(const uint16_t *both, int lg, const Range32 &r, const uint32_t bs[4], const uint32_t bh[4],
+                         uint64_t cb, std::integer_sequence<int, Ss...>)
 {
-    if (range_small(r)) {
-        BlockWalk w;
-        walk_init(w, r, bs, bh, cb);
-        return (uint32_t)__builtin_popcount(bits_walk(t, w, range_positions(r), std::make_integer_sequence<int, 16>{}));
+    uint32_t lin = (uint32_t)cb, st = 0, q[4];
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        lin += (uint32_t)(r.lo[d] >> 1) * bs[d];
+        const bool odd = r.lo[d] & 1, two = r.e[d] != 0;
+        st |= (odd && two ? 8u : 0u) >> d;
+        // the cells of the lower (or only) block on this axis
+        q[d] = odd ? PAR1[d] : two ? 0xffffu : 0xffffu ^ PAR1[d];
     }
-    uint32_t n = 0;
-    for_cells32(r, [&](const int64_t *c) { n += occ_bit(t.w, blocked_index(c, bs, cb, t.lg)); });
-    return n;
+    const uint32_t p = lin * HASH_MUL;
+    uint32_t b[16];
+    ((void)[&] {
+        b[Ss] = 0;
+        if ((Ss & ~st) == 0)
+            b[Ss] = both[hash_of_product(p + (Ss & 8 ? bh[0] : 0u) + (Ss & 4 ? bh[1] : 0u) + (Ss & 2 ? bh[2] : 0u) +
+                                             (Ss & 1 ? bh[3] : 0u),
+                                         lg - 4)];
+    }(), ...);
+    uint32_t c = 0;
+    ((void)[&] {
+        c |= b[Ss] & (Ss & 8 ? 0xffffu ^ PAR1[0] : q[0]) & (Ss & 4 ? 0xffffu ^ PAR1[1] : q[1]) &
+             (Ss & 2 ? 0xffffu ^ PAR1[2] : q[2]) & (Ss & 1 ? 0xffffu ^ PAR1[3] : q[3]);
+    }(), ...);
+    return c;
 }
 
 // Compact cell range: lo cell per axis in 12 bits (bits 0..47), extent per
@@ -735,6 +800,25 @@ MS_D void mark_quad(const TabRef &t, const Range32 &r1, bool ok1, const Range32 
     if (ok2) mark_range(t, r2, bs, bh, cb, v);
 }
 
+// Marks the regions of a quad's cells (u, if `some`).  A lone region that the
+// lane before has too (most do) is left to that lane.
+MS_D void mark_regions(uint8_t *table, const Range32 &u, bool some, const PairDesc &P, int lr, uint8_t v)
+{
+    int32_t more[4];
+    const uint32_t p = first_region(u, P.rbs, P.cell_base, more);
+    const bool lone = (more[0] | more[1] | more[2] | more[3]) == 0;
+    const uint32_t h = hash_of_product(p, lr);
+    const uint32_t prev = __shfl_up(some && lone ? h : ~0u, 1);
+    if (!some) return;
+    if (!lone)
+        each_region(p, more, P.rbh, lr, [&](uint32_t x) {
+            table[x] = v;
+            return false;
+        });
+    else if (lane_id() == 0 || prev != h)
+        table[h] = v;
+}
+
 // Cells of the four vertices of a quad (a = W(i,k), b = W(i+1,k),
 // c = W(i,k+1), d = W(i+1,k+1)) and whether each vertex is finite.
 struct QuadVerts {
@@ -860,9 +944,10 @@ __global__ void __launch_bounds__(BOUNDS_BLOCK) k_bounds(BatchView bv, double *p
     }
 }
 
-// Occupancy: one byte per hashed global cell and side, set with plain stores
-// (all writers store the same value), fine and coarse.  Stores each
-// triangle's compact cell range and per-block entry / non-finite totals.
+// Occupancy: one byte per hashed global cell and side and per hashed region,
+// set with plain stores (all writers store the same value; the grids whose
+// cells need 64 bits mark and test no regions).  Stores each triangle's compact
+// cell range, each tile's pair and per-block entry / non-finite totals.
 // Block 0 also clears the search's counters.  One thread per quad; each
 // block takes a contiguous run of quad tiles, and the runs of neighbouring
 // blocks share an XCD (xcd_block).
@@ -879,7 +964,7 @@ __global__ void __launch_bounds__(BLOCK) k_mark(BatchView bv, uint8_t *flags, co
     }
     const uint8_t v = epoch_value(epoch);
     unsigned long long all = 0, bad = 0;
-    const int lg = bv.bm_log2, lc = bv.bc_log2;
+    const int lg = bv.bm_log2, lr = bv.br_log2;
     const int64_t ntiles = bv.n_tiles;
     const int64_t per = ceil_div(ntiles, gridDim.x);
     const int64_t t0 = xcd_block(blockIdx.x, gridDim.x) * per;
@@ -889,13 +974,14 @@ __global__ void __launch_bounds__(BLOCK) k_mark(BatchView bv, uint8_t *flags, co
     for (int64_t tile = t0; tile < t1; ++tile) {
         const TileLoc L = tile_loc<ONE>(bv, tile, p);
         p = L.p;
+        if (!ONE && threadIdx.x == 0) bv.tile_pair[tile] = p;
         const int32_t q = (L.t0 >> 1) + (int32_t)threadIdx.x;
         if (2 * q >= L.n) continue;
         const int64_t g = tile * TILE_TRIS + 2 * (int64_t)threadIdx.x;
         const PairDesc &P = pair_desc<ONE>(bv, L.p);
         const MeshView &m = side_mesh(P, L.side);
         uint8_t *fine = flags + ((size_t)L.side << lg);
-        uint8_t *coarse = flags + ((size_t)2 << lg) + ((size_t)L.side << lc);
+        uint8_t *region = flags + ((size_t)2 << lg) + ((size_t)L.side << lr);
         // the other mesh's box when pruning: a triangle that misses it is
         // counted (its cells) but neither marked nor keyed
         const double *ob = P.prune ? pbox + 8 * (2 * (int64_t)L.p + (1 - L.side)) : nullptr;
@@ -915,8 +1001,7 @@ __global__ void __launch_bounds__(BLOCK) k_mark(BatchView bv, uint8_t *flags, co
             if (ok1) all += range_cells(r1);
             if (ok2) all += range_cells(r2);
             mark_quad(TabRef{flags, (uint32_t)L.side << lg, lg}, r1, k1, r2, k2, P.fbs, P.fbh, P.cell_base, v);
-            mark_quad(TabRef{flags, ((uint32_t)2 << lg) + ((uint32_t)L.side << lc), lc}, coarse_range(r1), k1,
-                      coarse_range(r2), k2, P.cbs, P.cbh, P.cell_base, v);
+            mark_regions(region, k1 && k2 ? range_union(r1, r2) : (k1 ? r1 : r2), k1 || k2, P, lr, v);
         } else {
             // grids of 2^31 cells or more along an axis: 64-bit cells, one triangle at a time
             const uint64_t cb = P.cell_base;
@@ -941,10 +1026,6 @@ __global__ void __launch_bounds__(BLOCK) k_mark(BatchView bv, uint8_t *flags, co
                 }
                 rng[g + h] = RNG_FROM_BOX;
                 for_cells_xy(r, P.g.n, [&](const int64_t *c, uint64_t) { fine[blocked_index(c, P.fbs, cb, lg)] = v; });
-                CellRange rc;
-                int64_t nc[4];
-                coarse_of(r, P.g.n, rc, nc);
-                for_cells_xy(rc, nc, [&](const int64_t *c, uint64_t) { coarse[blocked_index(c, P.cbs, cb, lc)] = v; });
             }
         }
     }
@@ -970,16 +1051,17 @@ MS_D uint32_t byte_mask(const uint8_t *f, uint32_t v)
     return m;
 }
 
-// The hashed cells that both meshes occupy, as bit tables (fine, then
-// coarse): the AND of the two sides' occupancy bytes.  Every set fine bit is
-// a cell group, whose entry counters and several-cells flag are cleared here.
-__global__ void __launch_bounds__(BLOCK) k_pack(const uint8_t *flags, const uint64_t *epoch, int bm_log2, int bc_log2,
+// The hashed cells, then the hashed regions, that both meshes occupy, as bit
+// tables: the AND of the two sides' occupancy bytes.  Every set bit of a cell
+// is a cell group, whose entry counters and several-cells flag are cleared
+// here.
+__global__ void __launch_bounds__(BLOCK) k_pack(const uint8_t *flags, const uint64_t *epoch, int bm_log2, int br_log2,
                                                 uint32_t *both, uint64_t *grp, uint32_t *mix, int64_t n_fwords,
-                                                int64_t n_cwords)
+                                                int64_t n_rwords)
 {
     const uint32_t v = epoch_value(epoch);
-    const size_t side = (size_t)1 << bm_log2, cside = (size_t)1 << bc_log2;
-    const int64_t n = n_fwords + n_cwords;
+    const size_t side = (size_t)1 << bm_log2, rside = (size_t)1 << br_log2;
+    const int64_t n = n_fwords + n_rwords;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t w = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; w < n; w += stride) {
         if (w < n_fwords) {
@@ -993,17 +1075,9 @@ __global__ void __launch_bounds__(BLOCK) k_pack(const uint8_t *flags, const uint
             }
         } else {
             const uint8_t *c = flags + 2 * side + 32 * (w - n_fwords);
-            both[w] = byte_mask(c, v) & byte_mask(c + cside, v);
+            both[w] = byte_mask(c, v) & byte_mask(c + rside, v);
         }
     }
-}
-
-// Whether any coarse cell of the range is occupied by both meshes (a
-// triangle whose coarse neighbourhood holds no cell of the other mesh has no
-// entry at all).
-MS_D bool coarse_any(const BatchView &bv, const uint32_t *cboth, const PairDesc &P, const Range32 &rc)
-{
-    return count_both(BitRef{cboth, bv.bc_log2}, rc, P.cbs, P.cbh, P.cell_base) != 0;
 }
 
 // Where an entry's cell lies in its triangle's range: its offset from the
@@ -1034,19 +1108,26 @@ struct KeysOut {
 };
 
 // Entries of each triangle: the cells of its range whose hashed cell both
-// meshes occupy (a cell holding one mesh only cannot hold a pair), after the
-// same test on the coarse cells.  One thread per triangle (KEYS_BLOCK =
-// TILE_TRIS threads: one tile per block).  Each block counts the entries of
-// its tile, reserves that many output slots with one atomic add (blocks
-// without entries take none) and writes the entries, listed in LDS first
-// when they are few enough, so that all threads write them together; every
-// stored entry is counted in its group and side (its rank there is kept for
-// the placement, its hashed cell with it), and the first of each side
-// leaves its cell as the group's sample.  One block more than the tiles
-// sums k_mark's per-block totals and clears the enumeration's counter
-// lines, beside the others.
+// meshes occupy (a cell holding one mesh only cannot hold a pair), if both
+// meshes occupy one of its regions.  One thread per triangle (KEYS_BLOCK =
+// TILE_TRIS threads: one tile per block).  The triangle's cells are tested a
+// block of 16 at a time, with one 16-bit load each, all of a small range's
+// together; a tile without entries is done after one barrier (most are).  Each block reserves its output slots with one
+// atomic add and lists its entries in LDS, one word each (the triangle's
+// thread, the block in its range, the parities); then every thread takes
+// every KEYS_BLOCK-th entry and works out the cell, so that the work and the
+// atomics of a triangle with many entries are spread and the entry stores are
+// contiguous.  Every stored entry is counted in its group and side (its rank
+// there is kept for the placement, its hashed cell with it), and the first of
+// each side leaves its cell as the group's sample.  One block more than the
+// tiles sums k_mark's per-block totals and clears the enumeration's counter
+// lines, beside the others.  Bound by the chains of dependent loads and by the
+// atomics: of the 192-pair family's 525 us, 202 go to the ranges and the
+// regions, 100 to the scan of the counts and the reservation, 110 to the
+// entries and 114 to their ranks; it took 745 with one lookup per cell and
+// every thread writing its own entries (14 layers: 445 from 582 us).
 constexpr int KEYS_BLOCK = TILE_TRIS;
-constexpr int KEYS_STAGE = 2048;          // entries of a block staged in LDS (more: each thread writes its own)
+constexpr int KEYS_STAGE = 4096;          // entries of a block listed in LDS (more: each thread writes its own)
 
 struct KeysTotals {
     const unsigned long long *mark_partial;   // per k_mark block: entries, non-finite triangles
@@ -1054,20 +1135,20 @@ struct KeysTotals {
     unsigned long long *shards;               // the enumeration's counter lines, cleared here
 };
 
-// Eight waves per SIMD (at most 64 registers; the batch forms spill a few
-// bytes): its blocks wait on dependent loads and atomics, and more of them
-// in flight shortened the family batch's k_keys from 648 to 609 us.
+// Eight waves per SIMD (at most 64 registers): its blocks wait on dependent
+// loads and atomics, and more of them in flight are faster.
 template <bool ONE, bool C32>
-__global__ void __launch_bounds__(KEYS_BLOCK) __attribute__((amdgpu_waves_per_eu(8, 8))) k_keys(BatchView bv, const uint32_t *both, const uint64_t *rng, KeysOut o,
-                                                     KeysTotals kt)
+__global__ void __launch_bounds__(KEYS_BLOCK) __attribute__((amdgpu_waves_per_eu(8, 8)))
+k_keys(BatchView bv, const uint32_t *both, const uint64_t *rng, KeysOut o, KeysTotals kt)
 {
     __shared__ uint64_t s_tmp[KEYS_BLOCK / WAVE];
+    __shared__ uint32_t s_wave[KEYS_BLOCK / WAVE], s_far;
     __shared__ unsigned long long s_blk0;
-    __shared__ uint32_t s_kh[KEYS_STAGE];     // staged entries: hashed cell, cell, thread
-    __shared__ uint64_t s_kc[KEYS_STAGE];
-    __shared__ uint16_t s_kt[KEYS_STAGE], s_ko[KEYS_STAGE];
-    const int lg = bv.bm_log2, lc = bv.bc_log2;
-    const uint32_t *cboth = both + ((size_t)1 << lg) / 32;
+    // entries: thread (bits 0..8), parities (9..12), block offset per axis (4 bits each from 13)
+    __shared__ uint32_t s_list[KEYS_STAGE];
+    const int lg = bv.bm_log2, lr = bv.br_log2;
+    const uint16_t *lines = reinterpret_cast<const uint16_t *>(both);
+    const uint32_t *rboth = both + ((size_t)1 << lg) / 32;
     const int64_t tile = blockIdx.x;
     if (tile >= bv.n_tiles) {
         if (tile == (bv.n_tiles > 0 ? bv.n_tiles : 1)) {
@@ -1098,126 +1179,151 @@ __global__ void __launch_bounds__(KEYS_BLOCK) __attribute__((amdgpu_waves_per_eu
         }
         return;
     }
-    __shared__ int s_p;
-    const TileLoc L = tile_loc<ONE>(bv, tile, tile_pair_search<ONE, KEYS_BLOCK>(bv, tile, &s_p));
+    const TileLoc L = tile_loc<ONE>(bv, tile, ONE ? 0 : __builtin_amdgcn_readfirstlane(bv.tile_pair[tile]));
     const int32_t t = L.t0 + (int32_t)threadIdx.x;
     const int64_t g = tile * TILE_TRIS + threadIdx.x;
     const PairDesc &P = pair_desc<ONE>(bv, L.p);
     const MeshView &m = side_mesh(P, L.side);
     const uint64_t cb = P.cell_base;
     uint32_t cnt = 0;
+    uint32_t small = 0;                  // a small range's cells (parities)
+    bool far = false;                    // a range that the list's words cannot hold
     Range32 r;
     if (t < L.n) {
         if constexpr (C32) {
-            if (range32_at(rng, g, m, t, P, r) && coarse_any(bv, cboth, P, coarse_range(r)))
-                cnt = count_both(BitRef{both, lg}, r, P.fbs, P.fbh, cb);
+            bool near = range32_at(rng, g, m, t, P, r);
+            if (near) {
+                int32_t more[4];
+                const uint32_t p = first_region(r, P.rbs, cb, more);
+                near = occ_bit(rboth, hash_of_product(p, lr)) != 0 ||
+                       ((more[0] | more[1] | more[2] | more[3]) != 0 &&
+                        each_region(p, more, P.rbh, lr, [&](uint32_t h) { return occ_bit(rboth, h) != 0; }));
+            }
+            if (near) {
+                if (range_small(r)) {
+                    small = small_both(lines, lg, r, P.fbs, P.fbh, cb, std::make_integer_sequence<int, 16>{});
+                    cnt = (uint32_t)__builtin_popcount(small);
+                } else {
+                    for_blocks(r, P.fbs, P.fbh, cb, lg, [&](const int32_t *, const uint32_t *pm, uint32_t line) {
+                        cnt += (uint32_t)__builtin_popcount(lines[line] & parity_cells(pm));
+                    });
+                    far = cnt > 0 && (r.e[0] | r.e[1] | r.e[2] | r.e[3]) > 15;
+                }
+            }
         } else {
             CellRange rr;
-            if (range_at(rng, g, m, t, P.g, rr)) {
-                CellRange rc;
-                int64_t nc[4];
-                coarse_of(rr, P.g.n, rc, nc);
-                uint32_t any = 0;
-                for_cells_xy(rc, nc, [&](const int64_t *c, uint64_t) {
-                    any |= occ_bit(cboth, blocked_index(c, P.cbs, cb, lc));
+            if (range_at(rng, g, m, t, P.g, rr))
+                for_cells_xy(rr, P.g.n, [&](const int64_t *c, uint64_t) {
+                    cnt += occ_bit(both, blocked_index(c, P.fbs, cb, lg));
                 });
-                if (any)
-                    for_cells_xy(rr, P.g.n, [&](const int64_t *c, uint64_t) {
-                        cnt += occ_bit(both, blocked_index(c, P.fbs, cb, lg));
-                    });
-            }
+            far = cnt > 0;
         }
     }
-    uint64_t btotal;
-    const uint64_t texcl = block_excl<KEYS_BLOCK>((uint64_t)cnt, s_tmp, &btotal);
+    // the exclusive sum of cnt within the wave; the block's waves after that
+    const int lane = lane_id(), wv = threadIdx.x / WAVE;
+    const uint64_t some = ballot(cnt > 0);
+    uint32_t inc = 0;
+    if (some) {
+        inc = cnt;
+        for (int o = 1; o < WAVE; o <<= 1) {
+            const uint32_t y = __shfl_up(inc, o);
+            if (lane >= o) inc += y;
+        }
+    }
+    if (lane == WAVE - 1) s_wave[wv] = inc;
+    if (threadIdx.x == 0) s_far = 0;
+    __syncthreads();
+    uint32_t before = 0, btotal = 0;
+#pragma unroll
+    for (int i = 0; i < KEYS_BLOCK / WAVE; ++i) {
+        const uint32_t v = s_wave[i];
+        if (i < wv) before += v;
+        btotal += v;
+    }
     if (btotal == 0) return;                      // uniform: every thread saw the same total
+    const uint32_t texcl = before + inc - cnt;
+    if (far) s_far = 1;
     if (threadIdx.x == 0) {
         const unsigned long long b0 = atomicAdd(o.n_keys, (unsigned long long)btotal);
         s_blk0 = b0;
         if ((int64_t)(b0 + btotal) > o.cap) atomicOr((unsigned long long *)&o.stats->overflow, 1ull);
     }
-    __syncthreads();
-    const uint64_t blk0 = s_blk0;
-    if (btotal <= KEYS_STAGE) {
-        // the block's entries through LDS: each thread lists its own at its
-        // offset, then every thread takes every KEYS_BLOCK-th entry, so
-        // that the group counters are advanced by all threads at once and
-        // the entry stores are contiguous
-        if (cnt) {
-            uint32_t k = (uint32_t)texcl;
-            auto stage = [&](uint64_t gc, uint32_t hh, uint32_t off) {
-                s_kh[k] = hh;
-                s_ko[k] = (uint16_t)off;
-                s_kc[k] = gc;
-                s_kt[k] = (uint16_t)threadIdx.x;
-                ++k;
-            };
-            if constexpr (C32) {
-                for_cells32(r, [&](const int64_t *c) {
-                    const uint32_t hh = blocked_index(c, P.fbs, cb, lg);
-                    if (occ_bit(both, hh))
-                        stage(cb + (uint64_t)c[0] * P.st[0] + (uint64_t)c[1] * P.st[1] + (uint64_t)c[2] * P.st[2] +
-                                  (uint64_t)c[3],
-                              hh, cell_offsets(c, r.lo));
-                });
+    if (cnt > 0 && !far && btotal <= KEYS_STAGE) {
+        if constexpr (C32) {
+            uint32_t k = texcl;
+            if (range_small(r)) {
+                // parities par of cell lo + b: par = par0 ^ b; the cell is in
+                // the upper block of a straddled axis where lo is odd and par 0
+                uint32_t par0 = 0;
+#pragma unroll
+                for (int d = 0; d < 4; ++d) par0 |= (uint32_t)(r.lo[d] & 1) << (3 - d);
+                for (uint32_t q = small; q; q &= q - 1) {
+                    const uint32_t par = (uint32_t)__builtin_ctz(q), up = par0 & ~par;
+                    s_list[k++] = threadIdx.x | par << 9 | (up >> 3 & 1) << 13 | (up >> 2 & 1) << 17 | (up >> 1 & 1) << 21 |
+                                  (up & 1) << 25;
+                }
             } else {
-                CellRange rr;
-                range_at(rng, g, m, t, P.g, rr);
-                for_cells_xy(rr, P.g.n, [&](const int64_t *c, uint64_t cell) {
-                    const uint32_t hh = blocked_index(c, P.fbs, cb, lg);
-                    if (occ_bit(both, hh)) stage(cb + cell, hh, cell_offsets(c, rr.lo));
+                for_blocks(r, P.fbs, P.fbh, cb, lg, [&](const int32_t *ob, const uint32_t *pm, uint32_t line) {
+                    for (uint32_t q = lines[line] & parity_cells(pm); q; q &= q - 1)
+                        s_list[k++] = threadIdx.x | (uint32_t)__builtin_ctz(q) << 9 | (uint32_t)ob[0] << 13 |
+                                      (uint32_t)ob[1] << 17 | (uint32_t)ob[2] << 21 | (uint32_t)ob[3] << 25;
                 });
             }
         }
-        __syncthreads();
-        const uint64_t side_bits = (uint64_t)L.side << bv.kl.tb;
-        for (uint32_t i = threadIdx.x; i < (uint32_t)btotal; i += KEYS_BLOCK) {
-            const int64_t pos = (int64_t)(blk0 + i);
-            if (pos >= o.cap) break;           // only stored entries are counted in their group
-            const uint32_t hh = s_kh[i];
-            const uint64_t gc = s_kc[i];
-            const uint32_t rank = atomicAdd(&o.grp[2 * (size_t)hh + L.side], 1u);
-            o.erank[pos] = rank;
-            o.ehash[pos] = hh;
-            o.eoff[pos] = s_ko[i];
-            if (rank == 0) o.own[hh] = gc;     // the first entry of each side: the group's sample
-            o.ent[pos] = (gc << bv.kl.cell_shift) | side_bits | (uint64_t)(uint32_t)(L.t0 + s_kt[i]);
-            if (!ONE) o.epair[pos] = L.p;
+    }
+    __syncthreads();
+    const uint64_t blk0 = s_blk0;
+    // only stored entries are counted in their group; the first entry of
+    // each side leaves its cell as the group's sample
+    auto put = [&](int64_t pos, uint64_t gc, uint32_t hh, uint32_t off, int32_t tri) {
+        if (pos >= o.cap) return;
+        const uint32_t rank = atomicAdd(&o.grp[2 * (size_t)hh + L.side], 1u);
+        o.erank[pos] = rank;
+        o.ehash[pos] = hh;
+        o.eoff[pos] = (uint16_t)off;
+        if (rank == 0) o.own[hh] = gc;
+        o.ent[pos] = (gc << bv.kl.cell_shift) | ((uint64_t)L.side << bv.kl.tb) | (uint64_t)(uint32_t)tri;
+        if (!ONE) o.epair[pos] = L.p;
+    };
+    if (C32 && btotal <= KEYS_STAGE && s_far == 0) {
+        for (uint32_t i = threadIdx.x; i < btotal; i += KEYS_BLOCK) {
+            const uint32_t w = s_list[i], tid = w & 511u;
+            Range32 rr;
+            range32_at(rng, tile * TILE_TRIS + tid, m, L.t0 + (int32_t)tid, P, rr);
+            uint32_t lin = (uint32_t)cb, off = 0;
+            uint64_t gc = cb;
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                const uint32_t b = ((uint32_t)rr.lo[d] >> 1) + ((w >> (13 + 4 * d)) & 15u);
+                const uint32_t c = 2 * b + ((w >> (12 - d)) & 1u);
+                lin += b * P.fbs[d];
+                gc += (uint64_t)c * P.st[d];
+                const uint32_t k = c - (uint32_t)rr.lo[d];
+                off |= (k < 15u ? k : 15u) << (4 * d);
+            }
+            put((int64_t)(blk0 + i), gc, hash_of_product(lin * HASH_MUL, lg - 4) << 4 | (w >> 9 & 15u), off,
+                L.t0 + (int32_t)tid);
         }
         return;
     }
+    // too many entries for the list, or a range too wide for its words: each
+    // thread writes its own
     if (cnt == 0) return;
     int64_t pos = (int64_t)(blk0 + texcl);
-    const uint64_t low = ((uint64_t)L.side << bv.kl.tb) | (uint64_t)t;
-    // only stored entries are counted in their group; the first entry of
-    // each side leaves its cell as the group's sample
-    auto put = [&](uint64_t gc, uint32_t hh, uint32_t off) {
-        if (pos < o.cap) {
-            const uint32_t rank = atomicAdd(&o.grp[2 * (size_t)hh + L.side], 1u);
-            o.erank[pos] = rank;
-            o.ehash[pos] = hh;
-            o.eoff[pos] = (uint16_t)off;
-            if (rank == 0) o.own[hh] = gc;
-            o.ent[pos] = (gc << bv.kl.cell_shift) | low;
-            if (!ONE) o.epair[pos] = L.p;
-        }
-        ++pos;
-    };
+    CellRange rr;
     if constexpr (C32) {
-        for_cells32(r, [&](const int64_t *c) {
-            const uint32_t hh = blocked_index(c, P.fbs, cb, lg);
-            if (occ_bit(both, hh))
-                put(cb + (uint64_t)c[0] * P.st[0] + (uint64_t)c[1] * P.st[1] + (uint64_t)c[2] * P.st[2] + (uint64_t)c[3],
-                    hh, cell_offsets(c, r.lo));
-        });
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            rr.lo[d] = r.lo[d];
+            rr.hi[d] = (int64_t)r.lo[d] + r.e[d];
+        }
     } else {
-        CellRange rr;
         range_at(rng, g, m, t, P.g, rr);
-        for_cells_xy(rr, P.g.n, [&](const int64_t *c, uint64_t cell) {
-            const uint32_t hh = blocked_index(c, P.fbs, cb, lg);
-            if (occ_bit(both, hh)) put(cb + cell, hh, cell_offsets(c, rr.lo));
-        });
     }
+    for_cells_xy(rr, P.g.n, [&](const int64_t *c, uint64_t cell) {
+        const uint32_t hh = blocked_index(c, P.fbs, cb, lg);
+        if (occ_bit(both, hh)) put(pos++, cb + cell, hh, cell_offsets(c, rr.lo), t);
+    });
 }
 
 // A kept cell group: its entries, A's then B's, from `start`; h is its
@@ -2100,7 +2206,7 @@ struct Geometry {
     int64_t n_pairs, n_tri, n_tiles, max_nA, max_nB;
     int tb, tbA, tbB, pb;
     int cell_bits;
-    int bm_log2, bc_log2;
+    int bm_log2, br_log2;
     int packable, c32;
     int enum_shape;
     int prune;          // some pair asks for world-bound pruning
@@ -2111,8 +2217,8 @@ struct Layout {
     int64_t ent_cap, cand_cap, hits_cap;
     size_t o_epoch, o_flags, o_both, o_pbox, o_grp, o_own, o_mix, o_gstat, o_ctrs, o_part, o_epart, o_rng, o_ent, o_epair, o_erank, o_ehash, o_sorted,
         o_eoff, o_spair, o_shome, o_qbox,
-        o_cells, o_ustart, o_htmp, o_hkeys, o_halt, o_misc, o_desc, o_toff, o_cbase, total;
-    int64_t n_kblocks, cell_cap, n_fwords, n_cwords, n_gtiles;
+        o_cells, o_ustart, o_htmp, o_hkeys, o_halt, o_misc, o_desc, o_toff, o_cbase, o_tpair, total;
+    int64_t n_kblocks, cell_cap, n_fwords, n_rwords, n_gtiles;
 };
 
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -2174,7 +2280,7 @@ int geometry(int64_t n_pairs, const ms_mesh *const *A, const ms_mesh *const *B, 
     for (int64_t i = 0; i < n_pairs; ++i)
         if (prm[i].table_log2 > req) req = prm[i].table_log2;
     if (req > 0) G.bm_log2 = req < 8 ? 8 : (req > 27 ? 27 : req);   // the automatic size stays within [12, 25]
-    G.bc_log2 = G.bm_log2 - 3;
+    G.br_log2 = G.bm_log2 - 3;
     G.enum_shape = 0;    // the shape of the first pair that asks for one, else MS_ENUM_HALF
     for (int64_t i = 0; i < n_pairs; ++i) {
         if (prm[i].enum_shape < 0 || prm[i].enum_shape > MS_ENUM_QUARTER)
@@ -2187,8 +2293,8 @@ int geometry(int64_t n_pairs, const ms_mesh *const *A, const ms_mesh *const *B, 
     return MS_OK;
 }
 
-// Occupancy bytes: fine table (2 sides x 2^bm_log2), then coarse (2 x 2^bc_log2).
-inline size_t flag_bytes(const Geometry &G) { return ((size_t)2 << G.bm_log2) + ((size_t)2 << G.bc_log2); }
+// Occupancy bytes: cells (2 sides x 2^bm_log2), then regions (2 x 2^br_log2).
+inline size_t flag_bytes(const Geometry &G) { return ((size_t)2 << G.bm_log2) + ((size_t)2 << G.br_log2); }
 
 void layout(const Geometry &G, Layout &L)
 {
@@ -2198,11 +2304,11 @@ void layout(const Geometry &G, Layout &L)
     L.n_kblocks = G.n_tiles > 0 ? G.n_tiles : 1;
     L.cell_cap = L.ent_cap / 2 + 1;
     L.n_fwords = n_ids / 32;
-    L.n_cwords = ((int64_t)1 << G.bc_log2) / 32;
+    L.n_rwords = ((int64_t)1 << G.br_log2) / 32;
     L.n_gtiles = ceil_div(L.n_fwords, GROUP_WORDS);
     L.o_epoch = take(64);         // first, so that every layout of a workspace shares it
     L.o_flags = take(flag_bytes(G));
-    L.o_both = take((size_t)(L.n_fwords + L.n_cwords) * 4);
+    L.o_both = take((size_t)(L.n_fwords + L.n_rwords) * 4);
     L.o_grp = take((size_t)n_ids * 8);
     L.o_own = take((size_t)n_ids * 8);
     L.o_mix = take((size_t)n_ids * 4);
@@ -2230,6 +2336,7 @@ void layout(const Geometry &G, Layout &L)
     L.o_desc = take((size_t)(G.n_pairs > 1 ? G.n_pairs : 1) * sizeof(PairDesc));
     L.o_toff = take((size_t)(G.n_pairs + 1) * 8);
     L.o_cbase = take((size_t)(G.n_pairs + 1) * 8);
+    L.o_tpair = take((size_t)(G.n_tiles + 1) * 4);
     L.total = o;
 }
 
@@ -2271,20 +2378,21 @@ PairDesc make_desc(const ms_mesh *A, const ms_mesh *B, const search_params_t *p,
     d.st[1] = n2 * n3;
     d.st[2] = n3;
     d.st[3] = 1;
-    // blocks of the fine table: (n + 1) / 2 per axis; of the coarse table: (n + 3) / 4
+    // blocks: (n + 1) / 2 per axis
     const uint64_t f1 = (n1 + 1) >> 1, f2 = (n2 + 1) >> 1, f3 = (n3 + 1) >> 1;
-    const uint64_t c1 = (n1 + 3) >> 2, c2 = (n2 + 3) >> 2, c3 = (n3 + 3) >> 2;
     d.fbs[0] = (uint32_t)(f1 * f2 * f3);
     d.fbs[1] = (uint32_t)(f2 * f3);
     d.fbs[2] = (uint32_t)f3;
     d.fbs[3] = 1;
-    d.cbs[0] = (uint32_t)(c1 * c2 * c3);
-    d.cbs[1] = (uint32_t)(c2 * c3);
-    d.cbs[2] = (uint32_t)c3;
-    d.cbs[3] = 1;
+    const uint64_t rn = ((uint64_t)1 << REGION) - 1;
+    const uint64_t r1 = (n1 + rn) >> REGION, r2 = (n2 + rn) >> REGION, r3 = (n3 + rn) >> REGION;
+    d.rbs[0] = (uint32_t)(r1 * r2 * r3);
+    d.rbs[1] = (uint32_t)(r2 * r3);
+    d.rbs[2] = (uint32_t)r3;
+    d.rbs[3] = 1;
     for (int k = 0; k < 4; ++k) {
         d.fbh[k] = d.fbs[k] * HASH_MUL;
-        d.cbh[k] = d.cbs[k] * HASH_MUL;
+        d.rbh[k] = d.rbs[k] * HASH_MUL;
         d.nm1[k] = (double)(p->n_cells[k] - 1);
     }
     return d;
@@ -2298,10 +2406,11 @@ BatchView make_view(const Geometry &G, const PairDesc &p0, char *ws, const Layou
     bv.pairs = (const PairDesc *)(ws + L.o_desc);
     bv.tile_off = (const int64_t *)(ws + L.o_toff);
     bv.cell_base = (const uint64_t *)(ws + L.o_cbase);
+    bv.tile_pair = (int32_t *)(ws + L.o_tpair);
     bv.n_tiles = G.n_tiles;
     bv.n_pairs = (int32_t)G.n_pairs;
     bv.bm_log2 = G.bm_log2;
-    bv.bc_log2 = G.bc_log2;
+    bv.br_log2 = G.br_log2;
     bv.packable = G.packable;
     bv.c32 = G.c32;
     bv.pb = G.pb;
@@ -2367,8 +2476,8 @@ int enqueue(const Geometry &G, const Layout &L, const BatchView &bv, char *ws, h
     else
         MS_LAUNCH("k_mark", (k_mark<ONE, false>), dim3(g_tri), dim3(BLOCK), 0, st, bv, flags, epoch, rng, pbox, mpart,
                   cs);
-    MS_LAUNCH("k_pack", k_pack, dim3(grid_for(L.n_fwords + L.n_cwords, 4096)), dim3(BLOCK), 0, st, flags, epoch,
-              G.bm_log2, G.bc_log2, both, grp, mix, L.n_fwords, L.n_cwords);
+    MS_LAUNCH("k_pack", k_pack, dim3(grid_for(L.n_fwords + L.n_rwords, 4096)), dim3(BLOCK), 0, st, flags, epoch,
+              G.bm_log2, G.br_log2, both, grp, mix, L.n_fwords, L.n_rwords);
     KeysOut ko;
     ko.ent = ent;
     ko.epair = epair;
@@ -2649,7 +2758,7 @@ extern "C" int search_intersections_noalloc(const ms_mesh *A, const ms_mesh *B, 
         int lg = G.bm_log2;
         for (; lg > 12; --lg) {
             G.bm_log2 = lg;
-            G.bc_log2 = lg - 3;
+            G.br_log2 = lg - 3;
             if (fixed_bytes(G, hits_cap) <= MS_NOALLOC_SCRATCH_BYTES / 2) break;
         }
         p.table_log2 = lg;

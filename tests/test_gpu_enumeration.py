@@ -79,3 +79,17 @@ def test_touching_boxes(ms):
         B = synth.affine_mesh([dx, dy, 0, 0], [1, 0, 0.25, 0], [0, 1, 0, 0.25], th, th)
         _check(ms, A, B, [-0.25] * 4, 4.0, [12, 12, 4, 4])
         _check(ms, A, B, [-0.25] * 4, 1.0 / 3.0, [1, 1, 1, 1])
+
+
+@pytest.mark.parametrize("table_log2", [0, 12])
+@pytest.mark.parametrize("inv", [1.5, 9.0, 20.0, 30.0])
+def test_ranges_of_many_blocks_and_regions(ms, inv, table_log2):
+    """Triangles of one cell to more than 15 per axis: ranges inside a 2^4
+    block, over several blocks and regions, tiles whose entries overflow the
+    list of a block and ranges too wide for its words."""
+    A, B = synth.torus_mesh(27, 20, synth.surface_coeffs(7)), synth.torus_mesh(16, 33, synth.surface_coeffs(8))
+    V = np.concatenate([A.verts.reshape(-1, 4), B.verts.reshape(-1, 4)])
+    lo, n = V.min(0) - 0.3 / inv, np.ceil((V.max(0) - V.min(0)) * inv).astype(np.int64) + 1
+    st, _ = _check(ms, A, B, list(lo), inv, [int(k) for k in n], table_log2=table_log2)
+    g = oracle.grid_search(A, B, lo, inv, n)
+    assert st["n_cells"] == g.n_boxes and st["n_slots"] == g.n_slots and st["n_entries_all"] == g.n_entries
