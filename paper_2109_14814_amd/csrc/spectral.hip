@@ -23,10 +23,12 @@
 // them.  The twiddle factors e^{-2 pi i m / N} come from a table of N values
 // made once per (device, N) on the host and read through the caches.
 //
-// theta_interp: one wave per query, the barycentric form of the
-// trigonometric interpolant (no transform): with theta = theta_i0 + delta,
+// theta_interp: the barycentric form of the trigonometric interpolant (no
+// transform): with theta = theta_i0 + delta,
 //   a(theta) = sin(N delta / 2) / N * sum_i (-1)^d a_i g(delta / 2 + pi d / N),
 // d = i0 - i reduced to [-N/2, N/2), g = cot for even N and 1 / sin for odd N.
+// The weights come from the row length's cotangents by the addition theorem;
+// up to four queries of a row share its samples.
 #include <math.h>
 
 #include <algorithm>
@@ -309,37 +311,26 @@ __global__ void __launch_bounds__(SP_THREADS) k_theta_spectrum(const double *in,
     pass<N, PL::radix(PM), NSM, false, PM == 0 ? FROM_GLOBAL : FROM_LDS, true, false>(z, tw, src, dst, 0.0, 0);
 }
 
-constexpr int IP_WAVES = 4;
+// ------------------------------------------------------------- interpolation
 
-__global__ void __launch_bounds__(64 * IP_WAVES) k_theta_interp(const double *in, int N, int64_t n_rows,
-                                                                const int64_t *rows, const double *theta, int64_t nq,
-                                                                double *out)
+constexpr int IP_BLOCK = 1024;
+constexpr int IP_MAX_N = 2048;            // the cotangents of a row length up to this lie in LDS
+constexpr int IP_MAX_Q = 256;             // queries of a block (grouped: its share)
+constexpr int IP_LIST = 3 * IP_MAX_Q;
+constexpr int IP_SLICE = 1 << 16;         // queries grouped together
+constexpr int IP_MAX_BINS = 8192;
+constexpr uint32_t IP_START = 0x1ffff;    // a bin's word: start (17 bits; all ones: too large), rank from bit 17
+
+// One query by the barycentric form with a sine and cosine per sample, by
+// one wave: any theta, any N.
+MS_D void interp_one(const double *a, int N, double th, double *o)
 {
-    const int64_t q = (int64_t)blockIdx.x * IP_WAVES + threadIdx.x / 64;
     const int lane = threadIdx.x % 64;
-    if (q >= nq) return;   // whole waves
-    const int64_t row = rows[q];
-    const double th = theta[q];
-    double *o = out + 4 * q;
-    if (row < 0 || row >= n_rows || !isfinite(th)) {
-        if (lane < 4) o[lane] = NAN;
-        return;
-    }
-    const double *a = in + row * (int64_t)N * 4;
     const double step = 2.0 * SP_PI / (double)N;
-    // nearest sample i0 (reduced to [0, N)) and the offset delta from it
     const double i0f = rint(th / step);
-    if (!isfinite(i0f)) {       // |theta| beyond any meaningful angle: no index to take
-        if (lane < 4) o[lane] = NAN;
-        return;
-    }
     const double delta = th - i0f * step;
     int64_t i0 = (int64_t)fmod(i0f, (double)N);   // exact, in (-N, N)
     if (i0 < 0) i0 += N;
-    if (fabs(delta) < 1e-200) {
-        if (lane < 4) o[lane] = a[4 * i0 + lane];
-        return;
-    }
     const bool even = (N & 1) == 0;
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
     for (int i = lane; i < N; i += 64) {
@@ -350,7 +341,7 @@ __global__ void __launch_bounds__(64 * IP_WAVES) k_theta_interp(const double *in
         sincos(0.5 * delta + SP_PI * (double)d / (double)N, &sn, &cs);
         double w = even ? cs / sn : 1.0 / sn;
         if (d & 1) w = -w;
-        d4 v = load_d4(a + 4 * i);
+        d4 v = load_d4(a + 4 * (int64_t)i);
         acc[0] += w * v.x;
         acc[1] += w * v.y;
         acc[2] += w * v.z;
@@ -364,6 +355,457 @@ __global__ void __launch_bounds__(64 * IP_WAVES) k_theta_interp(const double *in
         const double f = sin(0.5 * (double)N * delta) / (double)N;
         double s = lane == 0 ? acc[0] : lane == 1 ? acc[1] : lane == 2 ? acc[2] : acc[3];
         o[lane] = f * s;
+    }
+}
+
+// The same, a wave per query: where the tables of k_theta_interp do not fit
+// or do not pay.
+__global__ void __launch_bounds__(256) k_theta_interp_plain(const double *in, int N, int64_t n_rows,
+                                                           const int64_t *rows, const double *theta, int64_t nq,
+                                                           double *out)
+{
+    const int64_t q = (int64_t)blockIdx.x * 4 + threadIdx.x / 64;
+    const int lane = threadIdx.x % 64;
+    if (q >= nq) return;   // whole waves
+    const int64_t row = rows[q];
+    const double th = theta[q];
+    double *o = out + 4 * q;
+    const double step = 2.0 * SP_PI / (double)N;
+    const double i0f = rint(th / step);
+    if (row < 0 || row >= n_rows || !isfinite(th) || !isfinite(i0f)) {
+        if (lane < 4) o[lane] = NAN;
+        return;
+    }
+    const double *a = in + row * (int64_t)N * 4;
+    if (fabs(th - i0f * step) < 1e-200) {
+        int64_t i0 = (int64_t)fmod(i0f, (double)N);
+        if (i0 < 0) i0 += N;
+        if (lane < 4) o[lane] = a[4 * i0 + lane];
+        return;
+    }
+    interp_one(a, N, th, o);
+}
+
+MS_D double uni(double x)
+{
+    const uint64_t b = (uint64_t)__double_as_longlong(x);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
+    return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
+}
+
+// The queries of a block in LDS.
+struct IpList {
+    double t[IP_LIST];       // tan(delta / 2)
+    double f[IP_LIST];       // factor of the sum: (-1)^i0 sin(N delta / 2) / N (odd N: / cos(delta / 2))
+    int64_t row[IP_LIST];    // -1: nothing to do
+    int32_t i0[IP_LIST];     // -1: |theta| so large that delta is not below a step
+    uint32_t q[IP_LIST];     // query, from the slice's first; ~0: none
+    uint32_t tile[IP_LIST];  // first entry, entries << 16 (0: one with i0 = -1)
+    uint32_t n_tiles, unsorted;
+};
+
+// 1 / d[i] of four values of ordinary size with one reciprocal.
+MS_D void recip4(const double d[4], double r[4])
+{
+    const double p01 = d[0] * d[1], p23 = d[2] * d[3], p = p01 * p23;
+    double x = __builtin_amdgcn_rcp(p);
+    const double e = fma(-p, x, 1.0);
+    x = fma(x, fma(e, e, e), x);
+    const double a = x * p23, b = x * p01;
+    r[0] = a * d[1];
+    r[1] = a * d[0];
+    r[2] = b * d[3];
+    r[3] = b * d[2];
+}
+
+// QT queries of one row, U samples per lane and step (QT U = 4): with
+// t = tan(delta / 2) and d = i0 - i,
+//   cot(delta / 2 + pi d / N) = (cot(pi d / N) - t) / (1 + t cot(pi d / N))
+//   1 / sin(delta / 2 + pi d / N) = 1 / (sin(pi d / N) (1 + t cot(pi d / N)) cos(delta / 2)),
+// where |t cot| < 3/4 but for d = 0, whose weight is 1 / t.  Entry x of the
+// table is cot(-pi x / N), 0 < x < N, with 1 / sin(pi x / N) for odd N: a
+// lane's samples below i0 have x = i - i0 + N, those above x = i - i0, where
+// 1 / sin(pi d / N) is minus the entry's.  So the lane's sums change sign
+// there (odd N), and the sum's sign in the end.  The two steps in which lanes
+// pass i0, and the last one of a length that is no multiple of the step, go
+// sample by sample.  (-1)^d is (-1)^i0 for the query times (-1)^i, a sign per
+// lane: the steps are of 64 samples.
+template <bool ODD, int QT>
+MS_D void interp_tile(const IpList &s, int e0, int len, const double *tab, const double *__restrict__ in, int N,
+                      double *out)
+{
+    constexpr int U = 4 / QT;
+    const int lane = threadIdx.x % 64;
+    double t[QT];
+    int i0[QT], x[QT];
+    uint64_t fix = 0;
+#pragma unroll
+    for (int q = 0; q < QT; ++q) {
+        const int e = e0 + (q < len ? q : len - 1);
+        t[q] = uni(s.t[e]);
+        i0[q] = __builtin_amdgcn_readfirstlane(s.i0[e]);
+        fix |= 1ull << (i0[q] / (64 * U)) | 1ull << ((i0[q] + 63) / (64 * U));
+        x[q] = lane - i0[q] + N;
+    }
+    const uint64_t row = (uint64_t)s.row[e0];
+    const double *a = in + 4 * (int64_t)((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)row) |
+                                         (uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(row >> 32)) << 32) * N;
+    double acc[4 * QT] = {};
+    double num[4], den[4], r[4];
+    auto entry = [&](int j, int q, int k) {
+        if constexpr (ODD) {
+            const double2 c = reinterpret_cast<const double2 *>(tab)[k];
+            den[j] = fma(t[q], c.x, 1.0);
+            num[j] = c.y;
+        } else {
+            const double c = tab[k];
+            den[j] = fma(t[q], c, 1.0);
+            num[j] = c - t[q];
+        }
+    };
+    auto load = [&](d4 *v, int k) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = load_d4(a + 256 * (k + u) + 4 * lane);
+    };
+    auto add = [&](const d4 *v) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int q = j / U, u = j % U;
+            acc[4 * q] = fma(num[j], v[u].x, acc[4 * q]);
+            acc[4 * q + 1] = fma(num[j], v[u].y, acc[4 * q + 1]);
+            acc[4 * q + 2] = fma(num[j], v[u].z, acc[4 * q + 2]);
+            acc[4 * q + 3] = fma(num[j], v[u].w, acc[4 * q + 3]);
+        }
+    };
+    const int steps = (N + 64 * U - 1) / (64 * U), full = N / (64 * U);
+    if (full < steps) fix |= 1ull << full;
+    int k = 0;      // step: samples 64 U k + 64 u + lane
+    while (k < steps) {
+        const uint64_t ahead = fix >> k;
+        const int stop = ahead ? min(k + (int)__builtin_ctzll(ahead), steps) : steps;
+        if (k < stop) {
+            d4 v[U];
+            load(v, U * k);
+            for (; k < stop; ++k) {
+                d4 w[U];
+                load(w, U * (k + 1 < stop ? k + 1 : k));       // the next step's, in flight over this one
+#pragma unroll
+                for (int j = 0; j < 4; ++j) entry(j, j / U, x[j / U] + 64 * (j % U));
+                recip4(den, r);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) num[j] *= r[j];
+                add(v);
+#pragma unroll
+                for (int q = 0; q < QT; ++q) x[q] += 64 * U;
+#pragma unroll
+                for (int u = 0; u < U; ++u) v[u] = w[u];
+            }
+        }
+        if (k >= steps) break;
+        const int i_first = lane + 64 * U * k, i_last = i_first + 64 * (U - 1);
+        d4 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            v[u] = i_first + 64 * u < N ? load_d4(a + 4 * (i_first + 64 * u)) : d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int i = i_first + 64 * (j % U), d = i - i0[j / U];
+            entry(j, j / U, i >= N ? 0 : d < 0 ? d + N : d);
+        }
+        recip4(den, r);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int q = j / U, i = i_first + 64 * (j % U);
+            num[j] = i == i0[q] ? (ODD ? -1.0 : 1.0) / t[q] : num[j] * r[j];
+            if (ODD && i < i0[q] && i_last >= i0[q]) num[j] = -num[j];
+        }
+#pragma unroll
+        for (int q = 0; q < QT; ++q) {
+            // the lane passes i0 in this step
+            if (ODD && i_first - 64 < i0[q] && i_last >= i0[q])
+#pragma unroll
+                for (int c = 0; c < 4; ++c) acc[4 * q + c] = -acc[4 * q + c];
+            x[q] = i_last + 64 - i0[q] + (i_last < i0[q] ? N : 0);
+        }
+        add(v);
+        ++k;
+    }
+    // a row may end before a lane passes i0
+    if constexpr (ODD)
+#pragma unroll
+        for (int q = 0; q < QT; ++q)
+            if (lane + 64 * (U * steps - 1) < i0[q])
+#pragma unroll
+                for (int c = 0; c < 4; ++c) acc[4 * q + c] = -acc[4 * q + c];
+    // the lanes' sums: value j of 4 QT ends up on the lanes whose top bits are j
+#pragma unroll
+    for (int n = 2 * QT, off = 32; n >= 1; n >>= 1, off >>= 1) {
+        const bool hi = (lane & off) != 0;
+#pragma unroll
+        for (int j = 0; j < n; ++j) {
+            const double mine = hi ? acc[j + n] : acc[j], send = hi ? acc[j] : acc[j + n];
+            acc[j] = mine + __shfl_xor(send, off);
+        }
+    }
+    constexpr int SHARE = 64 / (4 * QT);
+#pragma unroll
+    for (int off = SHARE / 2; off > 1; off >>= 1) acc[0] += __shfl_xor(acc[0], off);
+    const double other = __shfl_xor(acc[0], 1);
+    if (lane % SHARE != 0) return;
+    const int j = lane / SHARE, q = j / 4;
+    if (q < len) out[4 * (int64_t)s.q[e0 + q] + j % 4] = s.f[e0 + q] * (acc[0] - other);
+}
+
+struct InterpArgs {
+    const double *in;
+    const int64_t *rows;
+    const double *theta;
+    double *out;
+    int64_t n_rows, nq;
+    int N;
+    int share;               // queries of a block
+    int slice, per_slice;    // grouped: queries of a slice, blocks of a slice
+    int bins, shift;         // grouped: bins of 2^shift rows
+};
+
+// A block takes `share` queries, keeps the row length's cotangents in LDS
+// and gives its waves tiles of up to four queries of the same row, whose
+// samples are then loaded once for all four.  GROUPED (many queries per row,
+// in any order): a slice of up to 65536 queries is dealt to its blocks by
+// rows.  Every block counts the slice's queries per bin of rows in LDS (one
+// scan of the row indices), takes the bins that start in its share of the
+// sorted order and, in a second scan, their queries.  A bin of more than a
+// share is left out of that order: its queries go to the blocks by their
+// place in the slice, so that a block has at most three shares whatever the
+// rows are.
+//
+// 65536 queries in 4096 rows of 2048 samples: 137 us, from 555 with a wave
+// per query and a sine, cosine and division per sample (about 100 FP64
+// instructions, now 13), which read the rows 16 times.  Without the grouping
+// 614: the rows' bytes bound it.  Now 25 us go to the grouping, 8 to the table
+// and the offsets, the rest to the sums, at about half the FP64 rate.  Four
+// queries in flight with their next samples take the 128 registers of four
+// waves per SIMD; a wave's two scalar steps cost as much as four others.
+template <bool ODD, bool GROUPED>
+__global__ void __launch_bounds__(IP_BLOCK) k_theta_interp(InterpArgs g)
+{
+    extern __shared__ double s_dyn[];     // the bins, then the cotangents
+    __shared__ IpList s;
+    const int tid = threadIdx.x, nt = GROUPED ? IP_BLOCK : (int)blockDim.x, lane = tid % 64, wv = tid / 64;
+    const int N = g.N;
+    int64_t q0;
+    int n_list;
+    if constexpr (GROUPED) {
+        __shared__ uint32_t s_wave[IP_BLOCK / 64], s_lo, s_hi;
+        if (tid == 0) {
+            s_lo = ~0u;
+            s_hi = 0;
+        }
+        uint32_t *bin = reinterpret_cast<uint32_t *>(s_dyn);
+        const int b = (int)(blockIdx.x % (unsigned)g.per_slice);
+        q0 = (int64_t)(blockIdx.x / (unsigned)g.per_slice) * g.slice;
+        const int n = (int)(g.nq - q0 < g.slice ? g.nq - q0 : g.slice);
+        const int64_t *rows = g.rows + q0;
+        auto bin_of = [&](int64_t r) { return r < 0 || r >= g.n_rows ? 0u : (uint32_t)(r >> g.shift); };
+        for (int i = tid; i < g.bins; i += IP_BLOCK) bin[i] = 0;
+        for (int i = tid; i < 3 * g.share; i += IP_BLOCK) s.q[i] = ~0u;
+        __syncthreads();
+        // the thread's row bins stay in registers, two in each
+        constexpr int PER = IP_SLICE / IP_BLOCK;
+        uint32_t mine[PER / 2];
+#pragma unroll
+        for (int c = 0; c < PER; c += 16) {
+            if (c * IP_BLOCK >= n) break;
+            int64_t r[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) {
+                const int i = tid + (c + u) * IP_BLOCK;
+                r[u] = i < n ? rows[i] : 0;
+            }
+#pragma unroll
+            for (int u = 0; u < 16; ++u) {
+                const uint32_t h = bin_of(r[u]);
+                const bool in = tid + (c + u) * IP_BLOCK < n;
+                // one row's queries one after another: one add for the wave
+                if (ballot(in && h == (uint32_t)__builtin_amdgcn_readfirstlane(h)) == ~0ull) {
+                    if (lane == 0) atomicAdd(&bin[h], 64u);
+                } else if (in) {
+                    atomicAdd(&bin[h], 1u);
+                }
+                mine[(c + u) / 2] = (u & 1) ? mine[(c + u) / 2] | h << 16 : h;
+            }
+        }
+        __syncthreads();
+        // starts of the bins in the sorted order
+        const int per = (g.bins + IP_BLOCK - 1) / IP_BLOCK;
+        const int b0 = tid * per, b1 = b0 + per < g.bins ? b0 + per : g.bins;
+        uint32_t sum = 0;
+        for (int i = b0; i < b1; ++i) sum += bin[i] <= (uint32_t)g.share ? bin[i] : 0;
+        uint32_t inc = sum;
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t y = __shfl_up(inc, o);
+            if (lane >= o) inc += y;
+        }
+        if (lane == 63) s_wave[wv] = inc;
+        __syncthreads();
+        uint32_t at = inc - sum;
+        for (int w = 0; w < wv; ++w) at += s_wave[w];
+        // the block's bins: those that start in its share of the order
+        const uint32_t first = (uint32_t)(b * g.share);
+        uint32_t lo = ~0u, hi = 0;
+        for (int i = b0; i < b1; ++i) {
+            const uint32_t c = bin[i];
+            const bool fits = c <= (uint32_t)g.share;
+            if (fits && c && at - first < (uint32_t)g.share) {
+                lo = min(lo, (uint32_t)i);
+                hi = (uint32_t)i + 1;
+            }
+            bin[i] = fits ? at : IP_START;
+            at += fits ? c : 0;
+        }
+        if (hi) {
+            atomicMin(&s_lo, lo);
+            atomicMax(&s_hi, hi);
+        }
+        __syncthreads();
+        lo = s_lo;
+        hi = s_hi;
+#pragma unroll
+        for (int c = 0; c < PER; ++c) {
+            const int i = tid + c * IP_BLOCK;
+            if (c * IP_BLOCK >= n) break;
+            if (i >= n) continue;
+            const uint32_t h = mine[c / 2] >> (c & 1 ? 16 : 0) & 0xffff;
+            const bool window = (uint32_t)i - first < (uint32_t)g.share;
+            if (!window && h - lo >= hi - lo) continue;
+            const uint32_t start = bin[h] & IP_START;
+            if (start == IP_START) {
+                if (window) s.q[2 * g.share + (uint32_t)i - first] = (uint32_t)i;
+            } else if (start - first < (uint32_t)g.share) {
+                const uint32_t rank = atomicAdd(&bin[h], IP_START + 1) >> 17;
+                s.q[start - first + rank] = (uint32_t)i;
+            }
+        }
+        n_list = 3 * g.share;
+        __syncthreads();
+    } else {
+        q0 = (int64_t)blockIdx.x * g.share;
+        n_list = (int)(g.nq - q0 < g.share ? g.nq - q0 : g.share);
+    }
+    if (tid == 0) s.n_tiles = s.unsorted = 0;
+    // A share may hold several queries of a row, but not side by side: those
+    // by their place in the slice, and a direct block's if the rows are few.
+    if (GROUPED || g.n_rows <= g.share) {
+        const int e0 = GROUPED ? 2 * g.share : 0, ne = n_list - e0;
+        for (int e = tid; e < ne; e += nt) {
+            if constexpr (!GROUPED) s.q[e] = (uint32_t)e;
+            s.row[e0 + e] = s.q[e0 + e] == ~0u ? INT64_MAX : g.rows[q0 + s.q[e0 + e]];
+            s.tile[e] = 0;
+        }
+        __syncthreads();
+        const int e = tid % g.share, part = tid / g.share, parts = nt / g.share;
+        if (tid < ne && tid > 0 && s.row[e0 + tid] < s.row[e0 + tid - 1]) s.unsorted = 1;
+        __syncthreads();
+        if (s.unsorted) {
+            if (e < ne && part < parts) {
+                const int64_t row = s.row[e0 + e];
+                uint32_t r = 0;
+                for (int j = part; j < ne; j += parts) {
+                    const int64_t o = s.row[e0 + j];
+                    r += o < row || (o == row && j < e);
+                }
+                atomicAdd(&s.tile[e], r);
+            }
+            uint32_t q = 0;
+            if (tid < ne) q = s.q[e0 + tid];
+            __syncthreads();
+            if (tid < ne) s.q[e0 + s.tile[tid]] = q;
+        }
+        __syncthreads();
+    } else {
+        for (int e = tid; e < n_list; e += nt) s.q[e] = (uint32_t)e;
+        __syncthreads();
+    }
+    for (int x = tid; x <= N / 2; x += nt) {
+        // entries x and N - x: cot(-pi x / N) and minus that (and 1 / sin(pi x / N) twice)
+        double sn = 1.0, cs = 0.0;
+        if (x) sincospi((double)x / (double)N, &sn, &cs);
+        const int y = x ? N - x : 0;
+        if constexpr (ODD) {
+            reinterpret_cast<double2 *>(s_dyn)[x] = make_double2(-cs / sn, 1.0 / sn);
+            reinterpret_cast<double2 *>(s_dyn)[y] = make_double2(cs / sn, 1.0 / sn);
+        } else {
+            s_dyn[x] = -cs / sn;
+            s_dyn[y] = cs / sn;
+        }
+    }
+    // the queries: offsets from their nearest samples
+    const double step = 2.0 * SP_PI / (double)N;
+    for (int e = tid; e < n_list; e += nt) {
+        int64_t row = -1;
+        if (s.q[e] != ~0u) {
+            const int64_t q = q0 + s.q[e];
+            row = g.rows[q];
+            const double th = g.theta[q];
+            const double i0f = rint(th / step);
+            double *o = g.out + 4 * q;
+            if (row < 0 || row >= g.n_rows || !isfinite(th) || !isfinite(i0f)) {
+                // no such row, or |theta| beyond any meaningful angle
+                row = -1;
+                o[0] = o[1] = o[2] = o[3] = NAN;
+            } else {
+                const double delta = th - i0f * step;
+                int32_t i0 = fabs(i0f) < 1e9 ? (int32_t)i0f % N : (int32_t)fmod(i0f, (double)N);
+                if (i0 < 0) i0 += N;
+                if (fabs(delta) < 1e-200) {
+                    const double *a = g.in + (row * (int64_t)N + i0) * 4;
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) o[c] = a[c];
+                    row = -1;
+                } else {
+                    double sn, cs;
+                    sincos(0.5 * delta, &sn, &cs);
+                    s.t[e] = sn / cs;
+                    double f = sin(0.5 * (double)N * delta) / (double)N;
+                    if (ODD) f /= cs;
+                    s.f[e] = ((i0 & 1) != 0) != ODD ? -f : f;      // (odd N: see interp_tile)
+                    s.i0[e] = fabs(delta) < 0.75 * step ? i0 : -1;
+                }
+            }
+        }
+        s.row[e] = row;
+    }
+    __syncthreads();
+    // tiles: up to four neighbours of the same row
+    for (int e = tid; e - lane < n_list; e += nt) {
+        const int64_t row = e < n_list ? s.row[e] : -1;
+        const bool lone = row >= 0 && s.i0[e] < 0;
+        const bool head = lane == 0 || row < 0 || lone || s.row[e - 1] != row || s.i0[e - 1] < 0;
+        const uint64_t heads = ballot(head);
+        const uint64_t below = heads & (~0ull >> (63 - lane));
+        const int at = lane - (63 - __builtin_clzll(below));
+        const bool start = row >= 0 && (at & 3) == 0;
+        const uint64_t after = lane == 63 ? 0 : heads >> (lane + 1);
+        const int run = after ? 1 + __builtin_ctzll(after) : 64 - lane;
+        const uint64_t starts = ballot(start);
+        uint32_t base = 0;
+        if (lane == 0) base = atomicAdd(&s.n_tiles, (uint32_t)__builtin_popcountll(starts));
+        base = __builtin_amdgcn_readfirstlane(base);
+        if (start)
+            s.tile[base + __builtin_popcountll(starts & ~(~0ull << lane))] =
+                (uint32_t)e | (lone ? 0u : (uint32_t)(run < 4 ? run : 4) << 16);
+    }
+    __syncthreads();
+    double *out = g.out + 4 * q0;
+    const int n_tiles = (int)s.n_tiles;
+    for (int k = wv; k < n_tiles; k += nt / 64) {
+        const uint32_t w = __builtin_amdgcn_readfirstlane(s.tile[k]);
+        const int e = (int)(w & 0xffff), len = (int)(w >> 16);
+        if (len > 2) interp_tile<ODD, 4>(s, e, len, s_dyn, g.in, N, out);
+        else if (len == 2) interp_tile<ODD, 2>(s, e, len, s_dyn, g.in, N, out);
+        else if (len == 1) interp_tile<ODD, 1>(s, e, len, s_dyn, g.in, N, out);
+        else interp_one(g.in + s.row[e] * (int64_t)N * 4, N, g.theta[q0 + s.q[e]], out + 4 * (int64_t)s.q[e]);
     }
 }
 
@@ -571,10 +1013,62 @@ extern "C" int theta_interp(const double *rows_dev, int32_t n_theta, int64_t n_r
         (n_query > 0 && (!rows_dev || !row_dev || !theta_dev || !out_dev)))
         return fail(MS_E_ARG, "theta_interp: bad argument");
     if (n_query == 0) return MS_OK;
-    const int64_t blocks = ceil_div(n_query, IP_WAVES);
+    hipStream_t st = (hipStream_t)stream;
+    const int N = (int)n_theta;
+    // A block's table and offsets cost some 8 us: short rows repay them only
+    // with many queries for each block (129 samples, 5000 queries: 11 to 16
+    // against 9 us; 256, 20000: 16 against 33), the shortest never (64
+    // samples, 20000 queries: 15 against 17; 33, 65536: 47 and 47).
+    if (N > IP_MAX_N || N < 64 || (N < 256 && n_query < 16384)) {
+        const int64_t blocks = ceil_div(n_query, 4);
+        if (blocks > 0x7fffffff) return fail(MS_E_ARG, "theta_interp: too many queries for one launch");
+        hipLaunchKernelGGL(k_theta_interp_plain, dim3((unsigned)blocks), dim3(256), 0, st, rows_dev, N, n_rows, row_dev,
+                           theta_dev, n_query, out_dev);
+        MS_HIP(hipGetLastError());
+        return MS_OK;
+    }
+    InterpArgs g;
+    g.in = rows_dev;
+    g.rows = row_dev;
+    g.theta = theta_dev;
+    g.out = out_dev;
+    g.n_rows = n_rows;
+    g.nq = n_query;
+    g.N = N;
+    g.slice = g.per_slice = g.bins = g.shift = 0;
+    const bool odd = (N & 1) != 0;
+    const size_t table = (size_t)(odd ? 16 : 8) * N;
+    // Grouped by rows where the rows do not stay in the caches (8 MB: twice
+    // an XCD's L2) and are read more than once: 2048 rows of 2048, 4096 queries:
+    // 40 us either way; 1024 rows, 4096 queries: 31 against 39; 4096 rows,
+    // 8192 queries: 54 against 78; 300 rows of 1024, 65536 queries: 118
+    // against 171; but 300 rows of 512: 94 against 60, 128 of 2048: 173
+    // against 149.
+    const bool grouped = n_query >= 4096 && n_query >= 2 * n_rows && n_rows > (8 << 20) / (32 * N);
+    int64_t blocks;
+    size_t lds = table;
+    int threads = IP_BLOCK;
+    if (grouped) {
+        const int64_t slices = ceil_div(n_query, (int64_t)IP_SLICE);
+        g.slice = (int)ceil_div(n_query, slices);
+        g.share = (int)std::max<int64_t>(32, ceil_div(g.slice, 256));
+        g.per_slice = (int)ceil_div(g.slice, g.share);
+        while ((((n_rows > 0 ? n_rows : 1) - 1) >> g.shift) >= IP_MAX_BINS) ++g.shift;
+        g.bins = n_rows > 0 ? (int)((n_rows - 1) >> g.shift) + 1 : 1;
+        lds = std::max(table, (size_t)g.bins * 4);
+        blocks = slices * g.per_slice;
+    } else {
+        threads = n_query >= 16384 ? 1024 : 256;     // few queries: spread over the CUs, a table each
+        const int w = threads / 64;
+        g.share = (int)std::min<int64_t>(IP_MAX_Q, w * ceil_div(n_query, w * (int64_t)(262144 / threads)));
+        blocks = ceil_div(n_query, g.share);
+    }
     if (blocks > 0x7fffffff) return fail(MS_E_ARG, "theta_interp: too many queries for one launch");
-    hipLaunchKernelGGL(k_theta_interp, dim3((unsigned)blocks), dim3(64 * IP_WAVES), 0, (hipStream_t)stream, rows_dev,
-                       (int)n_theta, n_rows, row_dev, theta_dev, n_query, out_dev);
+    const dim3 grid((unsigned)blocks), block((unsigned)threads);
+    if (odd && grouped) hipLaunchKernelGGL((k_theta_interp<true, true>), grid, block, lds, st, g);
+    else if (odd) hipLaunchKernelGGL((k_theta_interp<true, false>), grid, block, lds, st, g);
+    else if (grouped) hipLaunchKernelGGL((k_theta_interp<false, true>), grid, block, lds, st, g);
+    else hipLaunchKernelGGL((k_theta_interp<false, false>), grid, block, lds, st, g);
     MS_HIP(hipGetLastError());
     return MS_OK;
 }
