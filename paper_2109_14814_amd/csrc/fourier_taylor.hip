@@ -5,11 +5,12 @@
 //
 // The coefficients W_k are given by their spectra over theta (theta_spectrum
 // of each coefficient row, scaled by 1/N, the pairs (x, y) and (px, py)
-// packed as complex sequences).  One wave evaluates one query (theta, s):
-// each lane takes frequencies j = lane, lane + 64, ..., sums the series in s
-// at j by Horner's rule (the value and its s-derivative together), and adds
-// the terms e^{i j theta} V(j) and i j e^{i j theta} V(j); a wave reduction
-// gives W, dW/dtheta and dW/ds.  This is the paper's "evaluate in s, FFT
+// packed as complex sequences).  Per query (theta, s) and frequency j the
+// series in s is summed (the value V(j) and its s-derivative together), by
+// Horner's rule for few queries and as a matrix product for many, and the
+// terms e^{i j theta} V(j) and i j e^{i j theta} V(j) are added up over the
+// lanes, the waves of a block and their steps: W, dW/dtheta and dW/ds.  This
+// is the paper's "evaluate in s, FFT
 // derivative in theta, interpolate trigonometrically", done in the
 // frequency domain so that no per-query transform is needed: the
 // trigonometric interpolant of the samples is the sum over their spectrum.
@@ -23,6 +24,7 @@
 // one ft_partials per chart and one decision kernel per iteration.
 #include <math.h>
 
+#include <algorithm>
 #include <string>
 
 #include "newton.hpp"
@@ -30,78 +32,409 @@
 namespace ms {
 namespace {
 
-constexpr int FT_WAVES = 4;
+constexpr int FT_STEP = 32;          // frequencies of a wave's step
+template <int QT>
+constexpr int FT_R = 8;
+template <int QT>
+constexpr int FT_MAX_WAVES = QT > 2 ? 8 : 16;
 
-__global__ void __launch_bounds__(64 * FT_WAVES) k_ft_eval(const double *__restrict__ spec, int N, int P,
-                                                           const double *__restrict__ theta,
-                                                           const double *__restrict__ s, int64_t nq, double th_off,
-                                                           double s_scale, double *w, double *dth, double *ds)
+// --------------------------------------------------------------- phases
+//
+// e^{i x} by table and polynomial (Tang, "Table-driven implementation of the
+// elementary functions"): n = rint(x / (pi / 32)), r = x - n pi / 32 with the
+// constant in two parts, the first short enough that n times it is exact up to
+// |n| = 2^20, and cos and sin of n pi / 32, kept in two parts as well, turned
+// by r: the Taylor terms to r^8 and r^7 are below 1e-17 for |r| <= pi / 64.
+// The correction is added to the table's value in the end, so the error is
+// half a unit in the last place and little more.  About 25 FP64 instructions, a
+// quarter of sincos, which remains for |x| above 1e5.
+constexpr double PH_COS[17][2] = {      // cos(k pi / 32): rounded, and the rest
+    {0x1.0000000000000p+0, 0x0.0p+0},
+    {0x1.fd88da3d12526p-1, -0x1.87df6378811c7p-55},
+    {0x1.f6297cff75cb0p-1, 0x1.562172a361fd3p-56},
+    {0x1.e9f4156c62ddap-1, 0x1.760b1e2e3f81ep-55},
+    {0x1.d906bcf328d46p-1, 0x1.457e610231ac2p-56},
+    {0x1.c38b2f180bdb1p-1, -0x1.6e0b1757c8d07p-56},
+    {0x1.a9b66290ea1a3p-1, 0x1.9f630e8b6dac8p-60},
+    {0x1.8bc806b151741p-1, -0x1.2c5e12ed1336dp-55},
+    {0x1.6a09e667f3bcdp-1, -0x1.bdd3413b26456p-55},
+    {0x1.44cf325091dd6p-1, 0x1.8076a2cfdc6b3p-57},
+    {0x1.1c73b39ae68c8p-1, 0x1.b25dd267f6600p-55},
+    {0x1.e2b5d3806f63bp-2, 0x1.e0d891d3c6841p-58},
+    {0x1.87de2a6aea963p-2, -0x1.72cedd3d5a610p-57},
+    {0x1.294062ed59f06p-2, -0x1.5d28da2c4612dp-56},
+    {0x1.8f8b83c69a60bp-3, -0x1.26d19b9ff8d82p-57},
+    {0x1.917a6bc29b42cp-4, -0x1.e2718d26ed688p-60},
+    {0x0.0p+0, 0x0.0p+0}};
+constexpr double PH_INV = 0x1.45f306dc9c883p+3;      // 32 / pi
+constexpr double PH_P1 = 0x1.921fb54400000p-4, PH_P2 = 0x1.0b4611a626331p-38;
+
+struct PhaseTable {
+    double2 c[64], s[64];      // cos and sin of n pi / 32 in two parts
+};
+
+MS_D double2 ph_cos(int n)
 {
-    const int64_t q = (int64_t)blockIdx.x * FT_WAVES + threadIdx.x / 64;
-    const int lane = threadIdx.x % 64;
-    if (q >= nq) return;   // whole waves
-    const double t = theta[q] - th_off;
-    const double sl = s[q] * s_scale;
-    if (!isfinite(t) || !isfinite(sl)) {
-        if (lane < 4) w[4 * q + lane] = dth[4 * q + lane] = ds[4 * q + lane] = NAN;
+    n &= 63;
+    const int m = n > 32 ? 64 - n : n, k = m > 16 ? 32 - m : m;
+    double2 v;
+    v.x = PH_COS[k][0];
+    v.y = PH_COS[k][1];
+    if (m > 16) v = make_double2(-v.x, -v.y);
+    return v;
+}
+
+MS_D void phase_table(PhaseTable &tab)
+{
+    for (int n = threadIdx.x; n < 64; n += blockDim.x) {
+        tab.c[n] = ph_cos(n);
+        tab.s[n] = ph_cos(n + 48);
+    }
+}
+
+MS_D void phase(const PhaseTable &tab, double x, double &cs, double &sn)
+{
+    if (__builtin_expect(!(fabs(x) < 1e5), 0)) {
+        sincos(x, &sn, &cs);
         return;
     }
-    double aw[4] = {0, 0, 0, 0}, ath[4] = {0, 0, 0, 0}, as[4] = {0, 0, 0, 0};
-    for (int j = lane; j < N; j += 64) {
-        double v0 = 0, v1 = 0, v2 = 0, v3 = 0, d0 = 0, d1 = 0, d2 = 0, d3 = 0;
-        for (int k = P; k >= 0; --k) {
-            const d4 c = load_d4(spec + ((int64_t)k * N + j) * 4);
-            d0 = d0 * sl + v0; v0 = v0 * sl + c.x;
-            d1 = d1 * sl + v1; v1 = v1 * sl + c.y;
-            d2 = d2 * sl + v2; v2 = v2 * sl + c.z;
-            d3 = d3 * sl + v3; v3 = v3 * sl + c.w;
-        }
-        const double v[4] = {v0, v1, v2, v3}, dv[4] = {d0, d1, d2, d3};
-        const bool nyq = 2 * j == N;
-        const double js = 2 * j > N ? (double)(j - N) : (double)j;
-        double sn, cs;
-        sincos(nyq ? 0.5 * (double)N * t : js * t, &sn, &cs);
-        if (nyq) {
-            // the cosine mode cos(N theta / 2): real factor on both parts.  It
-            // adds nothing to the theta derivative: the derivative is taken
-            // at the samples (coefficient j times i j, whose real part is 0
-            // at j = N/2) and then interpolated.
+    const double n = rint(x * PH_INV);
+    const double r = fma(-n, PH_P2, fma(-n, PH_P1, x)), z = r * r;
+    const int k = (int)n & 63;
+    const double2 c = tab.c[k], s = tab.s[k];
+    const double sr = fma(r * z, fma(z, fma(z, -1.0 / 5040.0, 1.0 / 120.0), -1.0 / 6.0), r);
+    const double cr = z * fma(z, fma(z, fma(z, 1.0 / 40320.0, -1.0 / 720.0), 1.0 / 24.0), -0.5);
+    cs = c.x + fma(-s.x, sr, fma(c.x, cr, c.y));
+    sn = s.x + fma(c.x, sr, fma(s.x, cr, s.y));
+}
+
+struct FtArgs {
+    const double *spec, *theta, *s;
+    double *w, *dth, *ds;
+    int64_t nq;
+    double th_off, s_scale;
+    int N, P;
+};
+
+MS_D double uni(double x)
+{
+    const uint64_t b = (uint64_t)__double_as_longlong(x);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
+    return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
+}
+
+// v[0 .. 2 N) summed over the lanes' bits OFF ... LAST, halving: value j ends
+// up in the lanes whose top bits of these are j.
+template <int N, int OFF, int LAST>
+MS_D double lane_sums(const double *v)
+{
+    const bool hi = (threadIdx.x & OFF) != 0;
+    double h[N];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                aw[i] += v[i] * cs;
-                as[i] += dv[i] * cs;
+    for (int j = 0; j < N; ++j) {
+        const double mine = hi ? v[j + N] : v[j], send = hi ? v[j] : v[j + N];
+        h[j] = mine + __shfl_xor(send, OFF);
+    }
+    if constexpr (N > 1) {
+        return lane_sums<N / 2, OFF / 2, LAST>(h);
+    } else {
+#pragma unroll
+        for (int o = OFF / 2; o >= LAST; o /= 2) h[0] += __shfl_xor(h[0], o);
+        return h[0];
+    }
+}
+
+// QT queries per block by Horner's rule.  A lane takes one of the two complex
+// pairs of every 32nd frequency and all QT queries, so that a coefficient is
+// loaded once for QT of them; the next FT_R coefficients are in flight.  The
+// block's waves take steps of 32 frequencies in turn.  A table of 2048
+// frequencies to order 25 is 1.7 MB, so what bounds it is the L2's
+// 14 TB/s for many queries and the loads' latency for few: 4 queries per block
+// take 33 us for up to 700 queries and 36 for 1024, one 21 for up to 128 and
+// 38 for 300; a wave per query took 105 for up to 1024.  8 queries spill.
+template <int QT>
+struct FtShared {
+    double sum[FT_MAX_WAVES<QT>][3][4 * QT];
+    PhaseTable ph;
+};
+
+template <int QT>
+MS_D void ft_eval(FtShared<QT> &s_sum, int64_t q0, const FtArgs &g)
+{
+    phase_table(s_sum.ph);
+    __syncthreads();
+    const double *spec = g.spec, *theta = g.theta, *s = g.s;
+    const int N = g.N, P = g.P;
+    const int64_t nq = g.nq;
+    const double th_off = g.th_off, s_scale = g.s_scale;
+    const int lane = threadIdx.x % 64, wv = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), n_waves = blockDim.x / 64, p = lane & 1;
+    double t[QT], sl[QT];
+#pragma unroll
+    for (int q = 0; q < QT; ++q) {
+        const int64_t k = q0 + q < nq ? q0 + q : nq - 1;
+        t[q] = uni(theta[k] - th_off);
+        sl[q] = uni(s[k] * s_scale);
+    }
+    const int steps = (N + FT_STEP - 1) / FT_STEP;
+    const int lowest = -((N - 1) / 2);
+    double aw[2 * QT] = {}, ath[2 * QT] = {}, as[2 * QT] = {};
+    constexpr int R = FT_R<QT>;
+    double2 x[R];                   // coefficients in flight
+    const double *top = spec + 4 * (int64_t)N * P;
+    const int64_t row = 4 * (int64_t)N;
+    const double *ahead = top;      // row of the next coefficients to load, k_ahead rows below the top
+    int k_ahead = 0;
+    auto offset = [&](int m) {
+        const int idx = FT_STEP * m + (lane >> 1), js = lowest + idx;
+        return (uint32_t)(4 * (idx >= N ? 0 : js < 0 ? js + N : js) + 2 * p);
+    };
+    auto get = [&](uint32_t at) {
+        const double2 c = *reinterpret_cast<const double2 *>(ahead + at);
+        if (k_ahead < P) ahead -= row;      // (past the last row: once more, unused)
+        ++k_ahead;
+        return c;
+    };
+    auto fetch = [&](int m) {
+        const uint32_t at = offset(m);
+        ahead = top;
+        k_ahead = 0;
+#pragma unroll
+        for (int u = 0; u < R; ++u) x[u] = get(at);
+    };
+    auto step = [&](int m, auto last) {
+        const uint32_t at = offset(m);
+        const int idx = FT_STEP * m + (lane >> 1), js = lowest + idx;
+        // the series in s at this frequency, value and derivative together
+        double vr[QT] = {}, vi[QT] = {}, dr[QT] = {}, di[QT] = {};
+        auto horner = [&](int u) {
+#pragma unroll
+            for (int q = 0; q < QT; ++q) {
+                dr[q] = fma(dr[q], sl[q], vr[q]);
+                di[q] = fma(di[q], sl[q], vi[q]);
+                vr[q] = fma(vr[q], sl[q], x[u].x);
+                vi[q] = fma(vi[q], sl[q], x[u].y);
             }
+        };
+        int k = 0;
+        for (; k + R <= P + 1; k += R)
+#pragma unroll
+            for (int u = 0; u < R; ++u) {
+                horner(u);
+                x[u] = get(at);
+            }
+#pragma unroll
+        for (int u = 0; u < R - 1; ++u)
+            if (k + u <= P) horner(u);
+        if (m + n_waves < steps) fetch(m + n_waves);
+        if (last && idx >= N)
+#pragma unroll
+            for (int q = 0; q < QT; ++q) vr[q] = vi[q] = dr[q] = di[q] = 0.0;
+        // The mode N / 2 is the cosine: a real factor on both parts.  It adds
+        // nothing to the theta derivative: the derivative is taken at the
+        // samples (coefficient j times i j, whose real part is 0 at
+        // j = N/2) and then interpolated.
+        const bool nyq = last && 2 * js == N;
+        const double jd = nyq ? 0.0 : (double)js;
+        // the phases: the lanes of the two pairs take half of them each
+        double cs[QT], sn[QT];
+        if constexpr (QT == 1) {
+            phase(s_sum.ph, (double)js * t[0], cs[0], sn[0]);
         } else {
 #pragma unroll
-            for (int p = 0; p < 2; ++p) {
-                const double re = v[2 * p] * cs - v[2 * p + 1] * sn;
-                const double im = v[2 * p] * sn + v[2 * p + 1] * cs;
-                aw[2 * p] += re;
-                aw[2 * p + 1] += im;
-                ath[2 * p] += -js * im;      // i js (re + i im)
-                ath[2 * p + 1] += js * re;
-                as[2 * p] += dv[2 * p] * cs - dv[2 * p + 1] * sn;
-                as[2 * p + 1] += dv[2 * p] * sn + dv[2 * p + 1] * cs;
+            for (int q = 0; q < QT; q += 2) {
+                double c, e;
+                phase(s_sum.ph, (double)js * (p ? t[q + 1] : t[q]), c, e);
+                const double oc = __shfl_xor(c, 1), oe = __shfl_xor(e, 1);
+                cs[q] = p ? oc : c;
+                sn[q] = p ? oe : e;
+                cs[q + 1] = p ? c : oc;
+                sn[q + 1] = p ? e : oe;
             }
         }
-    }
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            aw[i] += __shfl_xor(aw[i], off);
-            ath[i] += __shfl_xor(ath[i], off);
-            as[i] += __shfl_xor(as[i], off);
+        for (int q = 0; q < QT; ++q) {
+            const double f = cs[q], e = nyq ? 0.0 : sn[q];
+            const double re = fma(vr[q], f, -(vi[q] * e)), im = fma(vr[q], e, vi[q] * f);
+            aw[2 * q] += re;
+            aw[2 * q + 1] += im;
+            ath[2 * q] = fma(-jd, im, ath[2 * q]);       // i js (re + i im)
+            ath[2 * q + 1] = fma(jd, re, ath[2 * q + 1]);
+            as[2 * q] = fma(dr[q], f, fma(-di[q], e, as[2 * q]));
+            as[2 * q + 1] = fma(dr[q], e, fma(di[q], f, as[2 * q + 1]));
         }
-    // every lane holds the totals after the butterfly reduction
-    if (lane == 0) {
+    };
+    if (wv < steps) fetch(wv);
+    for (int m = wv; m < steps; m += n_waves) {
+        if (m < steps - 1) step(m, std::false_type{});
+        else step(m, std::true_type{});
+    }
+    const double sums[3] = {lane_sums<QT, 32, 2>(aw), lane_sums<QT, 32, 2>(ath), lane_sums<QT, 32, 2>(as)};
+    constexpr int SHARE = 64 / (2 * QT);
+    if (lane % SHARE < 2) {
+        const int j = lane / SHARE;      // 2 query + part
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            w[4 * q + i] = aw[i];
-            dth[4 * q + i] = ath[i];
-            ds[4 * q + i] = as[i] * s_scale;   // d/ds of W(theta, lambda^-m s)
+        for (int i = 0; i < 3; ++i) s_sum.sum[wv][i][4 * (j >> 1) + 2 * p + (j & 1)] = sums[i];
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < 12 * QT; i += blockDim.x) {
+        const int kind = i / (4 * QT), e = i % (4 * QT);
+        const int64_t q = q0 + e / 4;
+        if (q >= nq) continue;
+        double v = s_sum.sum[0][kind][e];
+        for (int k = 1; k < n_waves; ++k) v += s_sum.sum[k][kind][e];
+        if (kind == 2) v *= s_scale;     // d/ds of W(theta, lambda^-m s)
+        if (!isfinite(theta[q] - th_off) || !isfinite(s[q] * s_scale)) v = NAN;
+        (kind == 0 ? g.w : kind == 1 ? g.dth : g.ds)[4 * q + e % 4] = v;
+    }
+}
+
+template <int QT>
+__global__ void __launch_bounds__(64 * FT_MAX_WAVES<QT>) k_ft_eval(FtArgs g)
+{
+    __shared__ FtShared<QT> s_sum;
+    ft_eval<QT>(s_sum, (int64_t)blockIdx.x * QT, g);
+}
+
+typedef double v4d __attribute__((ext_vector_type(4)));
+
+constexpr int FT_TILE = 16;
+constexpr int FT_TILE_WAVES = 8;
+
+// 16 queries per block on the matrix cores: V(j) and its derivative are the
+// products of the queries' powers s^k and k s^(k-1) (16 rows, kept in
+// registers, to order 4 KA - 1) with the coefficients at 16 frequencies.  A
+// wave takes one complex pair and every fourth step of 16 frequencies; a lane
+// then holds four queries at one frequency and adds their terms.  The powers
+// are rounded once and summed from the highest down, so that the result is as
+// close as Horner's (the error against longer arithmetic is the same, and
+// half of it is the sum over j).
+//
+// FP64 matrix instructions run at the rate of the vector ones here, but their
+// operands are the coefficients themselves, loaded once for 16 queries, and
+// the phases run beside them.  4096 queries of 2048 frequencies to order 25:
+// 84 to 94 us from 225 with a wave per query, 133 with four queries a block (the
+// L2's rate) and 53 at the card's matrix rate.
+template <int KA>
+__global__ void __launch_bounds__(64 * FT_TILE_WAVES) k_ft_tile(FtArgs g)
+{
+    __shared__ double s_sum[FT_TILE_WAVES / 2][3][4 * FT_TILE];
+    __shared__ FtShared<1> s_one;
+    __shared__ uint32_t s_bad;
+    const int N = g.N, P = g.P, lane = threadIdx.x % 64, quad = lane >> 4;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), p = wv & 1, part = wv >> 1;
+    constexpr int PARTS = FT_TILE_WAVES / 2;
+    const int64_t q0 = (int64_t)blockIdx.x * FT_TILE;
+    auto query = [&](int q) { return q0 + q < g.nq ? q0 + q : g.nq - 1; };
+    if (threadIdx.x == 0) s_bad = 0;
+    phase_table(s_one.ph);
+    __syncthreads();
+    // powers s^k (rows: queries) and k s^(k - 1), k = 4 a + 3 - quad; rounded once
+    double pv[KA], pd[KA];
+    {
+        const double sl = g.s[query(lane & 15)] * g.s_scale;
+        double hi = 1.0, lo = 0.0, prev = 0.0;
+#pragma unroll
+        for (int k = 0; k < 4 * KA; ++k) {
+            if (3 - (k & 3) == quad) {
+                pv[k >> 2] = k <= P ? hi : 0.0;
+                pd[k >> 2] = k <= P ? (double)k * prev : 0.0;
+            }
+            prev = hi;
+            const double x = hi * sl, e = fma(lo, sl, fma(hi, sl, -x));
+            hi = x + e;
+            lo = e - (hi - x);
         }
     }
+    const int steps = (N + 15) / 16, lowest = -((N - 1) / 2);
+    double t[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) t[r] = g.theta[query(quad + 4 * r)] - g.th_off;
+    double aw[8] = {}, ath[8] = {}, as[8] = {};
+    double2 x[KA];
+    auto fetch = [&](int m) {
+        const int idx = 16 * m + (lane & 15), js = lowest + idx;
+        const uint32_t at = (uint32_t)(4 * (idx >= N ? 0 : js < 0 ? js + N : js) + 2 * p);
+#pragma unroll
+        for (int a = 0; a < KA; ++a) {
+            const int k = 4 * a + 3 - quad;
+            x[a] = *reinterpret_cast<const double2 *>(g.spec + 4 * (int64_t)N * (k <= P ? k : P) + at);
+        }
+    };
+    if (part < steps) fetch(part);
+    for (int m = part; m < steps; m += PARTS) {
+        v4d vr = {}, vi = {}, dr = {}, di = {};
+#pragma unroll
+        for (int a = KA - 1; a >= 0; --a) {
+            vr = __builtin_amdgcn_mfma_f64_16x16x4f64(pv[a], x[a].x, vr, 0, 0, 0);
+            vi = __builtin_amdgcn_mfma_f64_16x16x4f64(pv[a], x[a].y, vi, 0, 0, 0);
+            dr = __builtin_amdgcn_mfma_f64_16x16x4f64(pd[a], x[a].x, dr, 0, 0, 0);
+            di = __builtin_amdgcn_mfma_f64_16x16x4f64(pd[a], x[a].y, di, 0, 0, 0);
+        }
+        if (m + PARTS < steps) fetch(m + PARTS);
+        const int idx = 16 * m + (lane & 15), js = lowest + idx;
+        if (idx >= N) vr = vi = dr = di = v4d{};
+        const bool nyq = 2 * js == N;
+        const double jd = nyq ? 0.0 : (double)js;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            double f, e;
+            phase(s_one.ph, (double)js * t[r], f, e);
+            if (nyq) e = 0.0;
+            const double re = fma(vr[r], f, -(vi[r] * e)), im = fma(vr[r], e, vi[r] * f);
+            aw[2 * r] += re;
+            aw[2 * r + 1] += im;
+            ath[2 * r] = fma(-jd, im, ath[2 * r]);
+            ath[2 * r + 1] = fma(jd, re, ath[2 * r + 1]);
+            as[2 * r] = fma(dr[r], f, fma(-di[r], e, as[2 * r]));
+            as[2 * r + 1] = fma(dr[r], e, fma(di[r], f, as[2 * r + 1]));
+        }
+    }
+    const double sums[3] = {lane_sums<4, 8, 1>(aw), lane_sums<4, 8, 1>(ath), lane_sums<4, 8, 1>(as)};
+    if ((lane & 1) == 0) {
+        const int j = (lane & 15) >> 1, q = quad + 4 * (j >> 1);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) s_sum[part][i][4 * q + 2 * p + (j & 1)] = sums[i];
+    }
+    __syncthreads();
+    if (threadIdx.x < 12 * FT_TILE) {
+        const int kind = threadIdx.x / (4 * FT_TILE), e = threadIdx.x % (4 * FT_TILE);
+        const int64_t q = q0 + e / 4;
+        if (q < g.nq) {
+            double v = 0.0;
+#pragma unroll
+            for (int k = 0; k < PARTS; ++k) v += s_sum[k][kind][e];
+            if (kind == 2) v *= g.s_scale;     // d/ds of W(theta, lambda^-m s)
+            const bool fin = isfinite(g.theta[q] - g.th_off) && isfinite(g.s[q] * g.s_scale);
+            if (fin && !isfinite(v)) atomicOr(&s_bad, 1u << (e / 4));
+            (kind == 0 ? g.w : kind == 1 ? g.dth : g.ds)[4 * q + e % 4] = fin ? v : NAN;
+        }
+    }
+    __syncthreads();
+    // Horner's rule gives a number in cases where 0 times a power or a
+    // coefficient that is none does not
+    for (uint32_t bad = s_bad; bad; bad &= bad - 1) {
+        ft_eval<1>(s_one, q0 + __builtin_ctz(bad), g);
+        __syncthreads();
+    }
+}
+
+template <int QT>
+void launch_ft_eval(const FtArgs &g, hipStream_t st)
+{
+    const int64_t blocks = ceil_div(g.nq, (int64_t)QT), steps = ceil_div((int64_t)g.N, (int64_t)FT_STEP);
+    // two waves per SIMD over the card, each with a step at least
+    int64_t waves = ceil_div((int64_t)2048, blocks);
+    waves = std::max<int64_t>(waves, 4);
+    waves = std::min<int64_t>(std::min<int64_t>(waves, FT_MAX_WAVES<QT>), steps);
+    hipLaunchKernelGGL(k_ft_eval<QT>, dim3((unsigned)blocks), dim3((unsigned)(64 * waves)), 0, st, g);
+}
+
+template <int KA>
+void launch_ft_tile(const FtArgs &g, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_ft_tile<KA>, dim3((unsigned)ceil_div(g.nq, (int64_t)FT_TILE)), dim3(64 * FT_TILE_WAVES), 0, st,
+                       g);
 }
 
 // dth <- M dth, ds <- M ds per query (M row-major 4 x 4).
@@ -321,13 +654,19 @@ extern "C" int ft_partials(const double *spec_dev, int32_t n_theta, int32_t orde
     if (m != 0 && !(lambda > 0.0 && isfinite(lambda) && isfinite(omega)))
         return fail(MS_E_ARG, "ft_partials: need a finite omega and lambda > 0");
     if (n_query == 0) return MS_OK;
-    const int64_t blocks = ceil_div(n_query, FT_WAVES);
-    if (blocks > 0x7fffffff) return fail(MS_E_ARG, "ft_partials: too many queries for one launch");
+    if (ceil_div(n_query, 4) > 0x7fffffff) return fail(MS_E_ARG, "ft_partials: too many queries for one launch");
     hipStream_t st = (hipStream_t)stream;
     const double th_off = (double)m * omega;
     const double s_scale = m == 0 ? 1.0 : pow(lambda, -(double)m);
-    hipLaunchKernelGGL(k_ft_eval, dim3((unsigned)blocks), dim3(64 * FT_WAVES), 0, st, spec_dev, (int)n_theta,
-                       (int)order, theta_dev, s_dev, n_query, th_off, s_scale, w_dev, dth_dev, ds_dev);
+    const FtArgs g{spec_dev, theta_dev, s_dev, w_dev, dth_dev, ds_dev, n_query, th_off, s_scale, (int)n_theta, (int)order};
+    // A block of 16 queries takes as long for 1 as for 4096 (a CU each), and
+    // its powers are held in registers: 2048 queries to order 25: 77 us against
+    // 68 by fours, 3000: 79 against 103.  A block of four against single
+    // queries: 512 queries 33 against 38 us, 128: 32 against 21.
+    const auto eval = n_query < 256 ? launch_ft_eval<1>
+                      : n_query < 2304 || order > 27 ? launch_ft_eval<4>
+                      : order <= 7 ? launch_ft_tile<2> : order <= 15 ? launch_ft_tile<4> : launch_ft_tile<7>;
+    eval(g, st);
     MS_HIP(hipGetLastError());
     if (m == 0) return MS_OK;
     int rc = pertbp_map_stm(w_dev, w_dev, stm_dev, n_query, map, 0, stream);
