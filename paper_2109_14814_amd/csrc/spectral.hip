@@ -8,20 +8,30 @@
 // are the signed ones; for even n_theta the coefficient at n_theta / 2 acts
 // as the real mode cos(n_theta theta / 2), so real rows stay real.
 //
-// theta_shift: one workgroup per row.  The two real pairs of a vertex are
-// packed as complex sequences z0 = x + i y and z1 = px + i py (the spectral
-// multiplier is Hermitian, so it acts on both parts independently) and go
-// through a Stockham FFT of radix 8 (a last pass of radix 4 or 2 for the
-// remaining factor) that keeps both sequences in LDS, in place: each pass
-// reads its butterflies into registers, waits, then writes them back.  The
-// LDS index is padded by one slot per 8 so that the strided writes of the
-// first passes spread over the banks.  The first forward pass reads the row
-// straight from global memory and the last inverse pass writes it back
-// (scaled by 1 / N); the inverse runs the radices in reverse order, so the
-// last forward pass, the multiplier (j k)^order e^{j k rho} and the first
-// inverse pass work on the same registers with no LDS round trip between
-// them.  The twiddle factors e^{-2 pi i m / N} come from a table of N values
-// made once per (device, N) on the host and read through the caches.
+// theta_shift: eight samples per thread, so a workgroup takes one row of 2048
+// or several shorter ones.  The two real pairs of a vertex are packed as
+// complex sequences z0 = x + i y and z1 = px + i py (the spectral multiplier is
+// Hermitian, so it acts on both parts independently) and go through a Stockham
+// FFT of radix 8 (a last pass of radix 4 or 2 for the remaining factor) in
+// registers; between passes the sequences change places through LDS, one after
+// the other in the same 36 KB, so that three workgroups fit a CU and one's
+// loads and stores run beside another's butterflies.  The LDS index is padded
+// by one slot per 8 so that the strided writes of the first passes spread over
+// the banks.  The first forward pass reads the row straight from global memory
+// and the last inverse pass writes it back (scaled by 1 / N); the inverse runs
+// the radices in reverse order, so the last forward pass, the multiplier
+// (j k)^order e^{j k rho} and the first inverse pass work on the same registers
+// with no exchange between them.  The twiddle factors come from a table made
+// once per (device, N) on the host and read through the caches, each pass's
+// own in the order in which its lanes read them; the multiplier's phases from
+// phase.hpp.
+//
+// 4096 rows of 2048, 268 MB read and as many written, which a copy does in
+// 109 us: 140 us from 185 with both sequences in 72 KB, a sine and cosine per
+// coefficient and one table of N factors gathered at strides (which alone
+// cost 25); with four workgroups on a CU the 128 registers spill: 167.  The
+// spectrum alone takes 108, from 130.  4096 rows of 64, 32 rows to a
+// workgroup: 9 us from 43.
 //
 // theta_interp: the barycentric form of the trigonometric interpolant (no
 // transform): with theta = theta_i0 + delta,
@@ -38,30 +48,33 @@
 #include <utility>
 #include <vector>
 
-#include "ms_internal.hpp"
+#include "phase.hpp"
 
 namespace ms {
 namespace {
 
 constexpr int SP_THREADS = 256;
-constexpr int SP_MAX_LOG2 = 11;   // n_theta <= 2048: 2 x 36 KiB of LDS per row
+constexpr int SP_MAX_LOG2 = 11;   // n_theta <= 2048
 constexpr double SP_PI = 3.141592653589793238462643383279502884;
-#ifndef SP_RADIX
-#define SP_RADIX 8                // largest radix of a pass (4 or 8)
-#endif
-#ifndef SP_PAD_SHIFT
-#define SP_PAD_SHIFT 3            // one pad slot per 2^SP_PAD_SHIFT LDS elements (0: none)
-#endif
+constexpr int SP_RADIX = 8;               // largest radix of a pass
 
 // LDS slot of element i: padded so that the strided writes of the first
 // passes (stride R elements) spread over the banks.
-MS_D int pslot(int i) { return SP_PAD_SHIFT ? i + (i >> SP_PAD_SHIFT) : i; }
+MS_D int pslot(int i) { return i + (i >> 3); }
 template <int N>
-constexpr int padded_size() { return SP_PAD_SHIFT ? N + (N >> SP_PAD_SHIFT) : N; }
+constexpr int padded_size() { return N + (N >> 3); }
+
+// Threads of a row, rows of a workgroup and samples of a thread.
+template <int N>
+constexpr int row_threads() { return N >= 8 ? N / 8 : 1; }
+template <int N>
+constexpr int block_rows() { return SP_THREADS / row_threads<N>(); }
+template <int N>
+constexpr int per_thread() { return N >= 8 ? 8 : N; }
 
 MS_D double2 cmul(double2 a, double2 b)
 {
-    return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
+    return make_double2(fma(a.x, b.x, -(a.y * b.y)), fma(a.x, b.y, a.y * b.x));
 }
 
 MS_D double2 cadd(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
@@ -127,7 +140,7 @@ MS_D void small_dft(double2 *v)
 // forward pass leaves in each thread's registers.
 template <int LOGN>
 struct Plan {
-    static constexpr int LR = SP_RADIX == 8 ? 3 : 2;
+    static constexpr int LR = 3;
     static constexpr int FULL = LOGN / LR;
     static constexpr int REST = LOGN % LR;
     static constexpr int NP = FULL + (REST ? 1 : 0);
@@ -136,179 +149,205 @@ struct Plan {
     static constexpr int ns_fwd(int p) { return p == 0 ? 1 : ns_fwd(p - 1) * radix(p - 1); }
     static constexpr int radix_inv(int p) { return radix(NP - 1 - p); }
     static constexpr int ns_inv(int p) { return p == 0 ? 1 : ns_inv(p - 1) * radix_inv(p - 1); }
+    // where a pass's twiddle factors begin in the table: (radix - 1) Ns of
+    // each pass but the first, the forward ones before the inverse ones
+    static constexpr int tw_fwd(int p) { return p <= 1 ? 0 : tw_fwd(p - 1) + (radix(p - 1) - 1) * ns_fwd(p - 1); }
+    static constexpr int tw_inv(int p) { return p <= 1 ? tw_fwd(NP) : tw_inv(p - 1) + (radix_inv(p - 1) - 1) * ns_inv(p - 1); }
 };
 
-// Where a pass takes its inputs from and puts its outputs.
-enum { FROM_LDS = 0, FROM_GLOBAL = 1 };
+// The registers of a thread: both sequences.  Pass of radix R: butterfly q of
+// the thread, j = t + q row_threads, holds element r of it in v[s][q R + r].
+template <int N>
+using Regs = double2[2][per_thread<N>()];
 
-// Stockham pass of radix R, sub-transform length Ns, over both sequences.
-// Butterfly j takes element j + r N/R (r = 0..R-1), twiddles it by
-// e^{-+2 pi i r (j mod Ns) / (Ns R)} (entry r (j mod Ns) N / (Ns R) of the
-// table, conjugated for the inverse), transforms, and gives element
-// (j / Ns) Ns R + (j mod Ns) + r Ns.  Inputs come from LDS or, for the first
-// forward pass, from the row in global memory; outputs go to LDS or, for the
-// last inverse pass, to global memory scaled by 1/N.  With MID the pass is
-// the last forward pass fused with the spectral multiplier and the first
-// inverse pass (radix R, Ns = 1).  One thread carries both sequences of its
-// butterflies, so vertices move between global memory and registers whole.
-template <int N, int R, int Ns, bool INV, int SRC, bool TO_GLOBAL, bool MID>
-MS_D void pass(double2 (*z)[padded_size<N>()], const double2 *__restrict__ tw, const double *src, double *dst,
-               double rho, int order)
+// Stockham pass of radix R, sub-transform length Ns, over both sequences in
+// registers.  Butterfly j holds element j + r N/R (r = 0..R-1), twiddles it by
+// e^{-+2 pi i r (j mod Ns) / (Ns R)} (entry (r - 1) Ns + (j mod Ns) of the pass's
+// table, conjugated for the inverse) and transforms.
+template <int N, int R, int Ns, bool INV>
+MS_D void butterflies(Regs<N> &v, int t, const double2 *__restrict__ tw)
 {
-    constexpr int NB = N / R;
-    constexpr int PER = (NB + SP_THREADS - 1) / SP_THREADS;
-    double2 v[2][PER][R];
+    constexpr int T = row_threads<N>();
 #pragma unroll
-    for (int q = 0; q < PER; ++q) {
-        const int j = threadIdx.x + q * SP_THREADS;
-        if (NB % SP_THREADS == 0 || j < NB) {
+    for (int q = 0; q < per_thread<N>() / R; ++q) {
+        double2 w[R];
+        if constexpr (Ns > 1) {
+            const int k = (t + q * T) % Ns;
 #pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const int e = j + r * NB;
-                if constexpr (SRC == FROM_GLOBAL) {
-                    d4 w = load_d4(src + 4 * e);
-                    v[0][q][r] = make_double2(w.x, w.y);
-                    v[1][q][r] = make_double2(w.z, w.w);
-                } else {
-                    v[0][q][r] = z[0][pslot(e)];
-                    v[1][q][r] = z[1][pslot(e)];
-                }
-            }
-            const int k = j % Ns;
-            if (k != 0) {
-                constexpr int stride = N / (Ns * R);
-#pragma unroll
-                for (int r = 1; r < R; ++r) {
-                    double2 w = tw[r * k * stride];
-                    if (INV) w.y = -w.y;
-#pragma unroll
-                    for (int s = 0; s < 2; ++s) v[s][q][r] = cmul(v[s][q][r], w);
-                }
-            }
-#pragma unroll
-            for (int s = 0; s < 2; ++s) small_dft<R, INV>(v[s][q]);
-            if constexpr (MID) {
-                // here Ns = N / R, so the outputs are the coefficients k = j + r N/R
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    const int kk = j + r * NB;
-                    double2 m;
-                    if (2 * kk == N) {
-                        // the cosine mode: Re[(j N/2)^order e^{j (N/2) rho}]
-                        const double h = 0.5 * (double)N;
-                        double sn, cs;
-                        sincos(h * rho, &sn, &cs);
-                        m = make_double2(order == 0 ? cs : order == 1 ? -h * sn : -h * h * cs, 0.0);
-                    } else {
-                        const double ks = 2 * kk > N ? (double)(kk - N) : (double)kk;
-                        double sn, cs;
-                        sincos(ks * rho, &sn, &cs);
-                        m = make_double2(cs, sn);
-                        if (order == 1) m = make_double2(-ks * sn, ks * cs);
-                        else if (order == 2) m = make_double2(-ks * ks * cs, -ks * ks * sn);
-                    }
-                    v[0][q][r] = cmul(v[0][q][r], m);
-                    v[1][q][r] = cmul(v[1][q][r], m);
-                }
-                // first inverse pass: the same butterfly j, Ns = 1, no twiddles
-#pragma unroll
-                for (int s = 0; s < 2; ++s) small_dft<R, true>(v[s][q]);
+            for (int r = 1; r < R; ++r) {
+                w[r] = tw[(r - 1) * Ns + k];
+                if (INV) w[r].y = -w[r].y;
             }
         }
-    }
-    // outputs of the fused pass follow the first inverse pass (Ns = 1)
-    constexpr int ns_out = MID ? 1 : Ns;
-    if constexpr (SRC == FROM_LDS && !TO_GLOBAL) __syncthreads();   // all reads before any write
 #pragma unroll
-    for (int q = 0; q < PER; ++q) {
-        const int j = threadIdx.x + q * SP_THREADS;
-        if (NB % SP_THREADS == 0 || j < NB) {
-            const int base = (j / ns_out) * ns_out * R + j % ns_out;
+        for (int s = 0; s < 2; ++s) {
+            if constexpr (Ns > 1) {
 #pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const int e = base + r * ns_out;
-                if constexpr (TO_GLOBAL) {
-                    const double inv = 1.0 / (double)N;
-                    double2 *o = reinterpret_cast<double2 *>(dst + 4 * e);
-                    o[0] = make_double2(v[0][q][r].x * inv, v[0][q][r].y * inv);
-                    o[1] = make_double2(v[1][q][r].x * inv, v[1][q][r].y * inv);
-                } else {
-                    z[0][pslot(e)] = v[0][q][r];
-                    z[1][pslot(e)] = v[1][q][r];
-                }
+                for (int r = 1; r < R; ++r) v[s][q * R + r] = cmul(v[s][q * R + r], w[r]);
             }
+            small_dft<R, INV>(v[s] + q * R);
+            __builtin_amdgcn_sched_barrier(0);      // one sequence's butterfly at a time in the registers
         }
     }
-    if constexpr (!TO_GLOBAL) __syncthreads();
 }
 
+// Element that a pass of radix R and length Ns leaves in register i, where
+// butterfly j's are (j / Ns) Ns R + (j mod Ns) + r Ns.
+template <int N, int R, int Ns>
+MS_D int element(int t, int i)
+{
+    const int j = t + i / R * row_threads<N>();
+    return (j / Ns) * Ns * R + j % Ns + i % R * Ns;
+}
+
+// From the places of a pass (R, Ns) to the inputs of the next, of radix R2.
+template <int N, int R, int Ns, int R2>
+MS_D void exchange(Regs<N> &v, int t, double2 *z)
+{
+    constexpr int E = per_thread<N>(), T = row_threads<N>();
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        if (s) __syncthreads();
+#pragma unroll
+        for (int i = 0; i < E; ++i) z[pslot(element<N, R, Ns>(t, i))] = v[s][i];
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < E; ++i) v[s][i] = z[pslot(t + i / R2 * T + i % R2 * (N / R2))];
+    }
+}
+
+// The multiplier at the coefficients that the last forward pass (radix R,
+// Ns = N / R: coefficient j + r N/R) leaves in the registers.  z: the row's
+// LDS, where the thread's own inputs of that pass are free.
+template <int N, int R>
+MS_D void multiply(Regs<N> &v, int t, const PhaseTable &ph, double rho, int order, double2 *z)
+{
+    constexpr int E = per_thread<N>(), T = row_threads<N>();
+    auto coef = [&](int i) { return t + i / R * T + i % R * (N / R); };
+    auto freq = [&](int k) { return 2 * k > N ? (double)(k - N) : (double)k; };
+    const bool near = fabs(rho) * (0.5 * N) < PH_MAX;
+    if (!near) {
+#pragma nounroll
+        for (int i = 0; i < E; ++i) {
+            double sn, cs;
+            sincos(freq(coef(i)) * rho, &sn, &cs);
+            z[pslot(coef(i))] = make_double2(cs, sn);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < E; ++i) {
+        const int k = coef(i);
+        const double ks = freq(k);
+        double2 m;
+        if (near) phase_near(ph, ks * rho, m.x, m.y);
+        else m = z[pslot(k)];
+        if (order == 1) m = make_double2(-ks * m.y, ks * m.x);
+        else if (order == 2) m = make_double2(-ks * ks * m.x, -ks * ks * m.y);
+        // the cosine mode: Re[(j N/2)^order e^{j (N/2) rho}]
+        if (2 * k == N) m.y = 0.0;
+        v[0][i] = cmul(v[0][i], m);
+        v[1][i] = cmul(v[1][i], m);
+        __builtin_amdgcn_sched_barrier(0);      // (eight phases at a time do not fit the registers)
+    }
+}
+
+// Forward passes P.. up to the last.
 template <int LOGN, int P>
-MS_D void forward_passes(double2 (*z)[padded_size<1 << LOGN>()], const double2 *tw, const double *src)
+MS_D void forward_passes(Regs<1 << LOGN> &v, int t, const double2 *tw, double2 *z)
 {
     using PL = Plan<LOGN>;
+    constexpr int N = 1 << LOGN, R = PL::radix(P), NS = PL::ns_fwd(P), TW = PL::tw_fwd(P);
+    butterflies<N, R, NS, false>(v, t, tw + TW);
     if constexpr (P < PL::NP - 1) {
-        constexpr int N = 1 << LOGN;
-        constexpr int NS = PL::ns_fwd(P);
-        pass<N, PL::radix(P), NS, false, P == 0 ? FROM_GLOBAL : FROM_LDS, false, false>(z, tw, src, nullptr, 0.0, 0);
-        forward_passes<LOGN, P + 1>(z, tw, src);
+        if constexpr (P > 0) __syncthreads();
+        exchange<N, R, NS, PL::radix(P + 1)>(v, t, z);
+        forward_passes<LOGN, P + 1>(v, t, tw, z);
     }
 }
 
+// Inverse passes P.. up to the last (the inputs in place).
 template <int LOGN, int P>
-MS_D void inverse_passes(double2 (*z)[padded_size<1 << LOGN>()], const double2 *tw, double *dst)
+MS_D void inverse_passes(Regs<1 << LOGN> &v, int t, const double2 *tw, double2 *z)
 {
     using PL = Plan<LOGN>;
-    if constexpr (P < PL::NP) {
-        constexpr int N = 1 << LOGN;
-        constexpr int NS = PL::ns_inv(P);
-        pass<N, PL::radix_inv(P), NS, true, FROM_LDS, P == PL::NP - 1, false>(z, tw, nullptr, dst, 0.0, 0);
-        inverse_passes<LOGN, P + 1>(z, tw, dst);
+    constexpr int N = 1 << LOGN, R = PL::radix_inv(P), NS = PL::ns_inv(P), TW = PL::tw_inv(P);
+    butterflies<N, R, NS, true>(v, t, tw + TW);
+    if constexpr (P < PL::NP - 1) {
+        __syncthreads();
+        exchange<N, R, NS, PL::radix_inv(P + 1)>(v, t, z);
+        inverse_passes<LOGN, P + 1>(v, t, tw, z);
+    }
+}
+
+// A row's samples as the inputs of the first pass (radix R).
+template <int N, int R>
+MS_D void load_row(Regs<N> &v, int t, const double *src, bool live)
+{
+#pragma unroll
+    for (int i = 0; i < per_thread<N>(); ++i) {
+        const int e = t + i / R * row_threads<N>() + i % R * (N / R);
+        const d4 w = live ? load_d4(src + 4 * e) : d4{0.0, 0.0, 0.0, 0.0};
+        v[0][i] = make_double2(w.x, w.y);
+        v[1][i] = make_double2(w.z, w.w);
+    }
+}
+
+// The outputs of the last pass (radix R, Ns), scaled by 1 / N.
+template <int N, int R, int Ns>
+MS_D void store_row(const Regs<N> &v, int t, double *dst)
+{
+    const double inv = 1.0 / (double)N;
+#pragma unroll
+    for (int i = 0; i < per_thread<N>(); ++i) {
+        double2 *o = reinterpret_cast<double2 *>(dst + 4 * element<N, R, Ns>(t, i));
+        o[0] = make_double2(v[0][i].x * inv, v[0][i].y * inv);
+        o[1] = make_double2(v[1][i].x * inv, v[1][i].y * inv);
     }
 }
 
 // row_map (optional): output row of each input row; a negative entry drops
 // the row.
 template <int LOGN>
-__global__ void __launch_bounds__(SP_THREADS) k_theta_shift(const double *in, double *out,
-                                                            const double2 *__restrict__ tw, const double *rho_dev,
-                                                            double rho, int order, const int64_t *row_map)
+__global__ void __launch_bounds__(SP_THREADS) __attribute__((amdgpu_waves_per_eu(3)))
+k_theta_shift(const double *in, double *out, const double2 *__restrict__ tw, const double *rho_dev, double rho, int order,
+              const int64_t *row_map, int64_t n_rows)
 {
     using PL = Plan<LOGN>;
-    constexpr int N = 1 << LOGN;
-    __shared__ double2 z[2][padded_size<N>()];
-    const int64_t row = blockIdx.x;
-    const int64_t orow = row_map ? row_map[row] : row;
-    if (orow < 0) return;   // the whole block
-    const double *src = in + row * (int64_t)N * 4;
-    double *dst = out + orow * (int64_t)N * 4;
-    const double r = rho_dev ? rho_dev[row] : rho;
-    forward_passes<LOGN, 0>(z, tw, src);
-    // last forward pass + multiplier + first inverse pass, in registers
-    constexpr int PM = PL::NP - 1;
-    constexpr int NSM = PL::ns_fwd(PM);
-    pass<N, PL::radix(PM), NSM, false, PM == 0 ? FROM_GLOBAL : FROM_LDS, PL::NP == 1, true>(z, tw, src, dst, r,
-                                                                                            order);
-    inverse_passes<LOGN, 1>(z, tw, dst);
+    constexpr int N = 1 << LOGN, T = row_threads<N>(), RM = PL::radix(PL::NP - 1);
+    __shared__ double2 s_z[block_rows<N>()][padded_size<N>()];
+    __shared__ PhaseTable s_ph;
+    const int t = threadIdx.x % T;
+    const int64_t row = (int64_t)blockIdx.x * block_rows<N>() + threadIdx.x / T;
+    double2 *z = s_z[threadIdx.x / T];
+    const int64_t orow = row >= n_rows ? -1 : row_map ? row_map[row] : row;
+    const bool live = orow >= 0;
+    phase_table(s_ph);
+    Regs<N> v;
+    load_row<N, PL::radix(0)>(v, t, in + row * (int64_t)N * 4, live);
+    const double r = live ? (rho_dev ? rho_dev[row] : rho) : 0.0;
+    forward_passes<LOGN, 0>(v, t, tw, z);
+    if constexpr (PL::NP == 1) __syncthreads();      // the phases' table
+    multiply<N, RM>(v, t, s_ph, r, order, z);
+    inverse_passes<LOGN, 0>(v, t, tw, z);
+    if (live) store_row<N, PL::radix_inv(PL::NP - 1), PL::ns_inv(PL::NP - 1)>(v, t, out + orow * (int64_t)N * 4);
 }
 
 // Forward transform only: out(r, j) = (Z0(j), Z1(j)) / N in natural order,
 // four doubles per frequency (Re Z0, Im Z0, Re Z1, Im Z1), the layout of the
 // input rows.
 template <int LOGN>
-__global__ void __launch_bounds__(SP_THREADS) k_theta_spectrum(const double *in, double *out,
-                                                               const double2 *__restrict__ tw)
+__global__ void __launch_bounds__(SP_THREADS) __attribute__((amdgpu_waves_per_eu(4)))
+k_theta_spectrum(const double *in, double *out, const double2 *__restrict__ tw, int64_t n_rows)
 {
     using PL = Plan<LOGN>;
-    constexpr int N = 1 << LOGN;
-    __shared__ double2 z[2][padded_size<N>()];
-    const int64_t row = blockIdx.x;
-    const double *src = in + row * (int64_t)N * 4;
-    double *dst = out + row * (int64_t)N * 4;
-    forward_passes<LOGN, 0>(z, tw, src);
-    constexpr int PM = PL::NP - 1;
-    constexpr int NSM = PL::ns_fwd(PM);
-    // the last forward pass (Ns = N / R) writes coefficient j + r N/R of butterfly j
-    pass<N, PL::radix(PM), NSM, false, PM == 0 ? FROM_GLOBAL : FROM_LDS, true, false>(z, tw, src, dst, 0.0, 0);
+    constexpr int N = 1 << LOGN, T = row_threads<N>();
+    __shared__ double2 s_z[block_rows<N>()][padded_size<N>()];
+    const int t = threadIdx.x % T;
+    const int64_t row = (int64_t)blockIdx.x * block_rows<N>() + threadIdx.x / T;
+    Regs<N> v;
+    load_row<N, PL::radix(0)>(v, t, in + row * (int64_t)N * 4, row < n_rows);
+    forward_passes<LOGN, 0>(v, t, tw, s_z[threadIdx.x / T]);
+    if (row < n_rows) store_row<N, PL::radix(PL::NP - 1), PL::ns_fwd(PL::NP - 1)>(v, t, out + row * (int64_t)N * 4);
 }
 
 // ------------------------------------------------------------- interpolation
@@ -809,72 +848,98 @@ __global__ void __launch_bounds__(IP_BLOCK) k_theta_interp(InterpArgs g)
     }
 }
 
+// The twiddle factors of all passes (Plan) per (device, N), kept for the life
+// of the process (11 lengths, at most 56 KB each).  2 m / N is exact for a
+// power of two N, so each entry is the rounded cosine and sine of one rounded
+// argument.
 template <int LOGN>
-void launch_shift(const double *in, double *out, const double2 *tw, int64_t n_rows, const double *rho_dev,
-                  double rho, int order, hipStream_t st, const int64_t *row_map = nullptr)
+std::vector<double2> make_twiddles()
 {
-    hipLaunchKernelGGL(k_theta_shift<LOGN>, dim3((unsigned)n_rows), dim3(SP_THREADS), 0, st, in, out, tw, rho_dev,
-                       rho, order, row_map);
+    using PL = Plan<LOGN>;
+    constexpr int N = 1 << LOGN;
+    std::vector<double2> w;
+    auto add = [&](int R, int Ns) {
+        for (int r = 1; r < R; ++r)
+            for (int k = 0; k < Ns; ++k) {
+                const double a = SP_PI * (2.0 * (double)(r * k * (N / (Ns * R))) / (double)N);
+                w.push_back(make_double2(cos(a), -sin(a)));
+            }
+    };
+    for (int p = 1; p < PL::NP; ++p) add(PL::radix(p), PL::ns_fwd(p));
+    for (int p = 1; p < PL::NP; ++p) add(PL::radix_inv(p), PL::ns_inv(p));
+    if (w.empty()) w.push_back(make_double2(1.0, 0.0));
+    return w;
 }
 
-// e^{-2 pi i m / N}, m = 0..N-1, per (device, N), kept for the life of the
-// process.  2 m / N is exact for a power of two N, so each entry is the
-// rounded cosine and sine of one rounded argument.
 std::mutex g_tw_mu;
 std::map<std::pair<int, int>, double2 *> g_tw;
 
-int twiddles(int N, const double2 **out)
+template <int LOGN>
+int twiddles(const double2 **out)
 {
     int dev = 0;
     MS_HIP(hipGetDevice(&dev));
     std::lock_guard<std::mutex> lk(g_tw_mu);
-    auto key = std::make_pair(dev, N);
+    auto key = std::make_pair(dev, LOGN);
     auto it = g_tw.find(key);
     if (it != g_tw.end()) { *out = it->second; return MS_OK; }
-    std::vector<double2> w(N);
-    for (int m = 0; m < N; ++m) {
-        const double a = SP_PI * (2.0 * (double)m / (double)N);
-        w[m] = make_double2(cos(a), -sin(a));
-    }
+    const std::vector<double2> w = make_twiddles<LOGN>();
     double2 *d = nullptr;
-    MS_HIP(hipMalloc(&d, (size_t)N * sizeof(double2)));
-    hipError_t er = hipMemcpy(d, w.data(), (size_t)N * sizeof(double2), hipMemcpyHostToDevice);
+    MS_HIP(hipMalloc(&d, w.size() * sizeof(double2)));
+    hipError_t er = hipMemcpy(d, w.data(), w.size() * sizeof(double2), hipMemcpyHostToDevice);
     if (er != hipSuccess) { (void)hipFree(d); return hip_fail(er, "copy twiddle table"); }
     g_tw[key] = d;
     *out = d;
     return MS_OK;
 }
 
+struct ShiftArgs {
+    const double *in;
+    double *out;
+    const double *rho_dev;
+    double rho;
+    int order;
+    const int64_t *row_map;
+    int64_t n_rows;
+};
+
 template <int LOGN>
-void launch_spectrum(const double *in, double *out, const double2 *tw, int64_t n_rows, hipStream_t st)
+int launch_shift(const ShiftArgs &a, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_theta_spectrum<LOGN>, dim3((unsigned)n_rows), dim3(SP_THREADS), 0, st, in, out, tw);
+    const double2 *tw = nullptr;
+    if (int rc = twiddles<LOGN>(&tw)) return rc;
+    const dim3 grid((unsigned)ceil_div(a.n_rows, (int64_t)block_rows<1 << LOGN>()));
+    hipLaunchKernelGGL(k_theta_shift<LOGN>, grid, dim3(SP_THREADS), 0, st, a.in, a.out, tw, a.rho_dev, a.rho, a.order,
+                       a.row_map, a.n_rows);
+    MS_HIP(hipGetLastError());
+    return MS_OK;
 }
+
+template <int LOGN>
+int launch_spectrum(const ShiftArgs &a, hipStream_t st)
+{
+    const double2 *tw = nullptr;
+    if (int rc = twiddles<LOGN>(&tw)) return rc;
+    const dim3 grid((unsigned)ceil_div(a.n_rows, (int64_t)block_rows<1 << LOGN>()));
+    hipLaunchKernelGGL(k_theta_spectrum<LOGN>, grid, dim3(SP_THREADS), 0, st, a.in, a.out, tw, a.n_rows);
+    MS_HIP(hipGetLastError());
+    return MS_OK;
+}
+
+typedef int (*RowsLaunch)(const ShiftArgs &, hipStream_t);
+constexpr RowsLaunch SHIFT_OF[SP_MAX_LOG2 + 1] = {
+    nullptr, launch_shift<1>, launch_shift<2>, launch_shift<3>, launch_shift<4>, launch_shift<5>,
+    launch_shift<6>, launch_shift<7>, launch_shift<8>, launch_shift<9>, launch_shift<10>, launch_shift<11>};
+constexpr RowsLaunch SPECTRUM_OF[SP_MAX_LOG2 + 1] = {
+    nullptr, launch_spectrum<1>, launch_spectrum<2>, launch_spectrum<3>, launch_spectrum<4>, launch_spectrum<5>,
+    launch_spectrum<6>, launch_spectrum<7>, launch_spectrum<8>, launch_spectrum<9>, launch_spectrum<10>,
+    launch_spectrum<11>};
 
 // theta_shift on validated arguments (n_theta a power of two in range).
 int shift_rows(const double *in, double *out, int n_theta, int64_t n_rows, const double *rho_dev, double rho,
                int order, const int64_t *row_map, hipStream_t st)
 {
-    const double2 *tw = nullptr;
-    int rc = twiddles(n_theta, &tw);
-    if (rc) return rc;
-    int lg = 0;
-    while ((1 << lg) < n_theta) ++lg;
-    switch (lg) {
-    case 1: launch_shift<1>(in, out, tw, n_rows, rho_dev, rho, order, st, row_map); break;
-    case 2: launch_shift<2>(in, out, tw, n_rows, rho_dev, rho, order, st, row_map); break;
-    case 3: launch_shift<3>(in, out, tw, n_rows, rho_dev, rho, order, st, row_map); break;
-    case 4: launch_shift<4>(in, out, tw, n_rows, rho_dev, rho, order, st, row_map); break;
-    case 5: launch_shift<5>(in, out, tw, n_rows, rho_dev, rho, order, st, row_map); break;
-    case 6: launch_shift<6>(in, out, tw, n_rows, rho_dev, rho, order, st, row_map); break;
-    case 7: launch_shift<7>(in, out, tw, n_rows, rho_dev, rho, order, st, row_map); break;
-    case 8: launch_shift<8>(in, out, tw, n_rows, rho_dev, rho, order, st, row_map); break;
-    case 9: launch_shift<9>(in, out, tw, n_rows, rho_dev, rho, order, st, row_map); break;
-    case 10: launch_shift<10>(in, out, tw, n_rows, rho_dev, rho, order, st, row_map); break;
-    default: launch_shift<11>(in, out, tw, n_rows, rho_dev, rho, order, st, row_map); break;
-    }
-    MS_HIP(hipGetLastError());
-    return MS_OK;
+    return SHIFT_OF[__builtin_ctz(n_theta)]({in, out, rho_dev, rho, order, row_map, n_rows}, st);
 }
 
 // Row copies through a row map (negative entries dropped): the unshifted
@@ -970,27 +1035,7 @@ extern "C" int theta_spectrum(const double *in_dev, double *out_dev, int32_t n_t
         return fail(MS_E_ARG, "theta_spectrum: n_theta must be a power of two in [2, 2048]");
     if (n_rows > 0x7fffffff) return fail(MS_E_ARG, "theta_spectrum: too many rows for one launch");
     if (n_rows == 0) return MS_OK;
-    hipStream_t st = (hipStream_t)stream;
-    const double2 *tw = nullptr;
-    int rc = twiddles(n_theta, &tw);
-    if (rc) return rc;
-    int lg = 0;
-    while ((1 << lg) < n_theta) ++lg;
-    switch (lg) {
-    case 1: launch_spectrum<1>(in_dev, out_dev, tw, n_rows, st); break;
-    case 2: launch_spectrum<2>(in_dev, out_dev, tw, n_rows, st); break;
-    case 3: launch_spectrum<3>(in_dev, out_dev, tw, n_rows, st); break;
-    case 4: launch_spectrum<4>(in_dev, out_dev, tw, n_rows, st); break;
-    case 5: launch_spectrum<5>(in_dev, out_dev, tw, n_rows, st); break;
-    case 6: launch_spectrum<6>(in_dev, out_dev, tw, n_rows, st); break;
-    case 7: launch_spectrum<7>(in_dev, out_dev, tw, n_rows, st); break;
-    case 8: launch_spectrum<8>(in_dev, out_dev, tw, n_rows, st); break;
-    case 9: launch_spectrum<9>(in_dev, out_dev, tw, n_rows, st); break;
-    case 10: launch_spectrum<10>(in_dev, out_dev, tw, n_rows, st); break;
-    default: launch_spectrum<11>(in_dev, out_dev, tw, n_rows, st); break;
-    }
-    MS_HIP(hipGetLastError());
-    return MS_OK;
+    return SPECTRUM_OF[__builtin_ctz(n_theta)]({in_dev, out_dev, nullptr, 0.0, 0, nullptr, n_rows}, (hipStream_t)stream);
 }
 
 extern "C" int theta_shift(const double *in_dev, double *out_dev, int32_t n_theta, int64_t n_rows,

@@ -73,3 +73,22 @@ def test_grouped_by_rows(ms, N, n_rows, order):
     theta[rng.integers(0, nq, 9)] = 1e18
     rows = torch.from_numpy(rng.standard_normal((n_rows, N, 4))).cuda()
     _check(ms, rows, at, theta, rng)
+
+
+@pytest.mark.parametrize("N", [2, 4, 8, 16, 64, 512, 1024, 2048])
+@pytest.mark.parametrize("n_rows", [1, 7, 301])
+def test_rows_per_workgroup(ms, N, n_rows):
+    """theta_shift and theta_spectrum where a workgroup takes several rows and
+    the last one not all of them; shifts so large that the phases' table does
+    not reach.  Bars: 1e-13 N^order x max|a|, the spectrum 1e-13 x log2 N."""
+    rng = np.random.default_rng(N + n_rows)
+    rows = rng.standard_normal((n_rows, N, 4))
+    rho = rng.uniform(-4, 4, n_rows)
+    rho[::5] *= 1e6
+    for order in (0, 1, 2):
+        got = ms.theta_shift(rows, rho, order).cpu().numpy()
+        ref = spectral.shift_derivative(rows, rho, order)
+        assert np.max(np.abs(got - ref)) < 1e-13 * N ** order * max(1.0, np.abs(rows).max()) * max(1.0, np.log2(N))
+    z = np.fft.fft(rows.reshape(n_rows, N, 2, 2) @ np.array([1.0, 1j]), axis=1) / N
+    ref = np.stack([z.real, z.imag], -1).reshape(n_rows, N, 4)
+    assert np.max(np.abs(ms.theta_spectrum(rows).cpu().numpy() - ref)) < 1e-13 * np.abs(rows).max() * max(1.0, np.log2(N))
