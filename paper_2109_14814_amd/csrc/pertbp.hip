@@ -16,7 +16,7 @@
 // variational equations integrated with the same stages, so the result is
 // the exact derivative of the discrete map): NC = 4 computes the field once
 // per state (the default for large batches: fastest on gfx950 although it
-// runs at one wave per SIMD: 61.0 ms for a period of 262,144 states, 62.8 at
+// runs at one wave per SIMD: 60.3 ms for a period of 262,144 states, 62 at
 // two waves with 140 bytes spilled), NC = 1 keeps the fewest registers live
 // and gives small batches four times the threads.
 #include <math.h>
@@ -28,7 +28,6 @@
 namespace ms {
 namespace {
 
-constexpr int S = RK_S;
 constexpr int PM_BLOCK = FLOW_BLOCK;
 
 // NC = 0: state only.  NC > 0: state and tangent columns g NC .. g NC + NC - 1
@@ -40,11 +39,7 @@ k_pm_flow(RkCoef, const double *in, double *out, double *stm, int64_t n, Model m
 {
     constexpr int G = NC > 0 ? 4 / NC : 1;   // threads per state
     constexpr int D = 4 + 4 * NC;            // the state, then the thread's columns
-    __shared__ double2 s_rn[RK_CHUNK * S];
-    __shared__ double s_c[S];
-#pragma unroll
-    for (int i = 0; i < S; ++i)
-        if (threadIdx.x == i) s_c[i] = RK_T.c[i];
+    __shared__ double2 s_rn[RK_VALUES];
     const FlowUnit u = flow_unit(plan, unit0 + blockIdx.x, nsteps);
     if (!u.ok) return;
     const int64_t gid = u.block * blockDim.x + threadIdx.x;
@@ -64,14 +59,14 @@ k_pm_flow(RkCoef, const double *in, double *out, double *stm, int64_t n, Model m
     int64_t n_in = u.s0 % steps;
     for (int64_t st0 = u.s0; st0 < u.s1; st0 += RK_CHUNK) {
         const int cnt = u.s1 - st0 < RK_CHUNK ? (int)(u.s1 - st0) : RK_CHUNK;
-        __syncthreads();      // the previous chunk's values are no longer read (and s_c is written)
-        fill_stage_chunk(s_rn, s_c, n_in, cnt, steps, [&](double t) { return kepler_rho_n(t, ecc); });
+        __syncthreads();      // the previous chunk's values are no longer read
+        fill_stage_chunk(s_rn, threadIdx.x, blockDim.x, n_in, cnt, steps, [&](double t) { return kepler_rho_n(t, ecc); });
         __syncthreads();
         n_in = (n_in + cnt) % steps;
         if (!live) continue;
         for (int jj = 0; jj < cnt; ++jj) {
-            const double2 *row = s_rn + jj * S;
-            rk_step<D>(z, step_coef(), [&](int i, double (&s)[D]) { pm_field<NC>(md, row[i].x, row[i].y, s); });
+            const double2 *row = s_rn + jj * RK_SLOTS;
+            rk_step<D>(z, step_coef(), [&](int i, double (&s)[D]) { pm_field<NC>(md, row[RK_SLOT[i]].x, row[RK_SLOT[i]].y, s); });
         }
     }
     if (!live) return;

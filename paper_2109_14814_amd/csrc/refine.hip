@@ -36,6 +36,7 @@ __constant__ Tableau c_cv = cv_make_tableau();
 namespace {
 
 constexpr int S = RK_S;
+constexpr int RF_CHUNK = 32;         // steps of stage values in LDS
 constexpr int RF_BLOCK = 64;
 
 struct SideMap {
@@ -99,7 +100,7 @@ constexpr int64_t PAIR_HITS = 16384;
 // stages, which is the exact derivative of the discrete step).  PAIR: two
 // lanes per trajectory, y = (own coordinate, own velocity, then the
 // column's); else y = (x, y, x', y', then the column).  The stage values of
-// RK_CHUNK steps lie in LDS and the next chunk's are on their way from the
+// RF_CHUNK steps lie in LDS and the next chunk's are on their way from the
 // tables meanwhile.  before(s, y) sees the state before step s.
 template <bool PAIR, bool COL>
 constexpr int flow_dim() { return (PAIR ? 2 : 4) * (COL ? 2 : 1); }
@@ -108,7 +109,7 @@ template <bool PAIR, bool COL, typename BEFORE>
 MS_D void ref_flow(const RefArgs &a, int side, bool live, int64_t s0, int64_t s1, bool ecol,
                    double (&y)[flow_dim<PAIR, COL>()], BEFORE &&before)
 {
-    constexpr int D = flow_dim<PAIR, COL>(), N = RK_CHUNK * S, PER = (N + RF_BLOCK - 1) / RF_BLOCK;
+    constexpr int D = flow_dim<PAIR, COL>(), N = RF_CHUNK * S, PER = (N + RF_BLOCK - 1) / RF_BLOCK;
     __shared__ double s_w[N], s_d[COL ? N : 1];
     const SideMap &sm = a.side[side];
     const int64_t tot = (int64_t)sm.steps * S;
@@ -134,7 +135,7 @@ MS_D void ref_flow(const RefArgs &a, int side, bool live, int64_t s0, int64_t s1
         L = pair_lane(a.md, threadIdx.x & 1);
     }
     if (s0 < s1) fetch(s0);
-    for (int64_t sc = s0; sc < s1; sc += RK_CHUNK) {
+    for (int64_t sc = s0; sc < s1; sc += RF_CHUNK) {
         __syncthreads();
 #pragma unroll
         for (int q = 0; q < PER; ++q) {
@@ -145,8 +146,8 @@ MS_D void ref_flow(const RefArgs &a, int side, bool live, int64_t s0, int64_t s1
             }
         }
         __syncthreads();
-        if (sc + RK_CHUNK < s1) fetch(sc + RK_CHUNK);
-        const int cnt = s1 - sc < RK_CHUNK ? (int)(s1 - sc) : RK_CHUNK;
+        if (sc + RF_CHUNK < s1) fetch(sc + RF_CHUNK);
+        const int cnt = s1 - sc < RF_CHUNK ? (int)(s1 - sc) : RF_CHUNK;
         if (!live) continue;
 #pragma unroll 1
         for (int jj = 0; jj < cnt; ++jj) {

@@ -3,7 +3,7 @@
 // explicit Runge-Kutta of order 8 (Cooper & Verner 1972, 11 stages).
 //
 // One thread per state; the scaled tableau is a kernel argument (scalar
-// loads).  Five waves per SIMD (96 registers, nothing spilled).  The
+// loads).  Five waves per SIMD (96 registers).  The
 // stage weights w(f) = 1 / (1 + e cos f) are the same for every state, so
 // each block computes them for RK_CHUNK steps at a time into LDS (w is 2 pi
 // periodic and even, so the values of one period serve every period and
@@ -59,11 +59,7 @@ __global__ void __launch_bounds__(RK_BLOCK) __attribute__((amdgpu_waves_per_eu(5
 k_rk8_map(RkCoef, const double *in, double *out, int64_t n, Model md, double e, int steps, int64_t nsteps,
           FlowPlan plan, int64_t unit0)
 {
-    __shared__ double s_w[RK_CHUNK * S];
-    __shared__ double s_c[S];
-#pragma unroll
-    for (int i = 0; i < S; ++i)
-        if (threadIdx.x == i) s_c[i] = RK_T.c[i];
+    __shared__ double s_w[RK_VALUES];
     const FlowUnit u = flow_unit(plan, unit0 + blockIdx.x, nsteps);
     if (!u.ok) return;
     const int64_t v = u.block * blockDim.x + threadIdx.x;
@@ -76,13 +72,14 @@ k_rk8_map(RkCoef, const double *in, double *out, int64_t n, Model md, double e, 
     int64_t n_in = u.s0 % steps;
     for (int64_t st0 = u.s0; st0 < u.s1; st0 += RK_CHUNK) {
         const int cnt = u.s1 - st0 < RK_CHUNK ? (int)(u.s1 - st0) : RK_CHUNK;
-        __syncthreads();      // the previous chunk's weights are no longer read (and s_c is written)
-        fill_stage_chunk(s_w, s_c, n_in, cnt, steps, [&](double f) { return 1.0 / (1.0 + e * cos(f)); });
+        __syncthreads();      // the previous chunk's weights are no longer read
+        fill_stage_chunk(s_w, threadIdx.x, blockDim.x, n_in, cnt, steps,
+                         [&](double f) { return 1.0 / (1.0 + e * cos(f)); });
         __syncthreads();
         if (live) {
             for (int jj = 0; jj < cnt; ++jj) {
-                const double *w = s_w + jj * S;
-                rk_step<4>(y, step_coef(), [&](int i, double (&s)[4]) { puls_field(md, w[i], s); });
+                const double *w = s_w + jj * RK_SLOTS;
+                rk_step<4>(y, step_coef(), [&](int i, double (&s)[4]) { puls_field(md, w[RK_SLOT[i]], s); });
             }
         }
         n_in = (n_in + cnt) % steps;

@@ -81,7 +81,21 @@ bool cv_pattern_ok();
 // compute them on the GPU: the maps a chunk of RK_CHUNK steps at a time
 // into LDS, the refinement once per call into its workspace.  Nothing is
 // allocated or copied from the host, so every call can be captured.
-constexpr int RK_CHUNK = 32;
+//
+// The 11 abscissae are 4 and the next step's first: the maps keep RK_SLOTS
+// values a step, and one more behind the last step.  A chunk's 253 are one
+// for each thread of a block (with 11 for each of 32 steps, two rounds of
+// Kepler's equation took 7% of the position-momentum map's time).
+constexpr int RK_CHUNK = 63;
+constexpr int RK_SLOTS = 4;
+constexpr int RK_VALUES = RK_CHUNK * RK_SLOTS + 1;
+constexpr double RK_SLOT_C[RK_SLOTS] = {RK_T.c[0], RK_T.c[1], RK_T.c[3], RK_T.c[6]};
+constexpr int RK_SLOT[RK_S] = {0, 1, 1, 2, 2, 1, 3, 3, 1, 2, RK_SLOTS};   // of each stage; RK_SLOTS: the next step's 0
+static_assert([] {
+    for (int i = 0; i < RK_S; ++i)
+        if (RK_T.c[i] != (RK_SLOT[i] == RK_SLOTS ? 1.0 : RK_SLOT_C[RK_SLOT[i] % RK_SLOTS])) return false;
+    return RK_SLOT_C[0] == 0.0;
+}(), "the stages' slots hold their abscissae");
 
 MS_D double stage_abscissa(int64_t n, double c, int steps)
 {
@@ -123,14 +137,16 @@ MS_D double2 kepler_rho_n(double t, double e)
     return make_double2(rho, sqrt(1.0 - e * e) / (rho * rho));
 }
 
-// The block's threads fill the stage values of steps n0 .. n0 + cnt - 1
-// (taken mod steps) into s_val[j * RK_S + i]; c_dev: the RK_S abscissae c_i.
+// `threads` threads (this one is `first`) fill the stage values of steps
+// n0 .. n0 + cnt - 1 (taken mod steps) into s_val[j * RK_SLOTS + slot], and the
+// first of the step after them.
 template <typename T, typename F>
-MS_D void fill_stage_chunk(T *s_val, const double *c_dev, int64_t n0, int cnt, int steps, F &&value)
+MS_D void fill_stage_chunk(T *s_val, int first, int threads, int64_t n0, int cnt, int steps, F &&value)
 {
-    for (int i = threadIdx.x; i < cnt * RK_S; i += blockDim.x) {
-        const int j = i / RK_S, q = i - j * RK_S;
-        s_val[i] = value(stage_abscissa((n0 + j) % steps, c_dev[q], steps));
+    for (int i = first; i <= cnt * RK_SLOTS; i += threads) {
+        const int j = i / RK_SLOTS, q = i % RK_SLOTS;
+        const double c = q == 0 ? RK_SLOT_C[0] : q == 1 ? RK_SLOT_C[1] : q == 2 ? RK_SLOT_C[2] : RK_SLOT_C[3];
+        s_val[i] = value(stage_abscissa((n0 + j) % steps, c, steps));
     }
 }
 
@@ -285,7 +301,8 @@ MS_D void pm_field(const Model &md, double rho, double n, double (&s)[4 + 4 * NC
 // Newton steps per square root; 1,795 against 2,808 for the state with four
 // tangent columns, where 440 live registers cost 770 moves a step to and
 // from the accumulation registers).  F^3 of 526,593 states at 4000 steps a
-// period: 114 ms, 133 before; DF of 262,144 states over a period: 61 ms, 84
+// period: 96 ms, 133 before (114 by the step alone, then the rounds of blocks
+// and the stage values' slots); DF of 262,144 states over a period: 60 ms, 84
 // before.
 template <int D, typename C, typename F>
 MS_D void rk_step(double (&y)[D], const C &c, F &&field)
@@ -435,7 +452,7 @@ inline FlowPlan flow_plan(int64_t blocks, int64_t nsteps, bool resume)
 {
     FlowPlan p{blocks, nsteps > 0 ? nsteps : 1, 1, (uint32_t)blocks};
     const int64_t m = blocks / FLOW_CUS;
-    const int64_t most = nsteps / (4 * RK_CHUNK);       // chunks of at least 128 steps
+    const int64_t most = nsteps / (2 * RK_CHUNK);       // chunks of at least 126 steps
     if (!resume || m == 0 || blocks % FLOW_CUS == 0 || most < 4) return p;
     const int64_t n = most < 32 ? most : 32;
     const int64_t chunk = ceil_div(ceil_div(nsteps, n), RK_CHUNK) * RK_CHUNK;

@@ -130,12 +130,8 @@ template <typename V, int COLS, typename STAGE, typename FIELD>
 MS_D void pair_flow(const RkCoef &hc, const double *in, double *out, double *stm, int64_t n, const Model &md, int steps,
                     int64_t nsteps, STAGE &&stage_value, FIELD &&field)
 {
-    constexpr int S = RK_S, D = COLS ? 4 : 2, PP = COLS ? COLS : 1;
-    __shared__ V s_val[2][RK_CHUNK * S];
-    __shared__ double s_c[S];
-#pragma unroll
-    for (int i = 0; i < S; ++i)
-        if (threadIdx.x == i) s_c[i] = RK_T.c[i];
+    constexpr int D = COLS ? 4 : 2, PP = COLS ? COLS : 1;
+    __shared__ V s_val[2][RK_VALUES];
     const bool producer = threadIdx.x >= PAIR_LANES;
     const int lane = threadIdx.x & 1;
     const int64_t pair = ((int64_t)blockIdx.x * (PAIR_LANES) + threadIdx.x) >> 1;
@@ -154,8 +150,7 @@ MS_D void pair_flow(const RkCoef &hc, const double *in, double *out, double *stm
             y[3] = col == 2 + lane ? 1.0 : 0.0;
         }
     }
-    __syncthreads();
-    fill_stage_chunk(s_val[0], s_c, 0, chunk_len(0), steps, stage_value);
+    fill_stage_chunk(s_val[0], threadIdx.x, PAIR_BLOCK, 0, chunk_len(0), steps, stage_value);
     __syncthreads();
     int64_t n_in = 0;
     int cur = 0;
@@ -170,17 +165,14 @@ MS_D void pair_flow(const RkCoef &hc, const double *in, double *out, double *stm
         n_in = (n_in + cnt) % steps;
         if (producer) {
             if (s0 + cnt < nsteps) {
-                const int m = chunk_len(s0 + cnt);
-                for (int i = threadIdx.x - PAIR_LANES; i < m * S; i += WAVE) {
-                    const int j = i / S, q = i - j * S;
-                    s_val[cur ^ 1][i] = stage_value(stage_abscissa((n_in + j) % steps, s_c[q], steps));
-                }
+                fill_stage_chunk(s_val[cur ^ 1], threadIdx.x - PAIR_LANES, WAVE, n_in, chunk_len(s0 + cnt), steps,
+                                 stage_value);
             }
         } else if (live) {
 #pragma unroll 1
             for (int jj = 0; jj < cnt; ++jj) {
-                const V *row = s_val[cur] + jj * S;
-                rk_step<D>(y, c, [&](int i, double (&s)[D]) { field(L, row[i], s); });
+                const V *row = s_val[cur] + jj * RK_SLOTS;
+                rk_step<D>(y, c, [&](int i, double (&s)[D]) { field(L, row[RK_SLOT[i]], s); });
             }
         }
         __syncthreads();
@@ -199,8 +191,8 @@ MS_D void pair_flow(const RkCoef &hc, const double *in, double *out, double *stm
 
 // Up to these sizes every compute wave has a SIMD of its own (256 CUs of
 // three, 32 pairs a wave).  A period of 4000 steps then takes 3.0 ms against
-// 4.7 ms with one lane per state (whose waves have a SIMD each up to 65,536
-// states), and with the matrix 6.2 ms against 8.5; with a second wave on a
+// 4.5 ms with one lane per state (whose waves have a SIMD each up to 65,536
+// states), and with the matrix 5.4 ms against 7.7; with a second wave on a
 // SIMD, 5.3 and 10.0 ms.
 constexpr int64_t PAIR_STATES = 256 * 3 * 32;
 constexpr int64_t PAIR_MATRICES = PAIR_STATES / 4;
