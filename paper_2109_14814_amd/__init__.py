@@ -273,9 +273,15 @@ def make_params(w_lo, inv_edge: float, n_cells, flags: int = 0, table_log2: int 
     return p
 
 
-def _stats_dict(buf) -> dict:
-    arr = buf.view(_torch().int64).cpu().numpy()
+def _stats_of(arr) -> dict:
     return {k: int(arr[i]) for i, k in enumerate(STATS_FIELDS)}
+
+
+def _stats_dict(buf) -> dict:
+    return _stats_of(buf.view(_torch().int64).cpu().numpy())
+
+
+READ_HITS = 128     # records that Searcher.results() reads along with the counters
 
 
 class Searcher:
@@ -285,16 +291,19 @@ class Searcher:
                  cand_cap: int = 1 << 20):
         self.A, self.B, self.params = A, B, params
         self.hits_cap, self.cand_cap = int(hits_cap), int(cand_cap)
-        self.stats = _dev_bytes(16 * 8)
-        self._alloc()
+        # the counters and the records in one allocation, so that results()
+        # reads both with one copy
+        self._out = _dev_bytes(16 * 8 + max(self.hits_cap * HIT_DTYPE.itemsize, 1))
+        self.stats = self._out[: 16 * 8]
+        self._alloc(self._out[16 * 8:])
 
-    def _alloc(self):
+    def _alloc(self, hits=None):
         nb = C.c_size_t()
         _check(lib().search_workspace_size(self.A.handle, self.B.handle, C.byref(self.params), self.cand_cap,
                                            self.hits_cap, _stream(), C.byref(nb)))
         self.ws_bytes = int(nb.value)
         self.ws = _workspace(self.ws_bytes)
-        self.hits = _dev_bytes(self.hits_cap * HIT_DTYPE.itemsize)
+        self.hits = hits if hits is not None else _dev_bytes(self.hits_cap * HIT_DTYPE.itemsize)
         want_cand = bool(self.params.flags & MS_SEARCH_CANDIDATES)
         self.cand = _dev_bytes(self.cand_cap * 8) if want_cand else None
 
@@ -339,9 +348,20 @@ class Searcher:
 
     def results(self):
         """(hits structured array sorted by (triA, triB), stats dict, candidates or None)."""
-        st = _stats_dict(self.stats)
-        nh = min(st["n_hits"], self.hits_cap)
-        hits = np.frombuffer(self.hits[: nh * HIT_DTYPE.itemsize].cpu().numpy().tobytes(), dtype=HIT_DTYPE)
+        size = HIT_DTYPE.itemsize
+        head = b""
+        if self.stats.data_ptr() == self._out.data_ptr() and self.hits.data_ptr() == self.stats.data_ptr() + 16 * 8:
+            # the counters and the first records at once: a copy to the host
+            # costs its round trip up to some tens of KB
+            raw = self._out[: 16 * 8 + READ_HITS * size].cpu().numpy()
+            st = _stats_of(raw[: 16 * 8].view(np.int64))
+            head = raw[16 * 8:].tobytes()
+        else:                                    # the records moved to a larger buffer
+            st = _stats_dict(self.stats)
+        end = min(st["n_hits"], self.hits_cap) * size
+        if end > len(head):
+            head += self.hits[len(head): end].cpu().numpy().tobytes()
+        hits = np.frombuffer(head[:end], dtype=HIT_DTYPE)
         cand = None
         if self.cand is not None:
             nc = min(st["n_cand"], self.cand_cap)
