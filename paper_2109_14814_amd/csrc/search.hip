@@ -35,6 +35,7 @@
 // A batch numbers its cells with a per-pair cell offset, so entries of
 // different pairs never share a cell (they may share a group).
 #include <math.h>
+#include <stddef.h>
 #include <string.h>
 
 #include <mutex>
@@ -1127,13 +1128,172 @@ struct KeysOut {
 // entries and 114 to their ranks; it took 745 with one lookup per cell and
 // every thread writing its own entries (14 layers: 445 from 582 us).
 constexpr int KEYS_BLOCK = TILE_TRIS;
-constexpr int KEYS_STAGE = 4096;          // entries of a block listed in LDS (more: each thread writes its own)
+constexpr uint32_t KEYS_LIST = 4096;      // entries of a block that its list holds
+constexpr uint32_t KEYS_DENSE = 1024;     // a plain search's block with more entries counts them by groups,
+constexpr uint32_t KEYS_STAGE = 2048;     //   so many at a time
+constexpr int KEYS_GROUPS_LOG2 = 10;      // table of the groups that they fall in (behind the list)
+constexpr uint32_t KEYS_GROUPS = 1u << KEYS_GROUPS_LOG2;
+constexpr int KEYS_PROBES = 8;            // places tried; an entry that finds none is counted by itself
+constexpr uint32_t KEYS_NONE = ~0u;       // no group (a hashed cell has at most 31 bits)
+constexpr uint32_t KEYS_DONE = ~0u;       // a listed entry with nothing left to do
+static_assert(KEYS_STAGE + 2 * KEYS_GROUPS <= KEYS_LIST, "a dense block's list and table share the list's memory");
 
 struct KeysTotals {
     const unsigned long long *mark_partial;   // per k_mark block: entries, non-finite triangles
     int n_mark_partial;
     unsigned long long *shards;               // the enumeration's counter lines, cleared here
 };
+
+// The arguments of k_keys, as they lie in the kernel's argument segment.
+struct KeysArgs {
+    BatchView bv;
+    const uint32_t *both;
+    const uint64_t *rng;
+    KeysOut o;
+    KeysTotals kt;
+};
+static_assert(offsetof(KeysArgs, both) == sizeof(BatchView) && offsetof(KeysArgs, rng) == sizeof(BatchView) + 8 &&
+                  offsetof(KeysArgs, o) == sizeof(BatchView) + 16 && offsetof(KeysArgs, kt) == offsetof(KeysArgs, o) + sizeof(KeysOut),
+              "k_keys' arguments follow each other without gaps");
+
+MS_D uint64_t uniform64(uint64_t v)
+{
+    return (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(v >> 32)) << 32 |
+           (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)v);
+}
+
+template <bool ONE>
+MS_D void store_entry(const KeysOut &o, const BatchView &bv, const TileLoc &L, int64_t pos, uint64_t gc, uint32_t hh,
+                      uint32_t off, int32_t tri)
+{
+    o.ehash[pos] = hh;
+    o.eoff[pos] = (uint16_t)off;
+    o.ent[pos] = (gc << bv.kl.cell_shift) | ((uint64_t)L.side << bv.kl.tb) | (uint64_t)(uint32_t)tri;
+    if (!ONE) o.epair[pos] = L.p;
+}
+
+// A stored entry counted in its group and side; the first leaves its cell as
+// the group's sample.
+MS_D void count_entry(const KeysOut &o, int side, int64_t pos, uint64_t gc, uint32_t hh)
+{
+    const uint32_t rank = atomicAdd(&o.grp[2 * (size_t)hh + side], 1u);
+    o.erank[pos] = rank;
+    if (rank == 0) o.own[hh] = gc;
+}
+
+// The entries of a plain search's block that has more than KEYS_DENSE (crowded
+// cells: most of its triangles share a few groups): KEYS_STAGE at a time they
+// are listed, counted by groups in LDS, and ranked after one atomic a group.
+// (cnt, texcl: the thread's entries and those before them in the block.)  An
+// atomic an entry waits for the same few addresses: two propagated patches
+// (4.9 million entries) 636 us in k_keys, 185 so (the whole search 855 to
+// 690).  A block with few entries is slower with the barriers more (the
+// 256-pair family 606 us, 704 with every block here); above 512, 1024 or 2048
+// entries measured alike within 2%.  Batches of many small pairs have few
+// such blocks and lose 1.4% (14 layers: 1021 to 1036 us) to the larger kernel:
+// they keep an atomic an entry.  Not inlined, for the registers of k_keys,
+// which passes the address of its arguments (a function that is called cannot
+// ask for it).
+__device__ __attribute__((noinline)) void
+keys_dense(uint64_t args, int64_t tile, TileLoc L, uint32_t cnt, uint32_t texcl, uint32_t btotal, uint64_t blk0,
+           uint32_t *list)
+{
+    typedef __attribute__((address_space(3))) uint32_t lds_u32;
+    uint32_t *s_list = (uint32_t *)(lds_u32 *)list, *s_group = s_list + KEYS_STAGE, *s_count = s_group + KEYS_GROUPS;
+    // the same for every thread of the block
+    args = uniform64(args);
+    blk0 = uniform64(blk0);
+    tile = (int64_t)uniform64((uint64_t)tile);
+    btotal = __builtin_amdgcn_readfirstlane(btotal);
+    L.p = __builtin_amdgcn_readfirstlane(L.p);
+    L.side = __builtin_amdgcn_readfirstlane(L.side);
+    L.t0 = __builtin_amdgcn_readfirstlane(L.t0);
+    const KeysArgs &a = *(const KeysArgs *)(const __attribute__((address_space(4))) KeysArgs *)args;
+    const BatchView &bv = a.bv;
+    const KeysOut &o = a.o;
+    const uint64_t *rng = a.rng;
+    const uint16_t *lines = reinterpret_cast<const uint16_t *>(a.both);
+    const int lg = bv.bm_log2;
+    const PairDesc &P = bv.p0;
+    const MeshView &m = side_mesh(P, L.side);
+    const uint64_t cb = P.cell_base;
+    const int32_t t = L.t0 + (int32_t)threadIdx.x;
+    const int64_t g = tile * TILE_TRIS + threadIdx.x;
+#pragma unroll 1
+    for (uint32_t w0 = 0; w0 < btotal; w0 += KEYS_STAGE) {
+        __syncthreads();                     // the window before is done with the list and the table
+        for (uint32_t s = threadIdx.x; s < KEYS_GROUPS; s += KEYS_BLOCK) {
+            s_group[s] = KEYS_NONE;
+            s_count[s] = 0;
+        }
+        // this thread's entries in the window [w0, w0 + KEYS_STAGE) of the
+        // block's; the range is read again (held from above it would
+        // cost registers that the loops below need)
+        if (cnt > 0 && texcl + cnt > w0 && texcl < w0 + KEYS_STAGE) {
+            Range32 lr2;
+            range32_at(rng, g, m, t, P, lr2);
+            uint32_t k = texcl - w0;         // (wraps below the window, and is not listed there)
+            for_blocks(lr2, P.fbs, P.fbh, cb, lg, [&](const int32_t *ob, const uint32_t *pm, uint32_t line) {
+                for (uint32_t q = lines[line] & parity_cells(pm); q; q &= q - 1, ++k)
+                    if (k < KEYS_STAGE)
+                        s_list[k] = threadIdx.x | (uint32_t)__builtin_ctz(q) << 9 | (uint32_t)ob[0] << 13 |
+                                    (uint32_t)ob[1] << 17 | (uint32_t)ob[2] << 21 | (uint32_t)ob[3] << 25;
+            });
+        }
+        __syncthreads();
+        const uint32_t n = btotal - w0 < KEYS_STAGE ? btotal - w0 : KEYS_STAGE;
+        const int64_t pos0 = (int64_t)(blk0 + w0);
+#pragma unroll 1
+        for (uint32_t i = threadIdx.x; i < n; i += KEYS_BLOCK) {
+            const uint32_t w = s_list[i], tid = w & 511u;
+            s_list[i] = KEYS_DONE;
+            if (pos0 + i >= o.cap) continue;
+            Range32 rr;
+            range32_at(rng, tile * TILE_TRIS + tid, m, L.t0 + (int32_t)tid, P, rr);
+            uint32_t lin = (uint32_t)cb, off = 0;
+            uint64_t gc = cb;
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                const uint32_t b = ((uint32_t)rr.lo[d] >> 1) + ((w >> (13 + 4 * d)) & 15u);
+                const uint32_t c = 2 * b + ((w >> (12 - d)) & 1u);
+                lin += b * P.fbs[d];
+                gc += (uint64_t)c * P.st[d];
+                const uint32_t k = c - (uint32_t)rr.lo[d];
+                off |= (k < 15u ? k : 15u) << (4 * d);
+            }
+            const uint32_t hh = hash_of_product(lin * HASH_MUL, lg - 4) << 4 | (w >> 9 & 15u);
+            store_entry<true>(o, bv, L, pos0 + i, gc, hh, off, L.t0 + (int32_t)tid);
+            // the entry's group among the window's, and its rank among
+            // the window's entries of the group
+            uint32_t slot = hh * HASH_MUL >> (32 - KEYS_GROUPS_LOG2);
+            bool placed = false;
+#pragma unroll 1
+            for (int probe = 0; probe < KEYS_PROBES; ++probe) {
+                const uint32_t was = atomicCAS(&s_group[slot], KEYS_NONE, hh);
+                placed = was == KEYS_NONE || was == hh;
+                if (placed) break;
+                slot = (slot + 1) & (KEYS_GROUPS - 1);
+            }
+            if (placed) s_list[i] = slot << 16 | atomicAdd(&s_count[slot], 1u);
+            else count_entry(o, L.side, pos0 + i, gc, hh);
+        }
+        __syncthreads();
+#pragma unroll 1
+        for (uint32_t s = threadIdx.x; s < KEYS_GROUPS; s += KEYS_BLOCK) {
+            const uint32_t c = s_count[s];
+            if (c) s_count[s] = atomicAdd(&o.grp[2 * (size_t)s_group[s] + L.side], c);
+        }
+        __syncthreads();
+#pragma unroll 1
+        for (uint32_t i = threadIdx.x; i < n; i += KEYS_BLOCK) {
+            const uint32_t w = s_list[i];
+            if (w == KEYS_DONE) continue;
+            const uint32_t rank = s_count[w >> 16] + (w & 0xffffu);
+            o.erank[pos0 + i] = rank;
+            if (rank == 0) o.own[s_group[w >> 16]] = o.ent[pos0 + i] >> bv.kl.cell_shift;   // (its own store)
+        }
+    }
+}
 
 // Eight waves per SIMD (at most 64 registers): its blocks wait on dependent
 // loads and atomics, and more of them in flight are faster.
@@ -1145,7 +1305,7 @@ k_keys(BatchView bv, const uint32_t *both, const uint64_t *rng, KeysOut o, KeysT
     __shared__ uint32_t s_wave[KEYS_BLOCK / WAVE], s_far;
     __shared__ unsigned long long s_blk0;
     // entries: thread (bits 0..8), parities (9..12), block offset per axis (4 bits each from 13)
-    __shared__ uint32_t s_list[KEYS_STAGE];
+    __shared__ uint32_t s_list[KEYS_LIST];
     const int lg = bv.bm_log2, lr = bv.br_log2;
     const uint16_t *lines = reinterpret_cast<const uint16_t *>(both);
     const uint32_t *rboth = both + ((size_t)1 << lg) / 32;
@@ -1248,7 +1408,8 @@ k_keys(BatchView bv, const uint32_t *both, const uint64_t *rng, KeysOut o, KeysT
         s_blk0 = b0;
         if ((int64_t)(b0 + btotal) > o.cap) atomicOr((unsigned long long *)&o.stats->overflow, 1ull);
     }
-    if (cnt > 0 && !far && btotal <= KEYS_STAGE) {
+    constexpr uint32_t LISTED = ONE ? KEYS_DENSE : KEYS_LIST;
+    if (cnt > 0 && !far && btotal <= LISTED) {
         if constexpr (C32) {
             uint32_t k = texcl;
             if (range_small(r)) {
@@ -1285,7 +1446,7 @@ k_keys(BatchView bv, const uint32_t *both, const uint64_t *rng, KeysOut o, KeysT
         o.ent[pos] = (gc << bv.kl.cell_shift) | ((uint64_t)L.side << bv.kl.tb) | (uint64_t)(uint32_t)tri;
         if (!ONE) o.epair[pos] = L.p;
     };
-    if (C32 && btotal <= KEYS_STAGE && s_far == 0) {
+    if (C32 && btotal <= LISTED && s_far == 0) {
         for (uint32_t i = threadIdx.x; i < btotal; i += KEYS_BLOCK) {
             const uint32_t w = s_list[i], tid = w & 511u;
             Range32 rr;
@@ -1306,8 +1467,14 @@ k_keys(BatchView bv, const uint32_t *both, const uint64_t *rng, KeysOut o, KeysT
         }
         return;
     }
-    // too many entries for the list, or a range too wide for its words: each
-    // thread writes its own
+    if constexpr (ONE && C32) {
+        if (s_far == 0) {
+            keys_dense((uint64_t)__builtin_amdgcn_kernarg_segment_ptr(), tile, L, cnt, texcl, btotal, blk0, s_list);
+            return;
+        }
+    }
+    // too many entries for the list, a range too wide for its words, or cells
+    // of 64 bits: each thread writes its own entries
     if (cnt == 0) return;
     int64_t pos = (int64_t)(blk0 + texcl);
     CellRange rr;
