@@ -48,11 +48,11 @@ def algorithmic_bytes(kernel: str, st: dict, mesh_sizes) -> float | None:
     nvtot = sum(nv for _, nv in mesh_sizes)
     table = {
         "k_mark": 32.0 * nvtot + 8.0 * ntot,          # vertices read once, compact cell ranges written
-        "k_keys": 8.0 * ntot + 16.0 * E,              # cell ranges read, entries and their group ranks written
-        # entries, ranks and hashed cells read; grouped entries and their boxes written
-        "k_scatter": 88.0 * E,
-        # grouped entries, their boxes and their groups; the 6 vertices of every candidate; hit records
-        "k_enum": 72.0 * E + 24.0 * nc + 192.0 * C + 120.0 * H,
+        "k_keys": 8.0 * ntot + 18.0 * E,              # cell ranges read; entries, hashed cells, ranks, offsets written
+        # the same read; grouped entries, home bits and 16-bit boxes written
+        "k_scatter": 46.0 * E,
+        # grouped entries, home bits, boxes and their groups; the 6 vertices of every candidate; hit records
+        "k_enum": 28.0 * E + 24.0 * nc + 192.0 * C + 120.0 * H,
     }
     return table.get(kernel)
 
@@ -90,8 +90,8 @@ SEARCH_SOURCES = ("mesh.hip", "small_sort.hip", "search.hip", "predicate.hpp", "
 # The sources each kernel family is built from (counters are valid only for these).
 SOURCE_GROUPS = {
     "search": SEARCH_SOURCES,
-    "rk8": ("rk8.hip", "rk8_core.hpp", "ms_internal.hpp"),
-    "pertbp": ("pertbp.hip", "rk8.hip", "rk8_core.hpp", "ms_internal.hpp"),
+    "rk8": ("rk8.hip", "rk8_core.hpp", "rk8_pair.hpp", "ms_internal.hpp"),
+    "pertbp": ("pertbp.hip", "rk8.hip", "rk8_core.hpp", "rk8_pair.hpp", "ms_internal.hpp"),
 }
 
 
