@@ -86,7 +86,7 @@ PAIR_TEST_FLOPS = 166
 # a 16-lane SIMD for 4 cycles; 256 CUs x 4 SIMDs at 2.4 GHz.
 FP64_WAVE_INSTS_PER_S = 256 * 4 * 2.4e9 / 4
 
-SEARCH_SOURCES = ("mesh.hip", "small_sort.hip", "search.hip", "predicate.hpp", "ms_internal.hpp")
+SEARCH_SOURCES = ("mesh.hip", "small_sort.hip", "search.hip", "predicate.hpp", "tile_sum.hpp", "ms_internal.hpp")
 # The sources each kernel family is built from (counters are valid only for these).
 SOURCE_GROUPS = {
     "search": SEARCH_SOURCES,

@@ -45,6 +45,7 @@
 
 #include "ms_internal.hpp"
 #include "predicate.hpp"
+#include "tile_sum.hpp"
 
 namespace ms {
 
@@ -1301,8 +1302,8 @@ template <bool ONE, bool C32>
 __global__ void __launch_bounds__(KEYS_BLOCK) __attribute__((amdgpu_waves_per_eu(8, 8)))
 k_keys(BatchView bv, const uint32_t *both, const uint64_t *rng, KeysOut o, KeysTotals kt)
 {
-    __shared__ uint64_t s_tmp[KEYS_BLOCK / WAVE];
-    __shared__ uint32_t s_wave[KEYS_BLOCK / WAVE], s_far;
+    __shared__ uint64_t s_wave[KEYS_BLOCK / WAVE];
+    __shared__ uint32_t s_far;
     __shared__ unsigned long long s_blk0;
     // entries: thread (bits 0..8), parities (9..12), block offset per axis (4 bits each from 13)
     __shared__ uint32_t s_list[KEYS_LIST];
@@ -1329,8 +1330,8 @@ k_keys(BatchView bv, const uint32_t *both, const uint64_t *rng, KeysOut o, KeysT
                     bad += b[u];
                 }
             }
-            all = block_sum<KEYS_BLOCK>(all, (unsigned long long *)s_tmp);
-            bad = block_sum<KEYS_BLOCK>(bad, (unsigned long long *)s_tmp);
+            all = block_sum<KEYS_BLOCK>(all, (unsigned long long *)s_wave);
+            bad = block_sum<KEYS_BLOCK>(bad, (unsigned long long *)s_wave);
             if (threadIdx.x == 0) {
                 o.stats->n_entries_all = (int64_t)all;
                 o.stats->n_nonfinite = (int64_t)bad;
@@ -1364,18 +1365,22 @@ k_keys(BatchView bv, const uint32_t *both, const uint64_t *rng, KeysOut o, KeysT
                     small = small_both(lines, lg, r, P.fbs, P.fbh, cb, std::make_integer_sequence<int, 16>{});
                     cnt = (uint32_t)__builtin_popcount(small);
                 } else {
+                    uint64_t n = 0;
                     for_blocks(r, P.fbs, P.fbh, cb, lg, [&](const int32_t *, const uint32_t *pm, uint32_t line) {
-                        cnt += (uint32_t)__builtin_popcount(lines[line] & parity_cells(pm));
+                        n += (uint64_t)__builtin_popcount(lines[line] & parity_cells(pm));
                     });
+                    cnt = tile_count(n);
                     far = cnt > 0 && (r.e[0] | r.e[1] | r.e[2] | r.e[3]) > 15;
                 }
             }
         } else {
             CellRange rr;
+            uint64_t n = 0;
             if (range_at(rng, g, m, t, P.g, rr))
                 for_cells_xy(rr, P.g.n, [&](const int64_t *c, uint64_t) {
-                    cnt += occ_bit(both, blocked_index(c, P.fbs, cb, lg));
+                    n += occ_bit(both, blocked_index(c, P.fbs, cb, lg));
                 });
+            cnt = tile_count(n);
             far = cnt > 0;
         }
     }
@@ -1383,31 +1388,30 @@ k_keys(BatchView bv, const uint32_t *both, const uint64_t *rng, KeysOut o, KeysT
     const int lane = lane_id(), wv = threadIdx.x / WAVE;
     const uint64_t some = ballot(cnt > 0);
     uint32_t inc = 0;
+    uint64_t wtotal = 0;                          // (the last lane's counts)
     if (some) {
         inc = cnt;
         for (int o = 1; o < WAVE; o <<= 1) {
             const uint32_t y = __shfl_up(inc, o);
             if (lane >= o) inc += y;
         }
+        wtotal = inc;
+        if (ballot(cnt >= TILE_WIDE)) wtotal = wave_sum_u64(cnt);
     }
-    if (lane == WAVE - 1) s_wave[wv] = inc;
+    if (lane == WAVE - 1) s_wave[wv] = wtotal;
     if (threadIdx.x == 0) s_far = 0;
     __syncthreads();
-    uint32_t before = 0, btotal = 0;
-#pragma unroll
-    for (int i = 0; i < KEYS_BLOCK / WAVE; ++i) {
-        const uint32_t v = s_wave[i];
-        if (i < wv) before += v;
-        btotal += v;
-    }
-    if (btotal == 0) return;                      // uniform: every thread saw the same total
-    const uint32_t texcl = before + inc - cnt;
-    if (far) s_far = 1;
+    uint32_t before;
+    const uint64_t total = tile_total<KEYS_BLOCK / WAVE>(s_wave, wv, before);
+    if (total == 0) return;                       // uniform: every thread saw the same total
     if (threadIdx.x == 0) {
-        const unsigned long long b0 = atomicAdd(o.n_keys, (unsigned long long)btotal);
+        const unsigned long long b0 = atomicAdd(o.n_keys, (unsigned long long)total);
         s_blk0 = b0;
-        if ((int64_t)(b0 + btotal) > o.cap) atomicOr((unsigned long long *)&o.stats->overflow, 1ull);
+        if ((int64_t)(b0 + total) > o.cap) atomicOr((unsigned long long *)&o.stats->overflow, 1ull);
     }
+    if (!tile_placed(total)) return;              // (no workspace holds so many: the overflow is set)
+    const uint32_t btotal = (uint32_t)total, texcl = before + inc - cnt;
+    if (far) s_far = 1;
     constexpr uint32_t LISTED = ONE ? KEYS_DENSE : KEYS_LIST;
     if (cnt > 0 && !far && btotal <= LISTED) {
         if constexpr (C32) {
