@@ -111,6 +111,10 @@ MS_D void ref_flow(const RefArgs &a, int side, bool live, int64_t s0, int64_t s1
 {
     constexpr int D = flow_dim<PAIR, COL>(), N = RF_CHUNK * S, PER = (N + RF_BLOCK - 1) / RF_BLOCK;
     __shared__ double s_w[N], s_d[COL ? N : 1];
+    // A wave whose hits are all done (the block is one wave) leaves at once:
+    // the refinement queues all its passes in advance, and one that goes
+    // through the chunks of 12,000 steps without a step takes 274 us, not 4.
+    if (ballot(live) == 0) return;
     const SideMap &sm = a.side[side];
     const int64_t tot = (int64_t)sm.steps * S;
     const double ec = ecol ? 1.0 : 0.0;
