@@ -88,11 +88,16 @@ MS_D bool hit_active(const RefArgs &a, int64_t k) { return a.status == nullptr |
 // every thread.
 MS_D CoefPtr side_coef(int side) { return step_coef() + side * RK_NC; }
 
-// Hits up to which trajectories run on pairs of lanes (one wave per SIMD then
-// holds them all: 12,000 steps in 9.1 ms, 16 ms with one lane each); the rule
-// depends on K alone, so that the forward pass and the adjoint's
-// recomputation run the same code.
-constexpr int64_t PAIR_HITS = 16384;
+// Hits up to which trajectories run on pairs of lanes: those whose waves have
+// a SIMD each (1,024 waves of 32 pairs, and two trajectories a hit; with the
+// tangents' three columns, six).  The state pass then takes 9.1 ms for 12,000
+// steps, 16 with one lane each, and the tangent pass 1.52 us a step against
+// 1.9; with a second wave on a SIMD pairs take longer than one lane a column
+// (8,192 hits: 1,062 us for 400 steps against 820).  The rules
+// depend on K alone, so that the forward pass and the adjoint's recomputation
+// run the same code.
+constexpr int64_t PAIR_HITS = 1024 * 32 / 2;
+constexpr int64_t PAIR_TANGENT_HITS = 1024 * 32 / 6;
 
 // Steps [s0, s1) of a trajectory, on a block of one wave: of the state alone
 // (COL = false) or of the state and one tangent column (the variational
@@ -593,7 +598,7 @@ unsigned blocks_for(int64_t n) { return (unsigned)ceil_div(n > 0 ? n : 1, RF_BLO
 
 void launch_tangent(const RefArgs &a, hipStream_t st)
 {
-    if (a.K <= PAIR_HITS)
+    if (a.K <= PAIR_TANGENT_HITS)
         MS_LAUNCH("k_ref_tangent", k_ref_tangent<true>, dim3(blocks_for(6 * a.K), 2), dim3(RF_BLOCK), 0, st, a);
     else
         MS_LAUNCH("k_ref_tangent", k_ref_tangent<false>, dim3(blocks_for(3 * a.K), 2), dim3(RF_BLOCK), 0, st, a);
