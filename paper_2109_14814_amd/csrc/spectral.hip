@@ -361,15 +361,10 @@ constexpr int IP_MAX_BINS = 8192;
 constexpr uint32_t IP_START = 0x1ffff;    // a bin's word: start (17 bits; all ones: too large), rank from bit 17
 
 // One query by the barycentric form with a sine and cosine per sample, by
-// one wave: any theta, any N.
-MS_D void interp_one(const double *a, int N, double th, double *o)
+// one wave: any offset delta from sample i0, any N.
+MS_D void interp_one(const double *a, int N, int64_t i0, double delta, double *o)
 {
     const int lane = threadIdx.x % 64;
-    const double step = 2.0 * SP_PI / (double)N;
-    const double i0f = rint(th / step);
-    const double delta = th - i0f * step;
-    int64_t i0 = (int64_t)fmod(i0f, (double)N);   // exact, in (-N, N)
-    if (i0 < 0) i0 += N;
     const bool even = (N & 1) == 0;
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
     for (int i = lane; i < N; i += 64) {
@@ -416,13 +411,14 @@ __global__ void __launch_bounds__(256) k_theta_interp_plain(const double *in, in
         return;
     }
     const double *a = in + row * (int64_t)N * 4;
-    if (fabs(th - i0f * step) < 1e-200) {
-        int64_t i0 = (int64_t)fmod(i0f, (double)N);
-        if (i0 < 0) i0 += N;
+    const double delta = th - i0f * step;
+    int64_t i0 = (int64_t)fmod(i0f, (double)N);   // exact, in (-N, N)
+    if (i0 < 0) i0 += N;
+    if (fabs(delta) < 1e-200) {
         if (lane < 4) o[lane] = a[4 * i0 + lane];
         return;
     }
-    interp_one(a, N, th, o);
+    interp_one(a, N, i0, delta, o);
 }
 
 MS_D double uni(double x)
@@ -444,18 +440,16 @@ struct IpList {
     uint32_t n_tiles, unsorted;
 };
 
-// 1 / d[i] of four values of ordinary size with one reciprocal.
-MS_D void recip4(const double d[4], double r[4])
+// n / d for d of ordinary size: the hardware reciprocal (about 23 correct
+// bits) and one cubic correction of the quotient.  Every weight has its own:
+// with one reciprocal for four (138 us for 65536 queries in 4096 rows of 2048
+// samples, 143 so) a query's last bits depend on the queries beside it, and so on the
+// order in which the grouping takes them.
+MS_D double quotient(double n, double d)
 {
-    const double p01 = d[0] * d[1], p23 = d[2] * d[3], p = p01 * p23;
-    double x = __builtin_amdgcn_rcp(p);
-    const double e = fma(-p, x, 1.0);
-    x = fma(x, fma(e, e, e), x);
-    const double a = x * p23, b = x * p01;
-    r[0] = a * d[1];
-    r[1] = a * d[0];
-    r[2] = b * d[3];
-    r[3] = b * d[2];
+    const double y = __builtin_amdgcn_rcp(d);
+    const double e = fma(-d, y, 1.0), t = n * y;
+    return fma(t, fma(e, e, e), t);
 }
 
 // QT queries of one row, U samples per lane and step (QT U = 4): with
@@ -491,7 +485,7 @@ MS_D void interp_tile(const IpList &s, int e0, int len, const double *tab, const
     const double *a = in + 4 * (int64_t)((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)row) |
                                          (uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(row >> 32)) << 32) * N;
     double acc[4 * QT] = {};
-    double num[4], den[4], r[4];
+    double num[4], den[4];
     auto entry = [&](int j, int q, int k) {
         if constexpr (ODD) {
             const double2 c = reinterpret_cast<const double2 *>(tab)[k];
@@ -531,9 +525,8 @@ MS_D void interp_tile(const IpList &s, int e0, int len, const double *tab, const
                 load(w, U * (k + 1 < stop ? k + 1 : k));       // the next step's, in flight over this one
 #pragma unroll
                 for (int j = 0; j < 4; ++j) entry(j, j / U, x[j / U] + 64 * (j % U));
-                recip4(den, r);
 #pragma unroll
-                for (int j = 0; j < 4; ++j) num[j] *= r[j];
+                for (int j = 0; j < 4; ++j) num[j] = quotient(num[j], den[j]);
                 add(v);
 #pragma unroll
                 for (int q = 0; q < QT; ++q) x[q] += 64 * U;
@@ -552,11 +545,10 @@ MS_D void interp_tile(const IpList &s, int e0, int len, const double *tab, const
             const int i = i_first + 64 * (j % U), d = i - i0[j / U];
             entry(j, j / U, i >= N ? 0 : d < 0 ? d + N : d);
         }
-        recip4(den, r);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int q = j / U, i = i_first + 64 * (j % U);
-            num[j] = i == i0[q] ? (ODD ? -1.0 : 1.0) / t[q] : num[j] * r[j];
+            num[j] = i == i0[q] ? (ODD ? -1.0 : 1.0) / t[q] : quotient(num[j], den[j]);
             if (ODD && i < i0[q] && i_last >= i0[q]) num[j] = -num[j];
         }
 #pragma unroll
@@ -619,11 +611,12 @@ struct InterpArgs {
 // place in the slice, so that a block has at most three shares whatever the
 // rows are.
 //
-// 65536 queries in 4096 rows of 2048 samples: 137 us, from 555 with a wave
+// 65536 queries in 4096 rows of 2048 samples: 143 us, from 555 with a wave
 // per query and a sine, cosine and division per sample (about 100 FP64
-// instructions, now 13), which read the rows 16 times.  Without the grouping
-// 614: the rows' bytes bound it.  Now 25 us go to the grouping, 8 to the table
-// and the offsets, the rest to the sums, at about half the FP64 rate.  Four
+// instructions, now 12 and a reciprocal), which read the rows 16 times.
+// Without the grouping 614: the rows' bytes bound it.  Now 25 us go to the
+// grouping, 8 to the table and the offsets, the rest to the sums, at about
+// half the FP64 rate.  Four
 // queries in flight with their next samples take the 128 registers of four
 // waves per SIMD; a wave's two scalar steps cost as much as four others.
 template <bool ODD, bool GROUPED>
@@ -844,7 +837,12 @@ __global__ void __launch_bounds__(IP_BLOCK) k_theta_interp(InterpArgs g)
         if (len > 2) interp_tile<ODD, 4>(s, e, len, s_dyn, g.in, N, out);
         else if (len == 2) interp_tile<ODD, 2>(s, e, len, s_dyn, g.in, N, out);
         else if (len == 1) interp_tile<ODD, 1>(s, e, len, s_dyn, g.in, N, out);
-        else interp_one(g.in + s.row[e] * (int64_t)N * 4, N, g.theta[q0 + s.q[e]], out + 4 * (int64_t)s.q[e]);
+        else {
+            const double th = g.theta[q0 + s.q[e]], i0f = rint(th / step);
+            int64_t i0 = (int64_t)fmod(i0f, (double)N);
+            if (i0 < 0) i0 += N;
+            interp_one(g.in + s.row[e] * (int64_t)N * 4, N, i0, th - i0f * step, out + 4 * (int64_t)s.q[e]);
+        }
     }
 }
 
