@@ -27,7 +27,7 @@
 // phase.hpp.
 //
 // 4096 rows of 2048, 268 MB read and as many written, which a copy does in
-// 109 us: 140 us from 185 with both sequences in 72 KB, a sine and cosine per
+// 109 us: 135 us from 185 with both sequences in 72 KB, a sine and cosine per
 // coefficient and one table of N factors gathered at strides (which alone
 // cost 25); with four workgroups on a CU the 128 registers spill: 167.  The
 // spectrum alone takes 108, from 130.  4096 rows of 64, 32 rows to a
@@ -164,7 +164,7 @@ using Regs = double2[2][per_thread<N>()];
 // registers.  Butterfly j holds element j + r N/R (r = 0..R-1), twiddles it by
 // e^{-+2 pi i r (j mod Ns) / (Ns R)} (entry (r - 1) Ns + (j mod Ns) of the pass's
 // table, conjugated for the inverse) and transforms.
-template <int N, int R, int Ns, bool INV>
+template <bool FEW, int N, int R, int Ns, bool INV>
 MS_D void butterflies(Regs<N> &v, int t, const double2 *__restrict__ tw)
 {
     constexpr int T = row_threads<N>();
@@ -186,7 +186,8 @@ MS_D void butterflies(Regs<N> &v, int t, const double2 *__restrict__ tw)
                 for (int r = 1; r < R; ++r) v[s][q * R + r] = cmul(v[s][q * R + r], w[r]);
             }
             small_dft<R, INV>(v[s] + q * R);
-            __builtin_amdgcn_sched_barrier(0);      // one sequence's butterfly at a time in the registers
+            // one sequence's butterfly at a time in the registers
+            if constexpr (!FEW) __builtin_amdgcn_sched_barrier(0);
         }
     }
 }
@@ -201,81 +202,103 @@ MS_D int element(int t, int i)
 }
 
 // From the places of a pass (R, Ns) to the inputs of the next, of radix R2.
-template <int N, int R, int Ns, int R2>
+// FEW: both sequences at once, z holds room for two; the threads beyond the
+// row's have no part in it.
+template <bool FEW, int N, int R, int Ns, int R2>
 MS_D void exchange(Regs<N> &v, int t, double2 *z)
 {
-    constexpr int E = per_thread<N>(), T = row_threads<N>();
+    constexpr int E = per_thread<N>(), T = row_threads<N>(), STEP = FEW ? padded_size<N>() : 0;
+    const bool on = !FEW || (int)threadIdx.x < T;
+    auto put = [&](int s) {
+        if (!on) return;
 #pragma unroll
-    for (int s = 0; s < 2; ++s) {
-        if (s) __syncthreads();
+        for (int i = 0; i < E; ++i) z[s * STEP + pslot(element<N, R, Ns>(t, i))] = v[s][i];
+    };
+    auto get = [&](int s) {
+        if (!on) return;
 #pragma unroll
-        for (int i = 0; i < E; ++i) z[pslot(element<N, R, Ns>(t, i))] = v[s][i];
+        for (int i = 0; i < E; ++i) v[s][i] = z[s * STEP + pslot(t + i / R2 * T + i % R2 * (N / R2))];
+    };
+    put(0);
+    if constexpr (FEW) put(1);
+    __syncthreads();
+    get(0);
+    if constexpr (!FEW) {
         __syncthreads();
-#pragma unroll
-        for (int i = 0; i < E; ++i) v[s][i] = z[pslot(t + i / R2 * T + i % R2 * (N / R2))];
+        put(1);
+        __syncthreads();
     }
+    get(1);
+}
+
+template <int N>
+MS_D double frequency(int k) { return 2 * k > N ? (double)(k - N) : (double)k; }
+
+template <int N>
+MS_D double2 row_phase(int k, double rho)
+{
+    double sn, cs;
+    sincos(frequency<N>(k) * rho, &sn, &cs);
+    return make_double2(cs, sn);
 }
 
 // The multiplier at the coefficients that the last forward pass (radix R,
 // Ns = N / R: coefficient j + r N/R) leaves in the registers.  z: the row's
-// LDS, where the thread's own inputs of that pass are free.
-template <int N, int R>
-MS_D void multiply(Regs<N> &v, int t, const PhaseTable &ph, double rho, int order, double2 *z)
+// LDS, where the thread's own inputs of that pass are free.  FEW: the phases
+// are in z, one of each coefficient.
+template <bool FEW, int N, int R>
+MS_D void multiply(Regs<N> &v, int t, const PhaseTable *ph, double rho, int order, double2 *z)
 {
     constexpr int E = per_thread<N>(), T = row_threads<N>();
     auto coef = [&](int i) { return t + i / R * T + i % R * (N / R); };
-    auto freq = [&](int k) { return 2 * k > N ? (double)(k - N) : (double)k; };
-    const bool near = fabs(rho) * (0.5 * N) < PH_MAX;
-    if (!near) {
+    const bool near = !FEW && fabs(rho) * (0.5 * N) < PH_MAX;
+    if (!FEW && !near) {
 #pragma nounroll
-        for (int i = 0; i < E; ++i) {
-            double sn, cs;
-            sincos(freq(coef(i)) * rho, &sn, &cs);
-            z[pslot(coef(i))] = make_double2(cs, sn);
-        }
+        for (int i = 0; i < E; ++i) z[pslot(coef(i))] = row_phase<N>(coef(i), rho);
     }
 #pragma unroll
     for (int i = 0; i < E; ++i) {
         const int k = coef(i);
-        const double ks = freq(k);
+        const double ks = frequency<N>(k);
         double2 m;
-        if (near) phase_near(ph, ks * rho, m.x, m.y);
-        else m = z[pslot(k)];
+        if (near) phase_near(*ph, ks * rho, m.x, m.y);
+        else m = z[FEW ? k : pslot(k)];
         if (order == 1) m = make_double2(-ks * m.y, ks * m.x);
         else if (order == 2) m = make_double2(-ks * ks * m.x, -ks * ks * m.y);
         // the cosine mode: Re[(j N/2)^order e^{j (N/2) rho}]
         if (2 * k == N) m.y = 0.0;
         v[0][i] = cmul(v[0][i], m);
         v[1][i] = cmul(v[1][i], m);
-        __builtin_amdgcn_sched_barrier(0);      // (eight phases at a time do not fit the registers)
+        // (eight phases at a time do not fit the registers)
+        if constexpr (!FEW) __builtin_amdgcn_sched_barrier(0);
     }
 }
 
 // Forward passes P.. up to the last.
-template <int LOGN, int P>
+template <bool FEW, int LOGN, int P>
 MS_D void forward_passes(Regs<1 << LOGN> &v, int t, const double2 *tw, double2 *z)
 {
     using PL = Plan<LOGN>;
     constexpr int N = 1 << LOGN, R = PL::radix(P), NS = PL::ns_fwd(P), TW = PL::tw_fwd(P);
-    butterflies<N, R, NS, false>(v, t, tw + TW);
+    butterflies<FEW, N, R, NS, false>(v, t, tw + TW);
     if constexpr (P < PL::NP - 1) {
         if constexpr (P > 0) __syncthreads();
-        exchange<N, R, NS, PL::radix(P + 1)>(v, t, z);
-        forward_passes<LOGN, P + 1>(v, t, tw, z);
+        exchange<FEW, N, R, NS, PL::radix(P + 1)>(v, t, z);
+        forward_passes<FEW, LOGN, P + 1>(v, t, tw, z);
     }
 }
 
 // Inverse passes P.. up to the last (the inputs in place).
-template <int LOGN, int P>
+template <bool FEW, int LOGN, int P>
 MS_D void inverse_passes(Regs<1 << LOGN> &v, int t, const double2 *tw, double2 *z)
 {
     using PL = Plan<LOGN>;
     constexpr int N = 1 << LOGN, R = PL::radix_inv(P), NS = PL::ns_inv(P), TW = PL::tw_inv(P);
-    butterflies<N, R, NS, true>(v, t, tw + TW);
+    butterflies<FEW, N, R, NS, true>(v, t, tw + TW);
     if constexpr (P < PL::NP - 1) {
         __syncthreads();
-        exchange<N, R, NS, PL::radix_inv(P + 1)>(v, t, z);
-        inverse_passes<LOGN, P + 1>(v, t, tw, z);
+        exchange<FEW, N, R, NS, PL::radix_inv(P + 1)>(v, t, z);
+        inverse_passes<FEW, LOGN, P + 1>(v, t, tw, z);
     }
 }
 
@@ -305,48 +328,69 @@ MS_D void store_row(const Regs<N> &v, int t, double *dst)
     }
 }
 
+// A workgroup's rows and threads, and the LDS of a row.  FEW, for the few rows
+// that do not fill the chip, where a row's chain of waits is the time: one row
+// a workgroup, both sequences side by side in LDS, which halves the waits
+// between the passes, and up to 256 threads, of which those beyond the row's
+// only take their share of the phases' sines and cosines.
+template <int N, bool FEW>
+constexpr int group_rows() { return FEW ? 1 : block_rows<N>(); }
+template <int N, bool FEW>
+constexpr int group_threads() { return !FEW || N >= 512 ? SP_THREADS : N >= 128 ? N / 2 : 64; }
+template <int N, bool FEW>
+constexpr int row_slots() { return (FEW ? 2 : 1) * padded_size<N>(); }
+
 // row_map (optional): output row of each input row; a negative entry drops
 // the row.
-template <int LOGN>
-__global__ void __launch_bounds__(SP_THREADS) __attribute__((amdgpu_waves_per_eu(3)))
+template <int LOGN, bool FEW>
+__global__ void __launch_bounds__(SP_THREADS) __attribute__((amdgpu_waves_per_eu(FEW ? 1 : 3)))
 k_theta_shift(const double *in, double *out, const double2 *__restrict__ tw, const double *rho_dev, double rho, int order,
               const int64_t *row_map, int64_t n_rows)
 {
     using PL = Plan<LOGN>;
     constexpr int N = 1 << LOGN, T = row_threads<N>(), RM = PL::radix(PL::NP - 1);
-    __shared__ double2 s_z[block_rows<N>()][padded_size<N>()];
-    __shared__ PhaseTable s_ph;
-    const int t = threadIdx.x % T;
-    const int64_t row = (int64_t)blockIdx.x * block_rows<N>() + threadIdx.x / T;
-    double2 *z = s_z[threadIdx.x / T];
+    __shared__ double2 s_z[group_rows<N, FEW>()][row_slots<N, FEW>()];
+    const int t = threadIdx.x % T, own = FEW ? 0 : threadIdx.x / T;
+    const int64_t row = (int64_t)blockIdx.x * group_rows<N, FEW>() + own;
+    double2 *z = s_z[own];
     const int64_t orow = row >= n_rows ? -1 : row_map ? row_map[row] : row;
-    const bool live = orow >= 0;
-    phase_table(s_ph);
+    const bool live = orow >= 0 && (!FEW || (int)threadIdx.x < T);
     Regs<N> v;
-    load_row<N, PL::radix(0)>(v, t, in + row * (int64_t)N * 4, live);
-    const double r = live ? (rho_dev ? rho_dev[row] : rho) : 0.0;
-    forward_passes<LOGN, 0>(v, t, tw, z);
-    if constexpr (PL::NP == 1) __syncthreads();      // the phases' table
-    multiply<N, RM>(v, t, s_ph, r, order, z);
-    inverse_passes<LOGN, 0>(v, t, tw, z);
+    const double r = orow >= 0 ? (rho_dev ? rho_dev[row] : rho) : 0.0;
+    if constexpr (FEW) {
+        __shared__ double2 s_ph[N];
+        load_row<N, PL::radix(0)>(v, t, in + row * (int64_t)N * 4, live);
+        for (int k = threadIdx.x; k < N; k += group_threads<N, FEW>()) s_ph[k] = row_phase<N>(k, r);
+        forward_passes<FEW, LOGN, 0>(v, t, tw, z);
+        if constexpr (PL::NP == 1) __syncthreads();
+        multiply<FEW, N, RM>(v, t, nullptr, r, order, s_ph);
+    } else {
+        __shared__ PhaseTable s_ph;
+        phase_table(s_ph);
+        load_row<N, PL::radix(0)>(v, t, in + row * (int64_t)N * 4, live);
+        forward_passes<FEW, LOGN, 0>(v, t, tw, z);
+        if constexpr (PL::NP == 1) __syncthreads();      // the phases' table
+        multiply<FEW, N, RM>(v, t, &s_ph, r, order, z);
+    }
+    inverse_passes<FEW, LOGN, 0>(v, t, tw, z);
     if (live) store_row<N, PL::radix_inv(PL::NP - 1), PL::ns_inv(PL::NP - 1)>(v, t, out + orow * (int64_t)N * 4);
 }
 
 // Forward transform only: out(r, j) = (Z0(j), Z1(j)) / N in natural order,
 // four doubles per frequency (Re Z0, Im Z0, Re Z1, Im Z1), the layout of the
 // input rows.
-template <int LOGN>
-__global__ void __launch_bounds__(SP_THREADS) __attribute__((amdgpu_waves_per_eu(4)))
+template <int LOGN, bool FEW>
+__global__ void __launch_bounds__(SP_THREADS) __attribute__((amdgpu_waves_per_eu(FEW ? 1 : 4)))
 k_theta_spectrum(const double *in, double *out, const double2 *__restrict__ tw, int64_t n_rows)
 {
     using PL = Plan<LOGN>;
     constexpr int N = 1 << LOGN, T = row_threads<N>();
-    __shared__ double2 s_z[block_rows<N>()][padded_size<N>()];
+    __shared__ double2 s_z[group_rows<N, FEW>()][row_slots<N, FEW>()];
     const int t = threadIdx.x % T;
-    const int64_t row = (int64_t)blockIdx.x * block_rows<N>() + threadIdx.x / T;
+    const int64_t row = (int64_t)blockIdx.x * group_rows<N, FEW>() + threadIdx.x / T;
     Regs<N> v;
     load_row<N, PL::radix(0)>(v, t, in + row * (int64_t)N * 4, row < n_rows);
-    forward_passes<LOGN, 0>(v, t, tw, s_z[threadIdx.x / T]);
+    forward_passes<FEW, LOGN, 0>(v, t, tw, s_z[threadIdx.x / T]);
     if (row < n_rows) store_row<N, PL::radix(PL::NP - 1), PL::ns_fwd(PL::NP - 1)>(v, t, out + row * (int64_t)N * 4);
 }
 
@@ -901,43 +945,75 @@ struct ShiftArgs {
     int64_t n_rows;
 };
 
-template <int LOGN>
+template <int LOGN, bool FEW>
 int launch_shift(const ShiftArgs &a, hipStream_t st)
 {
+    constexpr int N = 1 << LOGN;
     const double2 *tw = nullptr;
     if (int rc = twiddles<LOGN>(&tw)) return rc;
-    const dim3 grid((unsigned)ceil_div(a.n_rows, (int64_t)block_rows<1 << LOGN>()));
-    hipLaunchKernelGGL(k_theta_shift<LOGN>, grid, dim3(SP_THREADS), 0, st, a.in, a.out, tw, a.rho_dev, a.rho, a.order,
-                       a.row_map, a.n_rows);
+    const dim3 grid((unsigned)ceil_div(a.n_rows, (int64_t)group_rows<N, FEW>()));
+    hipLaunchKernelGGL((k_theta_shift<LOGN, FEW>), grid, dim3(group_threads<N, FEW>()), 0, st, a.in, a.out, tw, a.rho_dev,
+                       a.rho, a.order, a.row_map, a.n_rows);
     MS_HIP(hipGetLastError());
     return MS_OK;
 }
 
-template <int LOGN>
+template <int LOGN, bool FEW>
 int launch_spectrum(const ShiftArgs &a, hipStream_t st)
 {
+    constexpr int N = 1 << LOGN;
     const double2 *tw = nullptr;
     if (int rc = twiddles<LOGN>(&tw)) return rc;
-    const dim3 grid((unsigned)ceil_div(a.n_rows, (int64_t)block_rows<1 << LOGN>()));
-    hipLaunchKernelGGL(k_theta_spectrum<LOGN>, grid, dim3(SP_THREADS), 0, st, a.in, a.out, tw, a.n_rows);
+    const dim3 grid((unsigned)ceil_div(a.n_rows, (int64_t)group_rows<N, FEW>()));
+    hipLaunchKernelGGL((k_theta_spectrum<LOGN, FEW>), grid, dim3(FEW ? row_threads<N>() : SP_THREADS), 0, st, a.in, a.out, tw,
+                       a.n_rows);
     MS_HIP(hipGetLastError());
     return MS_OK;
 }
 
 typedef int (*RowsLaunch)(const ShiftArgs &, hipStream_t);
 constexpr RowsLaunch SHIFT_OF[SP_MAX_LOG2 + 1] = {
-    nullptr, launch_shift<1>, launch_shift<2>, launch_shift<3>, launch_shift<4>, launch_shift<5>,
-    launch_shift<6>, launch_shift<7>, launch_shift<8>, launch_shift<9>, launch_shift<10>, launch_shift<11>};
+    nullptr, launch_shift<1, false>, launch_shift<2, false>, launch_shift<3, false>, launch_shift<4, false>,
+    launch_shift<5, false>, launch_shift<6, false>, launch_shift<7, false>, launch_shift<8, false>,
+    launch_shift<9, false>, launch_shift<10, false>, launch_shift<11, false>};
 constexpr RowsLaunch SPECTRUM_OF[SP_MAX_LOG2 + 1] = {
-    nullptr, launch_spectrum<1>, launch_spectrum<2>, launch_spectrum<3>, launch_spectrum<4>, launch_spectrum<5>,
-    launch_spectrum<6>, launch_spectrum<7>, launch_spectrum<8>, launch_spectrum<9>, launch_spectrum<10>,
-    launch_spectrum<11>};
+    nullptr, launch_spectrum<1, false>, launch_spectrum<2, false>, launch_spectrum<3, false>, launch_spectrum<4, false>,
+    launch_spectrum<5, false>, launch_spectrum<6, false>, launch_spectrum<7, false>, launch_spectrum<8, false>,
+    launch_spectrum<9, false>, launch_spectrum<10, false>, launch_spectrum<11, false>};
+
+// Up to three rows a CU go one to a workgroup (see group_rows), all in flight
+// at once; more share workgroups.  theta_shift of 50 rows of 64, 256 and 1024:
+// 4.6, 6.4 and 9.1 us (shared: 6.5, 9.2 and 11.6), of 768 rows 5.8, 9.3 and 20.5
+// (6.8, 10.7 and 23), of 2000 rows of 256: 17.6 (15.4); the spectrum of 200
+// rows of 8, 128 and 512: 2.4, 4.1 and 4.6 us (4.8, 5.3 and 6.0).  Up to twice
+// as many where a shared workgroup is a long chain (the shortest rows, a thread
+// each; 1000 rows of 8: 5.4 us against 7.5) or a small part of the chip (1000 rows
+// of 128 and 256: 7.8 and 10.4 against 9.8 and 11.6; of 512: 17 against 15).
+// Rows of 2048 have all of a workgroup's threads either way (50 rows: 12.6 us,
+// 12.1).
+constexpr int64_t FEW_ROWS = 768, FEW_SAMPLES = 1 << 18;
+constexpr int FEW_MAX_LOG2 = 10;
+constexpr RowsLaunch SHIFT_FEW[FEW_MAX_LOG2 + 1] = {
+    nullptr, launch_shift<1, true>, launch_shift<2, true>, launch_shift<3, true>, launch_shift<4, true>,
+    launch_shift<5, true>, launch_shift<6, true>, launch_shift<7, true>, launch_shift<8, true>, launch_shift<9, true>,
+    launch_shift<10, true>};
+constexpr RowsLaunch SPECTRUM_FEW[FEW_MAX_LOG2 + 1] = {
+    nullptr, launch_spectrum<1, true>, launch_spectrum<2, true>, launch_spectrum<3, true>, launch_spectrum<4, true>,
+    launch_spectrum<5, true>, launch_spectrum<6, true>, launch_spectrum<7, true>, launch_spectrum<8, true>,
+    launch_spectrum<9, true>, launch_spectrum<10, true>};
+
+RowsLaunch rows_launch(const RowsLaunch *many, const RowsLaunch *few, int n_theta, int64_t n_rows)
+{
+    const int lg = __builtin_ctz(n_theta);
+    const bool twice = n_theta <= 8 || (n_theta >= 128 && n_rows * n_theta <= FEW_SAMPLES);
+    return lg <= FEW_MAX_LOG2 && n_rows <= (twice ? 2 * FEW_ROWS : FEW_ROWS) ? few[lg] : many[lg];
+}
 
 // theta_shift on validated arguments (n_theta a power of two in range).
 int shift_rows(const double *in, double *out, int n_theta, int64_t n_rows, const double *rho_dev, double rho,
                int order, const int64_t *row_map, hipStream_t st)
 {
-    return SHIFT_OF[__builtin_ctz(n_theta)]({in, out, rho_dev, rho, order, row_map, n_rows}, st);
+    return rows_launch(SHIFT_OF, SHIFT_FEW, n_theta, n_rows)({in, out, rho_dev, rho, order, row_map, n_rows}, st);
 }
 
 // Row copies through a row map (negative entries dropped): the unshifted
@@ -1033,7 +1109,8 @@ extern "C" int theta_spectrum(const double *in_dev, double *out_dev, int32_t n_t
         return fail(MS_E_ARG, "theta_spectrum: n_theta must be a power of two in [2, 2048]");
     if (n_rows > 0x7fffffff) return fail(MS_E_ARG, "theta_spectrum: too many rows for one launch");
     if (n_rows == 0) return MS_OK;
-    return SPECTRUM_OF[__builtin_ctz(n_theta)]({in_dev, out_dev, nullptr, 0.0, 0, nullptr, n_rows}, (hipStream_t)stream);
+    return rows_launch(SPECTRUM_OF, SPECTRUM_FEW, n_theta, n_rows)({in_dev, out_dev, nullptr, 0.0, 0, nullptr, n_rows},
+                                                                   (hipStream_t)stream);
 }
 
 extern "C" int theta_shift(const double *in_dev, double *out_dev, int32_t n_theta, int64_t n_rows,
