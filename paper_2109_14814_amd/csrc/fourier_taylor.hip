@@ -82,8 +82,8 @@ MS_D double lane_sums(const double *v)
 // block's waves take steps of 32 frequencies in turn.  A table of 2048
 // frequencies to order 25 is 1.7 MB, so what bounds it is the L2's
 // 14 TB/s for many queries and the loads' latency for few: 4 queries per block
-// take 33 us for up to 700 queries and 36 for 1024, one 21 for up to 128 and
-// 38 for 300; a wave per query took 105 for up to 1024.  8 queries spill.
+// take 31 us for 256 queries and 33 for 1000, one 20 for 64, 24 for 256 and 38
+// for 300; a wave per query took 105 for up to 1024.  8 queries spill.
 template <int QT>
 struct FtShared {
     double sum[FT_MAX_WAVES<QT>][3][4 * QT];
@@ -368,6 +368,25 @@ void launch_ft_tile(const FtArgs &g, hipStream_t st)
                        g);
 }
 
+// Whether the matrix cores take a call.  Their blocks of 16 queries, one to a
+// CU, take as long for 1 query as for 4096, and whole steps of orders; blocks
+// of four go by the query.  With 2048 frequencies a round of 4096 queries takes
+// 38, 45, 59 or 81 us up to order 3, 7, 15 or 27; blocks of four (46 + 2.9
+// order) us per 4096, and no less than three quarters of that from about 1536
+// queries on (below, they are the faster ones).  So 4096 queries to order 3 or
+// 25 take 38 and 82 us here (more than 45 and 118 by fours), 2304 to order 0, 8 and 16
+// 34, 50 and 67 by fours (38, 59 and 81 here), 5000 to order 0 and 25 52 and 144 by
+// fours (76 and 163).  With some hundred frequencies a block's start weighs
+// more than the queries (58 for 46; 512 frequencies, 2000 queries to order 0:
+// 12.7 us here, 15.4 by fours).
+inline bool tiles_pay(int64_t nq, int N, int order)
+{
+    if (order > 27 || nq <= 1536) return false;
+    const double round = order <= 3 ? 38.0 : order <= 7 ? 45.0 : order <= 15 ? 59.0 : 81.0;
+    const double fours = (N >= 128 && N < 1024 ? 58.0 : 46.0) + 2.9 * order;
+    return (double)ceil_div(nq, (int64_t)4096) * round < (double)std::max<int64_t>(nq, 3072) / 4096.0 * fours;
+}
+
 // dth <- M dth, ds <- M ds per query (M row-major 4 x 4).
 __global__ void __launch_bounds__(256) k_apply_stm(const double *__restrict__ stm, double *dth, double *ds, int64_t nq)
 {
@@ -590,13 +609,10 @@ extern "C" int ft_partials(const double *spec_dev, int32_t n_theta, int32_t orde
     const double th_off = (double)m * omega;
     const double s_scale = m == 0 ? 1.0 : pow(lambda, -(double)m);
     const FtArgs g{spec_dev, theta_dev, s_dev, w_dev, dth_dev, ds_dev, n_query, th_off, s_scale, (int)n_theta, (int)order};
-    // A block of 16 queries takes as long for 1 as for 4096 (a CU each), and
-    // its powers are held in registers: 2048 queries to order 25: 77 us against
-    // 68 by fours, 3000: 79 against 103.  A block of four against single
-    // queries: 512 queries 33 against 38 us, 128: 32 against 21.
-    const auto eval = n_query < 256 ? launch_ft_eval<1>
-                      : n_query < 2304 || order > 27 ? launch_ft_eval<4>
-                      : order <= 7 ? launch_ft_tile<2> : order <= 15 ? launch_ft_tile<4> : launch_ft_tile<7>;
+    const auto eval = n_query <= 256 ? launch_ft_eval<1>
+                      : !tiles_pay(n_query, n_theta, order) ? launch_ft_eval<4>
+                      : order <= 3 ? launch_ft_tile<1> : order <= 7 ? launch_ft_tile<2>
+                      : order <= 15 ? launch_ft_tile<4> : launch_ft_tile<7>;
     eval(g, st);
     MS_HIP(hipGetLastError());
     if (m == 0) return MS_OK;
