@@ -853,7 +853,9 @@ __global__ void __launch_bounds__(IP_BLOCK) k_theta_interp(InterpArgs g)
         s.row[e] = row;
     }
     __syncthreads();
-    // tiles: up to four neighbours of the same row
+    // tiles: up to four neighbours of the same row, fewer where a tile for
+    // each of the block's waves takes that
+    const int waves = nt / 64, more = GROUPED || n_list >= 4 * waves ? 3 : n_list >= 2 * waves ? 1 : 0;
     for (int e = tid; e - lane < n_list; e += nt) {
         const int64_t row = e < n_list ? s.row[e] : -1;
         const bool lone = row >= 0 && s.i0[e] < 0;
@@ -861,7 +863,7 @@ __global__ void __launch_bounds__(IP_BLOCK) k_theta_interp(InterpArgs g)
         const uint64_t heads = ballot(head);
         const uint64_t below = heads & (~0ull >> (63 - lane));
         const int at = lane - (63 - __builtin_clzll(below));
-        const bool start = row >= 0 && (at & 3) == 0;
+        const bool start = row >= 0 && (at & more) == 0;
         const uint64_t after = lane == 63 ? 0 : heads >> (lane + 1);
         const int run = after ? 1 + __builtin_ctzll(after) : 64 - lane;
         const uint64_t starts = ballot(start);
@@ -870,12 +872,12 @@ __global__ void __launch_bounds__(IP_BLOCK) k_theta_interp(InterpArgs g)
         base = __builtin_amdgcn_readfirstlane(base);
         if (start)
             s.tile[base + __builtin_popcountll(starts & ~(~0ull << lane))] =
-                (uint32_t)e | (lone ? 0u : (uint32_t)(run < 4 ? run : 4) << 16);
+                (uint32_t)e | (lone ? 0u : (uint32_t)(run <= more ? run : more + 1) << 16);
     }
     __syncthreads();
     double *out = g.out + 4 * q0;
     const int n_tiles = (int)s.n_tiles;
-    for (int k = wv; k < n_tiles; k += nt / 64) {
+    for (int k = wv; k < n_tiles; k += waves) {
         const uint32_t w = __builtin_amdgcn_readfirstlane(s.tile[k]);
         const int e = (int)(w & 0xffff), len = (int)(w >> 16);
         if (len > 2) interp_tile<ODD, 4>(s, e, len, s_dyn, g.in, N, out);
@@ -1137,9 +1139,10 @@ extern "C" int theta_interp(const double *rows_dev, int32_t n_theta, int64_t n_r
     const int N = (int)n_theta;
     // A block's table and offsets cost some 8 us: short rows repay them only
     // with many queries for each block (129 samples, 5000 queries: 11 to 16
-    // against 9 us; 256, 20000: 16 against 33), the shortest never (64
-    // samples, 20000 queries: 15 against 17; 33, 65536: 47 and 47).
-    if (N > IP_MAX_N || N < 64 || (N < 256 && n_query < 16384)) {
+    // against 9 us; 256, 20000: 16 against 33; 256 and 300, 500: 5.5 and 6.0
+    // against 5.1 and 5.5, 4096: 7.6 and 8.4 against 9.4 and 10.7), the shortest
+    // never (64 samples, 20000 queries: 15 against 17; 33, 65536: 47 and 47).
+    if (N > IP_MAX_N || N < 64 || (N < 256 && n_query < 16384) || (N < 320 && n_query < 2048)) {
         const int64_t blocks = ceil_div(n_query, 4);
         if (blocks > 0x7fffffff) return fail(MS_E_ARG, "theta_interp: too many queries for one launch");
         hipLaunchKernelGGL(k_theta_interp_plain, dim3((unsigned)blocks), dim3(256), 0, st, rows_dev, N, n_rows, row_dev,
@@ -1160,11 +1163,13 @@ extern "C" int theta_interp(const double *rows_dev, int32_t n_theta, int64_t n_r
     const size_t table = (size_t)(odd ? 16 : 8) * N;
     // Grouped by rows where the rows do not stay in the caches (8 MB: twice
     // an XCD's L2) and are read more than once: 2048 rows of 2048, 4096 queries:
-    // 40 us either way; 1024 rows, 4096 queries: 31 against 39; 4096 rows,
-    // 8192 queries: 54 against 78; 300 rows of 1024, 65536 queries: 118
-    // against 171; but 300 rows of 512: 94 against 60, 128 of 2048: 173
-    // against 149.
-    const bool grouped = n_query >= 4096 && n_query >= 2 * n_rows && n_rows > (8 << 20) / (32 * N);
+    // 39 us against 42; 4096 rows, 8192 queries: 56 against 78; 300 rows of 1024,
+    // 65536 queries: 118 against 171; but 300 rows of 512: 94 against 60, 128 of
+    // 2048: 173 against 149.  The grouping's own 9 us want some 5 million samples:
+    // 1000 rows of 300, 512 and 1024, 4096 queries: 16.4, 18.3 and 22.6 against
+    // 8.6, 12.4 and 21.3; of 700, 8192 queries: 20.3 against 25.5.
+    const bool grouped = n_query >= 4096 && n_query >= 2 * n_rows && n_rows > (8 << 20) / (32 * N) &&
+                         n_query * N >= (int64_t)5 << 20;
     int64_t blocks;
     size_t lds = table;
     int threads = IP_BLOCK;
