@@ -1885,6 +1885,11 @@ MS_D void wave_sync()
     __builtin_amdgcn_wave_barrier();
 }
 
+// Memory that no kernel running beside this one writes, read through the
+// scalar cache (uniform addresses).
+template <typename T>
+using ScalarPtr = const __attribute__((address_space(4))) T *;
+
 // Exact cell statistics of a group holding several cells (cells whose hashes
 // collide), by one wave: each cell's A and B entries are counted in an LDS
 // table keyed by the cell (s_tab: GS_SLOTS keys, then as many count words),
@@ -1930,11 +1935,21 @@ MS_D void group_stats(const uint64_t *keys, const CellRec &cr, int sh, uint64_t 
             xc += (a > 0 && b > 0);
         }
     } else {
-        for (int i = lane; i < cr.nA; i += WAVE) {
-            const uint64_t ci = keys[(int64_t)cr.start + i] >> sh;
+        // 64 A entries at a time, the others by scalar loads, eight at once
+        // (up to seven past the group's are not counted; the list is padded).
+        // 256 x 256 quads on 2^8 hashed cells, where this is most of a search:
+        // 5.9 ms, 8.6 with a load of one entry at a time.
+        ScalarPtr<uint64_t> pa = (ScalarPtr<uint64_t>)(keys + cr.start), pb = pa + cr.nA;
+        for (int i0 = 0; i0 < cr.nA; i0 += WAVE) {
+            const int i = i0 + lane;
+            const uint64_t ci = i < cr.nA ? keys[(int64_t)cr.start + i] >> sh : EMPTY;
             uint32_t nb = 0, before = 0;
-            for (int j = 0; j < cr.nB; ++j) nb += (keys[(int64_t)cr.start + cr.nA + j] >> sh) == ci;
-            for (int j = 0; j < i; ++j) before += (keys[(int64_t)cr.start + j] >> sh) == ci;
+            for (int j = 0; j < cr.nB; j += 8)
+#pragma unroll
+                for (int u = 0; u < 8; ++u) nb += j + u < cr.nB && (pb[j + u] >> sh) == ci;
+            for (int j = 0; j < i0 + WAVE && j < cr.nA; j += 8)
+#pragma unroll
+                for (int u = 0; u < 8; ++u) before += j + u < i && (pa[j + u] >> sh) == ci;
             xs += nb;
             xc += (nb > 0 && before == 0);
         }
@@ -1960,11 +1975,6 @@ MS_D uint32_t sub_sat16(uint32_t a, uint32_t b)
     __builtin_memcpy(&o, &r, 4);
     return o;
 }
-
-// Memory that no kernel running beside this one writes, read through the
-// scalar cache (uniform addresses).
-template <typename T>
-using ScalarPtr = const __attribute__((address_space(4))) T *;
 
 struct EnumArgs {
     const uint64_t *keys;         // grouped entries [cell | side | triangle]
@@ -2494,7 +2504,7 @@ void layout(const Geometry &G, Layout &L)
     L.o_erank = take((size_t)(L.ent_cap + 1) * 4);
     L.o_ehash = take((size_t)(L.ent_cap + 1) * 4);
     L.o_eoff = take((size_t)(L.ent_cap + 1) * 2);
-    L.o_sorted = take((size_t)(L.ent_cap + 1) * 8);
+    L.o_sorted = take((size_t)(L.ent_cap + 8) * 8);
     L.o_spair = take((size_t)(L.ent_cap + 1) * 4);
     L.o_shome = take((size_t)(L.ent_cap + 1) * 4);
     L.o_qbox = take((size_t)(L.ent_cap + 1 + STRIP_UNROLL) * 16);
