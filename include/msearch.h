@@ -198,10 +198,9 @@ typedef struct {
     int64_t overflow;        /* bit 0: entries > capacity, bit 1: cand, bit 2: hits */
     int64_t n_groups;        /* groups enumerated: hashed cells with A and B entries (>= n_cells) */
     int64_t n_group_slots;   /* sum over those groups of nA * nB (>= n_slots) */
-    int64_t n_chunks_unstaged; /* pieces of the enumeration that take more boxes than the on-chip memories
-                                  hold and stream them from device memory: chunks of 2,048 slots of a
-                                  group with more than 470 A entries (crowded cells), and runs of one
-                                  wave over more than 470 entries (many small groups) */
+    int64_t n_chunks_unstaged; /* strips of the enumeration (64 boxes of one mesh in a group against the entries
+                                  of the other) that several waves share, each of which reads the 64 boxes:
+                                  those of crowded cells, longer than a wave's share of the work */
     int64_t reserved[2];     /* zero */
 } search_stats_t;
 

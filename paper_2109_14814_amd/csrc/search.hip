@@ -71,7 +71,7 @@ inline unsigned mark_grid(int64_t n_tiles)
 static_assert(MAX_GRID <= MS_COUNT_PARTIALS, "count partials fit the mesh scratch");
 constexpr int TILE_TRIS = 2 * BLOCK;                  // triangles of a tile: one quad per thread
 // Counter lines of the enumeration (cand, moller, degen, outside, cells,
-// slots, and k_groups' crowded chunks and group slots), one 128-byte line each.
+// slots, shared strips, and k_groups' group slots), one 128-byte line each.
 constexpr int STAT_SHARDS = 8;
 constexpr int SHARD_WORDS = 16;
 constexpr uint64_t SFLAG_AGG = 1ull << 62;
@@ -1557,7 +1557,6 @@ constexpr int GROUP_WORDS = BLOCK * GROUP_ITEMS;
 constexpr int GROUP_SEG = 8;                     // set bits per thread when the tile's are listed
 constexpr int GROUP_LIST = BLOCK * GROUP_SEG;
 constexpr uint64_t GRP_DROP = 0x8000000080000000ull;
-constexpr int64_t CROWDED = 470;                 // A entries above which a group counts as crowded
 
 struct GroupsOut {
     const uint32_t *both;     // fine both-occupied bits
@@ -1569,7 +1568,7 @@ struct GroupsOut {
     uint64_t *stat;           // 2 look-back words per tile (cleared)
     uint32_t *tile_ctr;       // (cleared)
     search_stats_t *stats;
-    unsigned long long *shards;   // the counter lines: [6] crowded chunks, [7] slots
+    unsigned long long *shards;   // the counter lines: [7] slots
 };
 
 // Tiles at most this many take their tile from the block index: every block
@@ -1602,14 +1601,13 @@ __global__ void __launch_bounds__(BLOCK) k_groups(GroupsOut o)
         const int64_t w0 = tile * GROUP_WORDS + (int64_t)threadIdx.x * GROUP_ITEMS;
         uint32_t m[GROUP_ITEMS];
         uint64_t kc = 0, pc = 0;     // (kept << 32) | entries; units of enumeration
-        unsigned long long slots = 0, crowded = 0;
+        unsigned long long slots = 0;
         auto count = [&](uint64_t v) {
             const uint64_t a = v & 0xffffffffull, b = v >> 32;
             if (a && b) {
                 kc += (1ull << 32) + a + b;
                 pc += group_units((uint32_t)a, (uint32_t)b);
                 slots += a * b;
-                if ((int64_t)a > CROWDED) crowded += (a * b + 2047) / 2048;
             }
         };
         uint32_t nb = 0;
@@ -1684,12 +1682,7 @@ __global__ void __launch_bounds__(BLOCK) k_groups(GroupsOut o)
                 }
             }
         }
-        if (slots) {
-            // (spread over the counter lines and added without a reply)
-            unsigned long long *w = o.shards + SHARD_WORDS * (tile % STAT_SHARDS);
-            atomicAdd(&s_slots[0], slots);
-            if (crowded) atomicAdd(w + 6, crowded);
-        }
+        if (slots) atomicAdd(&s_slots[0], slots);
         __syncthreads();
         if (threadIdx.x == 0 && s_slots[0]) {
             atomicAdd(o.shards + SHARD_WORDS * (tile % STAT_SHARDS) + 7, s_slots[0]);
@@ -2019,7 +2012,7 @@ k_enum(BatchView bv, EnumArgs a)
     uint32_t q1n = 0, q2n = 0;
     unsigned long long xc = 0, xs = 0;               // exact cells and slots (per lane)
     uint32_t n_cand = 0, n_moller = 0, n_degen = 0, n_out = 0;   // per wave
-    int64_t touched = 0;                             // entries whose boxes the wave took
+    uint32_t shared = 0;                             // strips begun here and left to the next wave
     // the group that holds unit w
     int64_t g = 0;
     if (w < wend) {
@@ -2080,13 +2073,13 @@ k_enum(BatchView bv, EnumArgs a)
             const uint64_t off = local - strip * gs.unit;                 // where in the strip
             const uint64_t left = gs.unit - off < (uint64_t)(wend - w) ? gs.unit - off : (uint64_t)(wend - w);
             w = uni(w + (int64_t)left);
+            shared += off == 0 && left < gs.unit;
             si = uni(off > STRIP_UNITS ? (uint32_t)(off - STRIP_UNITS) : 0u);
             s1 = uni(off + left > STRIP_UNITS ? (uint32_t)(off + left - STRIP_UNITS) : 0u);
             const uint32_t l = (uint32_t)strip * WAVE + lane;
             eL = cr.start + (gs.lanes_b ? (uint32_t)cr.nA : 0u) + l;
             eS0 = uni(cr.start + (gs.lanes_b ? 0u : (uint32_t)cr.nA));
             if (si < s1) {
-                touched += WAVE + (s1 - si);
                 lmask = ballot(l < gs.nl);
                 if (l < gs.nl) {
                     lq = a.qbox[eL];
@@ -2218,7 +2211,7 @@ k_enum(BatchView bv, EnumArgs a)
     xc = wave_sum_u64(xc);
     xs = wave_sum_u64(xs);
     if (lane == 0) {
-        const unsigned long long v[7] = {a.cand ? 0ull : n_cand, n_moller, n_degen, n_out, xc, xs, touched > CROWDED};
+        const unsigned long long v[7] = {a.cand ? 0ull : n_cand, n_moller, n_degen, n_out, xc, xs, shared};
 #pragma unroll
         for (int k = 0; k < 7; ++k)
             if (v[k]) atomicAdd(&s_cnt[k], v[k]);
