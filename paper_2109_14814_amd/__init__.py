@@ -291,19 +291,20 @@ class Searcher:
                  cand_cap: int = 1 << 20):
         self.A, self.B, self.params = A, B, params
         self.hits_cap, self.cand_cap = int(hits_cap), int(cand_cap)
-        # the counters and the records in one allocation, so that results()
-        # reads both with one copy
-        self._out = _dev_bytes(16 * 8 + max(self.hits_cap * HIT_DTYPE.itemsize, 1))
-        self.stats = self._out[: 16 * 8]
-        self._alloc(self._out[16 * 8:])
+        self.stats = _dev_bytes(0)
+        self._alloc()
 
-    def _alloc(self, hits=None):
+    def _alloc(self):
         nb = C.c_size_t()
         _check(lib().search_workspace_size(self.A.handle, self.B.handle, C.byref(self.params), self.cand_cap,
                                            self.hits_cap, _stream(), C.byref(nb)))
         self.ws_bytes = int(nb.value)
         self.ws = _workspace(self.ws_bytes)
-        self.hits = hits if hits is not None else _dev_bytes(self.hits_cap * HIT_DTYPE.itemsize)
+        # the counters and the records in one allocation, so that results()
+        # reads both with one copy; the tensor `stats` stays the same one
+        self._out = _dev_bytes(16 * 8 + max(self.hits_cap * HIT_DTYPE.itemsize, 1))
+        self.stats.set_(self._out[: 16 * 8])
+        self.hits = self._out[16 * 8:]
         want_cand = bool(self.params.flags & MS_SEARCH_CANDIDATES)
         self.cand = _dev_bytes(self.cand_cap * 8) if want_cand else None
 
@@ -356,7 +357,7 @@ class Searcher:
             raw = self._out[: 16 * 8 + READ_HITS * size].cpu().numpy()
             st = _stats_of(raw[: 16 * 8].view(np.int64))
             head = raw[16 * 8:].tobytes()
-        else:                                    # the records moved to a larger buffer
+        else:                                    # (buffers of the caller's)
             st = _stats_dict(self.stats)
         end = min(st["n_hits"], self.hits_cap) * size
         if end > len(head):
