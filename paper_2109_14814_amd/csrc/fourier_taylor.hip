@@ -166,7 +166,7 @@ MS_D void ft_eval(FtShared<QT> &s_sum, int64_t q0, const FtArgs &g)
         // samples (coefficient j times i j, whose real part is 0 at
         // j = N/2) and then interpolated.
         const bool nyq = last && 2 * js == N;
-        const double jd = nyq ? 0.0 : (double)js;
+        const double jd = (double)js;
         // the phases: the lanes of the two pairs take half of them each
         double cs[QT], sn[QT];
         if constexpr (QT == 1) {
@@ -186,13 +186,15 @@ MS_D void ft_eval(FtShared<QT> &s_sum, int64_t q0, const FtArgs &g)
 #pragma unroll
         for (int q = 0; q < QT; ++q) {
             const double f = cs[q], e = nyq ? 0.0 : sn[q];
-            const double re = fma(vr[q], f, -(vi[q] * e)), im = fma(vr[q], e, vi[q] * f);
+            // (each part by itself at the cosine mode: 0 times an infinite one is no number)
+            const double xr = nyq ? 0.0 : vr[q], xi = nyq ? 0.0 : vi[q];
+            const double re = fma(vr[q], f, -(xi * e)), im = fma(xr, e, vi[q] * f);
             aw[2 * q] += re;
             aw[2 * q + 1] += im;
-            ath[2 * q] = fma(-jd, im, ath[2 * q]);       // i js (re + i im)
-            ath[2 * q + 1] = fma(jd, re, ath[2 * q + 1]);
-            as[2 * q] = fma(dr[q], f, fma(-di[q], e, as[2 * q]));
-            as[2 * q + 1] = fma(dr[q], e, fma(di[q], f, as[2 * q + 1]));
+            ath[2 * q] = fma(-jd, nyq ? 0.0 : im, ath[2 * q]);       // i js (re + i im)
+            ath[2 * q + 1] = fma(jd, nyq ? 0.0 : re, ath[2 * q + 1]);
+            as[2 * q] = fma(dr[q], f, fma(nyq ? 0.0 : -di[q], e, as[2 * q]));
+            as[2 * q + 1] = fma(nyq ? 0.0 : dr[q], e, fma(di[q], f, as[2 * q + 1]));
         }
     };
     if (wv < steps) fetch(wv);
