@@ -629,38 +629,13 @@ MS_D int64_t xcd_block(int64_t b, int64_t nb)
     return (b % 8) * (nb / 8) + b / 8;
 }
 
-// Decoupled look-back over 64-bit status words [flag:2 | value:62] of the
-// tiles before `tile` (word of tile i at status[i * stride]), run by all 64
-// lanes of one wave: each round reads 64 predecessors at once, finds the
-// nearest inclusive prefix with a ballot and re-reads when a predecessor
-// before it has not published yet.  Returns the exclusive prefix in every
-// lane.
-MS_D uint64_t wave_lookback_s(const uint64_t *status, int64_t stride, int64_t tile)
-{
-    const int lane = lane_id();
-    uint64_t excl = 0;
-    int64_t t = tile - 1;
-    for (;;) {
-        const int64_t idx = t - lane;
-        const uint64_t v = idx >= 0 ? __hip_atomic_load(status + idx * stride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-                                    : SFLAG_PRE;
-        const uint64_t fl = v & ~SVAL_MASK;
-        const uint64_t pre = ballot(fl == SFLAG_PRE);
-        const uint64_t zero = ballot(fl == 0);
-        const int k = pre ? __builtin_ctzll(pre) : 63;
-        const uint64_t upto = (2ull << k) - 1;     // lanes 0..k
-        if (zero & upto) continue;
-        excl += wave_sum_u64(lane <= k ? (v & SVAL_MASK) : 0ull);
-        if (pre) return excl;
-        t -= 64;
-    }
-}
-
-MS_D uint64_t wave_lookback(const uint64_t *status, int64_t tile) { return wave_lookback_s(status, 1, tile); }
-
-// The same over pairs of words (a, b) published together (tile i's pair at
-// status[i * stride], status[i * stride + 1]): a predecessor is ready when
-// both words carry the same non-zero flag.
+// Decoupled look-back over pairs of 64-bit status words [flag:2 | value:62]
+// (a, b), published together, of the tiles before `tile` (tile i's pair at
+// status[i * stride], status[i * stride + 1]), run by all 64 lanes of one wave:
+// each round reads 64 predecessors at once, finds the nearest inclusive prefix
+// with a ballot and re-reads when a predecessor before it is not ready (ready:
+// both words carry the same non-zero flag).  The exclusive prefixes go to
+// every lane.
 MS_D void wave_lookback2(const uint64_t *status, int64_t stride, int64_t tile, uint64_t &ea, uint64_t &eb)
 {
     const int lane = lane_id();
@@ -1157,6 +1132,15 @@ static_assert(offsetof(KeysArgs, both) == sizeof(BatchView) && offsetof(KeysArgs
                   offsetof(KeysArgs, o) == sizeof(BatchView) + 16 && offsetof(KeysArgs, kt) == offsetof(KeysArgs, o) + sizeof(KeysOut),
               "k_keys' arguments follow each other without gaps");
 
+// A listed entry's word: the thread whose triangle it is of (bits 0..8), the
+// parities of its cell (9..12) and its block's offset from the range's first
+// per axis (4 bits each from 13); read in keys_dense and in k_keys.
+MS_D uint32_t list_word(uint32_t parities, const int32_t *block)
+{
+    return threadIdx.x | parities << 9 | (uint32_t)block[0] << 13 | (uint32_t)block[1] << 17 | (uint32_t)block[2] << 21 |
+           (uint32_t)block[3] << 25;
+}
+
 MS_D uint64_t uniform64(uint64_t v)
 {
     return (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(v >> 32)) << 32 |
@@ -1236,9 +1220,7 @@ keys_dense(uint64_t args, int64_t tile, TileLoc L, uint32_t cnt, uint32_t texcl,
             uint32_t k = texcl - w0;         // (wraps below the window, and is not listed there)
             for_blocks(lr2, P.fbs, P.fbh, cb, lg, [&](const int32_t *ob, const uint32_t *pm, uint32_t line) {
                 for (uint32_t q = lines[line] & parity_cells(pm); q; q &= q - 1, ++k)
-                    if (k < KEYS_STAGE)
-                        s_list[k] = threadIdx.x | (uint32_t)__builtin_ctz(q) << 9 | (uint32_t)ob[0] << 13 |
-                                    (uint32_t)ob[1] << 17 | (uint32_t)ob[2] << 21 | (uint32_t)ob[3] << 25;
+                    if (k < KEYS_STAGE) s_list[k] = list_word((uint32_t)__builtin_ctz(q), ob);
             });
         }
         __syncthreads();
@@ -1305,8 +1287,7 @@ k_keys(BatchView bv, const uint32_t *both, const uint64_t *rng, KeysOut o, KeysT
     __shared__ uint64_t s_wave[KEYS_BLOCK / WAVE];
     __shared__ uint32_t s_far;
     __shared__ unsigned long long s_blk0;
-    // entries: thread (bits 0..8), parities (9..12), block offset per axis (4 bits each from 13)
-    __shared__ uint32_t s_list[KEYS_LIST];
+    __shared__ uint32_t s_list[KEYS_LIST];        // list_word of each entry
     const int lg = bv.bm_log2, lr = bv.br_log2;
     const uint16_t *lines = reinterpret_cast<const uint16_t *>(both);
     const uint32_t *rboth = both + ((size_t)1 << lg) / 32;
@@ -1430,31 +1411,26 @@ k_keys(BatchView bv, const uint32_t *both, const uint64_t *rng, KeysOut o, KeysT
             } else {
                 for_blocks(r, P.fbs, P.fbh, cb, lg, [&](const int32_t *ob, const uint32_t *pm, uint32_t line) {
                     for (uint32_t q = lines[line] & parity_cells(pm); q; q &= q - 1)
-                        s_list[k++] = threadIdx.x | (uint32_t)__builtin_ctz(q) << 9 | (uint32_t)ob[0] << 13 |
-                                      (uint32_t)ob[1] << 17 | (uint32_t)ob[2] << 21 | (uint32_t)ob[3] << 25;
+                        s_list[k++] = list_word((uint32_t)__builtin_ctz(q), ob);
                 });
             }
         }
     }
     __syncthreads();
     const uint64_t blk0 = s_blk0;
-    // only stored entries are counted in their group; the first entry of
-    // each side leaves its cell as the group's sample
+    // only stored entries are counted in their group
     auto put = [&](int64_t pos, uint64_t gc, uint32_t hh, uint32_t off, int32_t tri) {
         if (pos >= o.cap) return;
-        const uint32_t rank = atomicAdd(&o.grp[2 * (size_t)hh + L.side], 1u);
-        o.erank[pos] = rank;
-        o.ehash[pos] = hh;
-        o.eoff[pos] = (uint16_t)off;
-        if (rank == 0) o.own[hh] = gc;
-        o.ent[pos] = (gc << bv.kl.cell_shift) | ((uint64_t)L.side << bv.kl.tb) | (uint64_t)(uint32_t)tri;
-        if (!ONE) o.epair[pos] = L.p;
+        count_entry(o, L.side, pos, gc, hh);
+        store_entry<ONE>(o, bv, L, pos, gc, hh, off, tri);
     };
     if (C32 && btotal <= LISTED && s_far == 0) {
         for (uint32_t i = threadIdx.x; i < btotal; i += KEYS_BLOCK) {
             const uint32_t w = s_list[i], tid = w & 511u;
             Range32 rr;
             range32_at(rng, tile * TILE_TRIS + tid, m, L.t0 + (int32_t)tid, P, rr);
+            // (as in keys_dense; a function of its own for both costs the plain
+            // form 63 spilled scalar registers, 512 x 512 88.3 us for 86.9)
             uint32_t lin = (uint32_t)cb, off = 0;
             uint64_t gc = cb;
 #pragma unroll
@@ -1466,8 +1442,8 @@ k_keys(BatchView bv, const uint32_t *both, const uint64_t *rng, KeysOut o, KeysT
                 const uint32_t k = c - (uint32_t)rr.lo[d];
                 off |= (k < 15u ? k : 15u) << (4 * d);
             }
-            put((int64_t)(blk0 + i), gc, hash_of_product(lin * HASH_MUL, lg - 4) << 4 | (w >> 9 & 15u), off,
-                L.t0 + (int32_t)tid);
+            const uint32_t hh = hash_of_product(lin * HASH_MUL, lg - 4) << 4 | (w >> 9 & 15u);
+            put((int64_t)(blk0 + i), gc, hh, off, L.t0 + (int32_t)tid);
         }
         return;
     }
