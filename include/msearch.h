@@ -152,10 +152,13 @@ typedef struct {
     int32_t reserved;       /* 0 */
 } search_params_t;
 
-/* Enumeration work tiles: the least work a wave takes, in box tests of 64
- * pairs (the waves share the work out evenly once it is more than that). */
+/* Enumeration work tiles: the least work a wave takes, in units.  A strip of
+ * the enumeration (64 boxes of one mesh in a group) is 16 units for its start
+ * and one for each box of the other mesh that the 64 are tested against; the
+ * waves share all units out evenly once that is more for each.  (With the
+ * smallest a wave may get a strip's start alone.) */
 enum {
-    MS_ENUM_WIDE = 1,       /* 64 */
+    MS_ENUM_WIDE = 1,       /* 64 units */
     MS_ENUM_HALF = 2,       /* 32 */
     MS_ENUM_QUARTER = 3     /* 16 */
 };
@@ -383,7 +386,10 @@ typedef struct {
  * Cooper & Verner (1972) with fixed steps (the globalization maps
  * F^{+-k} of Sec. 4.3).  in_dev may equal out_dev.  Asynchronous: queues one
  * kernel, or several that each take part of the steps (the stage weights w(f)
- * are computed on the GPU inside them), allocates nothing, never synchronises, and can be captured into a HIP graph.
+ * are computed on the GPU inside them), allocates nothing, never synchronises,
+ * and can be captured into a HIP graph.  A state's result does not depend on
+ * the other states, but in its last bits on whether there are more than 24,576
+ * (up to there two GPU threads share a state, and its sums round differently).
  */
 int propagate_vertices(const double *in_dev, double *out_dev, int64_t n_vertices,
                        const map_params_t *params, void *stream);
@@ -407,7 +413,7 @@ int propagate_vertices(const double *in_dev, double *out_dev, int64_t n_vertices
  * stream; MS_E_ARG for a bad pointer, steps_per_period <= 0, e outside
  * [0, 1) or mu outside [0, 1].  The kernel solves Kepler's equation for the
  * stage times on the GPU; the call allocates nothing, never synchronises and
- * can be captured into a HIP graph. */
+ * can be captured into a HIP graph.  Last bits as for propagate_vertices. */
 int pertbp_map(const double *in_dev, double *out_dev, int64_t n_states, const map_params_t *params,
                void *stream);
 
@@ -445,7 +451,9 @@ int pertbp_map_stm(const double *in_dev, double *out_dev, double *stm_dev, int64
  * by an FFT, multiplication of coefficient k by (j k)^order e^{j k rho_r} and
  * the inverse FFT (the translation of Sec. 6.1, used with rho = -n omega to
  * put the points F^n(W(theta_i, s)) = W(theta_i + n omega, lambda^n s) back on
- * the theta grid; order 1 is the theta derivative of Sec. 7).
+ * the theta grid; order 1 is the theta derivative of Sec. 7).  A row's result
+ * does not depend on the other rows, but in its last bits on their number (up
+ * to 768, or 1536 of some lengths, the phases are worked out another way).
  *   rho_dev  n_rows doubles (one shift per row), or NULL to use rho for all.
  *   n_theta  a power of two, 2 ... 2048; order 0, 1 or 2.
  * in_dev may equal out_dev.  Asynchronous; MS_E_ARG for bad sizes or
@@ -490,7 +498,10 @@ int globalize_manifold(const double *grid_dev, const double *s_host, int32_t n_t
  * the value at theta_dev[q] of the trigonometric polynomial through the
  * samples of row row_dev[q] (coordinate c).  Any n_theta >= 1.  A query with
  * a row outside [0, n_rows), a non-finite theta, or a theta so large that
- * theta n_theta / (2 pi) overflows yields NaN.  Asynchronous. */
+ * theta n_theta / (2 pi) overflows yields NaN.  A query's result depends on
+ * its row and theta alone, in any order and company; only for 64 <= n_theta <
+ * 320 its last bits depend on the number of queries too (few are interpolated
+ * without the row length's table).  Asynchronous. */
 int theta_interp(const double *rows_dev, int32_t n_theta, int64_t n_rows, const int64_t *row_dev,
                  const double *theta_dev, int64_t n_query, double *out_dev, void *stream);
 
@@ -516,7 +527,9 @@ int theta_interp(const double *rows_dev, int32_t n_theta, int64_t n_rows, const 
  *   w_dev, dth_dev, ds_dev  n_query x 4 outputs.
  *   stm_dev    n_query x 16 doubles of workspace (DF^m per query, row-major;
  *              left there on return); required when m != 0.
- * Asynchronous.  A query with a non-finite theta or s yields NaN. */
+ * Asynchronous.  A query with a non-finite theta or s yields NaN.  Its last
+ * bits depend on the number of queries (few are summed by Horner's rule, many
+ * as a matrix product), not on the others. */
 int ft_partials(const double *spec_dev, int32_t n_theta, int32_t order, const double *theta_dev,
                 const double *s_dev, int64_t n_query, double omega, double lambda, const map_params_t *map,
                 double *w_dev, double *dth_dev, double *ds_dev, double *stm_dev, void *stream);
@@ -579,7 +592,9 @@ int refine_workspace_size(int64_t K, const map_params_t *fwd, const map_params_t
  * the discrete map.  ws: refine_workspace_size bytes (the call writes every
  * part it reads).  Asynchronous on `stream`: queues kernels only, allocates
  * nothing, never synchronises, and can be captured into a HIP graph whatever
- * the values of e and steps_per_period.
+ * the values of e and steps_per_period.  A hit's result does not depend on the
+ * other hits, but in its last bits on whether there are more than 16,384 (with
+ * tangents, here and in refine_newton, 5,461), as for propagate_vertices.
  */
 int refine_grad(const double *params_dev, int64_t K, const patch_t *U_dev, const patch_t *S_dev,
                 int32_t patch_stride, const map_params_t *fwd, const map_params_t *bwd, int32_t ckpt_every,

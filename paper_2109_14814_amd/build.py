@@ -1,9 +1,8 @@
 """Build libmsearch.so (the HIP kernels and the C ABI) for gfx950 with hipcc.
 
 Every source is compiled with FP contraction off (each FP64 operation
-rounds once, as written) except where a kernel opts in locally with
-`#pragma clang fp contract(fast)` (the Runge-Kutta map), and with packed
-FP32 instructions disabled.
+rounds once, as written; the kernels fuse where they write fma), and with
+packed FP32 instructions disabled.
 """
 from __future__ import annotations
 
