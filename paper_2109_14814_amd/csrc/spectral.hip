@@ -171,8 +171,12 @@ MS_D void butterflies(Regs<N> &v, int t, const double2 *__restrict__ tw)
 #pragma unroll
     for (int q = 0; q < per_thread<N>() / R; ++q) {
         double2 w[R];
+        bool turn = false;
         if constexpr (Ns > 1) {
             const int k = (t + q * T) % Ns;
+            // (a factor of 1 is left out, and with it what 0 times an infinite
+            // part, or one that is no number, would put into the other)
+            turn = INV || k != 0;
 #pragma unroll
             for (int r = 1; r < R; ++r) {
                 w[r] = tw[(r - 1) * Ns + k];
@@ -181,7 +185,7 @@ MS_D void butterflies(Regs<N> &v, int t, const double2 *__restrict__ tw)
         }
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
-            if constexpr (Ns > 1) {
+            if (turn) {
 #pragma unroll
                 for (int r = 1; r < R; ++r) v[s][q * R + r] = cmul(v[s][q * R + r], w[r]);
             }
