@@ -1831,16 +1831,18 @@ MS_D void emit_hit(bool hit, const hit_t &h, uint64_t key, hit_t *hits, uint64_t
 // takes the 4x4 solve (Sec. 6.2.4) likewise, so that neither runs with a few
 // lanes and the registers of the one are not held during the other.
 //
-// Measured (512 x 512 quads at kappa 1.5; two propagated patches; the 256
-// uneven pairs; the 112 half-layer pairs): 13.1, 84, 147 and 87 us.  With a
-// thread for every 256th slot of a chunk, the entries' FP64 boxes staged in
-// LDS and the narrow phase fused at two waves per SIMD it took 20.7, 381, 498
-// and 258 us, about 11 cycles per slot and CU of dependent LDS reads.  FP64
-// boxes broadcast from the lanes (v_readlane) took 19.0, 139, 249 and 136 us;
-// FP64 boxes by scalar loads, one at a time for want of scalar registers,
-// 20.8, 131, 294 and 150.  Five waves per SIMD spill: 18.0, 91, 182, 113.
-// One block for each resident place instead of two: 13.1, 118, 161, 90 (the
-// candidates lie in few runs; smaller runs share them out better).
+// Measured (512 x 512 quads at kappa 1.5; the 256 uneven pairs; the 112
+// half-layer pairs): 13.1, 147 and 87 us; two propagated patches (190 million
+// slots, 6.0 million candidates) 396 to 445.  With a thread for every 256th
+// slot of a chunk, the entries' FP64 boxes staged in LDS and the narrow phase
+// fused at two waves per SIMD it took 20.7, 498 and 258 us, about 11 cycles
+// per slot and CU of dependent LDS reads, and 2,119 for the patches.  FP64
+// boxes broadcast from the lanes (v_readlane) took 19.0, 249 and 136 us; FP64
+// boxes by scalar loads, one at a time for want of scalar registers, 20.8, 294
+// and 150.  Five waves per SIMD spill: 18.0, 182, 113.  One block for each
+// resident place instead of two: 13.1, 161, 90 (the candidates lie in few
+// runs; smaller runs share them out better: the patches, whose VALU
+// instructions are 92 us of the chip's rate, wait for the waves that own them).
 constexpr int ENUM_BLOCK = 256;
 constexpr int ENUM_WAVES = ENUM_BLOCK / WAVE;
 constexpr int ENUM_GRID = 2048;           // twice the resident blocks (four waves per SIMD)

@@ -26,12 +26,12 @@
 // own in the order in which its lanes read them; the multiplier's phases from
 // phase.hpp.
 //
-// 4096 rows of 2048, 268 MB read and as many written, which a copy does in
-// 109 us: 135 us from 185 with both sequences in 72 KB, a sine and cosine per
-// coefficient and one table of N factors gathered at strides (which alone
-// cost 25); with four workgroups on a CU the 128 registers spill: 167.  The
-// spectrum alone takes 108, from 130.  4096 rows of 64, 32 rows to a
-// workgroup: 9 us from 43.
+// 4096 rows of 2048, 268 MB read and as many written, 107 us at the rate of a
+// large copy (5.0 TB/s): 135 to 141 us from 184 with both sequences in 72 KB,
+// a sine and cosine per coefficient and one table of N factors gathered at
+// strides (which alone cost 25); with four workgroups on a CU the 128
+// registers spill: 167.  The spectrum alone takes 106, from 126.  4096 rows of
+// 64, 32 rows to a workgroup: 11 us a call from 43.
 //
 // theta_interp: the barycentric form of the trigonometric interpolant (no
 // transform): with theta = theta_i0 + delta,
