@@ -984,7 +984,7 @@ constexpr RowsLaunch SHIFT_OF[SP_MAX_LOG2 + 1] = {
     launch_shift<9, false>, launch_shift<10, false>, launch_shift<11, false>};
 constexpr RowsLaunch SPECTRUM_OF[SP_MAX_LOG2 + 1] = {
     nullptr, launch_spectrum<1, false>, launch_spectrum<2, false>, launch_spectrum<3, false>, launch_spectrum<4, false>,
-    launch_spectrum<5, false>, launch_spectrum<6, false>, launch_spectrum<7, false>, launch_spectrum<8, false>,
+    launch_spectrum<5, false>, launch_spectrum<6, false>, launch_spectrum<7, false>, nullptr,   // 256: always a row a workgroup
     launch_spectrum<9, false>, launch_spectrum<10, false>, launch_spectrum<11, false>};
 
 // Up to three rows a CU go one to a workgroup (see group_rows), all in flight
@@ -1008,18 +1008,35 @@ constexpr RowsLaunch SPECTRUM_FEW[FEW_MAX_LOG2 + 1] = {
     launch_spectrum<5, true>, launch_spectrum<6, true>, launch_spectrum<7, true>, launch_spectrum<8, true>,
     launch_spectrum<9, true>, launch_spectrum<10, true>};
 
-RowsLaunch rows_launch(const RowsLaunch *many, const RowsLaunch *few, int n_theta, int64_t n_rows)
+bool few_rows(int n_theta, int64_t n_rows)
 {
-    const int lg = __builtin_ctz(n_theta);
     const bool twice = n_theta <= 8 || (n_theta >= 128 && n_rows * n_theta <= FEW_SAMPLES);
-    return lg <= FEW_MAX_LOG2 && n_rows <= (twice ? 2 * FEW_ROWS : FEW_ROWS) ? few[lg] : many[lg];
+    return n_theta <= 1 << FEW_MAX_LOG2 && n_rows <= (twice ? 2 * FEW_ROWS : FEW_ROWS);
+}
+
+// The spectrum takes a row to a workgroup for more: its registers let four rows
+// of 1024 run on a CU, and once the rows' bytes are what it takes (from 2^22
+// samples on) small workgroups, which start and end by themselves, keep the
+// loads and stores going where shared ones do so in turns.  769 rows of 1024:
+// 14.1 us, 15.8 shared; 8192 of 512: 44.5 (47.2), 20000: 118 (124); 8192 of 1024:
+// 101 (103).  Between the two the shared ones' shorter exchange is ahead: 2300
+// rows of 512 and 1024 15.7 and 27.2 us against 17.0 and 30.2.  256 samples, half
+// a wave: 1300, 4000 and 12000 rows 7.4, 14.7 and 31.6 us, 8.4, 17.0 and 34.1
+// shared; of 128, 4000 rows 10.4 against 9.4.
+constexpr int64_t LONE_ROWS = 1024, LONE_SAMPLES = 1 << 22;
+
+bool lone_spectrum(int n_theta, int64_t n_rows)
+{
+    if (n_theta < 256 || n_theta > 1 << FEW_MAX_LOG2) return few_rows(n_theta, n_rows);
+    return n_theta == 256 || n_rows <= LONE_ROWS || n_rows * n_theta >= LONE_SAMPLES;
 }
 
 // theta_shift on validated arguments (n_theta a power of two in range).
 int shift_rows(const double *in, double *out, int n_theta, int64_t n_rows, const double *rho_dev, double rho,
                int order, const int64_t *row_map, hipStream_t st)
 {
-    return rows_launch(SHIFT_OF, SHIFT_FEW, n_theta, n_rows)({in, out, rho_dev, rho, order, row_map, n_rows}, st);
+    const RowsLaunch *launch = few_rows(n_theta, n_rows) ? SHIFT_FEW : SHIFT_OF;
+    return launch[__builtin_ctz(n_theta)]({in, out, rho_dev, rho, order, row_map, n_rows}, st);
 }
 
 // Row copies through a row map (negative entries dropped): the unshifted
@@ -1115,8 +1132,8 @@ extern "C" int theta_spectrum(const double *in_dev, double *out_dev, int32_t n_t
         return fail(MS_E_ARG, "theta_spectrum: n_theta must be a power of two in [2, 2048]");
     if (n_rows > 0x7fffffff) return fail(MS_E_ARG, "theta_spectrum: too many rows for one launch");
     if (n_rows == 0) return MS_OK;
-    return rows_launch(SPECTRUM_OF, SPECTRUM_FEW, n_theta, n_rows)({in_dev, out_dev, nullptr, 0.0, 0, nullptr, n_rows},
-                                                                   (hipStream_t)stream);
+    const RowsLaunch *launch = lone_spectrum(n_theta, n_rows) ? SPECTRUM_FEW : SPECTRUM_OF;
+    return launch[__builtin_ctz(n_theta)]({in_dev, out_dev, nullptr, 0.0, 0, nullptr, n_rows}, (hipStream_t)stream);
 }
 
 extern "C" int theta_shift(const double *in_dev, double *out_dev, int32_t n_theta, int64_t n_rows,
