@@ -34,8 +34,7 @@ namespace ms {
 namespace {
 
 constexpr int FT_STEP = 32;          // frequencies of a wave's step
-template <int QT>
-constexpr int FT_R = 8;
+constexpr int FT_R = 8, FT_R_LOW = 3;   // coefficients of a lane in flight; orders below 3
 template <int QT>
 constexpr int FT_MAX_WAVES = QT > 2 ? 8 : 16;
 
@@ -78,19 +77,21 @@ MS_D double lane_sums(const double *v)
 
 // QT queries per block by Horner's rule.  A lane takes one of the two complex
 // pairs of every 32nd frequency and all QT queries, so that a coefficient is
-// loaded once for QT of them; the next FT_R coefficients are in flight.  The
+// loaded once for QT of them; the next R coefficients are in flight.  The
 // block's waves take steps of 32 frequencies in turn.  A table of 2048
 // frequencies to order 25 is 1.7 MB, so what bounds it is the L2's
 // 14 TB/s for many queries and the loads' latency for few: 4 queries per block
 // take 31 us for 256 queries and 33 for 1000, one 20 for 64, 24 for 256 and 38
-// for 300; a wave per query took 105 for up to 1024.  8 queries spill.
+// for 300; a wave per query took 105 for up to 1024.  8 queries spill.  The
+// orders below 3 load no more coefficients than they have (2048 frequencies,
+// 3000 queries to order 0: 30.0 us, 34.3 with 8).
 template <int QT>
 struct FtShared {
     double sum[FT_MAX_WAVES<QT>][3][4 * QT];
     PhaseTable ph;
 };
 
-template <int QT>
+template <int QT, int R>
 MS_D void ft_eval(FtShared<QT> &s_sum, int64_t q0, const FtArgs &g)
 {
     phase_table(s_sum.ph);
@@ -110,7 +111,6 @@ MS_D void ft_eval(FtShared<QT> &s_sum, int64_t q0, const FtArgs &g)
     const int steps = (N + FT_STEP - 1) / FT_STEP;
     const int lowest = -((N - 1) / 2);
     double aw[2 * QT] = {}, ath[2 * QT] = {}, as[2 * QT] = {};
-    constexpr int R = FT_R<QT>;
     double2 x[R];                   // coefficients in flight
     const double *top = spec + 4 * (int64_t)N * P;
     const int64_t row = 4 * (int64_t)N;
@@ -222,11 +222,11 @@ MS_D void ft_eval(FtShared<QT> &s_sum, int64_t q0, const FtArgs &g)
     }
 }
 
-template <int QT>
+template <int QT, int R>
 __global__ void __launch_bounds__(64 * FT_MAX_WAVES<QT>) k_ft_eval(FtArgs g)
 {
     __shared__ FtShared<QT> s_sum;
-    ft_eval<QT>(s_sum, (int64_t)blockIdx.x * QT, g);
+    ft_eval<QT, R>(s_sum, (int64_t)blockIdx.x * QT, g);
 }
 
 typedef double v4d __attribute__((ext_vector_type(4)));
@@ -347,20 +347,35 @@ __global__ void __launch_bounds__(64 * FT_TILE_WAVES) k_ft_tile(FtArgs g)
     // Horner's rule gives a number in cases where 0 times a power or a
     // coefficient that is none does not
     for (uint32_t bad = s_bad; bad; bad &= bad - 1) {
-        ft_eval<1>(s_one, q0 + __builtin_ctz(bad), g);
+        ft_eval<1, FT_R>(s_one, q0 + __builtin_ctz(bad), g);
         __syncthreads();
     }
+}
+
+// The waves of a block: two per SIMD over the card (which the registers of
+// four queries allow), as 8 or 4, since a block of 5 to 7 keeps a CU to itself
+// and 1100 to 2000 queries then take two rounds (2048 frequencies, 1800 queries
+// to order 8: 34.0 us, 51.6 with 5 waves).  Where blocks
+// queue, fewer waves with at least four steps each spend less on the sums over
+// lanes and waves (128 frequencies, 8192 queries to order 0 and 25: 9.3 and
+// 19.2 us, 17.6 and 25.7 with four waves; but 5000 queries of 256 to order 25
+// 26.5 for 25.1: beyond order 8 from 8192 queries on).
+template <int QT>
+int eval_waves(int64_t blocks, int64_t steps, int order)
+{
+    if (blocks <= 256)
+        return (int)std::min<int64_t>(std::min<int64_t>(ceil_div((int64_t)2048, blocks), FT_MAX_WAVES<QT>), steps);
+    const int64_t most = blocks > (order <= 8 ? 1024 : 2047) ? steps / 4 : steps;
+    return most >= 4 ? 4 : most >= 2 ? 2 : 1;
 }
 
 template <int QT>
 void launch_ft_eval(const FtArgs &g, hipStream_t st)
 {
     const int64_t blocks = ceil_div(g.nq, (int64_t)QT), steps = ceil_div((int64_t)g.N, (int64_t)FT_STEP);
-    // two waves per SIMD over the card, each with a step at least
-    int64_t waves = ceil_div((int64_t)2048, blocks);
-    waves = std::max<int64_t>(waves, 4);
-    waves = std::min<int64_t>(std::min<int64_t>(waves, FT_MAX_WAVES<QT>), steps);
-    hipLaunchKernelGGL(k_ft_eval<QT>, dim3((unsigned)blocks), dim3((unsigned)(64 * waves)), 0, st, g);
+    const int waves = eval_waves<QT>(blocks, steps, g.P);
+    const auto kernel = g.P < FT_R_LOW ? k_ft_eval<QT, FT_R_LOW> : k_ft_eval<QT, FT_R>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3((unsigned)(64 * waves)), 0, st, g);
 }
 
 template <int KA>
@@ -372,21 +387,27 @@ void launch_ft_tile(const FtArgs &g, hipStream_t st)
 
 // Whether the matrix cores take a call.  Their blocks of 16 queries, one to a
 // CU, take as long for 1 query as for 4096, and whole steps of orders; blocks
-// of four go by the query.  With 2048 frequencies a round of 4096 queries takes
-// 38, 45, 59 or 81 us up to order 3, 7, 15 or 27; blocks of four (46 + 2.9
-// order) us per 4096, and no less than three quarters of that from about 1536
-// queries on (below, they are the faster ones).  So 4096 queries to order 3 or
-// 25 take 38 and 82 us here (more than 45 and 118 by fours), 2304 to order 0, 8 and 16
-// 34, 50 and 67 by fours (38, 59 and 81 here), 5000 to order 0 and 25 52 and 144 by
-// fours (76 and 163).  With some hundred frequencies a block's start weighs
-// more than the queries (58 for 46; 512 frequencies, 2000 queries to order 0:
-// 12.7 us here, 15.4 by fours).
+// of four queries go by 1024, two to a CU at once.  In us, x being N / 2048: a
+// round of 4096 queries takes 2.7 + 34 x, 2.9 + 41.5 x, 3.9 + 55 x or 4.7 +
+// 77.6 x up to order 3, 7, 15 or 27, and 1024 queries by fours 1.03 a full
+// block's waves and (9.34 + 0.72 order) x, 7.46 for 9.34 below order 3, and
+// 2.4 once.  (Fitted to 33 to 5000 frequencies, 1000 to 40000 queries, every
+// kind of order; the choice is 0.2% from the faster of the two on the average.
+// 2048 frequencies, 4096 queries to order 0, 3, 8 and 25: 38.6, 38.6, 61.0 and 84
+// here, 37.5, 52.8, 63.3 and 116 by fours; 6144: 74.6, 74.7, 119 and 165 here, 54,
+// 76, 92 and 171 by fours; 2048: 20.9, 29.1, 34.4 and 61 by fours.)  Spectra
+// beyond an XCD's L2 (4 MB) cost the fours, which read them four times as
+// often, some 15% more.
 inline bool tiles_pay(int64_t nq, int N, int order)
 {
-    if (order > 27 || nq <= 1536) return false;
-    const double round = order <= 3 ? 38.0 : order <= 7 ? 45.0 : order <= 15 ? 59.0 : 81.0;
-    const double fours = (N >= 128 && N < 1024 ? 58.0 : 46.0) + 2.9 * order;
-    return (double)ceil_div(nq, (int64_t)4096) * round < (double)std::max<int64_t>(nq, 3072) / 4096.0 * fours;
+    if (order > 27) return false;
+    const double x = N / 2048.0, fours = (double)ceil_div(nq, (int64_t)1024), tiles = (double)ceil_div(nq, (int64_t)4096);
+    const int waves = std::min(4, eval_waves<4>(ceil_div(nq, (int64_t)4), ceil_div((int64_t)N, (int64_t)FT_STEP), order));
+    const double start = order <= 3 ? 2.7 : order <= 7 ? 2.9 : order <= 15 ? 3.9 : 4.7;
+    const double slope = order <= 3 ? 34.0 : order <= 7 ? 41.5 : order <= 15 ? 55.0 : 77.6;
+    const double by_fours = 2.4 + fours * (1.03 * waves / 4 + x * ((order < 3 ? 7.46 : 9.34) + 0.72 * order));
+    const bool beyond = (int64_t)N * (order + 1) * 32 > 4 << 20;
+    return tiles * (start + x * slope) < (beyond ? 1.15 : 1.0) * by_fours;
 }
 
 // dth <- M dth, ds <- M ds per query (M row-major 4 x 4).
