@@ -500,8 +500,8 @@ int globalize_manifold(const double *grid_dev, const double *s_host, int32_t n_t
  * a row outside [0, n_rows), a non-finite theta, or a theta so large that
  * theta n_theta / (2 pi) overflows yields NaN.  A query's result depends on
  * its row and theta alone, in any order and company; only for 64 <= n_theta <
- * 320 its last bits depend on the number of queries too (few are interpolated
- * without the row length's table).  Asynchronous. */
+ * 320 (an odd n_theta: < 512) its last bits depend on the number of queries too
+ * (few are interpolated without the row length's table).  Asynchronous. */
 int theta_interp(const double *rows_dev, int32_t n_theta, int64_t n_rows, const int64_t *row_dev,
                  const double *theta_dev, int64_t n_query, double *out_dev, void *stream);
 

@@ -477,14 +477,18 @@ MS_D double uni(double x)
     return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
 }
 
-// The queries of a block in LDS.
+// The queries of a block in LDS: up to LEN.  (Ungrouped, 9 KB for 256 instead of
+// 28 for three shares: beside the table of an odd 1023 or an even 2048 a fourth
+// block fits a CU, and a third beside an odd 2047; 4096 queries of one row 16.1,
+// 15.4 and 26.2 us for 19.9, 18.1 and 26.8.)
+template <int LEN>
 struct IpList {
-    double t[IP_LIST];       // tan(delta / 2)
-    double f[IP_LIST];       // factor of the sum: (-1)^i0 sin(N delta / 2) / N (odd N: / cos(delta / 2))
-    int64_t row[IP_LIST];    // -1: nothing to do
-    int32_t i0[IP_LIST];     // -1: |theta| so large that delta is not below a step
-    uint32_t q[IP_LIST];     // query, from the slice's first; ~0: none
-    uint32_t tile[IP_LIST];  // first entry, entries << 16 (0: one with i0 = -1)
+    double t[LEN];       // tan(delta / 2)
+    double f[LEN];       // factor of the sum: (-1)^i0 sin(N delta / 2) / N (odd N: / cos(delta / 2))
+    int64_t row[LEN];    // -1: nothing to do
+    int32_t i0[LEN];     // -1: |theta| so large that delta is not below a step
+    uint32_t q[LEN];     // query, from the slice's first; ~0: none
+    uint32_t tile[LEN];  // first entry, entries << 16 (0: one with i0 = -1)
     uint32_t n_tiles, unsorted;
 };
 
@@ -512,8 +516,8 @@ MS_D double quotient(double n, double d)
 // pass i0, and the last one of a length that is no multiple of the step, go
 // sample by sample.  (-1)^d is (-1)^i0 for the query times (-1)^i, a sign per
 // lane: the steps are of 64 samples.
-template <bool ODD, int QT>
-MS_D void interp_tile(const IpList &s, int e0, int len, const double *tab, const double *__restrict__ in, int N,
+template <bool ODD, int QT, class List>
+MS_D void interp_tile(const List &s, int e0, int len, const double *tab, const double *__restrict__ in, int N,
                       double *out)
 {
     constexpr int U = 4 / QT;
@@ -671,7 +675,7 @@ template <bool ODD, bool GROUPED>
 __global__ void __launch_bounds__(IP_BLOCK) k_theta_interp(InterpArgs g)
 {
     extern __shared__ double s_dyn[];     // the bins, then the cotangents
-    __shared__ IpList s;
+    __shared__ IpList<GROUPED ? IP_LIST : IP_MAX_Q> s;
     const int tid = threadIdx.x, nt = GROUPED ? IP_BLOCK : (int)blockDim.x, lane = tid % 64, wv = tid / 64;
     const int N = g.N;
     int64_t q0;
@@ -1162,8 +1166,14 @@ extern "C" int theta_interp(const double *rows_dev, int32_t n_theta, int64_t n_r
     // with many queries for each block (129 samples, 5000 queries: 11 to 16
     // against 9 us; 256, 20000: 16 against 33; 256 and 300, 500: 5.5 and 6.0
     // against 5.1 and 5.5, 4096: 7.6 and 8.4 against 9.4 and 10.7), the shortest
-    // never (64 samples, 20000 queries: 15 against 17; 33, 65536: 47 and 47).
-    if (N > IP_MAX_N || N < 64 || (N < 256 && n_query < 16384) || (N < 320 && n_query < 2048)) {
+    // never (64 samples, 20000 queries: 15 against 17; 33, 65536: 47 and 47).  An
+    // odd length's table has two numbers a sample (319 and 511 samples, 4096
+    // queries of as many rows: 13.9 and 17.2 against 10.6 and 14.8, of one row 11.7
+    // and 11.9 against 10.0 and 13.0; 8192 of one row 13.5 and 15.6 against 16.3
+    // and 21.5).
+    const bool odd = (N & 1) != 0;
+    if (N > IP_MAX_N || N < 64 || (N < 256 && n_query < 16384) || (N < 320 && n_query < 2048) ||
+        (odd && N < 512 && n_query <= 4096)) {
         const int64_t blocks = ceil_div(n_query, 4);
         if (blocks > 0x7fffffff) return fail(MS_E_ARG, "theta_interp: too many queries for one launch");
         hipLaunchKernelGGL(k_theta_interp_plain, dim3((unsigned)blocks), dim3(256), 0, st, rows_dev, N, n_rows, row_dev,
@@ -1180,7 +1190,6 @@ extern "C" int theta_interp(const double *rows_dev, int32_t n_theta, int64_t n_r
     g.nq = n_query;
     g.N = N;
     g.slice = g.per_slice = g.bins = g.shift = 0;
-    const bool odd = (N & 1) != 0;
     const size_t table = (size_t)(odd ? 16 : 8) * N;
     // Grouped by rows where the rows do not stay in the caches (8 MB: twice
     // an XCD's L2) and are read more than once: 2048 rows of 2048, 4096 queries:
